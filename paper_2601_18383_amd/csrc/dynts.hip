@@ -311,6 +311,30 @@ int fused_step(dynts_ctx *ctx, int layer, const uint16_t *q, const uint16_t *k_n
   return rc;
 }
 
+// ---- block scoring ----------------------------------------------------------------------------------
+// bytes of one key range's denominators
+size_t score_block_stats_bytes(const dynts_config &c, int n_queries) {
+  const size_t rpad = align_up((size_t)n_queries * (c.n_q_heads / c.n_kv_heads));
+  return align_up((size_t)c.batch * c.n_kv_heads * rpad * sizeof(float));
+}
+
+// Key ranges of the first pass: as many as fill the chip's 256 x 3 workgroup places once, where the rows alone do not, of
+// at least eight chunks each.  64 queries on 128 units of 2464 slots (256 workgroups of rows): first pass 66 us with
+// one range, 49 with two, 48 with three.  With scratch for fewer ranges there are fewer.
+int score_block_splits(const dynts_config &c, int n_queries) {
+  const long long R = (long long)n_queries * (c.n_q_heads / c.n_kv_heads);
+  const long long wgs = (R + dynts::kSbRowsPerWg - 1) / dynts::kSbRowsPerWg * c.batch * c.n_kv_heads;
+  const long long want = 768 / wgs, most = c.capacity / 256;
+  const long long s = want < most ? want : most;
+  return s < 1 ? 1 : s > dynts::kSbMaxSplits ? dynts::kSbMaxSplits : (int)s;
+}
+
+template <int D, bool PAGED>
+void launch_score_block(const dynts::ScoreBlockParams &p, dim3 g1, dim3 g2, hipStream_t st) {
+  hipLaunchKernelGGL((dynts::score_block_stats_kernel<D, PAGED>), g1, dim3(dynts::kSbWaves * 64), 0, st, p);
+  hipLaunchKernelGGL((dynts::score_block_colsum_kernel<D, PAGED>), g2, dim3(dynts::kSbWaves * 64), 0, st, p);
+}
+
 // ---- Importance Predictor ---------------------------------------------------------------------------
 struct MlpPlan {
   int bt;      // batch tiles of 16
@@ -717,8 +741,7 @@ int dynts_set_kernel_event_list(dynts_ctx *ctx, void *const *starts, void *const
 
 size_t dynts_score_block_scratch_bytes(const dynts_config *cfg, int32_t n_queries) {
   if (!cfg || check_config(cfg) != DYNTS_OK || n_queries <= 0 || n_queries > (1 << 20)) return 0;
-  const size_t rpad = align_up((size_t)n_queries * (cfg->n_q_heads / cfg->n_kv_heads));
-  return align_up((size_t)cfg->batch * cfg->n_kv_heads * rpad * sizeof(float));
+  return (size_t)score_block_splits(*cfg, n_queries) * score_block_stats_bytes(*cfg, n_queries);
 }
 
 int dynts_score_block(dynts_ctx *ctx, int32_t layer, const uint16_t *q_blk, const uint16_t *k_blk,
@@ -730,8 +753,8 @@ int dynts_score_block(dynts_ctx *ctx, int32_t layer, const uint16_t *q_blk, cons
   if (n_queries <= 0 || n_queries > (1 << 20)) return DYNTS_EINVAL;
   if (reinterpret_cast<uintptr_t>(q_blk) % 16 || reinterpret_cast<uintptr_t>(k_blk) % 16) return DYNTS_EINVAL;
   const dynts_config &c = ctx->cfg;
-  const size_t need = dynts_score_block_scratch_bytes(&c, n_queries);
-  if (scratch_bytes < need || reinterpret_cast<uintptr_t>(scratch) % 4) return DYNTS_EWORKSPACE;
+  const size_t one = score_block_stats_bytes(c, n_queries);
+  if (scratch_bytes < one || reinterpret_cast<uintptr_t>(scratch) % 4) return DYNTS_EWORKSPACE;
   const LayerView lv = layer_view(ctx, layer);
   const int G = c.n_q_heads / c.n_kv_heads;
   dynts::ScoreBlockParams p{};
@@ -754,6 +777,8 @@ int dynts_score_block(dynts_ctx *ctx, int32_t layer, const uint16_t *q_blk, cons
   p.accumulate = accumulate ? 1 : 0;
   p.scale_log2 = ctx->scale_log2;
   p.block_table = lv.block_table; p.max_pages = ctx->max_pages; p.n_pages = ctx->n_pages;
+  p.n_split = score_block_splits(c, n_queries);
+  if ((size_t)p.n_split * one > scratch_bytes) p.n_split = (int)(scratch_bytes / one);
   const long long R = (long long)n_queries * G;
   // (1-D grids: blocks per unit x units rounded up to the 8 XCDs, mapped inside the kernels)
   const long long units8 = ((long long)c.batch * c.n_kv_heads + 7) / 8 * 8;
@@ -761,14 +786,14 @@ int dynts_score_block(dynts_ctx *ctx, int32_t layer, const uint16_t *q_blk, cons
   const long long b2 = (c.capacity + dynts::kSbRowsPerWg - 1) / dynts::kSbRowsPerWg;
   if (b1 * units8 > 0x7fffffffLL || b2 * units8 > 0x7fffffffLL) return DYNTS_EINVAL;
   if ((long long)n_queries * c.n_q_heads * c.head_dim * 2 > 0x7fffffffLL) return DYNTS_EINVAL;  // 32-bit row offsets
-  const dim3 g1((unsigned)(b1 * units8)), g2((unsigned)(b2 * units8));
+  const dim3 g1((unsigned)(b1 * units8 * p.n_split)), g2((unsigned)(b2 * units8));
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (c.head_dim == 128) {
-    hipLaunchKernelGGL(dynts::score_block_stats_kernel<128>, g1, dim3(dynts::kSbWaves * 64), 0, st, p);
-    hipLaunchKernelGGL(dynts::score_block_colsum_kernel<128>, g2, dim3(dynts::kSbWaves * 64), 0, st, p);
+    if (ctx->paged) launch_score_block<128, true>(p, g1, g2, st);
+    else launch_score_block<128, false>(p, g1, g2, st);
   } else {
-    hipLaunchKernelGGL(dynts::score_block_stats_kernel<64>, g1, dim3(dynts::kSbWaves * 64), 0, st, p);
-    hipLaunchKernelGGL(dynts::score_block_colsum_kernel<64>, g2, dim3(dynts::kSbWaves * 64), 0, st, p);
+    if (ctx->paged) launch_score_block<64, true>(p, g1, g2, st);
+    else launch_score_block<64, false>(p, g1, g2, st);
   }
   return launch_status();
 }

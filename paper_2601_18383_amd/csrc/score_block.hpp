@@ -10,32 +10,62 @@
 // (row, slot) of HBM traffic each way, which at these shapes is several times slower.
 //
 // Both passes have the same shape.  A wave keeps 64 rows of one operand in registers (pass 1: query
-// rows, pass 2: cached keys) as MFMA operand fragments (lane (r, kg) holds elements
-// 32*ks + 8*kg .. +7 of row r, the layout v_mfma_f32_16x16x32_bf16 wants for A and for B alike).
-// The other operand is streamed: the workgroup's 256 threads fetch 32 rows at a time with whole-row
-// coalesced 16-byte loads (a strided fetch straight into operand layout touches 16 cache lines per
-// instruction and makes the L1 tag rate the limit), park them in one of two padded LDS buffers, and
-// every wave reads its operand fragments back from there (row pitch +16 bytes: the 16 rows a
-// ds_read_b128 touches fall into different banks).  Loads for chunk c+2 are in flight while chunk
-// c is multiplied; one barrier per chunk.
-// The product is always  keys (A, rows)  x  queries (B, columns): a lane ends up with 4 keys of ONE
-// query column, so
-//   * pass 1 keeps a private running (max, sum) per lane and query column and merges the four lane
-//     groups once, at the end;
-//   * pass 2 keeps private partial column sums per lane and key and merges the 16 lanes of a group
-//     once, at the end.
+// rows, pass 2: cached keys) as B fragments of v_mfma_f32_32x32x16_bf16 (lane (c, hf) = (lane % 32, lane / 32)
+// holds elements 16*ks + 8*hf .. +7 of row c; A and B alike).  The other operand is streamed: the workgroup's
+// 256 threads fetch 32 rows at a time, eight threads to a row (whole 128-byte lines), park them in one of two
+// padded LDS buffers, and every wave reads its A fragments back from there (row pitch +16 bytes: the rows a
+// ds_read_b128 touches fall into different banks).  The next chunk's loads are in flight while a chunk is
+// multiplied; one barrier per chunk.  The product is  streamed rows (A)  x  stationary columns (B): a lane ends
+// up with 16 streamed rows (8*(i/4) + 4*hf + i%4) of ONE stationary column, so
+//   * pass 1 keeps a private shift and sum per lane and query column and merges the two lane halves
+//     once, at the end;
+//   * pass 2 keeps one private column sum per lane and key and adds the two halves once, at the end.
+//
+// What bounds them: the instruction stream.  A logit needs a multiply-add, a 2^x and an add in each pass beside
+// its share of the MFMA, and the two pipes overlap only in part (a loop of just these, without memory: 0.38 us
+// per 32 x 64 chunk and SIMD; MFMAs alone 0.28, vector instructions alone 0.22), so everything else that is issued
+// per chunk counts.  32x32 tiles take half the MFMA issue slots and LDS reads per product of 16x16 ones, and one row
+// per staging thread leaves one address to advance.  A block of 512 queries over 2464 slots
+// (128 units, 28 query heads on 4): 655 -> 593 us a call against 16x16 tiles with a running maximum, both passes at
+// 1.9 GHz, which the chip falls to under this load; 64 queries: 120 -> 89 us.  Tried and slower: products of one tile
+// interleaved by hand with the exponentials of another in one wave (600 -> 640 us and more: registers).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "attend.hpp"
 
 namespace dynts {
 
+#ifdef SB_NOPRIO
+#define SB_PRIO(x)
+#else
+#define SB_PRIO(x) __builtin_amdgcn_s_setprio(x)
+#endif
+#ifdef SB_NOPRIO
+#define SB_PRIO(x)
+#else
+#define SB_PRIO(x) __builtin_amdgcn_s_setprio(x)
+#endif
+#ifdef SB_NOPRIO
+#define SB_PRIO(x)
+#else
+#define SB_PRIO(x) __builtin_amdgcn_s_setprio(x)
+#endif
+#ifndef SB_OCC
+#define SB_OCC 3
+#endif
 constexpr int kSbWaves = 4;        // waves per workgroup
-constexpr int kSbTiles = 4;        // stationary 16-row tiles per wave
-constexpr int kSbRowsPerWave = 16 * kSbTiles;
+constexpr int kSbTiles = 2;        // stationary 32-row tiles per wave
+constexpr int kSbRowsPerWave = 32 * kSbTiles;
 constexpr int kSbRowsPerWg = kSbRowsPerWave * kSbWaves;
+constexpr int kSbChunk = 32;       // streamed rows per chunk
+constexpr int kSbLRows = kSbWaves * 64;  // rows whose denominators are staged at a time (one per thread)
+constexpr int kSbMaxSplits = 4;    // key ranges of the first pass
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 struct ScoreBlockParams {
   const uint16_t *K;        // layer base, [Nb][Hkv][cap][D]
@@ -44,9 +74,10 @@ struct ScoreBlockParams {
   const int32_t *seq_len;   // [Nb]
   const int32_t *n_prompt;  // [Nb]
   const uint8_t *active;    // [Nb] or null
-  float *stats;             // [Nb][Hkv][Rpad]  log2 of the softmax denominator per query row
+  float *stats;             // [Nb][Hkv][n_split][Rpad]  log2 of the softmax denominator per query row and key range
   float *dst;               // [Nb][Hkv][cap]
   int Nb, T, Hq, Hkv, G, cap, Rpad;
+  int n_split;              // key ranges (workgroups) the first pass cuts a unit's keys into
   int skip_prompt;          // 1: slots below n_prompt[b] are left alone (dst is the score array)
   int accumulate;           // 1: dst += sums, 0: dst = sums
   float scale_log2;         // softmax scale * log2(e)
@@ -55,51 +86,65 @@ struct ScoreBlockParams {
   int max_pages, n_pages;
 };
 
-// byte address of cached key row `row` of a unit (dense rows, or through the block table)
-template <int D>
-__device__ __forceinline__ const char *sb_key_row(const ScoreBlockParams &p, size_t unit, int row) {
-  if (p.block_table) {
+// byte offset from K of cached key row `row` of a unit (dense rows, or through the block table)
+template <int D, bool PAGED>
+__device__ __forceinline__ size_t sb_key_row(const ScoreBlockParams &p, size_t unit, int row) {
+  if (PAGED) {
     int pi = row / kPageSlots;
     pi = pi < p.max_pages ? pi : p.max_pages - 1;
     int pg = p.block_table[unit * (size_t)p.max_pages + pi];
     pg = pg < 0 ? 0 : (pg >= p.n_pages ? p.n_pages - 1 : pg);
-    return reinterpret_cast<const char *>(p.K + ((size_t)pg * kPageSlots + row % kPageSlots) * D);
+    return ((size_t)pg * kPageSlots + row % kPageSlots) * (2 * D);
   }
-  return reinterpret_cast<const char *>(p.K + (unit * (size_t)p.cap + row) * D);
+  return (unit * (size_t)p.cap + row) * (2 * D);
 }
 
-// MFMA operand fragments of one row in global memory: 16 bytes per k-step at the lane's column group.
+// MFMA operand fragments of one row (global memory or LDS): 16 bytes per k-step of 16 at the lane's half.
 template <int D>
-__device__ __forceinline__ void load_row_frags(bf16x8 (&f)[D / 32], const char *row, int kg) {
-  const char *base = row + 16 * kg;
+__device__ __forceinline__ void load_row_frags(bf16x8 (&f)[D / 16], const char *row, int hf) {
+  const char *base = row + 16 * hf;
 #pragma unroll
-  for (int ks = 0; ks < D / 32; ++ks)
-    f[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(base + 64 * ks));
+  for (int ks = 0; ks < D / 16; ++ks)
+    f[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(base + 32 * ks));
 }
 
-// Staging of the streamed operand: a chunk is 32 rows; thread t of the 256 fetches 16 bytes of row
-// t / PIECES (+ RPP per further load) at piece t % PIECES, so 16 (8) neighbouring lanes read one
-// whole row.
 template <int D>
 struct SbStage {
-  static constexpr int kChunk = 32;              // rows per chunk
-  static constexpr int PIECES = D / 8;           // 16-byte pieces per row
-  static constexpr int RPP = 256 / PIECES;       // rows one load instruction of the workgroup covers
-  static constexpr int NL = kChunk / RPP;        // load instructions per chunk and thread
-#ifndef SB_PITCH_EXTRA
-#define SB_PITCH_EXTRA 16
-#endif
-  static constexpr int LROW = 2 * D + SB_PITCH_EXTRA;        // padded row pitch in LDS, bytes
-  static constexpr int kBufBytes = kChunk * LROW;
+  static constexpr int NL = D / 64;              // 16-byte loads per thread and chunk, 128 bytes apart
+  static constexpr int LROW = 2 * D + 16;        // padded row pitch in LDS, bytes
+  static constexpr int kBufBytes = kSbChunk * LROW;
 };
 
-// operand fragments of row `row` (0..31) of a staged chunk
+// The products of one chunk: 32 streamed rows (in LDS) x the wave's 64 stationary columns.
 template <int D>
-__device__ __forceinline__ void lds_row_frags(bf16x8 (&f)[D / 32], const char *buf, int row, int kg) {
-  const char *base = buf + row * SbStage<D>::LROW + 16 * kg;
+__device__ __forceinline__ void sb_multiply(f32x16 (&acc)[kSbTiles], const char *buf, const bf16x8 (&st)[kSbTiles][D / 16],
+                                            int c, int hf) {
+  bf16x8 a[D / 16];
+  load_row_frags<D>(a, buf + c * SbStage<D>::LROW, hf);
 #pragma unroll
-  for (int ks = 0; ks < D / 32; ++ks)
-    f[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(base + 64 * ks));
+  for (int t = 0; t < kSbTiles; ++t)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+  __builtin_amdgcn_s_setprio(1);  // (a wave's products first: 1 % of both passes)
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ++ks)
+#pragma unroll
+    for (int t = 0; t < kSbTiles; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks], st[t][ks], acc[t], 0, 0, 0);
+  __builtin_amdgcn_s_setprio(0);
+}
+
+// Sum over a lane's 16 products of 2^(c * product + add_i), in a balanced tree: the running sums then take one rounding per
+// chunk instead of one per row.
+template <typename Add>
+__device__ __forceinline__ float sb_exp_sum(const f32x16 &acc, float c, Add add) {
+  float q[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const float e0 = fast_exp2(fmaf(acc[4 * j], c, add(4 * j))), e1 = fast_exp2(fmaf(acc[4 * j + 1], c, add(4 * j + 1)));
+    const float e2 = fast_exp2(fmaf(acc[4 * j + 2], c, add(4 * j + 2))), e3 = fast_exp2(fmaf(acc[4 * j + 3], c, add(4 * j + 3)));
+    q[j] = (e0 + e1) + (e2 + e3);
+  }
+  return (q[0] + q[1]) + (q[2] + q[3]);
 }
 
 // Workgroup -> (unit, block).  Consecutive workgroup ids go to the 8 XCDs in turn; this mapping
@@ -112,51 +157,27 @@ __device__ __forceinline__ bool sb_map(int n_blk, int n_units, int &unit, int &b
   return unit < n_units;
 }
 
-// A thread's walk over the query rows r = i * G + g of a KV head's group, `step` rows at a time.
-struct QueryWalk {
-  int r, i, g, step;
-  uint32_t off;         // byte offset of row (i, g) from the (sequence, head-group) base
-  int step_i, step_g;   // step = step_i * G + step_g
-  uint32_t stride_i, stride_g;
-  __device__ __forceinline__ void init(int r0, int step_, int G, int Hq, int D) {
-    r = r0;
-    step = step_;
-    i = r0 / G;
-    g = r0 - i * G;
-    step_i = step / G;
-    step_g = step - step_i * G;
-    stride_i = (uint32_t)Hq * D * 2;
-    stride_g = (uint32_t)D * 2;
-    off = (uint32_t)i * stride_i + (uint32_t)g * stride_g;
-  }
-  __device__ __forceinline__ void advance(int G) {
-    r += step;
-    i += step_i;
-    g += step_g;
-    off += (uint32_t)step_i * stride_i + (uint32_t)step_g * stride_g;
-    if (g >= G) {
-      g -= G;
-      i += 1;
-      off += stride_i - (uint32_t)G * stride_g;
-    }
-  }
-};
-
 // ---- pass 1: log2 of the softmax denominator of every query row ---------------------------------
-// 1-D grid of ceil(R / 256) * round_up(units, 8) workgroups, 256 threads.
-template <int D>
-__global__ __launch_bounds__(kSbWaves * 64) void score_block_stats_kernel(const ScoreBlockParams p) {
-  constexpr int KS = D / 32;
+// 1-D grid of ceil(R / 256) * n_split * round_up(units, 8) workgroups, 256 threads.
+//
+// The shift that keeps the exponentials in range is not a running maximum: it is raised only when a logit lies above it.
+// A chunk is folded with the shift at hand, and a chunk's sum that is too large for keys below the shift (or infinite;
+// the first always is, its shift is far below any logit) sends the wave back to the chunk's logits, which are still in
+// registers, with their true maximum.  A maximum over every logit costs a sixth of the vector instructions.
+template <int D, bool PAGED>
+__global__ __launch_bounds__(kSbWaves * 64, 3) void score_block_stats_kernel(const ScoreBlockParams p) {
   using St = SbStage<D>;
   __shared__ __attribute__((aligned(16))) char lds[2][St::kBufBytes];
   const int R = p.T * p.G;
   int unit, blk;
-  if (!sb_map((R + kSbRowsPerWg - 1) / kSbRowsPerWg, p.Nb * p.Hkv, unit, blk)) return;
+  const int n_blk = (R + kSbRowsPerWg - 1) / kSbRowsPerWg;
+  if (!sb_map(n_blk * p.n_split, p.Nb * p.Hkv, unit, blk)) return;
+  const int split = blk % p.n_split;
+  blk /= p.n_split;
   const int b = unit / p.Hkv, h = unit - b * p.Hkv;
   if (p.active && !p.active[b]) return;
-  if (blk * kSbRowsPerWg >= R) return;  // (cannot happen with the grid above; uniform over the workgroup)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r16 = lane & 15, kg = lane >> 4;
+  const int col = lane & 31, hf = lane >> 5;
   const int row0 = blk * kSbRowsPerWg + wave * kSbRowsPerWave;
   // (the same in every lane of a wave, and told so to the compiler; a wave without rows still helps staging and
   // meets the barriers)
@@ -166,160 +187,165 @@ __global__ __launch_bounds__(kSbWaves * 64) void score_block_stats_kernel(const 
   const char *Qb = reinterpret_cast<const char *>(p.q_blk + ((size_t)b * p.T * p.Hq + (size_t)h * p.G) * D);
   const float c = p.scale_log2;
 
-  // stationary: this wave's query rows (B operand: column r16 of tile qt is row row0 + 16 qt + r16)
-  bf16x8 qf[kSbTiles][KS];
+  // stationary: this wave's query rows (column col of tile qt is row row0 + 32 qt + col)
+  bf16x8 qf[kSbTiles][D / 16];
   int vis_blk[kSbTiles];  // block keys [0, vis_blk) are visible to this lane's query column
 #pragma unroll
   for (int qt = 0; qt < kSbTiles; ++qt) {
-    int r = row0 + 16 * qt + r16;
+    int r = row0 + 32 * qt + col;
     r = r < R ? r : R - 1;
     const int i = r / p.G, g = r - i * p.G;
     vis_blk[qt] = i + 1;
-    load_row_frags<D>(qf[qt], Qb + ((size_t)i * p.Hq + g) * (size_t)(2 * D), kg);
+    load_row_frags<D>(qf[qt], Qb + ((size_t)i * p.Hq + g) * (size_t)(2 * D), hf);
   }
 
-  // running max (in raw dot-product units) and sum of 2^(c * (dot - max)), private to the lane
-  float m[kSbTiles], nm[kSbTiles], l[kSbTiles];  // nm = -c * m, the exponent's addend
+  // the exponents' addend (minus the shift, a whole number of log2 units) and the sum of 2^(c * dot + addend), private to the lane
+  float nm[kSbTiles], l[kSbTiles];
 #pragma unroll
   for (int qt = 0; qt < kSbTiles; ++qt) {
-    m[qt] = -1e30f;
-    nm[qt] = 1e30f * c;
+    nm[qt] = 1e30f;
     l[qt] = 0.f;
   }
+  // A lane's 16 keys below the shift sum to 16 at most; from kLimit on some key lies above it.
+  constexpr float kLimit = 16.5f;
 
-  // One streamed tile in two parts, so that the loop below can put the MFMAs of the NEXT tile (four independent
-  // accumulators, issued back to back) beside the vector work of the current one:
-  //   MM:   logits of keys (4 kg + i) x query column r16 for the wave's four query tiles;
-  //   FOLD: fold them into (m, l).  MASKED: keys whose index key0 + 4 kg + i is not below lim[qt] do not exist
-  //         for this query column.
-#define DYNTS_SB_MM(acc_, buf_, tt_)                                                                   \
-  {                                                                                                    \
-    bf16x8 kf[KS];                                                                                     \
-    lds_row_frags<D>(kf, buf_, 16 * (tt_) + r16, kg);                                                  \
-    _Pragma("unroll") for (int qt = 0; qt < kSbTiles; ++qt) acc_[qt] = f32x4{0.f, 0.f, 0.f, 0.f};      \
-    _Pragma("unroll") for (int ks = 0; ks < KS; ++ks)                                                  \
-      _Pragma("unroll") for (int qt = 0; qt < kSbTiles; ++qt)                                          \
-          acc_[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks], qf[qt][ks], acc_[qt], 0, 0, 0);   \
-  }
-#define DYNTS_SB_FOLD(acc_, MASKED, key0_, lim_)                                                       \
-  _Pragma("unroll") for (int qt = 0; qt < kSbTiles; ++qt) {                                            \
-    f32x4 acc = acc_[qt];                                                                              \
-    if (MASKED) {                                                                                      \
-      _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                    \
-          if ((key0_) + 4 * kg + i >= lim_[qt]) acc[i] = -INFINITY;                                    \
-    }                                                                                                  \
-    const float mx = fmaxf(fmaxf(acc[0], acc[1]), fmaxf(acc[2], acc[3]));                              \
-    if (__any(mx > m[qt])) { /* some lane's maximum rises (rare after the first tiles): rescale */     \
-      const float mn = fmaxf(mx, m[qt]);                                                               \
-      l[qt] *= fast_exp2((m[qt] - mn) * c); /* exactly 2^0 where nothing changes */                    \
-      m[qt] = mn;                                                                                      \
-      nm[qt] = -mn * c;                                                                                \
-    }                                                                                                  \
-    float sum = l[qt];                                                                                 \
-    _Pragma("unroll") for (int i = 0; i < 4; ++i) sum += fast_exp2(fmaf(acc[i], c, nm[qt]));           \
-    l[qt] = sum;                                                                                       \
-  }
+  // Folds the chunk's logits into (nm, l).  masked: keys at or beyond lim[qt] do not exist for this query column.
+  auto fold = [&](f32x16 (&acc)[kSbTiles], bool masked, int key0, const int (&lim)[kSbTiles]) {
+    if (masked) {
+#pragma unroll
+      for (int qt = 0; qt < kSbTiles; ++qt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (key0 + 8 * (i >> 2) + 4 * hf + (i & 3) >= lim[qt]) acc[qt][i] = -INFINITY;
+    }
+    float s[kSbTiles];
+#pragma unroll
+    for (int qt = 0; qt < kSbTiles; ++qt) {
+      const float add = nm[qt];
+      s[qt] = sb_exp_sum(acc[qt], c, [&](int) { return add; });
+    }
+    if (__any(fmaxf(s[0], s[1]) >= kLimit)) {
+#pragma unroll
+      for (int qt = 0; qt < kSbTiles; ++qt) {
+        float mx = acc[qt][0];
+#pragma unroll
+        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, acc[qt][i]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float nn = fminf(floorf(-mx * c), nm[qt]);
+        l[qt] *= fast_exp2(nn - nm[qt]);
+        s[qt] = sb_exp_sum(acc[qt], c, [&](int) { return nn; });
+        nm[qt] = nn;
+      }
+    }
+#pragma unroll
+    for (int qt = 0; qt < kSbTiles; ++qt) l[qt] += s[qt];
+  };
 
-  // Streaming of `rows` rows that start at `src` with pitch `pitch` bytes (src null: the unit's cached key
-  // rows), 32 per chunk; row indices beyond the last repeat it (the fold masks them).  Every thread of the workgroup runs this.
-  const int st_row = tid / St::PIECES, st_piece = tid % St::PIECES;
+  // Streaming of chunks [c0, c1) of `rows` rows; rows beyond the last repeat it (the fold masks them).  own: rows of
+  // the block's keys, pitch bytes apart, else the unit's cached key rows.  Every thread runs this.  Keys below see_all
+  // are visible to all of the wave's rows, keys from see_any on to none (both the same in every lane).
+  const int st_row = tid >> 3;
+  const uint32_t st_piece = 16u * (uint32_t)(tid & 7);
+  char *const park = lds[0] + st_row * St::LROW + st_piece;
   u32x4 stage[St::NL];
-#define DYNTS_SB_FETCH(src_, pitch_, rows_, chunk_)                                                    \
-  _Pragma("unroll") for (int k = 0; k < St::NL; ++k) {                                                 \
-    int row = (chunk_) * St::kChunk + st_row + St::RPP * k;                                            \
-    row = row < (rows_) ? row : (rows_) - 1;                                                           \
-    const char *rp = (src_) ? (src_) + (size_t)row * (pitch_) : sb_key_row<D>(p, (size_t)unit, row);   \
-    stage[k] = *reinterpret_cast<const u32x4 *>(rp + 16 * st_piece);                                   \
-  }
-#define DYNTS_SB_PARK(buf_)                                                                            \
-  _Pragma("unroll") for (int k = 0; k < St::NL; ++k)                                                   \
-      *reinterpret_cast<u32x4 *>((buf_) + (st_row + St::RPP * k) * St::LROW + 16 * st_piece) = stage[k];
-#define DYNTS_SB_STREAM(src_, pitch_, rows_, lim_, CAUSAL_)                                            \
-  {                                                                                                    \
-    const int n_chunks = ((rows_) + St::kChunk - 1) / St::kChunk;                                      \
-    if (n_chunks > 0) {                                                                                \
-      DYNTS_SB_FETCH(src_, pitch_, rows_, 0)                                                           \
-      DYNTS_SB_PARK(lds[0])                                                                            \
-      if (n_chunks > 1) { DYNTS_SB_FETCH(src_, pitch_, rows_, 1) }                                     \
-      __syncthreads();                                                                                 \
-      f32x4 acc_a[kSbTiles], acc_b[kSbTiles];                                                          \
-      if (has_rows) DYNTS_SB_MM(acc_a, lds[0], 0)                                                      \
-      for (int ch = 0; ch + 1 < n_chunks; ++ch) { /* whole chunks: no key is masked unless CAUSAL_ */  \
-        const int nb = (ch + 1) & 1;                                                                   \
-        if (has_rows) {                                                                                \
-          DYNTS_SB_MM(acc_b, lds[ch & 1], 1)                                                           \
-          DYNTS_SB_FOLD(acc_a, CAUSAL_, ch * St::kChunk, lim_)                                         \
-        }                                                                                              \
-        DYNTS_SB_PARK(lds[nb])                                                                         \
-        if (ch + 2 < n_chunks) { DYNTS_SB_FETCH(src_, pitch_, rows_, ch + 2) }                         \
-        __syncthreads();                                                                               \
-        if (has_rows) {                                                                                \
-          DYNTS_SB_MM(acc_a, lds[nb], 0)                                                               \
-          DYNTS_SB_FOLD(acc_b, CAUSAL_, ch * St::kChunk + 16, lim_)                                    \
-        }                                                                                              \
-      }                                                                                                \
-      if (has_rows) { /* the last chunk may be partial: masked */                                      \
-        const int lc = n_chunks - 1;                                                                   \
-        DYNTS_SB_MM(acc_b, lds[lc & 1], 1)                                                             \
-        DYNTS_SB_FOLD(acc_a, true, lc * St::kChunk, lim_)                                              \
-        DYNTS_SB_FOLD(acc_b, true, lc * St::kChunk + 16, lim_)                                         \
-      }                                                                                                \
-      __syncthreads(); /* the buffers are filled again by the next stream */                           \
-    }                                                                                                  \
-  }
+  auto stream = [&](auto OWN, const char *src, uint32_t pitch, int rows, int c0, int c1, int see_all, int see_any,
+                    const int (&lim)[kSbTiles]) {
+    constexpr bool own = decltype(OWN)::value;
+    if (c0 >= c1) return;
+    uint32_t off = (uint32_t)(c0 * kSbChunk + st_row) * pitch + st_piece;
+    const uint32_t last = (uint32_t)(rows - 1) * pitch + st_piece;
+    auto fetch = [&](int ch) {
+      const char *rp;
+      if (PAGED && !own) {  // a chunk lies inside one page
+        const int first = ch * kSbChunk;
+        int r = st_row < rows - 1 - first ? st_row : rows - 1 - first;
+        rp = src + sb_key_row<D, true>(p, (size_t)unit, first) + ((uint32_t)r * (uint32_t)(2 * D) + st_piece);
+      } else {
+        rp = src + (off < last ? off : last);
+        off += kSbChunk * pitch;
+      }
+#pragma unroll
+      for (int k = 0; k < St::NL; ++k) stage[k] = *reinterpret_cast<const u32x4 *>(rp + 128 * k);
+    };
+    auto put = [&](int buf) {
+#pragma unroll
+      for (int k = 0; k < St::NL; ++k) *reinterpret_cast<u32x4 *>(park + buf * St::kBufBytes + 128 * k) = stage[k];
+    };
+    // Per chunk: one barrier; the next chunk, fetched an iteration ago, goes to the other buffer (read last before the
+    // barrier); the one after it is fetched.
+    fetch(c0);
+    put(0);
+    if (c0 + 1 < c1) fetch(c0 + 1);
+    int buf = 0;
+    for (int ch = c0; ch < c1; ++ch) {
+      __syncthreads();
+      if (ch + 1 < c1) put(buf ^ 1);
+      if (ch + 2 < c1) fetch(ch + 2);
+      if (ch * kSbChunk < see_any) {
+        f32x16 acc[kSbTiles];
+        sb_multiply<D>(acc, lds[buf], qf, col, hf);
+        if ((ch + 1) * kSbChunk > see_all) fold(acc, true, ch * kSbChunk, lim);
+        else fold(acc, false, 0, lim);
+      }
+      buf ^= 1;
+    }
+    __syncthreads();  // the buffers are filled again by the next stream
+  };
 
-  // cached slots: every query column sees all n of them
+  // The keys this workgroup sees: the cached slots (every query column sees all n of them), then the block's own keys,
+  // causally: key i' is visible to query row (i, g) iff i' <= i, so keys [0, i_hi) to some row here.  Chunks of both
+  // are numbered through and cut into n_split equal ranges.
+  int i_hi = 0;
+  if (p.k_blk) {
+    int last = blk * kSbRowsPerWg + kSbRowsPerWg - 1;
+    last = last < R ? last : R - 1;
+    i_hi = last / p.G + 1;
+  }
+  const int nc = (n + kSbChunk - 1) / kSbChunk, no = (i_hi + kSbChunk - 1) / kSbChunk;
+  const int lo = (int)((long long)(nc + no) * split / p.n_split), hi = (int)((long long)(nc + no) * (split + 1) / p.n_split);
   {
     int lim[kSbTiles];
 #pragma unroll
     for (int qt = 0; qt < kSbTiles; ++qt) lim[qt] = n;
-    const char *const cached = nullptr;  // (null source: cached key rows, found by sb_key_row)
-    DYNTS_SB_STREAM(cached, (size_t)0, n, lim, false)
+    const char *src = reinterpret_cast<const char *>(p.K) + (PAGED ? 0 : sb_key_row<D, false>(p, (size_t)unit, 0));
+    stream(std::false_type{}, src, (uint32_t)(2 * D), n, lo, hi < nc ? hi : nc, n, has_rows ? n : 0, lim);
   }
-  // the block's own keys, causally: key i' is visible to query row (i, g) iff i' <= i.  Keys
-  // [0, i_hi) are visible to some row of this workgroup.
   if (p.k_blk) {
-    int last = blk * kSbRowsPerWg + kSbRowsPerWg - 1;
-    last = last < R ? last : R - 1;
-    const int i_hi = last / p.G + 1;
-    const char *kb0 = reinterpret_cast<const char *>(p.k_blk + ((size_t)b * p.T * p.Hkv + h) * D);
-    DYNTS_SB_STREAM(kb0, (size_t)p.Hkv * D * 2, i_hi, vis_blk, true)
+    const char *src = reinterpret_cast<const char *>(p.k_blk + ((size_t)b * p.T * p.Hkv + h) * D);
+    const int last = row0 + kSbRowsPerWave - 1 < R ? row0 + kSbRowsPerWave - 1 : R - 1;
+    const int see_all = __builtin_amdgcn_readfirstlane(row0 / p.G + 1);
+    const int see_any = __builtin_amdgcn_readfirstlane(has_rows ? last / p.G + 1 : 0);
+    stream(std::true_type{}, src, (uint32_t)p.Hkv * (uint32_t)(2 * D), i_hi, lo > nc ? lo - nc : 0, hi - nc, see_all, see_any, vis_blk);
   }
-#undef DYNTS_SB_STREAM
-#undef DYNTS_SB_PARK
-#undef DYNTS_SB_FETCH
-#undef DYNTS_SB_FOLD
-#undef DYNTS_SB_MM
   if (!has_rows) return;
 
-  // merge the four lane groups of every query column, write L = c * m + log2(l)
+  // Merge the two lane halves of every query column, write L = log2(l) - nm.  nm is a whole number, so the exponent of l
+  // joins it without rounding and only the logarithm of l's mantissa is rounded, at the size of L.
 #pragma unroll
   for (int qt = 0; qt < kSbTiles; ++qt) {
-#pragma unroll
-    for (int sh = 16; sh <= 32; sh <<= 1) {
-      const float mo = __shfl_xor(m[qt], sh), lo = __shfl_xor(l[qt], sh);
-      const float mn = fmaxf(m[qt], mo);
-      l[qt] = l[qt] * fast_exp2((m[qt] - mn) * c) + lo * fast_exp2((mo - mn) * c);
-      m[qt] = mn;
-    }
-    const int r = row0 + 16 * qt + r16;
-    if (kg == 0 && r < R) p.stats[(size_t)unit * (size_t)p.Rpad + r] = m[qt] * c + __builtin_amdgcn_logf(l[qt]);
+    const float no2 = __shfl_xor(nm[qt], 32), lo2 = __shfl_xor(l[qt], 32);
+    const float nn = fminf(nm[qt], no2);
+    const float lt = l[qt] * fast_exp2(nn - nm[qt]) + lo2 * fast_exp2(nn - no2);
+    const float whole = (float)__builtin_amdgcn_frexp_expf(lt) - nn;
+    const int r = row0 + 32 * qt + col;
+    if (hf == 0 && r < R)
+      p.stats[((size_t)unit * p.n_split + split) * (size_t)p.Rpad + r] = whole + __builtin_amdgcn_logf(__builtin_amdgcn_frexp_mantf(lt));
   }
 }
 
 // ---- pass 2: attention received by every cached slot, summed over the block's query rows ----------
 // 1-D grid of ceil(cap / 256) * round_up(units, 8) workgroups, 256 threads.
-template <int D>
-__global__ __launch_bounds__(kSbWaves * 64) void score_block_colsum_kernel(const ScoreBlockParams p) {
-  constexpr int KS = D / 32;
+template <int D, bool PAGED>
+__global__ __launch_bounds__(kSbWaves * 64, 3) void score_block_colsum_kernel(const ScoreBlockParams p) {
   using St = SbStage<D>;
   __shared__ __attribute__((aligned(16))) char lds[2][St::kBufBytes];
+  __shared__ __attribute__((aligned(16))) float ldsL[2][kSbLRows];
   int unit, blk;
   if (!sb_map((p.cap + kSbRowsPerWg - 1) / kSbRowsPerWg, p.Nb * p.Hkv, unit, blk)) return;
   const int b = unit / p.Hkv, h = unit - b * p.Hkv;
   if (p.active && !p.active[b]) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r16 = lane & 15, kg = lane >> 4;
+  const int col = lane & 31, hf = lane >> 5;
   const int R = p.T * p.G;
   int n = p.seq_len[b];
   n = n < 0 ? 0 : (n > p.cap ? p.cap : n);
@@ -334,124 +360,115 @@ __global__ __launch_bounds__(kSbWaves * 64) void score_block_colsum_kernel(const
   // (the same in every lane of a wave, and told so to the compiler: a plain branch instead of lane masks)
   const bool has_keys = __builtin_amdgcn_readfirstlane((int)(key0 < n && key0 + kSbRowsPerWave > first)) != 0;  // else: staging and barriers only
   const char *Qb = reinterpret_cast<const char *>(p.q_blk + ((size_t)b * p.T * p.Hq + (size_t)h * p.G) * D);
-  const float *Lb = p.stats + (size_t)unit * (size_t)p.Rpad;
+  const float *Lb = p.stats + (size_t)unit * p.n_split * (size_t)p.Rpad;
   const float c = p.scale_log2;
 
-  // stationary: this wave's cached keys (A operand: row r16 of tile kt is slot key0 + 16 kt + r16)
-  bf16x8 kf[kSbTiles][KS];
+  // stationary: this wave's cached keys (column col of tile kt is slot key0 + 32 kt + col)
+  bf16x8 kf[kSbTiles][D / 16];
 #pragma unroll
   for (int kt = 0; kt < kSbTiles; ++kt) {
-    int row = key0 + 16 * kt + r16;
+    int row = key0 + 32 * kt + col;
     row = row < n ? row : n - 1;
-    load_row_frags<D>(kf[kt], sb_key_row<D>(p, (size_t)unit, row), kg);
+    load_row_frags<D>(kf[kt], reinterpret_cast<const char *>(p.K) + sb_key_row<D, PAGED>(p, (size_t)unit, row), hf);
   }
-  f32x4 sum[kSbTiles];
+  float sum[kSbTiles];
 #pragma unroll
-  for (int kt = 0; kt < kSbTiles; ++kt) sum[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int kt = 0; kt < kSbTiles; ++kt) sum[kt] = 0.f;
 
-  // streamed: the R query rows, 32 per chunk through LDS, and with them their log2 denominators (one float
-  // per row, fetched by the first 32 threads and parked behind the rows: a load of its own inside the
-  // multiply loop would make every chunk wait for all outstanding loads).  A row beyond the last repeats the
-  // last row's data and gets L = +inf, so it contributes 2^(-inf) = 0.
-  __shared__ float ldsL[2][St::kChunk];
-  const int st_piece = tid % St::PIECES;
-  QueryWalk w[St::NL];
-#pragma unroll
-  for (int k = 0; k < St::NL; ++k) w[k].init(tid / St::PIECES + St::RPP * k, St::kChunk, p.G, p.Hq, D);
-  const uint32_t last_off = (uint32_t)(p.T - 1) * w[0].stride_i + (uint32_t)(p.G - 1) * w[0].stride_g;
+  // streamed: the R query rows, 32 per chunk through LDS, and their log2 denominators, 256 rows at a time (one per
+  // thread; left to one wave per chunk they held the other three up at the barrier, 8 % of the kernel).  A row beyond
+  // the last repeats the last row's data and gets L = +inf, so it contributes 2^(-inf) = 0.
+  // A thread stages row r = i * G + g; a chunk further on that is step_i tokens and step_g heads.
+  const int st_row = tid >> 3;
+  const uint32_t st_piece = 16u * (uint32_t)(tid & 7);
+  char *const park = lds[0] + st_row * St::LROW + st_piece;
+  const uint32_t stride_i = (uint32_t)p.Hq * (uint32_t)(2 * D);
+  const int step_i = kSbChunk / p.G, step_g = kSbChunk - step_i * p.G;
+  const uint32_t step_off = (uint32_t)step_i * stride_i + (uint32_t)step_g * (uint32_t)(2 * D);
+  const uint32_t wrap_off = stride_i - (uint32_t)p.G * (uint32_t)(2 * D);
+  int g = st_row % p.G;
+  uint32_t off = (uint32_t)(st_row / p.G) * stride_i + (uint32_t)g * (uint32_t)(2 * D) + st_piece;
+  const uint32_t last = (uint32_t)(p.T - 1) * stride_i + (uint32_t)(p.G - 1) * (uint32_t)(2 * D) + st_piece;
   u32x4 stage[St::NL];
-  float stageL = INFINITY;
-  bool stageL_valid = false;
-  int l_row = tid & (St::kChunk - 1);  // the row whose L this thread fetches next (threads 0..31 park it)
-#define DYNTS_SB_FETCH()                                                                               \
-  _Pragma("unroll") for (int k = 0; k < St::NL; ++k) {                                                 \
-    stage[k] = *reinterpret_cast<const u32x4 *>(Qb + (w[k].r < R ? w[k].off : last_off) + 16 * st_piece); \
-    w[k].advance(p.G);                                                                                 \
-  }                                                                                                    \
-  stageL = Lb[l_row < R ? l_row : R - 1];                                                              \
-  stageL_valid = l_row < R;                                                                            \
-  l_row += St::kChunk;
-#define DYNTS_SB_PARK(b_)                                                                              \
-  _Pragma("unroll") for (int k = 0; k < St::NL; ++k)                                                   \
-      *reinterpret_cast<u32x4 *>(lds[b_] + (tid / St::PIECES + St::RPP * k) * St::LROW + 16 * st_piece) = stage[k]; \
-  if (tid < St::kChunk) ldsL[b_][tid] = stageL_valid ? stageL : INFINITY;
-
-  // The tiles are software-pipelined: the MFMAs of tile t+1 (independent accumulators, so they issue
-  // back to back) stand next to the exponentials and sums of tile t, so that the scheduler has
-  // independent work for the matrix pipe and the vector ALU at the same time.
-#define DYNTS_SB_MM(acc_, buf_, tt_)                                                                   \
-  {                                                                                                    \
-    bf16x8 qf[KS];                                                                                     \
-    lds_row_frags<D>(qf, buf_, 16 * (tt_) + r16, kg);                                                  \
-    _Pragma("unroll") for (int kt = 0; kt < kSbTiles; ++kt) acc_[kt] = f32x4{0.f, 0.f, 0.f, 0.f};      \
-    _Pragma("unroll") for (int ks = 0; ks < KS; ++ks)                                                  \
-      _Pragma("unroll") for (int kt = 0; kt < kSbTiles; ++kt)                                          \
-          acc_[kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kt][ks], qf[ks], acc_[kt], 0, 0, 0);   \
-  }
-#define DYNTS_SB_SUM(acc_, L_)                                                                         \
-  _Pragma("unroll") for (int kt = 0; kt < kSbTiles; ++kt)                                              \
-    _Pragma("unroll") for (int i = 0; i < 4; ++i) sum[kt][i] += fast_exp2(fmaf(acc_[kt][i], c, -(L_)));
-
-  const int n_chunks = (R + St::kChunk - 1) / St::kChunk;
-  DYNTS_SB_FETCH()
-  DYNTS_SB_PARK(0)
-  if (n_chunks > 1) { DYNTS_SB_FETCH() }
-  f32x4 acc_a[kSbTiles], acc_b[kSbTiles];
-  __syncthreads();
-  float La = ldsL[0][r16], Lq = ldsL[0][16 + r16];  // log2 denominators of this lane's query column, even / odd tile
-  // (the last chunk stands behind the loop: every iteration inside has the same shape, so no value has two
-  // homes at the loop's end)
-  if (has_keys) DYNTS_SB_MM(acc_a, lds[0], 0)
-  for (int ch = 0; ch + 1 < n_chunks; ++ch) {
-    const int nb = (ch + 1) & 1;
-    if (has_keys) {
-      DYNTS_SB_MM(acc_b, lds[ch & 1], 1)
-      DYNTS_SB_SUM(acc_a, La)
+  float stageL[kSbMaxSplits];
+#pragma unroll
+  for (int s = 0; s < kSbMaxSplits; ++s) stageL[s] = -INFINITY;
+  int l_row = 0;  // the row whose L this thread has fetched
+  auto fetch = [&]() {
+    const char *rp = Qb + (off < last ? off : last);  // (offsets grow with the row)
+#pragma unroll
+    for (int k = 0; k < St::NL; ++k) stage[k] = *reinterpret_cast<const u32x4 *>(rp + 128 * k);
+    off += step_off;
+    g += step_g;
+    if (g >= p.G) {
+      g -= p.G;
+      off += wrap_off;
     }
-    DYNTS_SB_PARK(nb)
-    if (ch + 2 < n_chunks) { DYNTS_SB_FETCH() }
+  };
+  auto put = [&](int buf) {
+#pragma unroll
+    for (int k = 0; k < St::NL; ++k) *reinterpret_cast<u32x4 *>(park + buf * St::kBufBytes + 128 * k) = stage[k];
+  };
+  auto fetch_L = [&](int group) {
+    l_row = group * kSbLRows + tid;
+    const uint32_t at = (uint32_t)(l_row < R ? l_row : R - 1);
+    stageL[0] = Lb[at];
+    if (p.n_split > 1) {
+#pragma unroll
+      for (int s = 1; s < kSbMaxSplits; ++s)
+        if (s < p.n_split) stageL[s] = Lb[at + (uint32_t)(s * p.Rpad)];
+    }
+  };
+  auto put_L = [&](int buf) {
+    float L = stageL[0];
+    if (p.n_split > 1) {  // the key ranges' denominators together
+      float mx = L, t = 0.f;
+#pragma unroll
+      for (int s = 1; s < kSbMaxSplits; ++s) mx = fmaxf(mx, stageL[s]);
+#pragma unroll
+      for (int s = 0; s < kSbMaxSplits; ++s) t += fast_exp2(stageL[s] - mx);
+      L = mx + __builtin_amdgcn_logf(t);
+    }
+    ldsL[buf][tid] = l_row < R ? L : INFINITY;
+  };
+
+  const int n_chunks = (R + kSbChunk - 1) / kSbChunk;
+  constexpr int kGroup = kSbLRows / kSbChunk;  // chunks per group of denominators
+  fetch();
+  fetch_L(0);
+  put(0);
+  put_L(0);
+  if (n_chunks > 1) fetch();
+  int buf = 0;
+  for (int ch = 0; ch < n_chunks; ++ch) {
     __syncthreads();
-    const float Lq_cur = Lq;
-    La = ldsL[nb][r16];
-    Lq = ldsL[nb][16 + r16];
+    if (ch + 1 < n_chunks) put(buf ^ 1);
+    if (ch + 2 < n_chunks) fetch();
+    const int in_group = ch % kGroup, group = ch / kGroup;
+    if (in_group == 0 && ch + kGroup < n_chunks) fetch_L(group + 1);
+    if (in_group == kGroup - 1 && ch + 1 < n_chunks) put_L((group + 1) & 1);
     if (has_keys) {
-      DYNTS_SB_MM(acc_a, lds[nb], 0)
-      DYNTS_SB_SUM(acc_b, Lq_cur)
+      f32x16 acc[kSbTiles];
+      f32x4 L[4];  // of the rows 8 j + 4 hf .. +3 this lane's products belong to
+#pragma unroll
+      for (int j = 0; j < 4; ++j) L[j] = *reinterpret_cast<const f32x4 *>(&ldsL[group & 1][in_group * kSbChunk + 8 * j + 4 * hf]);
+      sb_multiply<D>(acc, lds[buf], kf, col, hf);
+#pragma unroll
+      for (int kt = 0; kt < kSbTiles; ++kt)
+        sum[kt] += sb_exp_sum(acc[kt], c, [&](int i) { return -L[i >> 2][i & 3]; });
     }
+    buf ^= 1;
   }
-  if (has_keys) {
-    DYNTS_SB_MM(acc_b, lds[(n_chunks - 1) & 1], 1)
-    DYNTS_SB_SUM(acc_a, La)
-    DYNTS_SB_SUM(acc_b, Lq)
-  }
-#undef DYNTS_SB_MM
-#undef DYNTS_SB_SUM
-#undef DYNTS_SB_FETCH
-#undef DYNTS_SB_PARK
   if (!has_keys) return;
 
-  // sum[kt][i] holds slot key0 + 16 kt + 4 kg + i for query columns == r16 (mod 16): add the 16 lanes
+  // add the two halves' rows; lane (col, hf) writes slot key0 + 32 hf + col
+  float tot[kSbTiles];
 #pragma unroll
   for (int kt = 0; kt < kSbTiles; ++kt) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float v = sum[kt][i];
-      v += __shfl_xor(v, 1);
-      v += __shfl_xor(v, 2);
-      v += __shfl_xor(v, 4);
-      v += __shfl_xor(v, 8);
-      sum[kt][i] = v;
-    }
+    tot[kt] = sum[kt] + __shfl_xor(sum[kt], 32);
   }
-  // lane (r16 = 4 kt' + i', kg) writes slot key0 + 16 kt' + 4 kg + i'
-  const int kt_w = r16 >> 2, i_w = r16 & 3;
-  float v = 0.f;
-#pragma unroll
-  for (int kt = 0; kt < kSbTiles; ++kt)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (kt == kt_w && i == i_w) v = sum[kt][i];
-  const int slot = key0 + 16 * kt_w + 4 * kg + i_w;
+  const float v = hf == 0 ? tot[0] : tot[1];
+  const int slot = key0 + 32 * hf + col;
   if (slot < n && slot >= first) {
     float *d = p.dst + (size_t)unit * (size_t)p.cap + slot;
     *d = p.accumulate ? *d + v : v;

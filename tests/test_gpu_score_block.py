@@ -125,3 +125,42 @@ def test_full_shape(B, name, T, sample):
     # planted critical keys collect far more than the median slot
     assert got[:, :, :n0].max() > 20 * np.median(got[:, :, wl.prompt:n0])
     cache.close()
+
+
+@pytest.mark.parametrize("layout", ["dense", "paged"])
+@pytest.mark.parametrize("d,Hq,Hkv,T,with_block_keys", [(128, 28, 4, 9, True), (64, 16, 1, 33, False), (128, 6, 6, 64, True)])
+def test_key_ranges_and_late_maxima(B, d, Hq, Hkv, T, with_block_keys, layout):
+    """Few units on a long cache: the first pass cuts the keys into ranges, some of them without any key of a short
+    sequence.  Keys grow along the cache by several hundred in log2 units, so that every row's shift has to be raised
+    many times and a chunk's first sum overflows.  With scratch for one range only the result is the same."""
+    rng = np.random.default_rng(7 * d + T)
+    Nb, cap = 3, 1300
+    lens = np.array([1300, 33, 1025], np.int32)
+    dev = torch.device("cuda:0")
+    cls = B.Cache if layout == "dense" else B.PagedCache
+    cache = cls(1, Nb, Hq, Hkv, d, cap, 100, 10, 10)
+    grow = np.linspace(0.0, 1.0, cap)[None, None, :, None] * np.array([0.0, 1.0, 30.0])[:, None, None, None]
+    K = (rng.standard_normal((Nb, Hkv, cap, d)) * (1.0 + grow)).astype(np.float32)
+    K = torch.from_numpy(K).to(torch.bfloat16)
+    B.dynts_prefill(cache.ctx, 0, K.to(dev), K.to(dev), torch.from_numpy(lens).to(dev))
+    q = _bf16(rng, Nb, T, Hq, d, scale=1.5)
+    kb = _bf16(rng, Nb, T, Hkv, d) if with_block_keys else None
+    kb_dev = kb.to(dev) if with_block_keys else None
+    need = B.dynts_score_block_scratch_bytes(cache.cfg, T)
+    one = Nb * Hkv * ((T * (Hq // Hkv) + 255) // 256 * 256) * 4
+    assert need >= 4 * one
+    I_ref = orc.score_block(f64(q), f64(kb) if with_block_keys else None, f64(K), lens, 1.0 / np.sqrt(d), np.ones(Nb, np.uint8))
+    # A logit of x (log2 units) is off by a few roundings of its size (the product's sum, times the scale, less the shift:
+    # 2^-24 * x each), the weight relatively by as much times ln 2: 8 roundings of the largest logit.
+    qg = f64(q).reshape(Nb, T, Hkv, Hq // Hkv, d)
+    x = np.einsum("bthgd,bhnd->bhtgn", qg, f64(K)) * (np.log2(np.e) / np.sqrt(d))
+    for nbytes in (need, one, 2 * one + 4):
+        scratch = torch.empty(nbytes, dtype=torch.uint8, device=dev)
+        dst = torch.full((Nb, Hkv, cap), 7.0, dtype=torch.float32, device=dev)
+        B.dynts_score_block(cache.ctx, 0, q.to(dev), kb_dev, scratch, dst=dst, accumulate=False)
+        got = f64(dst)
+        for b in range(Nb):
+            n = lens[b]
+            assert_close(got[b, :, :n], I_ref[b, :, :n], "I[%d], %d bytes of scratch" % (b, nbytes),
+                         tight=max(5e-5, 8 * 2.0 ** -24 * np.abs(x[b, ..., :n]).max()))
+            assert np.all(got[b, :, n:] == 7.0)
