@@ -64,8 +64,8 @@ struct AttendParams {
   uint64_t *part_ml;        // [Nb][Hkv][nsplit][G][2]
   uint32_t tag;             // this launch's serial number (never 0)
   int score_tiles;          // updated scores are written out every so many tiles of a wave (1 .. 16)
-  // When a trigger is known to follow this step, the step's own scaled logits (log2 units) are kept,
-  // [Nb][Hkv][G][cap_pad] fp32, so that its score update can be applied from them (apply_spill_kernel) instead of
+  // When this step's own score update will be asked for by itself (a trigger is known to follow, or it is the unfused
+  // attention call), the step's scaled logits (log2 units) are kept, [Nb][Hkv][G][cap_pad] fp32, so that its score update can be applied from them (apply_spill_kernel) instead of
   // a second pass over K.  Null: not kept.
   float *spill;
   int cap_pad;              // cap rounded up to a whole tile: row pitch of the kept logits (a tile's store stays inside its row)

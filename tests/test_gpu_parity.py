@@ -382,3 +382,67 @@ def test_native_loop_equals_single_calls(B, external):
             assert torch.equal(a.S[l, bb, :, :n], b_.S[l, bb, :, :n]) and torch.equal(a.pos[l, bb, :, :n], b_.pos[l, bb, :, :n])
     assert int(a.seq_len[0, 0]) < cap and int(flags.sum()) >= 3
     assert int(a.status.item()) == 0 and int(b_.status.item()) == 0
+
+
+@pytest.mark.parametrize("d,Hq,Hkv", [(64, 8, 2), (128, 14, 2), (128, 3, 3)])
+def test_attend_then_update_by_any_route(B, d, Hq, Hkv):
+    """The unfused attend call keeps its logits for the update behind it.  Two layers share the room for them: whoever
+    else uses it in between, and whatever asks for the update (dynts_update_scores, the next fused step, a trigger's
+    flush), every attend call's weights reach S once; those of an attend call that another one follows do not."""
+    rng = np.random.default_rng(d + Hq)
+    Nb, cap, M, G = 2, 203, 17, Hq // Hkv
+    lens = np.array([171, 96], np.int32)
+    dev = torch.device("cuda:0")
+    bf = lambda *s: torch.from_numpy(rng.standard_normal(s).astype(np.float32)).to(torch.bfloat16)
+    cache = B.Cache(2, Nb, Hq, Hkv, d, cap, 60, 40, 8)
+    K, V = [bf(Nb, Hkv, cap, d) for _ in range(2)], [bf(Nb, Hkv, cap, d) for _ in range(2)]
+    for l in range(2):
+        B.dynts_prefill(cache.ctx, l, K[l].to(dev), V[l].to(dev), torch.from_numpy(lens).to(dev))
+        cache.S[l, :, :, M:] = 0.0
+    cache.n_prompt.fill_(M)
+    n = [lens.copy(), lens.copy()]
+    want = np.zeros((2, Nb, Hkv, cap))
+    out = torch.zeros((Nb, Hq, d), dtype=torch.float32, device=dev)
+
+    def attend(l, counts, fused=False):
+        q = bf(Nb, Hq, d)
+        if fused:
+            k1, v1 = bf(Nb, Hkv, d), bf(Nb, Hkv, d)
+            B.dynts_decode_step(cache.ctx, l, q.to(dev), k1.to(dev), v1.to(dev), out)
+            for b in range(Nb):
+                K[l][b, :, n[l][b]], V[l][b, :, n[l][b]] = k1[b], v1[b]
+            n[l] += 1
+        else:
+            B.dynts_decode_attend(cache.ctx, l, q.to(dev), out)
+        for b in range(Nb):
+            for h in range(Hkv):
+                m = n[l][b]
+                x = f64(q)[b, h * G:(h + 1) * G] @ f64(K[l])[b, h, :m].T / np.sqrt(d)
+                a = np.exp(x - x.max(1, keepdims=True))
+                a /= a.sum(1, keepdims=True)
+                if counts:
+                    want[l, b, h, M:m] += a[:, M:].sum(0)
+                assert_close(f64(out)[b, h * G:(h + 1) * G], a @ f64(V[l])[b, h, :m], "out, layer %d" % l)
+
+    def check():
+        for l in range(2):
+            B.dynts_update_scores(cache.ctx, l)
+            for b in range(Nb):
+                assert_close(f64(cache.S[l])[b, :, M:n[l][b]], want[l, b, :, M:n[l][b]], "S, layer %d" % l)
+
+    attend(0, True)
+    check()
+    attend(0, True); attend(1, True)                      # the second layer takes the room
+    check()
+    attend(0, False); attend(0, True)                     # the first call's weights are dropped, as ever
+    check()
+    attend(0, True); attend(0, True, fused=True)          # the fused step's pass over K makes the update owed
+    check()
+    B.dynts_hint_trigger(cache.ctx, 0)
+    attend(0, True, fused=True); attend(1, True)          # announced logits stay: the other layer goes without
+    check()
+    attend(1, True)
+    B.dynts_hint_trigger(cache.ctx, 0)
+    attend(0, True, fused=True)                           # announced logits take the room from the other layer
+    check()
+    assert int(cache.status.item()) == 0
