@@ -75,6 +75,12 @@ struct AttendParams {
   int Nb, Hq, Hkv, G, cap, nsplit;
   int track;                // 1: scores are accumulated from attention (save q and statistics)
   float scale_log2;         // softmax scale * log2(e)
+  // Dense layout, K and V of all layers together beyond the 256 MB memory-side cache (the STREAM kernels): a cache that is
+  // read whole, step after step, through a cache it does not fit evicts every row before its next use.  So the slots
+  // below 32 * waves * rounds of each unit go through it and stay, the ones behind are loaded past it (non-temporal
+  // loads), once a sequence has more than fit_slots.  rounds = 0: the first tiles do not fit either.
+  int fit_slots;            // slots per unit up to which everything fits
+  int rounds;               // tiles of a wave at fixed places
   // paged layout only: K and V are page pools [n_pages][kPageSlots][D]; slot j of a unit lives in page
   // block_table[unit][j / kPageSlots], row j % kPageSlots
   const int32_t *block_table;  // layer base, [Nb][Hkv][max_pages]
@@ -96,10 +102,20 @@ __device__ __forceinline__ void store_bf16x8(uint16_t *p, bf16x8 v) {
   store_u32x4(p, __builtin_bit_cast(u32x4, v));
 }
 
+// (two branches that differ only in how they load would be merged into one)
+#define DYNTS_OWN_BRANCH asm volatile("; past the caches")
+
+// 16 bytes of a cache row; NT: past the caches (see AttendParams::fit_slots)
+template <bool NT>
+__device__ __forceinline__ u32x4 load_row_piece(const char *p) {
+  if (NT) return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+  return *reinterpret_cast<const u32x4 *>(p);
+}
+
 // K rows of the 32-slot tile at t as MFMA operand fragments; rows past `end` repeat row end-1.
 // Addresses are a uniform base plus a 32-bit byte offset (a unit's cache is far below 4 GiB), which
 // keeps the per-tile address arithmetic to a clamp and a multiply-add per 16 rows.
-template <int D>
+template <int D, bool NT = false>
 __device__ __forceinline__ void load_k_tile(bf16x8 (&kf)[2][D / 32], const uint16_t *Kb, int t, int r16, int kg,
                                             int end) {
   const char *base = reinterpret_cast<const char *>(Kb);
@@ -110,12 +126,12 @@ __device__ __forceinline__ void load_k_tile(bf16x8 (&kf)[2][D / 32], const uint1
     const uint32_t off = (uint32_t)row * (uint32_t)(2 * D) + 16u * (uint32_t)kg;
 #pragma unroll
     for (int ks = 0; ks < D / 32; ++ks)
-      kf[s][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(base + off + 64 * ks));
+      kf[s][ks] = __builtin_bit_cast(bf16x8, load_row_piece<NT>(base + off + 64 * ks));
   }
 }
 
 // V rows of the tile, whole rows across 16-byte pieces (coalesced); rows past `end` repeat row end-1
-template <int D>
+template <int D, bool NT = false>
 __device__ __forceinline__ void load_v_tile(u32x4 (&vf)[kTile / (64 / (D / 8))], const uint16_t *Vb, int t,
                                             int lane, int end) {
   constexpr int PIECES = D / 8, VROWS = 64 / PIECES;
@@ -125,7 +141,7 @@ __device__ __forceinline__ void load_v_tile(u32x4 (&vf)[kTile / (64 / (D / 8))],
   for (int it = 0; it < kTile / VROWS; ++it) {
     int row = t + VROWS * it + lane / PIECES;
     row = row < end ? row : end - 1;
-    vf[it] = *reinterpret_cast<const u32x4 *>(base + ((uint32_t)row * (uint32_t)(2 * D) + lane_off));
+    vf[it] = load_row_piece<NT>(base + ((uint32_t)row * (uint32_t)(2 * D) + lane_off));
   }
 }
 // Cross-workgroup traffic inside one launch (split partials, arrival counters) consists of relaxed
@@ -167,9 +183,11 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// BURST: updated scores leave in bursts through LDS (see flush_scores) instead of tile by tile.
+// LARGE: the caches do not fit the memory-side cache.  Dense layout: STREAM, see AttendParams::fit_slots.  Paged layout:
+// BURST, updated scores leave in bursts through LDS (see flush_scores) instead of tile by tile.  (Not both: loads past
+// the cache made paged launches 5 % slower, and with them bursts gained nothing in the dense layout.)
 // SPILL: the step keeps its logits (AttendParams::spill) for a trigger that follows.
-template <int D, int W, bool ATTEND, bool PENDING, bool APPEND, bool PAGED = false, bool BURST = false, bool SPILL = false>
+template <int D, int W, bool ATTEND, bool PENDING, bool APPEND, bool PAGED = false, bool LARGE = false, bool SPILL = false>
 __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p) {
   constexpr int kWaves = W, kThreads = W * 64;
   constexpr int KS = D / 32;              // MFMA k-steps per K row
@@ -179,6 +197,7 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   constexpr int VIT = kTile / VROWS;
   constexpr int VSTRIDE = 2 * D + 32;     // bytes per staged V row (+32: transposing reads hit distinct banks)
   constexpr int OSTRIDE = D + 4;          // floats per row of the cross-wave output reduction
+  constexpr bool STREAM = LARGE && !PAGED, BURST = LARGE && PAGED;
   static_assert(kWaves * kTile * VSTRIDE >= kWaves * 16 * OSTRIDE * 4, "LDS tile is reused for the reduction");
   __shared__ __align__(16) unsigned char smem[kWaves * kTile * VSTRIDE];
   __shared__ float sm_m[kWaves][16];
@@ -257,12 +276,25 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   bf16x8 kf[2][KS];
   u32x4 vf[VIT];
   float s_old = 0.f;
-  if (!PAGED) load_k_tile<D>(kf, Kb, t, r16, kg, p.cap);
+  const bool first_past = STREAM && p.rounds == 0;
+  if (first_past) {
+    DYNTS_OWN_BRANCH;
+    load_k_tile<D, true>(kf, Kb, t, r16, kg, p.cap);
+    DYNTS_OWN_BRANCH;
+  } else if (!PAGED) {
+    load_k_tile<D>(kf, Kb, t, r16, kg, p.cap);
+  }
   if (PENDING) {
     const int tok = t + (lane & (kTile - 1));
     s_old = Sb[tok < p.cap ? tok : p.cap - 1];
   }
-  if (ATTEND && !PAGED) load_v_tile<D>(vf, Vb, t, lane, p.cap);
+  if (ATTEND && first_past) {
+    DYNTS_OWN_BRANCH;
+    load_v_tile<D, true>(vf, Vb, t, lane, p.cap);
+    DYNTS_OWN_BRANCH;
+  } else if (ATTEND && !PAGED) {
+    load_v_tile<D>(vf, Vb, t, lane, p.cap);
+  }
   if (PAGED) {
     // The first tile's page is looked up right away and its 32 rows fetched whole (a tile lies inside one
     // page, and a page id is clamped into the pool, so the addresses are valid whatever the length turns
@@ -392,7 +424,8 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
     return;
   }
   // this wave's contiguous range [ra, rb) behind the first tiles
-  const int base = kTile * NW;
+  const int rounds = STREAM && p.rounds > 1 ? p.rounds : 1;
+  const int base = kTile * NW * rounds;
   int per = n_vis > base ? (n_vis - base + NW - 1) / NW : 0;
   // whole tiles per wave: only the last wave with work ends on a partial tile (measured 1-3 % faster than
   // byte-equal ranges that end mid-tile everywhere), and in the paged layout no tile straddles two pages
@@ -479,12 +512,17 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   // Row clamps of the prefetches: a prefetch must not pull another wave's rows, so rows are
   // clamped to the end of this wave's own range (or, with no range, of its first tile); the
   // clamp row is always a valid row of the allocation.
-  const int own_end = ra < rb ? rb : (t + kTile < n_vis ? t + kTile : n_vis);
+  int t_fix = t;  // this wave's last tile at a fixed place
+  if (STREAM) {
+    for (int f = 1; f < rounds; ++f) t_fix = t_fix + kTile * NW < n_vis ? t_fix + kTile * NW : t_fix;
+  }
+  const int own_end = ra < rb ? rb : (t_fix + kTile < n_vis ? t_fix + kTile : n_vis);
   const int k_last = own_end > 0 ? own_end : 1;
   const int v_end = own_end < n_rows ? own_end : n_rows;
   // (paged: V rows are clamped like K rows, so that one page serves both; slots below n_vis are allocated,
   // and whatever lies past n_rows meets a zero weight)
   const int v_last = PAGED ? k_last : (v_end > 0 ? v_end : 1);
+  const bool past_caches = STREAM && n_vis > p.fit_slots;
   // paged: the page of the next tile to fetch is looked up one tile ahead of its use
   int pg_nxt = 0;
   if (PAGED) pg_nxt = page_of(clamp_tile(ra, k_last));
@@ -527,7 +565,7 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   // unconditionally (clamped), so the loop never drains its outstanding loads.
   // t: first slot of the tile; hi: end of the slots of this tile that belong to this wave;
   // tn: first slot of the wave's next tile (any value when there is none: the loads are clamped)
-  auto tile = [&](int t, int hi, int tn) {
+  auto tile = [&](int t, int hi, int tn, bool past) {
     const int att_hi = hi < n_rows ? hi : n_rows;
     const int pend_hi = hi < n_prev ? hi : n_prev;
 
@@ -556,7 +594,13 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
       nv_end = v_last - page_start;
       pg_nxt = page_of(clamp_tile(tn + kTile, k_last));
     }
-    load_k_tile<D>(kf, Kb + nb, nt, r16, kg, nk_end);
+    if (STREAM && past) {
+      DYNTS_OWN_BRANCH;
+      load_k_tile<D, true>(kf, Kb + nb, nt, r16, kg, nk_end);
+      DYNTS_OWN_BRANCH;
+    } else {
+      load_k_tile<D>(kf, Kb + nb, nt, r16, kg, nk_end);
+    }
     if (PENDING) {
       const int tok = tn + (lane & (kTile - 1));
       s_old = Sb[tok < p.cap ? tok : p.cap - 1];
@@ -654,7 +698,13 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
       for (int it = 0; it < VIT; ++it)
         *reinterpret_cast<u32x4 *>(vst + (VROWS * it + vrow_l) * VSTRIDE + 16 * vpiece) = vf[it];
       wave_lds_fence();
-      load_v_tile<D>(vf, Vb + nb, nt, lane, nv_end);
+      if (STREAM && past) {
+        DYNTS_OWN_BRANCH;
+        load_v_tile<D, true>(vf, Vb + nb, nt, lane, nv_end);
+        DYNTS_OWN_BRANCH;
+      } else {
+        load_v_tile<D>(vf, Vb + nb, nt, lane, nv_end);
+      }
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) {
         // V^T operand: lane (c = 16 cb + r16, kg) gets V[t + 16 s + 4 kg + i][c] as element 4 s + i.
@@ -674,9 +724,15 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
     }
   };
 
-  if (t < n_vis) tile(t, t + kTile < n_vis ? t + kTile : n_vis, ra);
+  if (t < n_vis) tile(t, t + kTile < n_vis ? t + kTile : n_vis, t < t_fix ? t + kTile * NW : ra, t == t_fix && past_caches);
   seq_settle();
-  for (t = ra; t < rb; t += kTile) tile(t, rb, t + kTile);
+  if (STREAM) {
+    while (t < t_fix) {
+      t += kTile * NW;
+      tile(t, t + kTile < n_vis ? t + kTile : n_vis, t < t_fix ? t + kTile * NW : ra, t == t_fix && past_caches);
+    }
+  }
+  for (t = ra; t < rb; t += kTile) tile(t, rb, t + kTile, past_caches);
   flush_scores();
 
   if (!ATTEND) return;

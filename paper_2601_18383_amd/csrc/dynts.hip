@@ -171,19 +171,21 @@ LayerView layer_view(const dynts_ctx *ctx, int layer) {
 // kernel's own begin and end
 template <int D, int W, bool ATTEND, bool PENDING, bool APPEND>
 void launch_partial(const dynts::AttendParams &p, dim3 grid, hipStream_t st, hipEvent_t start, hipEvent_t stop) {
-  const bool burst = PENDING && p.score_tiles > 1;  // score writes in bursts: a kernel variant of its own (registers)
+  // larger than the memory-side cache: a kernel variant of its own, with score writes in bursts (paged) or with loads past
+  // that cache (dense)
+  const bool large = p.block_table ? PENDING && p.score_tiles > 1 : p.fit_slots < p.cap;
   const bool spill = ATTEND && p.spill != nullptr;   // so is the step that keeps its logits
-#define DYNTS_LAUNCH(PAGED, BURST, SPILL)                                                                           \
-  hipExtLaunchKernelGGL((dynts::attend_kernel<D, W, ATTEND, PENDING, APPEND, PAGED, BURST, SPILL>), grid,            \
+#define DYNTS_LAUNCH(PAGED, LARGE, SPILL)                                                                           \
+  hipExtLaunchKernelGGL((dynts::attend_kernel<D, W, ATTEND, PENDING, APPEND, PAGED, LARGE, SPILL>), grid,            \
                         dim3(W * 64), 0, st, start, stop, 0, p)
-#define DYNTS_LAUNCH2(PAGED, BURST)              \
-  if (spill) DYNTS_LAUNCH(PAGED, BURST, ATTEND); \
-  else DYNTS_LAUNCH(PAGED, BURST, false)
+#define DYNTS_LAUNCH2(PAGED, LARGE)              \
+  if (spill) DYNTS_LAUNCH(PAGED, LARGE, ATTEND); \
+  else DYNTS_LAUNCH(PAGED, LARGE, false)
   if (p.block_table) {
-    if (burst) { DYNTS_LAUNCH2(true, PENDING); }
+    if (large) { DYNTS_LAUNCH2(true, PENDING); }
     else { DYNTS_LAUNCH2(true, false); }
   } else {
-    if (burst) { DYNTS_LAUNCH2(false, PENDING); }
+    if (large) { DYNTS_LAUNCH2(false, true); }
     else { DYNTS_LAUNCH2(false, false); }
   }
 #undef DYNTS_LAUNCH2
@@ -238,9 +240,21 @@ int run_attend(dynts_ctx *ctx, int layer, const uint16_t *q, const uint16_t *k_n
   p.part_o = tr.part_o;
   p.part_ml = tr.part_ml;
   p.tag = next_launch_tag();
-  // score writes: tile by tile while the layer's K and V fit the memory-side cache (256 MB), in bursts beyond
+  // paged layout: scores are written tile by tile while the layer's K and V fit the memory-side cache (256 MB), in
+  // bursts beyond
   const double kv_bytes = 4.0 * c.batch * c.n_kv_heads * (double)c.capacity * c.head_dim;
   p.score_tiles = kv_bytes > 192e6 ? 16 : 1;
+  // K and V past the memory-side cache: only when all layers together are more than what still gains from it (one layer of
+  // 303 MB is 3 % faster through it, 323 MB is not), and when a launch is long enough to be bound by the stream (128 or
+  // more units, 100 MB or more; below, shorter and more uneven launches lose 2 - 4 % with it).  272 MB of fixed places:
+  // 320 MB costs up to 4 %, 410 MB all of the gain.  Per period, before and after: 512 units x 2640 slots x 2 layers
+  // 8.46 -> 7.40 ms; 384 units x 2464 slots 6.40 -> 5.77; 128 units x 4 layers 9.75 -> 8.64; 256 units x 16 layers of
+  // 63 MB x 2 28.2 -> 26.9.
+  const double slot_bytes = 4.0 * c.n_layers * c.batch * c.n_kv_heads * c.head_dim;
+  const bool stream_bound = (long long)c.batch * c.n_kv_heads >= 128 && kv_bytes >= 100e6;
+  const double fit = stream_bound ? 310e6 / slot_bytes : 1e9, rounds = 272e6 / (slot_bytes * pl.nsplit * pl.waves * dynts::kTile);
+  p.fit_slots = (int)(fit < 1e9 ? fit : 1e9);
+  p.rounds = (int)(rounds < 1e6 ? rounds : 1e6);
   p.spill = keep_logits ? reinterpret_cast<float *>(ctx->ws + pl.off_spill) : nullptr;
   p.cap_pad = pl.cap_pad;
   p.unit_cnt = tr.unit_cnt;

@@ -446,3 +446,62 @@ def test_attend_then_update_by_any_route(B, d, Hq, Hkv):
     attend(0, True, fused=True)                           # announced logits take the room from the other layer
     check()
     assert int(cache.status.item()) == 0
+
+
+@pytest.mark.parametrize("Nb,Hq,Hkv,d,cap,layers", [(16, 16, 8, 128, 5000, 1), (40, 8, 4, 64, 8100, 1), (16, 16, 8, 128, 1700, 3)])
+def test_caches_beyond_the_memory_side_cache(B, Nb, Hq, Hkv, d, cap, layers):
+    """Caches of more than 310 MB: tiles at fixed places first, the rest loaded past the memory-side cache.  Ragged lengths
+    around the ends of the rounds of fixed tiles, around the length from which the rest goes past the cache, around
+    tiles and at both ends, in every form of the step."""
+    units, G = Nb * Hkv, Hq // Hkv
+    slot = 4 * layers * units * d
+    assert slot * cap > 310e6 and units >= 128 and slot * cap / layers >= 100e6
+    fit, per_round = int(310e6 / slot), 8 * 32 * max(1, (256 + units // 2) // units)
+    full = int(272e6 / (slot * per_round)) * per_round
+    lens = [0, 1, 31, 33, per_round - 1, per_round, per_round + 1, 2 * per_round + 40, full - 1, full, full + 33, fit - 1,
+            fit, fit + 1, cap - 35, cap - 4]
+    lens = np.array([min(max(x, 0), cap - 4) for x in (lens * 3)[:Nb]], np.int32)
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev)
+    g.manual_seed(cap)
+    normal = lambda *s: torch.randn(s, generator=g, device=dev).to(torch.bfloat16)
+    cache = B.Cache(layers, Nb, Hq, Hkv, d, cap, cap - 200, 10, 10)
+    layer = layers - 1
+    cache.K[layer].copy_(normal(Nb, Hkv, cap, d))
+    cache.V[layer].copy_(normal(Nb, Hkv, cap, d))
+    M = 7
+    cache.S[layer, :, :, :M] = float("inf")
+    cache.n_prompt.fill_(M)
+    cache.seq_len[layer].copy_(torch.from_numpy(lens).to(dev))
+    K, V = cache.K[layer].cpu().double(), cache.V[layer].cpu().double()
+    want = torch.zeros((Nb, Hkv, cap), dtype=torch.float64)
+    out, lse = torch.zeros((Nb, Hq, d), device=dev), torch.zeros((Nb, Hq), device=dev)
+    n = lens.copy()
+    for step in ("first", "step", "hinted", "attend_update", "attend", "step"):
+        q, k1, v1 = normal(Nb, Hq, d), normal(Nb, Hkv, d), normal(Nb, Hkv, d)
+        if step.startswith("attend"):
+            (B.dynts_decode_attend if step == "attend" else B.dynts_decode_attend_update)(cache.ctx, layer, q, out, lse)
+        else:
+            if step == "hinted":
+                B.dynts_hint_trigger(cache.ctx, layer)
+            B.dynts_decode_step(cache.ctx, layer, q, k1, v1, out, lse=lse)
+            for b in range(Nb):
+                K[b, :, n[b]], V[b, :, n[b]] = k1[b].cpu().double(), v1[b].cpu().double()
+            n += 1
+        if step not in ("first", "step"):  # (an unfused call drops what the one before it still owes)
+            B.dynts_update_scores(cache.ctx, layer)
+        for b in range(Nb):
+            x = torch.matmul(q[b].cpu().double().view(Hkv, G, d), K[b, :, :n[b]].transpose(1, 2)) / np.sqrt(d)
+            if n[b] == 0:
+                continue
+            a = torch.softmax(x, dim=-1)
+            assert_close(f64(out)[b], torch.matmul(a, V[b, :, :n[b]]).reshape(Hq, d).numpy(), "out[%d], %s" % (b, step))
+            assert_close(f64(lse)[b], torch.logsumexp(x, dim=-1).reshape(Hq).numpy(), "lse[%d], %s" % (b, step))
+            want[b, :, M:n[b]] += a.sum(1)[:, M:]
+    B.dynts_update_scores(cache.ctx, layer)
+    S = f64(cache.S[layer])
+    for b in range(Nb):
+        assert_close(S[b, :, M:n[b]], want[b, :, M:n[b]].numpy(), "S[%d]" % b)
+        assert np.all(S[b, :, max(M, n[b]):] == 0)
+    assert int(cache.status.item()) == 0
+    cache.close()
