@@ -32,6 +32,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace dynts {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -743,45 +745,9 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   const bool has_partial = split < chunks_now;  // workgroup-uniform; false: the chunk only carried a deferred update
   if (chunks_vis == 1 && !has_partial) return;
 
-  // Merging (several chunks per unit): thread tid owns output elements tid + k * kThreads, in its own partial
-  // and in the merge; chunks are merged kMergeGroup at a time, in chunk order.  Asking for a group means:
-  // every thread requests its elements of the group's partials, and threads 0 .. 16 * kMergeGroup - 1 the
-  // (max, sum) of one (chunk, head) each; this workgroup's own partial never comes from memory.
   constexpr int NE = (16 * D + kThreads - 1) / kThreads;  // output elements per thread at the largest group size
-  constexpr int kMergeGroup = 4;
   const int ne = (G * D + kThreads - 1) / kThreads;
   const size_t ubase = unit * p.nsplit * (size_t)G;
-  uint64_t ask_o[NE][kMergeGroup], ask_m = 0, ask_l = 0;
-  auto ask_group = [&](int s0) {
-#pragma unroll
-    for (int k = 0; k < NE; ++k) {
-      const int idx = tid + k * kThreads;
-#pragma unroll
-      for (int j = 0; j < kMergeGroup; ++j) {
-        const int sj = s0 + j;
-        ask_o[k][j] = (uint64_t)p.tag << 32;  // nothing to wait for
-        if (k < ne && idx < G * D && sj < chunks_now && !(has_partial && sj == split))
-          ask_o[k][j] = tagged_load(&p.part_o[(ubase + (size_t)sj * G + idx / D) * D + idx % D]);
-      }
-    }
-    ask_m = ask_l = (uint64_t)p.tag << 32;
-    if (tid < 16 * kMergeGroup) {
-      const int sj = s0 + (tid >> 4), gg = tid & 15;
-      if (sj < chunks_now && gg < G && !(has_partial && sj == split)) {
-        const uint64_t *src = &p.part_ml[(ubase + (size_t)sj * G + gg) * 2];
-        ask_m = tagged_load(src);
-        ask_l = tagged_load(src + 1);
-      }
-    }
-  };
-  auto group_fresh = [&]() {
-    bool ok = tag_is(ask_m, p.tag) && tag_is(ask_l, p.tag);
-#pragma unroll
-    for (int k = 0; k < NE; ++k)
-#pragma unroll
-      for (int j = 0; j < kMergeGroup; ++j) ok = ok && tag_is(ask_o[k][j], p.tag);
-    return ok;
-  };
 
   // ---- combine the four waves ------------------------------------------------------------
   float *ored = reinterpret_cast<float *>(smem);
@@ -871,62 +837,110 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   if (tid == 0) __hip_atomic_store(&p.unit_cnt[unit], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (chunks_now == 0) return;
 
-  __shared__ float sm_pm[kMergeGroup][16], sm_pl[kMergeGroup][16];
-  float m_e[NE], L_e[NE], o_e[NE];
+  // Merging: thread tid owns output elements tid + k * kThreads, k < E, in its own partial and in the merge; chunks are
+  // merged N at a time, in chunk order.  Asking for a group means: every thread requests its elements of the group's
+  // partials, and threads 0 .. 16 * N - 1 the (max, sum) of one (chunk, head) each; this workgroup's own partial never
+  // comes from memory.  A round of asking takes a trip to the level all XCDs share, so with few elements per thread as
+  // many chunks are asked for at once as the same registers hold.  (One sequence on 8 KV heads, 18 chunks: five
+  // rounds of four took 17.3 us a launch, one of 32 takes 16.1; 7 heads a group, up to ten chunks in groups of eight
+  // instead of four: 15.2 -> 14.4.  Sixteen instead of eight there costs 2 - 17 % of every launch.)
+  constexpr int kMostChunks = kThreads / 16;  // whose statistics the workgroup's threads can ask for at once
+  __shared__ float sm_pm[kMostChunks][16], sm_pl[kMostChunks][16];
+  auto merge = [&](auto E_, auto N_) {
+    constexpr int E = decltype(E_)::value, N = decltype(N_)::value;
+    static_assert(N <= kMostChunks, "one thread per (chunk, head)");
+    uint64_t ask_o[E][N], ask_m, ask_l;
+    auto ask_group = [&](int s0) {
 #pragma unroll
-  for (int k = 0; k < NE; ++k) {
-    m_e[k] = -INFINITY;
-    L_e[k] = 0.f;
-    o_e[k] = 0.f;
-  }
-  for (int s0 = 0; s0 < chunks_now; s0 += kMergeGroup) {
-    ask_group(s0);
-    while (!group_fresh()) ask_group(s0);  // a word that is not this launch's yet is on its way: ask again
-    if (tid < 16 * kMergeGroup) {
-      const int j = tid >> 4, gg = tid & 15, sj = s0 + j;
-      if (sj < chunks_now && gg < G) {
-        const bool mine = has_partial && sj == split;
-        sm_pm[j][gg] = mine ? sm_fin[0][gg] : tagged_value(ask_m);
-        sm_pl[j][gg] = mine ? sm_fin[1][gg] : tagged_value(ask_l);
+      for (int k = 0; k < E; ++k) {
+        const int idx = tid + k * kThreads;
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+          const int sj = s0 + j;
+          ask_o[k][j] = (uint64_t)p.tag << 32;  // nothing to wait for
+          if (idx < G * D && sj < chunks_now && !(has_partial && sj == split))
+            ask_o[k][j] = tagged_load(&p.part_o[(ubase + (size_t)sj * G + idx / D) * D + idx % D]);
+        }
       }
+      ask_m = ask_l = (uint64_t)p.tag << 32;
+      if (tid < 16 * N) {
+        const int sj = s0 + (tid >> 4), gg = tid & 15;
+        if (sj < chunks_now && gg < G && !(has_partial && sj == split)) {
+          const uint64_t *src = &p.part_ml[(ubase + (size_t)sj * G + gg) * 2];
+          ask_m = tagged_load(src);
+          ask_l = tagged_load(src + 1);
+        }
+      }
+    };
+    auto group_fresh = [&]() {
+      bool ok = tag_is(ask_m, p.tag) && tag_is(ask_l, p.tag);
+#pragma unroll
+      for (int k = 0; k < E; ++k)
+#pragma unroll
+        for (int j = 0; j < N; ++j) ok = ok && tag_is(ask_o[k][j], p.tag);
+      return ok;
+    };
+    float m_e[E], L_e[E], o_e[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+      m_e[k] = -INFINITY;
+      L_e[k] = 0.f;
+      o_e[k] = 0.f;
     }
-    __syncthreads();
+    for (int s0 = 0; s0 < chunks_now; s0 += N) {
+      ask_group(s0);
+      while (!group_fresh()) ask_group(s0);  // a word that is not this launch's yet is on its way: ask again
+      if (tid < 16 * N) {
+        const int j = tid >> 4, gg = tid & 15, sj = s0 + j;
+        if (sj < chunks_now && gg < G) {
+          const bool mine = has_partial && sj == split;
+          sm_pm[j][gg] = mine ? sm_fin[0][gg] : tagged_value(ask_m);
+          sm_pl[j][gg] = mine ? sm_fin[1][gg] : tagged_value(ask_l);
+        }
+      }
+      __syncthreads();
 #pragma unroll
-    for (int k = 0; k < NE; ++k) {
+      for (int k = 0; k < E; ++k) {
+        const int idx = tid + k * kThreads;
+        if (idx < G * D) {
+          const int gg = idx / D;
+#pragma unroll
+          for (int j = 0; j < N; ++j) {
+            if (s0 + j < chunks_now) {
+              const float ms = sm_pm[j][gg], ls = sm_pl[j][gg];
+              const float ov = (has_partial && s0 + j == split) ? own_o[k] : tagged_value(ask_o[k][j]);
+              const float mn = fmaxf(m_e[k], ms);  // finite: a chunk that has a partial has attended a slot
+              const float fa = fast_exp2(m_e[k] - mn), fb = fast_exp2(ms - mn);
+              L_e[k] = L_e[k] * fa + ls * fb;
+              o_e[k] = o_e[k] * fa + ov * fb;
+              m_e[k] = mn;
+            }
+          }
+        }
+      }
+      if (s0 + N < chunks_now) __syncthreads();  // the statistics' LDS is written again
+    }
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
       const int idx = tid + k * kThreads;
-      if (k < ne && idx < G * D) {
-        const int gg = idx / D;
-#pragma unroll
-        for (int j = 0; j < kMergeGroup; ++j) {
-          if (s0 + j < chunks_now) {
-            const float ms = sm_pm[j][gg], ls = sm_pl[j][gg];
-            const float ov = (has_partial && s0 + j == split) ? own_o[k] : tagged_value(ask_o[k][j]);
-            const float mn = fmaxf(m_e[k], ms);  // finite: a chunk that has a partial has attended a slot
-            const float fa = fast_exp2(m_e[k] - mn), fb = fast_exp2(ms - mn);
-            L_e[k] = L_e[k] * fa + ls * fb;
-            o_e[k] = o_e[k] * fa + ov * fb;
-            m_e[k] = mn;
+      if (idx < G * D) {
+        const int gg = idx / D, c = idx % D;
+        p.out[(orow0 + gg) * D + c] = o_e[k] / L_e[k];
+        if (c == 0) {
+          if (p.lse) p.lse[orow0 + gg] = (m_e[k] + log2f(L_e[k])) * 0.6931471805599453f;
+          if (p.track) {
+            p.mlprev[(orow0 + gg) * 2] = m_e[k];
+            p.mlprev[(orow0 + gg) * 2 + 1] = L_e[k];
           }
         }
       }
     }
-    if (s0 + kMergeGroup < chunks_now) __syncthreads();  // the statistics' LDS is written again
-  }
-#pragma unroll
-  for (int k = 0; k < NE; ++k) {
-    const int idx = tid + k * kThreads;
-    if (k < ne && idx < G * D) {
-      const int gg = idx / D, c = idx % D;
-      p.out[(orow0 + gg) * D + c] = o_e[k] / L_e[k];
-      if (c == 0) {
-        if (p.lse) p.lse[orow0 + gg] = (m_e[k] + log2f(L_e[k])) * 0.6931471805599453f;
-        if (p.track) {
-          p.mlprev[(orow0 + gg) * 2] = m_e[k];
-          p.mlprev[(orow0 + gg) * 2 + 1] = L_e[k];
-        }
-      }
-    }
-  }
+  };
+  // (up to four chunks in groups of four, whatever the elements: most launches, and the shortest code on their way.  The
+  // paged kernel has that form only: with the others in it, 128 units of two chunks take 4 % longer.)
+  if (!PAGED && ne == 1 && chunks_now > 4) merge(std::integral_constant<int, 1>{}, std::integral_constant<int, 4 * kWaves>{});
+  else if (!PAGED && NE >= 2 && ne <= 2 && chunks_now > 4) merge(std::integral_constant<int, NE >= 2 ? 2 : 1>{}, std::integral_constant<int, 8>{});
+  else merge(std::integral_constant<int, NE>{}, std::integral_constant<int, 4>{});
 }
 
 // The score update of a step whose logits were kept (AttendParams::spill): S[slot] += sum over the group of

@@ -505,3 +505,30 @@ def test_caches_beyond_the_memory_side_cache(B, Nb, Hq, Hkv, d, cap, layers):
         assert np.all(S[b, :, max(M, n[b]):] == 0)
     assert int(cache.status.item()) == 0
     cache.close()
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,n,shape", [(4, 1, 128, 9001, (256, 8)), (4, 1, 128, 1300, (256, 8)), (8, 1, 128, 4700, (256, 8)),
+                                              (16, 1, 128, 2600, (256, 8)), (8, 1, 64, 8448, (256, 8)), (2, 1, 128, 2900, (256, 4)),
+                                              (16, 1, 128, 1500, (256, 4)), (5, 1, 64, 1153, (256, 4))])
+def test_merge_of_many_chunks(B, Hq, Hkv, d, n, shape):
+    """One unit cut into up to 36 chunks: every grouping of the merge (one, two and more output elements per thread), whole and
+    partial last groups, chunks that are empty because the sequence is shorter than the capacity."""
+    rng = np.random.default_rng(n + Hq)
+    dev = torch.device("cuda:0")
+    cap = n + 300
+    cache = B.Cache(1, 2, Hq, Hkv, d, cap, n, 10, 10, launch_shape=shape)
+    lens = [n, max(1, n // 3)]
+    cache.K[0].copy_(_bf16(rng, 2, Hkv, cap, d))
+    cache.V[0].copy_(_bf16(rng, 2, Hkv, cap, d))
+    cache.seq_len[0].copy_(torch.tensor(lens, dtype=torch.int32))
+    out, lse = torch.zeros((2, Hq, d), device=dev), torch.zeros((2, Hq), device=dev)
+    for _ in range(2):
+        q = _bf16(rng, 2, Hq, d, scale=1.5)
+        B.dynts_decode_attend_update(cache.ctx, 0, q.to(dev), out, lse)
+        for b in range(2):
+            x = f64(q)[b] @ f64(cache.K[0, b, 0, :lens[b]]).T / np.sqrt(d)
+            a = np.exp(x - x.max(1, keepdims=True))
+            assert_close(f64(out)[b], a / a.sum(1, keepdims=True) @ f64(cache.V[0, b, 0, :lens[b]]), "out[%d]" % b)
+            assert_close(f64(lse)[b], x.max(1) + np.log(a.sum(1)), "lse[%d]" % b)
+    B.dynts_update_scores(cache.ctx, 0)
+    assert abs(float(cache.S[0, 0].sum()) - 2 * Hq) < 1e-3 * Hq
