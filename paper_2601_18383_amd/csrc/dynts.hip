@@ -128,6 +128,15 @@ uint32_t next_launch_tag() {
   return t;
 }
 
+// What is recorded into a graph may be replayed in any order with other graphs and with eager calls, which the
+// context's bookkeeping does not see.  (An error of the query, the null stream beside a capture, counts as a capture.)
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 int check_call(const dynts_ctx *ctx, int32_t layer) {
   if (!ctx) return DYNTS_ENULL;
   if (!ctx->bound) return DYNTS_ENOTBOUND;
@@ -618,9 +627,12 @@ int dynts_decode_attend(dynts_ctx *ctx, int32_t layer, const uint16_t *q, const 
   // it (4 bytes per slot and head written, against a second pass over K), unless the buffer holds those of
   // another layer whose update rests on them alone.  32 x 8 units of 5256 slots, both calls: 182 -> 154 us
   // (the attention 117 -> 143, the update 62 -> 10).
+  // Not under capture: the buffer is one for all layers, so the update's graph would find in it whatever the last attention
+  // replayed or issued before it left there, while the saved query and statistics it needs for its pass over K are the
+  // layer's own.
   const bool track = ctx->cfg.score_mode == DYNTS_SCORE_ACCUMULATE;
-  const bool keep = track && (ctx->spill_layer < 0 || ctx->pending[ctx->spill_layer] == 3);
-  if (keep) release_spill(ctx, static_cast<hipStream_t>(stream));
+  const bool keep = track && (ctx->spill_layer < 0 || ctx->pending[ctx->spill_layer] == 3) && !capturing(static_cast<hipStream_t>(stream));
+  if (keep || ctx->spill_layer == layer) release_spill(ctx, static_cast<hipStream_t>(stream));
   rc = run_attend(ctx, layer, q, nullptr, nullptr, nullptr, active, out, lse, true, false, false,
                   static_cast<hipStream_t>(stream), nullptr, keep);
   if (rc == DYNTS_OK) {
@@ -634,6 +646,7 @@ int dynts_update_scores(dynts_ctx *ctx, int32_t layer, void *stream) {
   int rc = check_call(ctx, layer);
   if (rc != DYNTS_OK) return rc;
   if (!ctx->pending[layer]) return DYNTS_OK;
+  if (ctx->pending[layer] == 3 && capturing(static_cast<hipStream_t>(stream))) release_spill(ctx, static_cast<hipStream_t>(stream));
   if (ctx->pending[layer] >= 2) return apply_spill(ctx, layer, static_cast<hipStream_t>(stream));
   rc = run_attend(ctx, layer, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, false, true, false,
                   static_cast<hipStream_t>(stream));

@@ -448,6 +448,53 @@ def test_attend_then_update_by_any_route(B, d, Hq, Hkv):
     assert int(cache.status.item()) == 0
 
 
+@pytest.mark.parametrize("before", ["eager pair", "eager attend", ""])
+def test_captured_attend_and_update(B, before):
+    """The unfused pair recorded as graphs of their own, per layer: replayed in another order than recorded, with eager calls
+    of the same context between, every update adds the weights of its own layer's attention.  One workgroup per unit."""
+    dev = torch.device("cuda:0")
+    L, Nb, Hq, Hkv, d, M, n = 2, 2, 8, 4, 64, 5, 150
+    torch.manual_seed(3)
+    cache = B.Cache(L, Nb, Hq, Hkv, d, 200, 100, 20, 10, launch_shape=(1, 8))
+    cache.K.normal_()
+    cache.V.normal_()
+    cache.seq_len.fill_(n)
+    cache.n_prompt.fill_(M)
+    q = torch.randn(L, Nb, Hq, d, device=dev).to(torch.bfloat16)
+    q_other = torch.randn(Nb, Hq, d, device=dev).to(torch.bfloat16)
+    out, out_other = torch.zeros(L, Nb, Hq, d, device=dev), torch.zeros(Nb, Hq, d, device=dev)
+    if before:
+        B.dynts_decode_attend(cache.ctx, 0, q_other, out_other)
+    if before == "eager pair":
+        B.dynts_update_scores(cache.ctx, 0)
+    attend, update = [], []
+    torch.cuda.synchronize()
+    for l in range(L):
+        for what in (attend, update):
+            what.append(torch.cuda.CUDAGraph())
+            with torch.cuda.graph(what[l]):
+                if what is attend:
+                    B.dynts_decode_attend(cache.ctx, l, q[l], out[l])
+                else:
+                    B.dynts_update_scores(cache.ctx, l)
+    x = torch.matmul(q.cpu().double().view(L, Nb, Hkv, Hq // Hkv, d), cache.K[:, :, :, :n].cpu().double().transpose(3, 4)) / np.sqrt(d)
+    w = torch.softmax(x, dim=-1).sum(3)[..., M:].numpy()
+    for replay in range(3):
+        cache.S.zero_()
+        for g in attend:
+            g.replay()
+        if replay == 1:  # an attention outside the graphs, which leaves something in the workspace, too
+            B.dynts_decode_attend(cache.ctx, 1, q_other, out_other)
+            attend[1].replay()
+        torch.cuda.synchronize()
+        for g in update:
+            g.replay()
+        torch.cuda.synchronize()
+        for l in range(L):
+            assert_close(f64(cache.S[l])[..., M:n], w[l], "S, layer %d, replay %d" % (l, replay))
+    assert int(cache.status.item()) == 0
+
+
 @pytest.mark.parametrize("Nb,Hq,Hkv,d,cap,layers", [(16, 16, 8, 128, 5000, 1), (40, 8, 4, 64, 8100, 1), (16, 16, 8, 128, 1700, 3)])
 def test_caches_beyond_the_memory_side_cache(B, Nb, Hq, Hkv, d, cap, layers):
     """Caches of more than 310 MB: tiles at fixed places first, the rest loaded past the memory-side cache.  Ragged lengths
