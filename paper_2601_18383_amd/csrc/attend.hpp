@@ -92,6 +92,10 @@ struct AttendParams {
   int max_pages, n_pages;
 };
 
+// Chunks of a unit are merged four at a time; in the WIDE kernels with one output element per thread more than kWideFrom1
+// of them 32 at a time, with two (head_dim 128 only) more than kWideFrom2 of them eight at a time.
+constexpr int kWideFrom1 = 16, kWideFrom2 = 4;
+
 constexpr int kPageSlots = 64;  // slots per page: two tiles, so a tile never straddles pages
 
 
@@ -189,7 +193,9 @@ __device__ __forceinline__ void wave_lds_fence() {
 // BURST, updated scores leave in bursts through LDS (see flush_scores) instead of tile by tile.  (Not both: loads past
 // the cache made paged launches 5 % slower, and with them bursts gained nothing in the dense layout.)
 // SPILL: the step keeps its logits (AttendParams::spill) for a trigger that follows.
-template <int D, int W, bool ATTEND, bool PENDING, bool APPEND, bool PAGED = false, bool LARGE = false, bool SPILL = false>
+// WIDE: with the merges of 32 and of 8 chunks at a time (see merge below), whose registers every wave of the kernel pays for.
+template <int D, int W, bool ATTEND, bool PENDING, bool APPEND, bool PAGED = false, bool LARGE = false, bool SPILL = false,
+          bool WIDE = false>
 __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p) {
   constexpr int kWaves = W, kThreads = W * 64;
   constexpr int KS = D / 32;              // MFMA k-steps per K row
@@ -840,16 +846,17 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   // Merging: thread tid owns output elements tid + k * kThreads, k < E, in its own partial and in the merge; chunks are
   // merged N at a time, in chunk order.  Asking for a group means: every thread requests its elements of the group's
   // partials, and threads 0 .. 16 * N - 1 the (max, sum) of one (chunk, head) each; this workgroup's own partial never
-  // comes from memory.  A round of asking takes a trip to the level all XCDs share, so with few elements per thread as
-  // many chunks are asked for at once as the same registers hold.  (One sequence on 8 KV heads, 18 chunks: five
-  // rounds of four took 17.3 us a launch, one of 32 takes 16.1; 7 heads a group, up to ten chunks in groups of eight
-  // instead of four: 15.2 -> 14.4.  Sixteen instead of eight there costs 2 - 17 % of every launch.)
-  constexpr int kMostChunks = kThreads / 16;  // whose statistics the workgroup's threads can ask for at once
+  // comes from memory.  A round of asking takes a trip to the level all XCDs share, so with few elements per thread and many
+  // chunks as many are asked for at once as the same registers hold.
+  constexpr int kMostChunks = WIDE ? kThreads / 16 : 4;  // whose statistics are asked for at once, one thread per (chunk, head)
   __shared__ float sm_pm[kMostChunks][16], sm_pl[kMostChunks][16];
   auto merge = [&](auto E_, auto N_) {
     constexpr int E = decltype(E_)::value, N = decltype(N_)::value;
-    static_assert(N <= kMostChunks, "one thread per (chunk, head)");
+    static_assert(N <= kMostChunks && 16 * N <= kThreads, "one thread per (chunk, head)");
     uint64_t ask_o[E][N], ask_m, ask_l;
+    // (uniform.  At head_dim 64 it spares groups of up to eight heads the second element, 0.5 - 2 % of a launch of 10 to 33
+    // chunks; at head_dim 128 it costs the eight-chunk merges 1 %)
+    auto has = [&](int k) { return D == 128 || WIDE || PAGED || k < ne; };
     auto ask_group = [&](int s0) {
 #pragma unroll
       for (int k = 0; k < E; ++k) {
@@ -858,7 +865,7 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
         for (int j = 0; j < N; ++j) {
           const int sj = s0 + j;
           ask_o[k][j] = (uint64_t)p.tag << 32;  // nothing to wait for
-          if (idx < G * D && sj < chunks_now && !(has_partial && sj == split))
+          if (has(k) && idx < G * D && sj < chunks_now && !(has_partial && sj == split))
             ask_o[k][j] = tagged_load(&p.part_o[(ubase + (size_t)sj * G + idx / D) * D + idx % D]);
         }
       }
@@ -902,7 +909,7 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
 #pragma unroll
       for (int k = 0; k < E; ++k) {
         const int idx = tid + k * kThreads;
-        if (idx < G * D) {
+        if (has(k) && idx < G * D) {
           const int gg = idx / D;
 #pragma unroll
           for (int j = 0; j < N; ++j) {
@@ -936,11 +943,14 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
       }
     }
   };
-  // (up to four chunks in groups of four, whatever the elements: most launches, and the shortest code on their way.  The
-  // paged kernel has that form only: with the others in it, 128 units of two chunks take 4 % longer.)
-  if (!PAGED && ne == 1 && chunks_now > 4) merge(std::integral_constant<int, 1>{}, std::integral_constant<int, 4 * kWaves>{});
-  else if (!PAGED && NE >= 2 && ne <= 2 && chunks_now > 4) merge(std::integral_constant<int, NE >= 2 ? 2 : 1>{}, std::integral_constant<int, 8>{});
-  else merge(std::integral_constant<int, NE>{}, std::integral_constant<int, 4>{});
+  // (where the host chooses the wide merges: wide_merge in dynts.hip)
+  if constexpr (WIDE) {
+    if (ne == 1 && chunks_now > kWideFrom1) return merge(std::integral_constant<int, 1>{}, std::integral_constant<int, 32>{});
+    if constexpr (D == 128) {
+      if (ne == 2 && chunks_now > kWideFrom2) return merge(std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
+    }
+  }
+  merge(std::integral_constant<int, NE>{}, std::integral_constant<int, 4>{});
 }
 
 // The score update of a step whose logits were kept (AttendParams::spill): S[slot] += sum over the group of

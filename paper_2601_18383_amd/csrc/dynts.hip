@@ -176,6 +176,22 @@ LayerView layer_view(const dynts_ctx *ctx, int layer) {
   return v;
 }
 
+// Whether a launch takes the kernel with the wide merges.  Their registers (226 against 121 - 198) are every wave's, so a
+// head_dim 64 launch has them only where it has no second workgroup on a compute unit to lose (32 of an XCD's units'
+// chunks).  us a step, groups of four / wide:
+//   head_dim 128, 4 heads a group, 8 units: 10 chunks 14.2 / 14.5, 17 chunks 19.8 / 18.6, 18 chunks 17.4 / 16.1;
+//     12 units: 17 chunks 28.7 / 26.8; 16 units: 9 chunks 17.3 / 18.1, 11 chunks 21.5 / 22.0; 32 units: 6 chunks 20.1 / 22.1
+//   head_dim 128, 7 or 8 heads: 8 units, 10 chunks 15.5 / 14.6; 48 units, 5 chunks 25.4 / 24.3; every size between likewise
+//   head_dim 64, 4 heads: 8 units, 18 chunks 14.2 / 13.3, 17 chunks 15.0 / 14.4, 10 chunks 11.3 / 12.2; 12 units, 18 chunks
+//     16.4 / 17.6; 4 units (four XCDs), 33 chunks 19.0 / 21.2
+//   head_dim 64, 16 heads: 8 units, 18 chunks 16.3 / 16.8; 20 units, 9 chunks 14.8 / 15.4
+bool wide_merge(int D, int waves, int G, int nsplit, long long grid) {
+  const int ne = (G * D + 64 * waves - 1) / (64 * waves);  // output elements per thread
+  if (waves != 8) return false;
+  if (D == 64) return ne == 1 && nsplit > dynts::kWideFrom1 && grid <= 256;
+  return (ne == 1 && nsplit > dynts::kWideFrom1) || (ne == 2 && nsplit > dynts::kWideFrom2);
+}
+
 // start/stop (may be null) are attached to the dispatch itself, so their timestamps are the
 // kernel's own begin and end
 template <int D, int W, bool ATTEND, bool PENDING, bool APPEND>
@@ -184,18 +200,21 @@ void launch_partial(const dynts::AttendParams &p, dim3 grid, hipStream_t st, hip
   // that cache (dense)
   const bool large = p.block_table ? PENDING && p.score_tiles > 1 : p.fit_slots < p.cap;
   const bool spill = ATTEND && p.spill != nullptr;   // so is the step that keeps its logits
-#define DYNTS_LAUNCH(PAGED, LARGE, SPILL)                                                                           \
-  hipExtLaunchKernelGGL((dynts::attend_kernel<D, W, ATTEND, PENDING, APPEND, PAGED, LARGE, SPILL>), grid,            \
+#define DYNTS_LAUNCH(PAGED, LARGE, SPILL, WIDE)                                                                     \
+  hipExtLaunchKernelGGL((dynts::attend_kernel<D, W, ATTEND, PENDING, APPEND, PAGED, LARGE, SPILL, WIDE>), grid,      \
                         dim3(W * 64), 0, st, start, stop, 0, p)
-#define DYNTS_LAUNCH2(PAGED, LARGE)              \
-  if (spill) DYNTS_LAUNCH(PAGED, LARGE, ATTEND); \
-  else DYNTS_LAUNCH(PAGED, LARGE, false)
+#define DYNTS_LAUNCH2(PAGED, LARGE, WIDE)              \
+  if (spill) DYNTS_LAUNCH(PAGED, LARGE, ATTEND, WIDE); \
+  else DYNTS_LAUNCH(PAGED, LARGE, false, WIDE)
   if (p.block_table) {
-    if (large) { DYNTS_LAUNCH2(true, PENDING); }
-    else { DYNTS_LAUNCH2(true, false); }
+    if (large) { DYNTS_LAUNCH2(true, PENDING, false); }
+    else { DYNTS_LAUNCH2(true, false, false); }
+  } else if (large) {
+    DYNTS_LAUNCH2(false, true, false);
+  } else if (ATTEND && wide_merge(D, W, p.G, p.nsplit, grid.x)) {
+    DYNTS_LAUNCH2(false, false, (ATTEND && W == 8));
   } else {
-    if (large) { DYNTS_LAUNCH2(false, true); }
-    else { DYNTS_LAUNCH2(false, false); }
+    DYNTS_LAUNCH2(false, false, false);
   }
 #undef DYNTS_LAUNCH2
 #undef DYNTS_LAUNCH

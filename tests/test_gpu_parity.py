@@ -556,7 +556,8 @@ def test_caches_beyond_the_memory_side_cache(B, Nb, Hq, Hkv, d, cap, layers):
 
 @pytest.mark.parametrize("Hq,Hkv,d,n,shape", [(4, 1, 128, 9001, (256, 8)), (4, 1, 128, 1300, (256, 8)), (8, 1, 128, 4700, (256, 8)),
                                               (16, 1, 128, 2600, (256, 8)), (8, 1, 64, 8448, (256, 8)), (2, 1, 128, 2900, (256, 4)),
-                                              (16, 1, 128, 1500, (256, 4)), (5, 1, 64, 1153, (256, 4))])
+                                              (16, 1, 128, 1500, (256, 4)), (5, 1, 64, 1153, (256, 4)), (8, 1, 64, 6000, (256, 8)),
+                                              (3, 1, 64, 4205, (256, 8)), (2, 1, 128, 4097, (256, 8)), (5, 1, 128, 1040, (256, 8))])
 def test_merge_of_many_chunks(B, Hq, Hkv, d, n, shape):
     """One unit cut into up to 36 chunks: every grouping of the merge (one, two and more output elements per thread), whole and
     partial last groups, chunks that are empty because the sequence is shorter than the capacity."""
