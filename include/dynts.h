@@ -138,7 +138,12 @@ int dynts_append(dynts_ctx *ctx, int32_t layer, const uint16_t *k_new, const uin
 /* Decode attention (Eq. attn-score, Eq. attn-o): for each active sequence and query head,
  * out[b][hq][:] = sum_j softmax_j(q.k_j * scale) v_j over slots [0, seq_len[b]).
  * q bf16 [Nb][Hq][d]; out fp32 [Nb][Hq][d]; lse fp32 [Nb][Hq] (may be NULL) receives
- * log sum_j exp(logit_j).  Leaves what dynts_update_scores needs in the workspace. */
+ * log sum_j exp(logit_j).  Leaves what dynts_update_scores needs in the workspace.
+ * Where the last two such calls of the layer were each followed by its dynts_update_scores, before another attention that
+ * keeps its logits or a fused step of the layer (the first call of a context counts as such), and the group is small enough
+ * for it to pay, the call also leaves its logits there, 4 bytes per slot and query head: it takes up to a fifth longer, and
+ * the update adds them up instead of reading K again.  There is room for one layer's logits; under stream capture none are
+ * left. */
 int dynts_decode_attend(dynts_ctx *ctx, int32_t layer, const uint16_t *q, const uint8_t *active,
                         float *out, float *lse, void *stream);
 

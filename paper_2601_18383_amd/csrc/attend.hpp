@@ -66,9 +66,10 @@ struct AttendParams {
   uint64_t *part_ml;        // [Nb][Hkv][nsplit][G][2]
   uint32_t tag;             // this launch's serial number (never 0)
   int score_tiles;          // updated scores are written out every so many tiles of a wave (1 .. 16)
-  // When this step's own score update will be asked for by itself (a trigger is known to follow, or it is the unfused
-  // attention call), the step's scaled logits (log2 units) are kept, [Nb][Hkv][G][cap_pad] fp32, so that its score update can be applied from them (apply_spill_kernel) instead of
-  // a second pass over K.  Null: not kept.
+  // When this step's own score update is expected to be asked for by itself (a trigger is known to follow, or it is the
+  // unfused attention of a caller who asks for its update next), the step's scaled logits (log2 units) are kept,
+  // [Nb][Hkv][G][cap_pad] fp32, so that its score update can be applied from them (apply_spill_kernel) instead of by a
+  // second pass over K.  Null: not kept.
   float *spill;
   int cap_pad;              // cap rounded up to a whole tile: row pitch of the kept logits (a tile's store stays inside its row)
   uint32_t *unit_cnt;       // [Nb][Hkv] ticket counters, zero between launches
@@ -192,7 +193,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 // LARGE: the caches do not fit the memory-side cache.  Dense layout: STREAM, see AttendParams::fit_slots.  Paged layout:
 // BURST, updated scores leave in bursts through LDS (see flush_scores) instead of tile by tile.  (Not both: loads past
 // the cache made paged launches 5 % slower, and with them bursts gained nothing in the dense layout.)
-// SPILL: the step keeps its logits (AttendParams::spill) for a trigger that follows.
+// SPILL: the step keeps its logits (AttendParams::spill).
 // WIDE: with the merges of 32 and of 8 chunks at a time (see merge below), whose registers every wave of the kernel pays for.
 template <int D, int W, bool ATTEND, bool PENDING, bool APPEND, bool PAGED = false, bool LARGE = false, bool SPILL = false,
           bool WIDE = false>

@@ -80,7 +80,7 @@ Plan make_plan(const dynts_config &c, int target_wgs, int waves) {
   p.off_qprev = off;   off = align_up(off + 2 * LB * c.n_q_heads * c.head_dim * sizeof(uint16_t));  // two copies, used in turn
   p.off_mlprev = off;  off = align_up(off + LB * c.n_q_heads * 2 * sizeof(float));
   p.off_nprev = off;   off = align_up(off + LB * sizeof(int32_t));
-  // the logits of one step of one layer, kept when a trigger is known to follow (score_mode accumulate only)
+  // the logits of one step of one layer, where they are kept for its score update (score_mode accumulate only)
   p.cap_pad = (c.capacity + dynts::kTile - 1) / dynts::kTile * dynts::kTile;
   p.off_spill = off;
   if (c.score_mode == DYNTS_SCORE_ACCUMULATE) off = align_up(off + (size_t)units * p.G * p.cap_pad * sizeof(float));
@@ -104,6 +104,10 @@ struct dynts_ctx {
   std::vector<unsigned char> pending;
   std::vector<unsigned char> hint;     // per layer: a trigger follows the next fused step, keep its logits
   int spill_layer = -1;                // the layer the kept logits belong to (its pending is 2 or 3), or -1
+  // Whether an unfused attention's logits are worth keeping is learned from what follows it (see unfused_ends):
+  std::vector<unsigned char> pairs;    // per layer, up to 2: of its last ones in a row, those followed by their own update
+  int unfused_layer = -1;              // the layer whose unfused attention waits for that answer, or -1
+  bool pairs_known = false;            // some layer has had its answer
   std::vector<unsigned char> qslot;    // per layer: which copy of the saved query is current
   hipEvent_t ev_start = nullptr, ev_stop = nullptr;
   std::vector<hipEvent_t> ev_list_start, ev_list_stop;  // one pair per coming attend launch
@@ -316,7 +320,7 @@ int run_attend(dynts_ctx *ctx, int layer, const uint16_t *q, const uint16_t *k_n
 }
 
 
-// the score update of `layer` from its kept logits (pending == 2)
+// the score update of `layer` from its kept logits (pending 2 or 3)
 int apply_spill(dynts_ctx *ctx, int layer, hipStream_t st) {
   const dynts_config &c = ctx->cfg;
   const Plan &pl = ctx->plan;
@@ -344,6 +348,35 @@ int release_spill(dynts_ctx *ctx, hipStream_t st) {
   return DYNTS_OK;
 }
 
+// What came after the unfused attention that waits for an answer (if any does): `paired`, its own update, which kept logits
+// have served or would have; or not, a fused step, another attention of the layer, or of another layer, which would have taken the
+// buffer.  Logits are kept after two answers in a row for it, so that a caller who alternates does not pay for both; the
+// first answer on a context speaks for every layer until it has its own.
+constexpr unsigned char kPairsKeep = 2;
+void unfused_ends(dynts_ctx *ctx, bool paired) {
+  if (ctx->unfused_layer < 0) return;
+  if (!ctx->pairs_known) ctx->pairs.assign(ctx->pairs.size(), paired ? kPairsKeep : 0);
+  ctx->pairs_known = true;
+  unsigned char &n = ctx->pairs[ctx->unfused_layer];
+  n = !paired ? 0 : n < kPairsKeep ? n + 1 : n;
+  ctx->unfused_layer = -1;
+}
+
+// Kept logits are written and read once, 8 bytes per slot and head of the group; without them the update reads the slot's
+// K row again, 2 bytes per element.  us for both calls, second pass over K / kept:
+//   up to a quarter of the K row: 128 units of 5000 slots 82.2 / 62.3 (head_dim 128, 4 heads), 44.6 / 34.7 (64, 4); 8 units of
+//     5000 21.9 / 20.9 (128, 4), 24.0 / 24.4 (128, 8), 17.1 / 17.2 (64, 4)
+//   up to half of it: 128 units of 5000 44.2 / 37.7 (64, 8), 84.7 / 80.8 (128, 16); of 1200 16.9 / 18.1 (64, 8); 512 units of 1200
+//     40.0 / 35.3 (64, 8), 78.9 / 78.1 (128, 16); 8 units of 5000 17.7 / 19.5 (64, 8), 28.9 / 31.4 (128, 16); paged, 128 units of
+//     5000 85.6 / 94.9 (128, 16)
+//   all of it: 128 units of 1200 17.3 / 21.4 (64, 16), of 5000 44.5 / 43.8
+bool kept_logits_pay(const dynts_ctx *ctx) {
+  const dynts_config &c = ctx->cfg;
+  const int G = ctx->plan.G;
+  const double k_bytes = 2.0 * c.batch * c.n_kv_heads * (double)c.capacity * c.head_dim;
+  return 16 * G <= c.head_dim || (8 * G <= c.head_dim && !ctx->paged && k_bytes >= 64e6);
+}
+
 // One fused step (attention, the score update owed by the previous step, optionally the append) with the
 // bookkeeping of owed updates.  With a trigger announced for this layer (dynts_hint_trigger) the step keeps its
 // logits, and its own update is later applied from them instead of from a second pass over K.
@@ -353,6 +386,7 @@ int fused_step(dynts_ctx *ctx, int layer, const uint16_t *q, const uint16_t *k_n
   const bool track = ctx->cfg.score_mode == DYNTS_SCORE_ACCUMULATE;
   const bool keep = track && ctx->hint[layer];
   ctx->hint[layer] = 0;
+  if (keep || ctx->unfused_layer == layer) unfused_ends(ctx, false);
   int rc = DYNTS_OK;
   if (ctx->pending[layer] == 2) rc = apply_spill(ctx, layer, st);
   if (ctx->pending[layer] == 3 || keep) rc = rc == DYNTS_OK ? release_spill(ctx, st) : rc;
@@ -516,6 +550,7 @@ int dynts_create(const dynts_config *cfg, dynts_ctx **out) {
   ctx->scale_log2 = scale * 1.4426950408889634f;
   ctx->pending.assign((size_t)cfg->n_layers, 0);
   ctx->hint.assign((size_t)cfg->n_layers, 0);
+  ctx->pairs.assign((size_t)cfg->n_layers, kPairsKeep);
   ctx->qslot.assign((size_t)cfg->n_layers, 0);
   *out = ctx;
   return DYNTS_OK;
@@ -555,6 +590,9 @@ int dynts_bind(dynts_ctx *ctx, uint16_t *K, uint16_t *V, float *S, int32_t *pos,
   ctx->pending.assign(ctx->pending.size(), 0);
   ctx->hint.assign(ctx->hint.size(), 0);
   ctx->spill_layer = -1;
+  ctx->pairs.assign(ctx->pairs.size(), kPairsKeep);
+  ctx->pairs_known = false;
+  ctx->unfused_layer = -1;
   ctx->qslot.assign(ctx->qslot.size(), 0);
   ctx->bound = true;
   return DYNTS_OK;
@@ -603,6 +641,7 @@ int dynts_prefill(dynts_ctx *ctx, int32_t layer, const uint16_t *K0, const uint1
   }
   ctx->pending[layer] = 0;
   if (ctx->spill_layer == layer) ctx->spill_layer = -1;
+  if (ctx->unfused_layer == layer) ctx->unfused_layer = -1;
   return launch_status();
 }
 
@@ -642,21 +681,25 @@ int dynts_decode_attend(dynts_ctx *ctx, int32_t layer, const uint16_t *q, const 
     rc = apply_spill(ctx, layer, static_cast<hipStream_t>(stream));
     if (rc != DYNTS_OK) return rc;
   }
-  // Attention as a call of its own is what a caller makes who asks for the score update next: the logits are kept for
-  // it (4 bytes per slot and head written, against a second pass over K), unless the buffer holds those of
-  // another layer whose update rests on them alone.  32 x 8 units of 5256 slots, both calls: 182 -> 154 us
-  // (the attention 117 -> 143, the update 62 -> 10).
+  // A caller who asks for the score update next is served from the attention's logits (4 bytes per slot and head
+  // written, against a second pass over K): 32 x 8 units of 5256 slots, both calls 184 -> 135 us.  The attention by itself then
+  // takes longer (paged 121 -> 143 us), so they are kept only where the update has been seen to follow, and not while
+  // the buffer holds those of another layer whose update rests on them alone.
   // Not under capture: the buffer is one for all layers, so the update's graph would find in it whatever the last attention
   // replayed or issued before it left there, while the saved query and statistics it needs for its pass over K are the
   // layer's own.
+  unfused_ends(ctx, false);
   const bool track = ctx->cfg.score_mode == DYNTS_SCORE_ACCUMULATE;
-  const bool keep = track && (ctx->spill_layer < 0 || ctx->pending[ctx->spill_layer] == 3) && !capturing(static_cast<hipStream_t>(stream));
+  const bool keep = track && ctx->pairs[layer] == kPairsKeep && kept_logits_pay(ctx) &&
+                    (ctx->spill_layer < 0 || ctx->pending[ctx->spill_layer] == 3) &&
+                    !capturing(static_cast<hipStream_t>(stream));
   if (keep || ctx->spill_layer == layer) release_spill(ctx, static_cast<hipStream_t>(stream));
   rc = run_attend(ctx, layer, q, nullptr, nullptr, nullptr, active, out, lse, true, false, false,
                   static_cast<hipStream_t>(stream), nullptr, keep);
   if (rc == DYNTS_OK) {
     ctx->pending[layer] = track ? (keep ? 3 : 1) : 0;
     if (keep) ctx->spill_layer = layer;
+    if (track) ctx->unfused_layer = layer;
   }
   return rc;
 }
@@ -665,6 +708,7 @@ int dynts_update_scores(dynts_ctx *ctx, int32_t layer, void *stream) {
   int rc = check_call(ctx, layer);
   if (rc != DYNTS_OK) return rc;
   if (!ctx->pending[layer]) return DYNTS_OK;
+  if (ctx->unfused_layer == layer) unfused_ends(ctx, true);
   if (ctx->pending[layer] == 3 && capturing(static_cast<hipStream_t>(stream))) release_spill(ctx, static_cast<hipStream_t>(stream));
   if (ctx->pending[layer] >= 2) return apply_spill(ctx, layer, static_cast<hipStream_t>(stream));
   rc = run_attend(ctx, layer, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, false, true, false,
