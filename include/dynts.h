@@ -236,8 +236,8 @@ int dynts_decode_loop(dynts_ctx *ctx, int32_t n_steps, const uint16_t *q, const 
 /* Measurement hook: when both are non-NULL hipEvent_t handles (created by the caller with
  * timing enabled), every later attend launch of this context attaches them to the dispatch
  * of its streaming kernel (attention + deferred score update, the kernel that moves the K/V
- * bytes): `start` is stamped when that kernel begins, `stop` when it ends, so
- * hipEventElapsedTime(start, stop) is the kernel's own duration.  Pass NULLs to switch it off. */
+ * bytes; behind an unfused attention also its score update, from K or from kept logits): `start` is
+ * stamped when that kernel begins, `stop` when it ends, so hipEventElapsedTime(start, stop) is the kernel's own duration.  Pass NULLs to switch it off. */
 int dynts_set_kernel_events(dynts_ctx *ctx, void *start, void *stop);
 
 /* The same for a run of launches: `starts` and `stops` are host arrays of n hipEvent_t handles; the

@@ -320,15 +320,17 @@ int run_attend(dynts_ctx *ctx, int layer, const uint16_t *q, const uint16_t *k_n
 }
 
 
-// the score update of `layer` from its kept logits (pending 2 or 3)
+// the score update of `layer` from its kept logits (pending 2 or 3).  In place of the pass over K behind an unfused attention
+// it takes that launch's events.
 int apply_spill(dynts_ctx *ctx, int layer, hipStream_t st) {
   const dynts_config &c = ctx->cfg;
   const Plan &pl = ctx->plan;
   const LayerView lv = layer_view(ctx, layer);
   const dim3 grid((c.capacity + 256 * dynts::kApplyPerThread - 1) / (256 * dynts::kApplyPerThread), c.n_kv_heads * c.batch);
-  hipLaunchKernelGGL(dynts::apply_spill_kernel, grid, dim3(256), 0, st, lv.S,
-                     reinterpret_cast<const float *>(ctx->ws + pl.off_spill), lv.mlprev, lv.nprev, ctx->n_prompt,
-                     c.n_kv_heads, c.n_q_heads, pl.G, c.capacity, pl.cap_pad);
+  const bool timed = ctx->pending[layer] == 3;
+  hipExtLaunchKernelGGL(dynts::apply_spill_kernel, grid, dim3(256), 0, st, timed ? ctx->ev_start : nullptr,
+                        timed ? ctx->ev_stop : nullptr, 0, lv.S, reinterpret_cast<const float *>(ctx->ws + pl.off_spill),
+                        lv.mlprev, lv.nprev, ctx->n_prompt, c.n_kv_heads, c.n_q_heads, pl.G, c.capacity, pl.cap_pad);
   const int rc = launch_status();
   if (rc == DYNTS_OK) {
     ctx->pending[layer] = 0;

@@ -493,6 +493,27 @@ def test_unfused_attention_keeps_logits_where_its_update_follows(B, d, Hq, Hkv, 
     assert int(cache.status.item()) == 0
 
 
+@pytest.mark.parametrize("Hq", [4, 32])
+def test_kernel_events_of_the_update_behind_an_unfused_attention(B, Hq):
+    """dynts_set_kernel_events: the update's launch takes them, whether it adds up kept logits (two heads a group) or reads K."""
+    cache = B.Cache(1, 2, Hq, 2, 128, 200, 100, 20, 10)
+    cache.seq_len.fill_(150)
+    q = torch.randn(2, Hq, 128, device="cuda:0").to(torch.bfloat16)
+    out = torch.zeros(2, Hq, 128, device="cuda:0")
+    start, stop, between = [torch.cuda.Event(enable_timing=True) for _ in range(3)]
+    for e in (start, stop):
+        e.record()  # makes the handle
+    torch.cuda.synchronize()
+    B.dynts_set_kernel_events(cache.ctx, start.cuda_event, stop.cuda_event)
+    for _ in range(2):
+        B.dynts_decode_attend(cache.ctx, 0, q, out)
+        between.record()
+        B.dynts_update_scores(cache.ctx, 0)
+        torch.cuda.synchronize()
+        assert between.elapsed_time(start) > 0 and start.elapsed_time(stop) > 0
+    B.dynts_set_kernel_events(cache.ctx, None, None)
+
+
 @pytest.mark.parametrize("before", ["eager pair", "eager attend", ""])
 def test_captured_attend_and_update(B, before):
     """The unfused pair recorded as graphs of their own, per layer: replayed in another order than recorded, with eager calls
