@@ -97,6 +97,8 @@ struct AttendParams {
 // of them 32 at a time, with two (head_dim 128 only) more than kWideFrom2 of them eight at a time.
 constexpr int kWideFrom1 = 16, kWideFrom2 = 4;
 
+constexpr int kStream = 1, kBurst = 2;  // forms of the kernel for large caches
+
 constexpr int kPageSlots = 64;  // slots per page: two tiles, so a tile never straddles pages
 
 
@@ -190,12 +192,12 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// LARGE: the caches do not fit the memory-side cache.  Dense layout: STREAM, see AttendParams::fit_slots.  Paged layout:
-// BURST, updated scores leave in bursts through LDS (see flush_scores) instead of tile by tile.  (Not both: loads past
-// the cache made paged launches 5 % slower, and with them bursts gained nothing in the dense layout.)
+// LARGE: the caches do not fit the memory-side cache.  kStream (dense layout), see AttendParams::fit_slots.  kBurst: updated
+// scores leave in bursts through LDS (see flush_scores) instead of tile by tile.  (Not both: loads past the cache made
+// paged launches 5 % slower, and with them bursts gained nothing in the dense layout.)
 // SPILL: the step keeps its logits (AttendParams::spill).
 // WIDE: with the merges of 32 and of 8 chunks at a time (see merge below), whose registers every wave of the kernel pays for.
-template <int D, int W, bool ATTEND, bool PENDING, bool APPEND, bool PAGED = false, bool LARGE = false, bool SPILL = false,
+template <int D, int W, bool ATTEND, bool PENDING, bool APPEND, bool PAGED = false, int LARGE = 0, bool SPILL = false,
           bool WIDE = false>
 __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p) {
   constexpr int kWaves = W, kThreads = W * 64;
@@ -206,7 +208,8 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   constexpr int VIT = kTile / VROWS;
   constexpr int VSTRIDE = 2 * D + 32;     // bytes per staged V row (+32: transposing reads hit distinct banks)
   constexpr int OSTRIDE = D + 4;          // floats per row of the cross-wave output reduction
-  constexpr bool STREAM = LARGE && !PAGED, BURST = LARGE && PAGED;
+  constexpr bool STREAM = LARGE == kStream, BURST = LARGE == kBurst;
+  static_assert(!(STREAM && PAGED), "pages are loaded through the caches");
   static_assert(kWaves * kTile * VSTRIDE >= kWaves * 16 * OSTRIDE * 4, "LDS tile is reused for the reduction");
   __shared__ __align__(16) unsigned char smem[kWaves * kTile * VSTRIDE];
   __shared__ float sm_m[kWaves][16];
@@ -536,13 +539,12 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   int pg_nxt = 0;
   if (PAGED) pg_nxt = page_of(clamp_tile(ra, k_last));
 
-  // ---- updated scores leave in bursts -----------------------------------------------------------
+  // ---- updated scores leave in bursts (kBurst) ----------------------------------------------------
   // A tile updates 32 scores (128 bytes).  Written tile by tile these are small writes scattered through
-  // the read stream, which cost the memory system far more than their bytes (measured: 4 % of the launch
-  // for 1.2 % of the traffic).  So, when the launch says so (score_tiles > 1: the cache is larger than
-  // the memory-side cache; below that the single writes are absorbed and bursts at the end of a workgroup
-  // only lengthen its tail), a wave parks them in LDS and writes a run of consecutive tiles with
-  // 16 bytes per lane at once: when the run breaks, when score_tiles have gathered, and when the wave is
+  // the read stream, which beyond the memory-side cache cost the memory system far more than their bytes (measured: 4 % of
+  // the launch for 1.2 % of the traffic; within it they are absorbed, and bursts at the end of a workgroup only lengthen its
+  // tail).  So a wave parks them in LDS and writes a run of consecutive tiles with 16 bytes per lane at once: when the
+  // run breaks, when score_tiles have gathered, and when the wave is
   // done.  sc_base: first slot of the run, sc_n: tiles in it, [sc_lo, sc_hi): the slots that may be written
   // (thinking slots below the end of the deferred update and of this wave's share).
   float *sbuf = sm_score[PENDING && BURST ? wave : 0];

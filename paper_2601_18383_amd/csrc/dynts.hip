@@ -200,25 +200,25 @@ bool wide_merge(int D, int waves, int G, int nsplit, long long grid) {
 // kernel's own begin and end
 template <int D, int W, bool ATTEND, bool PENDING, bool APPEND>
 void launch_partial(const dynts::AttendParams &p, dim3 grid, hipStream_t st, hipEvent_t start, hipEvent_t stop) {
-  // larger than the memory-side cache: a kernel variant of its own, with score writes in bursts (paged) or with loads past
-  // that cache (dense)
-  const bool large = p.block_table ? PENDING && p.score_tiles > 1 : p.fit_slots < p.cap;
-  const bool spill = ATTEND && p.spill != nullptr;   // so is the step that keeps its logits
+  const bool spill = ATTEND && p.spill != nullptr;  // the step that keeps its logits: a form of its own
 #define DYNTS_LAUNCH(PAGED, LARGE, SPILL, WIDE)                                                                     \
   hipExtLaunchKernelGGL((dynts::attend_kernel<D, W, ATTEND, PENDING, APPEND, PAGED, LARGE, SPILL, WIDE>), grid,      \
                         dim3(W * 64), 0, st, start, stop, 0, p)
 #define DYNTS_LAUNCH2(PAGED, LARGE, WIDE)              \
   if (spill) DYNTS_LAUNCH(PAGED, LARGE, ATTEND, WIDE); \
   else DYNTS_LAUNCH(PAGED, LARGE, false, WIDE)
+  constexpr int kIfPending = PENDING ? dynts::kBurst : 0;  // (no scores to write otherwise)
   if (p.block_table) {
-    if (large) { DYNTS_LAUNCH2(true, PENDING, false); }
-    else { DYNTS_LAUNCH2(true, false, false); }
-  } else if (large) {
-    DYNTS_LAUNCH2(false, true, false);
-  } else if (ATTEND && wide_merge(D, W, p.G, p.nsplit, grid.x)) {
-    DYNTS_LAUNCH2(false, false, (ATTEND && W == 8));
+    if (PENDING && p.score_tiles > 1) { DYNTS_LAUNCH2(true, kIfPending, false); }
+    else { DYNTS_LAUNCH2(true, 0, false); }
+  } else if (p.fit_slots < p.cap) {
+    DYNTS_LAUNCH2(false, dynts::kStream, false);
+  } else if (ATTEND && wide_merge(D, W, p.G, p.nsplit, grid.x)) {  // (before bursts: 16 units of 30000 slots 46.3 us with those, 45.4 so)
+    DYNTS_LAUNCH2(false, 0, (ATTEND && W == 8));
+  } else if (PENDING && p.score_tiles > 1) {
+    DYNTS_LAUNCH2(false, kIfPending, false);
   } else {
-    DYNTS_LAUNCH2(false, false, false);
+    DYNTS_LAUNCH2(false, 0, false);
   }
 #undef DYNTS_LAUNCH2
 #undef DYNTS_LAUNCH
@@ -272,21 +272,23 @@ int run_attend(dynts_ctx *ctx, int layer, const uint16_t *q, const uint16_t *k_n
   p.part_o = tr.part_o;
   p.part_ml = tr.part_ml;
   p.tag = next_launch_tag();
-  // paged layout: scores are written tile by tile while the layer's K and V fit the memory-side cache (256 MB), in
-  // bursts beyond
-  const double kv_bytes = 4.0 * c.batch * c.n_kv_heads * (double)c.capacity * c.head_dim;
-  p.score_tiles = kv_bytes > 192e6 ? 16 : 1;
   // K and V past the memory-side cache: only when all layers together are more than what still gains from it (one layer of
   // 303 MB is 3 % faster through it, 323 MB is not), and when a launch is long enough to be bound by the stream (128 or
   // more units, 100 MB or more; below, shorter and more uneven launches lose 2 - 4 % with it).  272 MB of fixed places:
   // 320 MB costs up to 4 %, 410 MB all of the gain.  Per period, before and after: 512 units x 2640 slots x 2 layers
   // 8.46 -> 7.40 ms; 384 units x 2464 slots 6.40 -> 5.77; 128 units x 4 layers 9.75 -> 8.64; 256 units x 16 layers of
   // 63 MB x 2 28.2 -> 26.9.
+  const double kv_bytes = 4.0 * c.batch * c.n_kv_heads * (double)c.capacity * c.head_dim;
   const double slot_bytes = 4.0 * c.n_layers * c.batch * c.n_kv_heads * c.head_dim;
   const bool stream_bound = (long long)c.batch * c.n_kv_heads >= 128 && kv_bytes >= 100e6;
   const double fit = stream_bound ? 310e6 / slot_bytes : 1e9, rounds = 272e6 / (slot_bytes * pl.nsplit * pl.waves * dynts::kTile);
   p.fit_slots = (int)(fit < 1e9 ? fit : 1e9);
   p.rounds = (int)(rounds < 1e6 ? rounds : 1e6);
+  // Scores in bursts: where a layer's K and V do not fit the memory-side cache with room to spare, dense caches (those not loaded
+  // past it) only when all layers together do not fit.  us a step, tile by tile / in bursts: 64 units of 12000 slots
+  // 77.9 / 76.1, of 9800 60.6 / 57.8; 120 units of 6000 75.0 / 71.7; two layers of 112 units of 4000 49.1 / 48.0; head_dim 64, 64
+  // units of 24000 81.4 / 78.7; but one layer of 250 MB 42.3 / 42.7, of 295 MB 49.9 / 50.4.
+  p.score_tiles = kv_bytes > 192e6 && (ctx->paged || kv_bytes * c.n_layers > 310e6) ? 16 : 1;
   p.spill = keep_logits ? reinterpret_cast<float *>(ctx->ws + pl.off_spill) : nullptr;
   p.cap_pad = pl.cap_pad;
   p.unit_cnt = tr.unit_cnt;

@@ -561,24 +561,15 @@ def test_captured_attend_and_update(B, before):
     assert int(cache.status.item()) == 0
 
 
-@pytest.mark.parametrize("Nb,Hq,Hkv,d,cap,layers", [(16, 16, 8, 128, 5000, 1), (40, 8, 4, 64, 8100, 1), (16, 16, 8, 128, 1700, 3)])
-def test_caches_beyond_the_memory_side_cache(B, Nb, Hq, Hkv, d, cap, layers):
-    """Caches of more than 310 MB: tiles at fixed places first, the rest loaded past the memory-side cache.  Ragged lengths
-    around the ends of the rounds of fixed tiles, around the length from which the rest goes past the cache, around
-    tiles and at both ends, in every form of the step."""
-    units, G = Nb * Hkv, Hq // Hkv
-    slot = 4 * layers * units * d
-    assert slot * cap > 310e6 and units >= 128 and slot * cap / layers >= 100e6
-    fit, per_round = int(310e6 / slot), 8 * 32 * max(1, (256 + units // 2) // units)
-    full = int(272e6 / (slot * per_round)) * per_round
-    lens = [0, 1, 31, 33, per_round - 1, per_round, per_round + 1, 2 * per_round + 40, full - 1, full, full + 33, fit - 1,
-            fit, fit + 1, cap - 35, cap - 4]
-    lens = np.array([min(max(x, 0), cap - 4) for x in (lens * 3)[:Nb]], np.int32)
+def _steps_on_a_large_cache(B, Nb, Hq, Hkv, d, cap, layers, lens, launch_shape=None, masked=False):
+    """Every form of the step on the last layer of a dense cache of several hundred MB, against float64.  masked: a quarter of
+    the sequences, others each time, sit a step out."""
+    G = Hq // Hkv
     dev = torch.device("cuda:0")
     g = torch.Generator(device=dev)
     g.manual_seed(cap)
     normal = lambda *s: torch.randn(s, generator=g, device=dev).to(torch.bfloat16)
-    cache = B.Cache(layers, Nb, Hq, Hkv, d, cap, cap - 200, 10, 10)
+    cache = B.Cache(layers, Nb, Hq, Hkv, d, cap, cap - 200, 10, 10, launch_shape=launch_shape)
     layer = layers - 1
     cache.K[layer].copy_(normal(Nb, Hkv, cap, d))
     cache.V[layer].copy_(normal(Nb, Hkv, cap, d))
@@ -590,20 +581,24 @@ def test_caches_beyond_the_memory_side_cache(B, Nb, Hq, Hkv, d, cap, layers):
     want = torch.zeros((Nb, Hkv, cap), dtype=torch.float64)
     out, lse = torch.zeros((Nb, Hq, d), device=dev), torch.zeros((Nb, Hq), device=dev)
     n = lens.copy()
-    for step in ("first", "step", "hinted", "attend_update", "attend", "step"):
+    on, active = np.ones(Nb, bool), None
+    for i, step in enumerate(("first", "step", "hinted", "attend_update", "attend", "step")):
+        if masked:
+            on = (np.arange(Nb) + i) % 4 != 3
+            active = torch.from_numpy(on.astype(np.uint8)).to(dev)
         q, k1, v1 = normal(Nb, Hq, d), normal(Nb, Hkv, d), normal(Nb, Hkv, d)
         if step.startswith("attend"):
-            (B.dynts_decode_attend if step == "attend" else B.dynts_decode_attend_update)(cache.ctx, layer, q, out, lse)
+            (B.dynts_decode_attend if step == "attend" else B.dynts_decode_attend_update)(cache.ctx, layer, q, out, lse, active)
         else:
             if step == "hinted":
                 B.dynts_hint_trigger(cache.ctx, layer)
-            B.dynts_decode_step(cache.ctx, layer, q, k1, v1, out, lse=lse)
-            for b in range(Nb):
+            B.dynts_decode_step(cache.ctx, layer, q, k1, v1, out, lse=lse, active=active)
+            for b in np.flatnonzero(on):
                 K[b, :, n[b]], V[b, :, n[b]] = k1[b].cpu().double(), v1[b].cpu().double()
-            n += 1
+            n[on] += 1
         if step not in ("first", "step"):  # (an unfused call drops what the one before it still owes)
             B.dynts_update_scores(cache.ctx, layer)
-        for b in range(Nb):
+        for b in np.flatnonzero(on):
             x = torch.matmul(q[b].cpu().double().view(Hkv, G, d), K[b, :, :n[b]].transpose(1, 2)) / np.sqrt(d)
             if n[b] == 0:
                 continue
@@ -618,6 +613,50 @@ def test_caches_beyond_the_memory_side_cache(B, Nb, Hq, Hkv, d, cap, layers):
         assert np.all(S[b, :, max(M, n[b]):] == 0)
     assert int(cache.status.item()) == 0
     cache.close()
+
+
+@pytest.mark.parametrize("Nb,Hq,Hkv,d,cap,layers", [(16, 16, 8, 128, 5000, 1), (40, 8, 4, 64, 8100, 1), (16, 16, 8, 128, 1700, 3)])
+def test_caches_beyond_the_memory_side_cache(B, Nb, Hq, Hkv, d, cap, layers):
+    """Caches of more than 310 MB: tiles at fixed places first, the rest loaded past the memory-side cache.  Ragged lengths
+    around the ends of the rounds of fixed tiles, around the length from which the rest goes past the cache, around
+    tiles and at both ends, in every form of the step."""
+    units = Nb * Hkv
+    slot = 4 * layers * units * d
+    assert slot * cap > 310e6 and units >= 128 and slot * cap / layers >= 100e6
+    fit, per_round = int(310e6 / slot), 8 * 32 * max(1, (256 + units // 2) // units)
+    full = int(272e6 / (slot * per_round)) * per_round
+    lens = [0, 1, 31, 33, per_round - 1, per_round, per_round + 1, 2 * per_round + 40, full - 1, full, full + 33, fit - 1,
+            fit, fit + 1, cap - 35, cap - 4]
+    lens = np.array([min(max(x, 0), cap - 4) for x in (lens * 3)[:Nb]], np.int32)
+    _steps_on_a_large_cache(B, Nb, Hq, Hkv, d, cap, layers, lens)
+
+
+@pytest.mark.parametrize("Nb,Hq,Hkv,d,cap,layers,shape,rounds", [
+    (16, 16, 8, 128, 1560, 10, None, 0), (32, 28, 4, 128, 1560, 6, None, 1), (32, 8, 4, 128, 1560, 10, (256, 4), 1),
+    (32, 8, 4, 64, 3100, 70, (128, 4), 0), (16, 16, 8, 128, 5000, 1, None, 8)])
+def test_caches_beyond_the_memory_side_cache_in_deep_stacks(B, Nb, Hq, Hkv, d, cap, layers, shape, rounds):
+    """The same with more layers than leave every wave a second fixed tile, or any that go through the cache, with
+    four-wave workgroups, and with sequences that sit steps out."""
+    units = Nb * Hkv
+    slot, waves = 4 * layers * units * d, 8 if shape is None else shape[1]
+    per_round = waves * 32 * max(1, ((256 if shape is None else shape[0]) + units // 2) // units)
+    assert slot * cap > 310e6 and units >= 128 and slot * cap / layers >= 100e6 and int(272e6 / (slot * per_round)) == rounds
+    lens = [0, 1, 31, 32, 33, 65, per_round - 1, per_round, per_round + 1, int(310e6 / slot), int(310e6 / slot) + 1, cap // 2,
+            2 * per_round + 40, cap - 35, cap - 7, cap - 6]
+    lens = np.array([min(max(x, 0), cap - 6) for x in (lens * 3)[:Nb]], np.int32)
+    _steps_on_a_large_cache(B, Nb, Hq, Hkv, d, cap, layers, lens, shape, masked=True)
+
+
+@pytest.mark.parametrize("Nb,Hq,Hkv,d,cap,layers,shape", [(16, 16, 4, 128, 9700, 1, None), (12, 16, 8, 64, 12800, 1, (96, 4)),
+                                                          (25, 28, 4, 128, 3900, 2, None)])
+def test_dense_caches_that_write_scores_in_bursts(B, Nb, Hq, Hkv, d, cap, layers, shape):
+    """Large caches of fewer units than are loaded past the memory-side cache: a wave's scores leave in runs of up to 16 tiles.
+    Ragged lengths around those runs, around tiles and at both ends; a question window that ends inside the first run."""
+    assert 4 * Nb * Hkv * cap * d > 192e6 and 4 * layers * Nb * Hkv * cap * d > 310e6 and Nb * Hkv < 128
+    first = 32 * (8 if shape is None else shape[1]) * max(1, ((256 if shape is None else shape[0]) + Nb * Hkv // 2) // (Nb * Hkv))
+    lens = [0, 1, 31, 33, first - 1, first + 1, first + first * 15, first + first * 16 - 31, first + first * 17 + 5, cap // 3, cap - 35, cap - 4]
+    lens = np.array([min(max(x, 0), cap - 4) for x in (lens * 3)[:Nb]], np.int32)
+    _steps_on_a_large_cache(B, Nb, Hq, Hkv, d, cap, layers, lens, shape, masked=Nb > 16)
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,n,shape", [(4, 1, 128, 9001, (256, 8)), (4, 1, 128, 1300, (256, 8)), (8, 1, 128, 4700, (256, 8)),
