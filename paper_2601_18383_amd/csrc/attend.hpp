@@ -415,8 +415,13 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   // to check in advances the three words -- by then no workgroup of the sequence has a read of them
   // outstanding.  The check-in is issued early and its answer looked at later, so it costs no round
   // trip at the end of the workgroup.
+  // All of the prologue's loads are waited for right before it: answers come back in order, so a wait for one of
+  // those loads that the compiler puts behind the atomic is a wait for the atomic's round trip as well, which it did in
+  // some forms and not in others (15 x 8 units of 74 - 270 slots, head_dim 128: 10.3 us a step with such a wait, 9.6 so;
+  // one short sequence, head_dim 64: 6.95 and 6.74).
   uint32_t seq_ticket = 0xffffffffu;
   auto seq_checkin = [&]() {
+    if (ATTEND) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     if (ATTEND && tid == 0) seq_ticket = draw_ticket(&p.seq_cnt[b]);
   };
   auto seq_settle = [&]() {
