@@ -864,7 +864,7 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
     uint64_t ask_o[E][N], ask_m, ask_l;
     // (uniform.  At head_dim 64 it spares groups of up to eight heads the second element, 0.5 - 2 % of a launch of 10 to 33
     // chunks; at head_dim 128 it costs the eight-chunk merges 1 %)
-    auto has = [&](int k) { return D == 128 || WIDE || PAGED || k < ne; };
+    auto has = [&](int k) { return D == 128 || WIDE || k < ne; };
     auto ask_group = [&](int s0) {
 #pragma unroll
       for (int k = 0; k < E; ++k) {
