@@ -160,7 +160,8 @@ __device__ __forceinline__ void load_v_tile(u32x4 (&vf)[kTile / (64 / (D / 8))],
 // (a serial number no earlier launch of this process used), stored and loaded with single 64-bit
 // atomic accesses, so a word is either this launch's value or recognisably stale.  The workgroup
 // that draws the last ticket of a (sequence, KV head) merges: it re-reads a word until its tag is
-// this launch's.  That loop ends: a workgroup draws its ticket only when it is running, it issues its
+// this launch's.  (The replays of a launch recorded into a graph share one tag: there the words are cleared behind the
+// launch, see run_attend.)  That loop ends: a workgroup draws its ticket only when it is running, it issues its
 // stores without ever waiting for another workgroup, and issued stores become visible.  There is no
 // fence, no wait for store acknowledgements and no cache-wide write-back; no ordinary cached access
 // ever touches these words during a launch.

@@ -236,6 +236,10 @@ void launch_partial_d(const dynts::AttendParams &p, dim3 grid, hipStream_t st, h
   return launch_partial<D, W, true, false, false>(p, grid, st, e0, e1);
 }
 
+__global__ void clear_words_kernel(uint32_t *words, size_t n) {
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) words[i] = 0u;
+}
+
 // scratch of one attend launch: split partials (tagged words) and ticket counters (zero between launches)
 struct Transient {
   uint64_t *part_o, *part_ml;
@@ -315,6 +319,14 @@ int run_attend(dynts_ctx *ctx, int layer, const uint16_t *q, const uint16_t *k_n
   } else {
     if (pl.waves == 8) launch_partial_d<64, 8>(p, grid, st, e0, e1, attend, apply_pending, append);
     else launch_partial_d<64, 4>(p, grid, st, e0, e1, attend, apply_pending, append);
+  }
+  // Recorded into a graph: every replay has this tag, so what one leaves must not be there for the next, whose merging
+  // workgroup could take it for partials still on their way.  (A kernel of its own: the same clearing at the end of the merge
+  // costs every eager launch of the wide and paged forms 2 - 5 %, in registers and scheduling.)
+  if (attend && pl.nsplit > 1 && capturing(st)) {
+    const size_t rows = (size_t)c.batch * c.n_kv_heads * pl.nsplit * pl.G;
+    const size_t bytes = align_up(rows * c.head_dim * sizeof(uint64_t)) + rows * 2 * sizeof(uint64_t);  // part_ml lies behind part_o
+    hipLaunchKernelGGL(clear_words_kernel, dim3(256), dim3(256), 0, st, reinterpret_cast<uint32_t *>(p.part_o), bytes / sizeof(uint32_t));
   }
   const int rc = launch_status();
   if (rc == DYNTS_OK && attend && track) ctx->qslot[layer] ^= 1;  // the query just saved becomes the current one
@@ -494,10 +506,6 @@ constexpr size_t kStaticScratchBytes = DYNTS_STATIC_SCRATCH_BYTES;
 constexpr size_t kStaticCounters = size_t(1) << 20;  // the first MiB holds counters only
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
-__global__ void static_scratch_clear_kernel(uint32_t *words, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) words[i] = 0u;
-}
-
 constexpr int kMaxDevices = 64;
 std::mutex static_scratch_mutex;
 unsigned char *static_scratch_ptr[kMaxDevices] = {};
@@ -512,7 +520,7 @@ unsigned char *static_scratch(hipStream_t st) {
     if (hipGetSymbolAddress(reinterpret_cast<void **>(&ptr), HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return nullptr;
     // counters must start at zero (launches leave them at zero afterwards); the whole array, once, with a
     // fill kernel on the caller's stream -- stream order puts it before the first launch that uses the array
-    hipLaunchKernelGGL(static_scratch_clear_kernel, dim3(256), dim3(256), 0, st, reinterpret_cast<uint32_t *>(ptr),
+    hipLaunchKernelGGL(clear_words_kernel, dim3(256), dim3(256), 0, st, reinterpret_cast<uint32_t *>(ptr),
                        kStaticScratchBytes / sizeof(uint32_t));
     if (hipGetLastError() != hipSuccess) return nullptr;
     static_scratch_ptr[dev] = ptr;
@@ -962,7 +970,7 @@ int dynts_predict_scores(const dynts_predictor *w, const uint16_t *h, int32_t ba
   hipExtLaunchKernelGGL(dynts::mlp_reduce_dot_kernel, dim3((w->m2 + 255) / 256, batch), dim3(256), 0, st, nullptr,
                         static_cast<hipEvent_t>(stop), 0, P2, w->b2, l2.nsplit, batch, w->m2, w->activation, w->w3,
                         w->b3, reinterpret_cast<uint64_t *>(base + sc.off_part), next_launch_tag(),
-                        reinterpret_cast<uint32_t *>(base + sc.off_cnt), s_out, n_rep);
+                        reinterpret_cast<uint32_t *>(base + sc.off_cnt), s_out, n_rep, capturing(st) ? 1 : 0);
   return launch_status();
 }
 

@@ -209,7 +209,7 @@ __global__ __launch_bounds__(256) void mlp_reduce_act_kernel(const float *P, con
 __global__ __launch_bounds__(256) void mlp_reduce_dot_kernel(const float *P, const float *bias, int nsplit, int Nb,
                                                              int m, int act, const uint16_t *w3, const float *b3,
                                                              uint64_t *part, uint32_t tag, uint32_t *row_cnt,
-                                                             float *s_out, int n_rep) {
+                                                             float *s_out, int n_rep, int clear) {
   __shared__ float red[4];
   __shared__ int is_last;
   const int b = blockIdx.y, tid = threadIdx.x, o = blockIdx.x * 256 + tid;
@@ -239,6 +239,10 @@ __global__ __launch_bounds__(256) void mlp_reduce_dot_kernel(const float *P, con
       tot += tagged_value(w);
     }
     s_out[(size_t)b * n_rep + tid] = tot + (b3 ? b3[0] : 0.f);
+  }
+  if (clear) {  // recorded into a graph: the next replay has the same tag
+    __syncthreads();
+    for (unsigned k = tid; k < gridDim.x; k += 256) tagged_store(part + (size_t)b * gridDim.x + k, 0.f, 0u);
   }
 }
 

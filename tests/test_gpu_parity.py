@@ -448,6 +448,49 @@ def test_attend_then_update_by_any_route(B, d, Hq, Hkv):
     assert int(cache.status.item()) == 0
 
 
+@pytest.mark.parametrize("d,Hq,Hkv,cap,nsplit", [(128, 28, 4, 1300, 3), (64, 8, 2, 1500, 6), (128, 4, 1, 5000, 20)])
+def test_replayed_steps_leave_no_partial_of_theirs(B, d, Hq, Hkv, cap, nsplit):
+    """The replays of a recorded launch share one tag, so the partials of one must not be there for the next, whose merge would
+    take them for its own.  Two steps are recorded (the saved query alternates), behind an eager one, whose score update the first
+    of them finds owed as it later does the second's; replays against a twin's eager steps."""
+    dev = torch.device("cuda:0")
+    Nb, n, G, reps = 3, cap - 100, Hq // Hkv, 4
+    torch.manual_seed(cap)
+    caches = [B.Cache(1, Nb, Hq, Hkv, d, cap, 100, 20, 10, launch_shape=(64, 8)) for _ in range(2)]
+    K = torch.randn(Nb, Hkv, cap, d, device=dev).to(torch.bfloat16)
+    for c in caches:
+        c.K[0].copy_(K)
+        c.V[0].copy_(K.flip(2))
+        c.seq_len.fill_(n)
+        c.n_prompt.fill_(9)
+    tokens = [[torch.randn(Nb, h, d, device=dev).to(torch.bfloat16) for h in (Hq, Hkv, Hkv)] for _ in range(2 * reps)]
+    now = [[t.clone() for t in tokens[i]] for i in range(2)]
+    out = torch.zeros(2, Nb, Hq, d, device=dev)
+    for c in caches:
+        B.dynts_decode_step(c.ctx, 0, *tokens[0], out[0])
+    caches[0].workspace[:Nb * Hkv * nsplit * G * (d + 2) * 8].zero_()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        for i in range(2):
+            B.dynts_decode_step(caches[0].ctx, 0, *now[i], out[i])
+    rows = Nb * Hkv * nsplit * G
+    partials = caches[0].workspace[:rows * d * 8]  # the head of the workspace, and behind it the statistics
+    want = torch.zeros(2, Nb, Hq, d, device=dev)
+    for r in range(reps):
+        for i in range(2):
+            for dst, src in zip(now[i], tokens[2 * r + i]):
+                dst.copy_(src)
+            B.dynts_decode_step(caches[1].ctx, 0, *tokens[2 * r + i], want[i])
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        assert not partials.any() and not caches[0].workspace[(rows * d * 8 + 255) // 256 * 256:][:rows * 16].any()
+        assert caches[1].workspace[:rows * d * 8].view(torch.int64).ne(0).sum() > rows * d // 2  # (that is where they lie)
+    assert torch.equal(caches[0].S[0], caches[1].S[0]) and torch.equal(caches[0].seq_len, caches[1].seq_len)
+    assert int(caches[0].seq_len[0, 0]) == n + 1 + 2 * reps
+
+
 # a letter per call: A unfused attention, U its update, F a fused attention, of the layer behind it; and the attentions (by
 # number) that may still leave their logits in the workspace, the first of a context, which cannot know what follows
 @pytest.mark.parametrize("d,Hq,Hkv,calls,keepers", [

@@ -51,6 +51,32 @@ def test_small_shapes(B, d, m1, m2, batch, act):
     _run(B, rng, d, m1, m2, batch, act, bias=(batch % 2 == 1), n_rep=1 + batch % 4, pack=(act != 1))
 
 
+def test_replayed_calls_leave_no_partial_of_theirs(B):
+    """The replays of a recorded call share one tag, so the parts of the final dot product must not be there for the next."""
+    rng = np.random.default_rng(17)
+    dev = torch.device("cuda:0")
+    d, m1, m2, batch = 256, 512, 592, 24
+    pred = B.Predictor(*[w.to(dev) for w in _make(rng, d, m1, m2)], max_batch=32)
+    hs = [torch.from_numpy(rng.standard_normal((batch, d)).astype(np.float32)).to(torch.bfloat16).to(dev) for _ in range(4)]
+    h, s, want = hs[0].clone(), torch.zeros(batch, 1, device=dev), torch.zeros(batch, 1, device=dev)
+    n_parts = (m2 + 255) // 256 * batch
+    # the last room of the scratch: the counters, 4 bytes per sequence, in front of them the parts
+    end = B.dynts_predict_scratch_bytes(pred.w, batch) - 256
+    parts = pred.scratch[end - (8 * n_parts + 255) // 256 * 256:][:8 * n_parts]
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        B.dynts_predict_scores(pred, h, s)
+    for x in hs:
+        B.dynts_predict_scores(pred, x, want)
+        torch.cuda.synchronize()
+        assert parts.view(torch.int64).ne(0).all()  # (that is where they lie)
+        h.copy_(x)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(s, want) and not parts.any()
+
+
 @pytest.mark.parametrize("d,batch,hkv", [(3584, 32, 4), (4096, 64, 8), (4096, 128, 8)])
 def test_paper_sizes(B, d, batch, hkv):
     """App. C: 3584 -> 7168 -> 1792 -> 1 (R1-Qwen) and 4096 -> 8192 -> 2048 -> 1 (R1-Llama), decode batches of the
