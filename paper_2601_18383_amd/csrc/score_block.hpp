@@ -39,24 +39,6 @@
 
 namespace dynts {
 
-#ifdef SB_NOPRIO
-#define SB_PRIO(x)
-#else
-#define SB_PRIO(x) __builtin_amdgcn_s_setprio(x)
-#endif
-#ifdef SB_NOPRIO
-#define SB_PRIO(x)
-#else
-#define SB_PRIO(x) __builtin_amdgcn_s_setprio(x)
-#endif
-#ifdef SB_NOPRIO
-#define SB_PRIO(x)
-#else
-#define SB_PRIO(x) __builtin_amdgcn_s_setprio(x)
-#endif
-#ifndef SB_OCC
-#define SB_OCC 3
-#endif
 constexpr int kSbWaves = 4;        // waves per workgroup
 constexpr int kSbTiles = 2;        // stationary 32-row tiles per wave
 constexpr int kSbRowsPerWave = 32 * kSbTiles;
