@@ -421,7 +421,7 @@ def dynts_probe_exp_rate(n_workgroups, iters, sink, start=None, stop=None, strea
 
 
 def dynts_probe_issue_mix(n_workgroups, iters, what, sink, start=None, stop=None, stream=None):
-    """what: 1 = the MFMAs of a block-scoring tile, 2 = its vector instructions, 3 = both; sink: device float tensor."""
+    """what: 1 = the MFMAs of a block-scoring chunk, 2 = its vector instructions, 3 = both; sink: device float tensor."""
     _check(lib.dynts_probe_issue_mix(n_workgroups, iters, what, sink.data_ptr(), start, stop, _stream(stream)),
            "dynts_probe_issue_mix")
 

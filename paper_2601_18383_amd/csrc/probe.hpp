@@ -52,13 +52,15 @@ __global__ __launch_bounds__(kProbeThreads) void exp2_rate_kernel(int iters, flo
   if (s == magic) sink[0] = s;
 }
 
-// Third measurement aid: the instruction mix of the block-scoring kernels with no memory access at all.  Per round
-// a wave issues what one streamed 16-row tile costs it there: 16 v_mfma_f32_16x16x32_bf16 on four independent
-// accumulators (WHAT & 1) and 16 x (multiply-add, 2^x, add) on independent registers (WHAT & 2), in one basic
-// block, so that the compiler interleaves them as it does in the kernels.  The time per round is what a SIMD
-// needs for a tile when nothing but instruction issue and the two pipes limit it.
+// Third measurement aid: the instruction mix of the block-scoring kernels (head_dim 128) with no memory access at all.  Per
+// round a wave issues what one chunk of 32 streamed rows costs it there: 16 v_mfma_f32_32x32x16_bf16 on two independent
+// accumulators (WHAT & 1) and 32 x (multiply-add, 2^x, add) on independent registers (WHAT & 2), in one basic block, so
+// that the compiler interleaves them.  The time per round is what a SIMD needs for a chunk when nothing but instruction
+// issue and the two pipes limit it.
 template <int WHAT>
 __global__ __launch_bounds__(kProbeThreads) void issue_mix_kernel(int iters, float c, float L, float magic, float *sink) {
+  typedef float f32x16_t __attribute__((ext_vector_type(16)));
+  constexpr int kTiles = 2, kSteps = 8, kLogits = 16 * kTiles;  // of a wave and chunk: stationary tiles, k-steps, logits per lane
   const int lane = threadIdx.x & 63;
   bf16x8 a[4], b[4];
 #pragma unroll
@@ -68,35 +70,38 @@ __global__ __launch_bounds__(kProbeThreads) void issue_mix_kernel(int iters, flo
       a[i][e] = (__bf16)(0.001f * (float)(lane + i + e));
       b[i][e] = (__bf16)(0.002f * (float)(lane - i + e));
     }
-  f32x4 acc[4];
-  float sum[16], x[16];
+  f32x16_t acc[kTiles];
+  float sum[8], x[kLogits];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < kTiles; ++i)
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    sum[i] = 0.f;
-    x[i] = 0.01f * (float)(lane + i);
-  }
+    for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) sum[i] = 0.f;
+#pragma unroll
+  for (int i = 0; i < kLogits; ++i) x[i] = 0.01f * (float)(lane + i);
   for (int it = 0; it < iters; ++it) {
     if (WHAT & 1) {
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
+      for (int ks = 0; ks < kSteps; ++ks)
 #pragma unroll
-        for (int kt = 0; kt < 4; ++kt) acc[kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kt], b[ks], acc[kt], 0, 0, 0);
+        for (int kt = 0; kt < kTiles; ++kt)
+          acc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[(kt + ks) & 3], b[ks & 3], acc[kt], 0, 0, 0);
     }
     if (WHAT & 2) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) sum[i] += fast_exp2(fmaf(x[i], c, L));
-      // (the arguments are not loop-invariant as far as the compiler can tell)
-      asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]));
-      asm volatile("" : "+v"(x[8]), "+v"(x[9]), "+v"(x[10]), "+v"(x[11]), "+v"(x[12]), "+v"(x[13]), "+v"(x[14]), "+v"(x[15]));
+      for (int i = 0; i < kLogits; ++i) sum[i & 7] += fast_exp2(fmaf(x[i], c, L));
+#pragma unroll
+      for (int i = 0; i < kLogits; ++i) asm volatile("" : "+v"(x[i]));  // (not loop-invariant as far as the compiler can tell)
     }
   }
   float r = 0.f;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) r += sum[i];
+  for (int i = 0; i < 8; ++i) r += sum[i];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) r += acc[i][0] + acc[i][1] + acc[i][2] + acc[i][3];
+  for (int i = 0; i < kTiles; ++i)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) r += acc[i][e];
   if (r == magic) sink[0] = r;
 }
 

@@ -22,13 +22,13 @@
 //   * pass 2 keeps one private column sum per lane and key and adds the two halves once, at the end.
 //
 // What bounds them: the instruction stream.  A logit needs a multiply-add, a 2^x and an add in each pass beside
-// its share of the MFMA, and the two pipes overlap only in part (a loop of just these, without memory: 0.38 us
-// per 32 x 64 chunk and SIMD; MFMAs alone 0.28, vector instructions alone 0.22), so everything else that is issued
+// its share of the MFMA, and the two pipes overlap only in part (dynts_probe_issue_mix, just these without memory: 0.355 us
+// per 32 x 64 chunk and SIMD; MFMAs alone 0.267, vector instructions alone 0.211), so everything else that is issued
 // per chunk counts.  32x32 tiles take half the MFMA issue slots and LDS reads per product of 16x16 ones, and one row
 // per staging thread leaves one address to advance.  A block of 512 queries over 2464 slots
-// (128 units, 28 query heads on 4): 655 -> 593 us a call against 16x16 tiles with a running maximum, both passes at
-// 1.9 GHz, which the chip falls to under this load; 64 queries: 120 -> 89 us.  Tried and slower: products of one tile
-// interleaved by hand with the exponentials of another in one wave (600 -> 640 us and more: registers).
+// (128 units, 28 query heads on 4): 664 -> 597 us a call against 16x16 tiles with a running maximum, 67 % of that mix's
+// rate; 64 queries: 126 -> 98 us.  Tried and slower: products of one tile interleaved by hand with the exponentials of
+// another in one wave (600 -> 640 us and more: registers).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
