@@ -276,12 +276,14 @@ int run_attend(dynts_ctx *ctx, int layer, const uint16_t *q, const uint16_t *k_n
   p.part_o = tr.part_o;
   p.part_ml = tr.part_ml;
   p.tag = next_launch_tag();
-  // K and V past the memory-side cache: only when all layers together are more than what still gains from it (one layer of
-  // 303 MB is 3 % faster through it, 323 MB is not), and when a launch is long enough to be bound by the stream (128 or
-  // more units, 100 MB or more; below, shorter and more uneven launches lose 2 - 4 % with it).  272 MB of fixed places:
-  // 320 MB costs up to 4 %, 410 MB all of the gain.  Per period, before and after: 512 units x 2640 slots x 2 layers
-  // 8.46 -> 7.40 ms; 384 units x 2464 slots 6.40 -> 5.77; 128 units x 4 layers 9.75 -> 8.64; 256 units x 16 layers of
-  // 63 MB x 2 28.2 -> 26.9.
+  // K and V past the memory-side cache: only when all layers together are more than what still gains from it, and for
+  // launches of 128 or more units and 100 MB or more.  us a step, through it / past it:
+  //   one layer, 128 units: 303 MB 53.4 / 52.5, 314 MB 57.0 / 55.2, 323 MB 59.3 / 55.0, 382 MB 76.4 / 65.8
+  //   2 layers of 512 units of 2640 slots 129.2 / 114.4, 8 of them 133.5 / 129.7; 384 units of 2464 99.8 / 88.9; 4 layers of
+  //     128 units of 2464 37.3 / 33.4, 28 of them 37.6 / 34.5; 8 layers of 100 MB 26.0 / 24.1
+  //   short launches lose: 16 layers of 128 units of 700 17.4 / 18.1.  (The line is a cautious one: 96 units of 8000 would take
+  //     90.2 instead of 99.5, 8 layers of 64 units of 4000 28.8 instead of 30.9.)
+  // 272 MB of fixed places: with 320 MB 384 units of 2464 take 92.2 instead of 88.9, with 410 MB 103.9.
   const double kv_bytes = 4.0 * c.batch * c.n_kv_heads * (double)c.capacity * c.head_dim;
   const double slot_bytes = 4.0 * c.n_layers * c.batch * c.n_kv_heads * c.head_dim;
   const bool stream_bound = (long long)c.batch * c.n_kv_heads >= 128 && kv_bytes >= 100e6;
