@@ -257,7 +257,8 @@ int dynts_set_kernel_event_list(dynts_ctx *ctx, void *const *starts, void *const
  *     means the layer's score array S; then slots below n_prompt[b] keep their +inf.
  *   accumulate != 0 adds to dst, 0 overwrites it.
  *   scratch: >= dynts_score_block_scratch_bytes(cfg, n_queries) bytes of device memory, 4-byte
- *     aligned, contents irrelevant before and after.
+ *     aligned, contents irrelevant before and after.  (The first pass may cut the keys into up to four ranges with
+ *     denominators of their own; with less, down to the room of one range, there are fewer ranges.)
  * Independent of the deferred accumulation of the fused decode calls (sums commute).  The cache is
  * only read. */
 size_t dynts_score_block_scratch_bytes(const dynts_config *cfg, int32_t n_queries);

@@ -2,7 +2,8 @@
 //
 // The cache of one (sequence, KV head) is shared out over nsplit workgroups of W waves (8 by
 // default).  Wave number wi of the nsplit*W takes the 32-slot tile that starts at slot 32*wi -- its
-// loads are issued before the kernel knows the sequence length -- and then an equal, contiguous
+// loads are issued before the kernel knows the sequence length (kStream: and then more tiles at fixed
+// places, AttendParams::rounds) -- and then an equal, contiguous
 // share of the slots behind those first tiles, 32 at a time, with the next tile's loads already
 // in flight while it works on the current one:
 //   * K rows go straight from HBM into MFMA operand registers (16-byte loads; lane (r, kg)

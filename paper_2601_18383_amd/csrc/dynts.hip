@@ -276,8 +276,8 @@ int run_attend(dynts_ctx *ctx, int layer, const uint16_t *q, const uint16_t *k_n
   p.part_o = tr.part_o;
   p.part_ml = tr.part_ml;
   p.tag = next_launch_tag();
-  // K and V past the memory-side cache: only when all layers together are more than what still gains from it, and for
-  // launches of 128 or more units and 100 MB or more.  us a step, through it / past it:
+  // K and V past the memory-side cache: only when all layers together are more than what still gains from it (but for 2 % at
+  // 303 MB), and for launches of 128 or more units and 100 MB or more.  us a step, through it / past it:
   //   one layer, 128 units: 303 MB 53.4 / 52.5, 314 MB 57.0 / 55.2, 323 MB 59.3 / 55.0, 382 MB 76.4 / 65.8
   //   2 layers of 512 units of 2640 slots 129.2 / 114.4, 8 of them 133.5 / 129.7; 384 units of 2464 99.8 / 88.9; 4 layers of
   //     128 units of 2464 37.3 / 33.4, 28 of them 37.6 / 34.5; 8 layers of 100 MB 26.0 / 24.1
