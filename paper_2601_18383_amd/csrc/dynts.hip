@@ -444,15 +444,39 @@ void launch_score_block(const dynts::ScoreBlockParams &p, dim3 g1, dim3 g2, hipS
 
 // ---- Importance Predictor ---------------------------------------------------------------------------
 struct MlpPlan {
-  int bt;      // batch tiles of 16
-  int nsplit;  // workgroups along K (each covers mlp_slice_steps k-steps)
+  int bt;                 // batch tiles of 16
+  int ft1, ft2, ns;       // feature tiles of 16 a workgroup takes in either layer; workgroups that share the second's K
+  int wgs1, groups;       // workgroups of the first layer, groups of features of the second
+  size_t off_sum, off_group, off_dot, off_done, total;  // scratch: layer 1's output first, then the words the first kernel zeroes
 };
 
-MlpPlan mlp_plan(int batch, int K, int parts) {
+// us a call, by the number of tiles a workgroup takes (ft) and of workgroups that share the second layer's K (ns):
+//   ft1 = 1 / 2: d = 2048 (256 tiles of 16 features) batch 4 13.2 / 13.9, batch 128 28.8 / 29.4; d = 2560 (320) 18.6 / 17.1, 40.8 / 32.4;
+//     d = 3584 22.2 / 22.0, 49.9 / 39.0
+//   (ft2, ns) = (1, 2) / (1, 4) / (2, 4) / (2, 8): d = 2048 (64 tiles) batch 4 13.6 / 13.9 / 14.8 / 14.8, batch 128 30.1 / 25.9 / 27.4 / 29.3;
+//     d = 2560 (80) 18.0 / 19.2 / 17.3 / 21.6, 34.8 / 40.3 / 32.2 / 38.9; d = 3584 22.1 / 23.2 / 21.5 / 26.8, 43.4 / 50.3 / 39.0 / 50.9
+MlpPlan mlp_plan(const dynts_predictor *w, int batch) {
   MlpPlan pl;
-  pl.bt = batch <= 16 ? 1 : batch <= 32 ? 2 : batch <= 64 ? 4 : 8;
-  const int slice = dynts::mlp_slice_steps(pl.bt, parts);
-  pl.nsplit = (K / 32 + slice - 1) / slice;
+  pl.bt = batch <= 64 ? (batch + 15) / 16 : batch <= 96 ? 6 : 8;
+  const int t1 = w->m1 / 16, t2 = w->m2 / 16;
+  pl.ft1 = t1 > 256 ? 2 : 1;
+  pl.ft2 = t2 > 64 ? 2 : 1;
+  pl.wgs1 = (t1 + pl.ft1 - 1) / pl.ft1;
+  pl.groups = (t2 + pl.ft2 - 1) / pl.ft2;
+  const int want = pl.ft2 == 2 || pl.bt > 2 ? 4 : 2, room = 256 / pl.groups, most = w->m1 / 32 / (2 * dynts::kMlpWaves);
+  pl.ns = want < room ? want : room;
+  pl.ns = pl.ns < most ? pl.ns : most;
+  pl.ns = pl.ns < 1 ? 1 : pl.ns;
+  size_t off = align_up((size_t)w->m1 * 16 * pl.bt * 2 * sizeof(uint16_t));
+  pl.off_sum = off;
+  if (pl.ns > 1) off += align_up((size_t)pl.groups * pl.ns * pl.ft2 * pl.bt * 256 * sizeof(uint64_t));
+  pl.off_group = off;
+  if (pl.ns > 1) off += align_up((size_t)pl.groups * dynts::kMlpCntStride * sizeof(uint32_t));
+  pl.off_dot = off;
+  off += align_up((size_t)pl.groups * batch * sizeof(uint64_t));
+  pl.off_done = off;
+  off += align_up(sizeof(uint32_t));
+  pl.total = off;
   return pl;
 }
 
@@ -466,38 +490,28 @@ int check_predictor(const dynts_predictor *w, int batch) {
   return DYNTS_OK;
 }
 
-struct MlpScratch {
-  size_t off_p1, off_yhi, off_ylo, off_p2, off_part, off_cnt, total;
-};
-
-MlpScratch mlp_scratch(const dynts_predictor *w, int batch, const MlpPlan &l1, const MlpPlan &l2) {
-  MlpScratch sc;
-  size_t off = 0;
-  sc.off_p1 = off;
-  off += align_up((size_t)l1.nsplit * batch * w->m1 * sizeof(float));
-  sc.off_yhi = off;
-  off += align_up((size_t)batch * w->m1 * sizeof(uint16_t));
-  sc.off_ylo = off;
-  off += align_up((size_t)batch * w->m1 * sizeof(uint16_t));
-  sc.off_p2 = off;
-  off += align_up((size_t)l2.nsplit * batch * w->m2 * sizeof(float));
-  sc.off_part = off;
-  off += align_up((size_t)batch * ((w->m2 + 255) / 256) * sizeof(uint64_t));  // tagged words
-  sc.off_cnt = off;
-  off += align_up((size_t)batch * sizeof(uint32_t));
-  sc.total = off;
-  return sc;
+template <int FT, bool SECOND, bool PACKED>
+void launch_mlp_ft(const dynts::MlpParams &p, int bt, dim3 grid, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  const dim3 block(dynts::kMlpThreads);
+  switch (bt) {
+    case 1: hipExtLaunchKernelGGL((dynts::mlp_kernel<FT, 1, SECOND, PACKED>), grid, block, 0, st, e0, e1, 0, p); break;
+    case 2: hipExtLaunchKernelGGL((dynts::mlp_kernel<FT, 2, SECOND, PACKED>), grid, block, 0, st, e0, e1, 0, p); break;
+    case 3: hipExtLaunchKernelGGL((dynts::mlp_kernel<FT, 3, SECOND, PACKED>), grid, block, 0, st, e0, e1, 0, p); break;
+    case 4: hipExtLaunchKernelGGL((dynts::mlp_kernel<FT, 4, SECOND, PACKED>), grid, block, 0, st, e0, e1, 0, p); break;
+    case 6: hipExtLaunchKernelGGL((dynts::mlp_kernel<FT, 6, SECOND, PACKED>), grid, block, 0, st, e0, e1, 0, p); break;
+    default: hipExtLaunchKernelGGL((dynts::mlp_kernel<FT, 8, SECOND, PACKED>), grid, block, 0, st, e0, e1, 0, p); break;
+  }
 }
 
-template <int PARTS, bool PACKED>
-void launch_mlp_gemm(const dynts::MlpGemmParams &p, const MlpPlan &pl, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
-  const dim3 grid((p.m + dynts::kMlpFeaturesPerWg - 1) / dynts::kMlpFeaturesPerWg, pl.nsplit);
-  const dim3 block(dynts::kMlpThreads);
-  switch (pl.bt) {
-    case 1: hipExtLaunchKernelGGL((dynts::mlp_gemm_kernel<1, PARTS, PACKED>), grid, block, 0, st, e0, e1, 0, p); break;
-    case 2: hipExtLaunchKernelGGL((dynts::mlp_gemm_kernel<2, PARTS, PACKED>), grid, block, 0, st, e0, e1, 0, p); break;
-    case 4: hipExtLaunchKernelGGL((dynts::mlp_gemm_kernel<4, PARTS, PACKED>), grid, block, 0, st, e0, e1, 0, p); break;
-    default: hipExtLaunchKernelGGL((dynts::mlp_gemm_kernel<8, PARTS, PACKED>), grid, block, 0, st, e0, e1, 0, p); break;
+template <bool SECOND>
+void launch_mlp(const dynts::MlpParams &p, int packed, int ft, int bt, int wgs, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  const dim3 grid(wgs);
+  if (packed) {
+    if (ft == 1) launch_mlp_ft<1, SECOND, true>(p, bt, grid, st, e0, e1);
+    else launch_mlp_ft<2, SECOND, true>(p, bt, grid, st, e0, e1);
+  } else {
+    if (ft == 1) launch_mlp_ft<1, SECOND, false>(p, bt, grid, st, e0, e1);
+    else launch_mlp_ft<2, SECOND, false>(p, bt, grid, st, e0, e1);
   }
 }
 
@@ -938,8 +952,7 @@ int dynts_predictor_pack(const uint16_t *W, int32_t m, int32_t K, uint16_t *W_pa
 
 size_t dynts_predict_scratch_bytes(const dynts_predictor *w, int32_t batch) {
   if (check_predictor(w, batch) != DYNTS_OK) return 0;
-  const MlpPlan l1 = mlp_plan(batch, w->d, 1), l2 = mlp_plan(batch, w->m1, 2);
-  return mlp_scratch(w, batch, l1, l2).total;
+  return mlp_plan(w, batch).total;
 }
 
 int dynts_predict_scores(const dynts_predictor *w, const uint16_t *h, int32_t batch, float *s_out, int32_t n_rep,
@@ -952,27 +965,27 @@ int dynts_predict_scores(const dynts_predictor *w, const uint16_t *h, int32_t ba
   if (reinterpret_cast<uintptr_t>(h) % 16 || reinterpret_cast<uintptr_t>(w->W1) % 16 ||
       reinterpret_cast<uintptr_t>(w->W2) % 16)
     return DYNTS_EINVAL;
-  const MlpPlan l1 = mlp_plan(batch, w->d, 1), l2 = mlp_plan(batch, w->m1, 2);
-  const MlpScratch sc = mlp_scratch(w, batch, l1, l2);
-  if (scratch_bytes < sc.total || reinterpret_cast<uintptr_t>(scratch) % kAlign) return DYNTS_EWORKSPACE;
+  if ((long long)batch * w->d * 2 >= dynts::kMlpNowhere || (long long)w->m1 * 64 * 8 >= dynts::kMlpNowhere) return DYNTS_ESHAPE;  // 32-bit offsets
+  const MlpPlan pl = mlp_plan(w, batch);
+  if (scratch_bytes < pl.total || reinterpret_cast<uintptr_t>(scratch) % kAlign) return DYNTS_EWORKSPACE;
   unsigned char *base = static_cast<unsigned char *>(scratch);
-  float *P1 = reinterpret_cast<float *>(base + sc.off_p1), *P2 = reinterpret_cast<float *>(base + sc.off_p2);
-  uint16_t *yhi = reinterpret_cast<uint16_t *>(base + sc.off_yhi), *ylo = reinterpret_cast<uint16_t *>(base + sc.off_ylo);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  dynts::MlpParams p{};
+  p.W = w->W1; p.x = h; p.bias = w->b1;
+  p.Nb = batch; p.m = w->m1; p.K = w->d; p.act = w->activation;
+  p.y = reinterpret_cast<uint16_t *>(base);
+  p.clear = reinterpret_cast<uint32_t *>(base + pl.off_sum);
+  p.n_clear = (uint32_t)((pl.total - pl.off_sum) / 16);
   // the optional events bracket the whole call: start on the first kernel, stop on the last
-  dynts::MlpGemmParams g1{w->W1, h, nullptr, P1, batch, w->m1, w->d};
-  if (w->packed) launch_mlp_gemm<1, true>(g1, l1, st, static_cast<hipEvent_t>(start), nullptr);
-  else launch_mlp_gemm<1, false>(g1, l1, st, static_cast<hipEvent_t>(start), nullptr);
-  const size_t n1 = (size_t)batch * w->m1 / 4;
-  hipLaunchKernelGGL(dynts::mlp_reduce_act_kernel, dim3((unsigned)((n1 + 255) / 256)), dim3(256), 0, st, P1, w->b1,
-                     l1.nsplit, batch, w->m1, w->activation, yhi, ylo, reinterpret_cast<uint32_t *>(base + sc.off_cnt));
-  dynts::MlpGemmParams g2{w->W2, yhi, ylo, P2, batch, w->m2, w->m1};
-  if (w->packed) launch_mlp_gemm<2, true>(g2, l2, st, nullptr, nullptr);
-  else launch_mlp_gemm<2, false>(g2, l2, st, nullptr, nullptr);
-  hipExtLaunchKernelGGL(dynts::mlp_reduce_dot_kernel, dim3((w->m2 + 255) / 256, batch), dim3(256), 0, st, nullptr,
-                        static_cast<hipEvent_t>(stop), 0, P2, w->b2, l2.nsplit, batch, w->m2, w->activation, w->w3,
-                        w->b3, reinterpret_cast<uint64_t *>(base + sc.off_part), next_launch_tag(),
-                        reinterpret_cast<uint32_t *>(base + sc.off_cnt), s_out, n_rep, capturing(st) ? 1 : 0);
+  launch_mlp<false>(p, w->packed, pl.ft1, pl.bt, pl.wgs1, st, static_cast<hipEvent_t>(start), nullptr);
+  p.W = w->W2; p.x = p.y; p.bias = w->b2; p.m = w->m2; p.K = w->m1;
+  p.w3 = w->w3; p.b3 = w->b3; p.ns = pl.ns;
+  p.part_sum = reinterpret_cast<uint64_t *>(base + pl.off_sum);
+  p.part_dot = reinterpret_cast<uint64_t *>(base + pl.off_dot);
+  p.group_cnt = reinterpret_cast<uint32_t *>(base + pl.off_group);
+  p.done_cnt = reinterpret_cast<uint32_t *>(base + pl.off_done);
+  p.s_out = s_out; p.n_rep = n_rep; p.clear_dot = capturing(st) ? 1 : 0;
+  launch_mlp<true>(p, w->packed, pl.ft2, pl.bt, pl.groups * pl.ns, st, nullptr, static_cast<hipEvent_t>(stop));
   return launch_status();
 }
 

@@ -149,3 +149,24 @@ def test_paper_inference_mode_end_to_end(B):
     S = f64(cache.S[0])
     assert np.all(S[:, 0, :] == S[:, 1, :])
     assert int(cache.status.item()) == 0
+
+
+@pytest.mark.parametrize("d,m1,m2", [(96, 4128, 1072),   # two tiles a workgroup in both layers, the last of layer 2 alone; an odd number of k-steps
+                                     (32, 2080, 1024),   # one k-step in layer 1; four or two workgroups share the K of layer 2
+                                     (1056, 96, 16)])    # one group of features, and fewer k-steps than waves
+@pytest.mark.parametrize("batch", [1, 16, 17, 33, 49, 64, 65, 96, 97, 128])
+def test_tile_edges(B, d, m1, m2, batch):
+    """Every number of batch tiles at its edges, with both numbers of feature tiles and shared and unshared K."""
+    _run(B, np.random.default_rng(d + batch), d, m1, m2, batch, orc.ACT_RELU, bias=batch % 2 == 1, n_rep=2, pack=batch % 3 != 0)
+
+
+def test_one_scratch_serves_calls_of_any_batch(B):
+    """The scratch's layout follows the batch: what a call of one batch leaves is never taken for a word of another's."""
+    rng, dev = np.random.default_rng(3), torch.device("cuda:0")
+    ws = _make(rng, 128, 2048, 1040)
+    pred = B.Predictor(*[w.to(dev) for w in ws], activation=B.DYNTS_ACT_RELU)
+    for batch in (128, 3, 70, 128, 33, 17, 3, 48):
+        h = torch.from_numpy(rng.standard_normal((batch, 128)).astype(np.float32)).to(torch.bfloat16)
+        s = torch.zeros(batch, device=dev)
+        B.dynts_predict_scores(pred, h.to(dev), s)
+        assert_close(f64(s), orc.predictor(f64(h), *[f64(w) for w in ws], orc.ACT_RELU), "batch %d" % batch, tight=1e-4)
