@@ -6,8 +6,10 @@
 // places, AttendParams::rounds) -- and then an equal, contiguous
 // share of the slots behind those first tiles, 32 at a time, with the next tile's loads already
 // in flight while it works on the current one:
-//   * K rows go straight from HBM into MFMA operand registers (16-byte loads; lane (r, kg)
-//     holds row r, columns 32*ks + 8*kg .. +7).  One v_mfma_f32_16x16x32_bf16 per 32 columns
+//   * K rows are read whole, 1 KB a load instruction, and turned into MFMA operands through a wave-private LDS tile (lane (r, kg)
+//     gets row r, columns 32*ks + 8*kg .. +7): read from memory in that order, 16 rows x 64 bytes an instruction, a
+//     compute unit takes in 38 B/ns instead of 140, and the first tiles alone took it 2 us.
+//     One v_mfma_f32_16x16x32_bf16 per 32 columns
 //     gives the logits of 16 slots x 16 (padded) query heads of the group, so a K tile is read
 //     once for the whole GQA group (Eq. attn-score).
 //   * the same K registers are multiplied with the PREVIOUS step's query (operands swapped, so
@@ -73,8 +75,9 @@ struct AttendParams {
   // second pass over K.  Null: not kept.
   float *spill;
   int cap_pad;              // cap rounded up to a whole tile: row pitch of the kept logits (a tile's store stays inside its row)
-  uint32_t *unit_cnt;       // [Nb][Hkv] ticket counters, zero between launches
-  uint32_t *seq_cnt;        // [Nb]      arrival counters, zero between launches
+  uint32_t *unit_cnt;       // [Nb][Hkv][cnt_stride] ticket counters, zero between launches
+  uint32_t *seq_cnt;        // [Nb][cnt_stride]      arrival counters, zero between launches
+  int cnt_stride;           // words from one counter to the next
   int32_t *status;
   int Nb, Hq, Hkv, G, cap, nsplit;
   int track;                // 1: scores are accumulated from attention (save q and statistics)
@@ -122,36 +125,19 @@ __device__ __forceinline__ u32x4 load_row_piece(const char *p) {
   return *reinterpret_cast<const u32x4 *>(p);
 }
 
-// K rows of the 32-slot tile at t as MFMA operand fragments; rows past `end` repeat row end-1.
-// Addresses are a uniform base plus a 32-bit byte offset (a unit's cache is far below 4 GiB), which
-// keeps the per-tile address arithmetic to a clamp and a multiply-add per 16 rows.
+// The 32 rows of the tile at t, whole rows across 16-byte pieces: a load instruction reads contiguous memory.  (Read in the order in
+// which the MFMA operands want them, 16 rows x 64 bytes, a compute unit takes in 38 B/ns instead of 140.)  Rows past `end`
+// repeat row end-1.  Addresses are a uniform base plus a 32-bit byte offset (a unit's cache is far below 4 GiB).
 template <int D, bool NT = false>
-__device__ __forceinline__ void load_k_tile(bf16x8 (&kf)[2][D / 32], const uint16_t *Kb, int t, int r16, int kg,
-                                            int end) {
-  const char *base = reinterpret_cast<const char *>(Kb);
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    int row = t + 16 * s + r16;
-    row = row < end ? row : end - 1;
-    const uint32_t off = (uint32_t)row * (uint32_t)(2 * D) + 16u * (uint32_t)kg;
-#pragma unroll
-    for (int ks = 0; ks < D / 32; ++ks)
-      kf[s][ks] = __builtin_bit_cast(bf16x8, load_row_piece<NT>(base + off + 64 * ks));
-  }
-}
-
-// V rows of the tile, whole rows across 16-byte pieces (coalesced); rows past `end` repeat row end-1
-template <int D, bool NT = false>
-__device__ __forceinline__ void load_v_tile(u32x4 (&vf)[kTile / (64 / (D / 8))], const uint16_t *Vb, int t,
-                                            int lane, int end) {
+__device__ __forceinline__ void load_tile(u32x4 (&f)[kTile / (64 / (D / 8))], const uint16_t *base_, int t, int lane, int end) {
   constexpr int PIECES = D / 8, VROWS = 64 / PIECES;
-  const char *base = reinterpret_cast<const char *>(Vb);
+  const char *base = reinterpret_cast<const char *>(base_);
   const uint32_t lane_off = 16u * (uint32_t)(lane % PIECES);
 #pragma unroll
   for (int it = 0; it < kTile / VROWS; ++it) {
     int row = t + VROWS * it + lane / PIECES;
     row = row < end ? row : end - 1;
-    vf[it] = load_row_piece<NT>(base + ((uint32_t)row * (uint32_t)(2 * D) + lane_off));
+    f[it] = load_row_piece<NT>(base + ((uint32_t)row * (uint32_t)(2 * D) + lane_off));
   }
 }
 // Cross-workgroup traffic inside one launch (split partials, arrival counters) consists of relaxed
@@ -209,6 +195,7 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   constexpr int VROWS = 64 / PIECES;      // rows covered by one wave-wide 16-byte load
   constexpr int VIT = kTile / VROWS;
   constexpr int VSTRIDE = 2 * D + 32;     // bytes per staged V row (+32: transposing reads hit distinct banks)
+  constexpr int KSTRIDE = 2 * D + 16;     // bytes per staged K or query row (+16: 16 rows' pieces lie in distinct banks)
   constexpr int OSTRIDE = D + 4;          // floats per row of the cross-wave output reduction
   constexpr bool STREAM = LARGE == kStream, BURST = LARGE == kBurst;
   static_assert(!(STREAM && PAGED), "pages are loaded through the caches");
@@ -219,6 +206,9 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   __shared__ float sm_fin[2][16];
   __shared__ uint32_t sm_flag;
   __shared__ int32_t sm_hdr[5];
+  __shared__ __align__(16) unsigned char sm_q[2 * 16 * KSTRIDE];  // this step's query rows, the previous step's
+  __shared__ __align__(16) float sm_ml[32];                       // statistics of the previous step
+  __shared__ __align__(16) unsigned char sm_new[APPEND ? 4 * D : 16];  // the appended token's K and V row
   // updated scores of up to kScoreTiles consecutive tiles per wave, written out together (see flush_scores)
   constexpr int kScoreTiles = 16;
   __shared__ __align__(16) float sm_score[PENDING && BURST ? kWaves : 1][PENDING && BURST ? kScoreTiles * kTile : 4];
@@ -286,17 +276,39 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   } else if (tid == 4 && p.active) {
     hdr_word = (int)p.active[b];
   }
+  // The query rows, the previous step's and its statistics, and the appended token's rows: fetched once per workgroup, a piece
+  // a thread, and handed round through LDS.
+  const size_t qrow0 = ((size_t)b * p.Hq + (size_t)h * G) * D;
+  constexpr int NQ = (2 * 16 * PIECES + kThreads - 1) / kThreads;
+  u32x4 qpiece[NQ];
+#pragma unroll
+  for (int j = 0; j < NQ; ++j) {
+    const int i = tid + j * kThreads, row = i / PIECES % 16;
+    qpiece[j] = u32x4{0u, 0u, 0u, 0u};  // (rows past the group's heads)
+    if (row < G) {
+      if (i < 16 * PIECES) {
+        if (ATTEND) qpiece[j] = load_u32x4(p.q + qrow0 + 8 * (size_t)i);
+      } else if (PENDING && i < 2 * 16 * PIECES) {
+        qpiece[j] = load_u32x4(p.qprev + qrow0 + 8 * (size_t)(i - 16 * PIECES));
+      }
+    }
+  }
+  float ml_word = 0.f;
+  if (PENDING && wave == kWaves - 2 && lane < 2 * G) ml_word = p.mlprev[((size_t)b * p.Hq + (size_t)h * G) * 2 + lane];
+  const bool new_wave = APPEND && split == 0 && wave == 0;               // starts from the appended token
+  const bool row_wave = APPEND && split == 0 && wave == kWaves - 1;      // writes its row into the cache
+  u32x4 new_piece = u32x4{0u, 0u, 0u, 0u};
+  if (row_wave && lane < 2 * PIECES) new_piece = load_u32x4((lane < PIECES ? p.k_new : p.v_new) + unit * D + 8 * (lane % PIECES));
   __builtin_amdgcn_sched_barrier(0);
-  bf16x8 kf[2][KS];
-  u32x4 vf[VIT];
+  u32x4 kr[VIT], vf[VIT];
   float s_old = 0.f;
   const bool first_past = STREAM && p.rounds == 0;
   if (first_past) {
     DYNTS_OWN_BRANCH;
-    load_k_tile<D, true>(kf, Kb, t, r16, kg, p.cap);
+    load_tile<D, true>(kr, Kb, t, lane, p.cap);
     DYNTS_OWN_BRANCH;
   } else if (!PAGED) {
-    load_k_tile<D>(kf, Kb, t, r16, kg, p.cap);
+    load_tile<D>(kr, Kb, t, lane, p.cap);
   }
   if (PENDING) {
     const int tok = t + (lane & (kTile - 1));
@@ -304,10 +316,10 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   }
   if (ATTEND && first_past) {
     DYNTS_OWN_BRANCH;
-    load_v_tile<D, true>(vf, Vb, t, lane, p.cap);
+    load_tile<D, true>(vf, Vb, t, lane, p.cap);
     DYNTS_OWN_BRANCH;
   } else if (ATTEND && !PAGED) {
-    load_v_tile<D>(vf, Vb, t, lane, p.cap);
+    load_tile<D>(vf, Vb, t, lane, p.cap);
   }
   if (PAGED) {
     // The first tile's page is looked up right away and its 32 rows fetched whole (a tile lies inside one
@@ -315,65 +327,42 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
     // out to be; rows past the sequence hold finite stale data and meet masked logits and zero weights).
     const size_t b0 = page_base(page_of(t));
     const int tr = t & (kPageSlots - 1);
-    load_k_tile<D>(kf, Kb + b0, tr, r16, kg, tr + kTile);
-    if (ATTEND) load_v_tile<D>(vf, Vb + b0, tr, lane, tr + kTile);
+    load_tile<D>(kr, Kb + b0, tr, lane, tr + kTile);
+    if (ATTEND) load_tile<D>(vf, Vb + b0, tr, lane, tr + kTile);
   }
   __builtin_amdgcn_sched_barrier(0);
 
+  // Hand them round.  The tile loads are still in flight across this barrier.
+  if (tid < 5) sm_hdr[tid] = hdr_word;
+#pragma unroll
+  for (int j = 0; j < NQ; ++j) {
+    const int i = tid + j * kThreads;
+    if (i < (PENDING ? 2 : 1) * 16 * PIECES) *reinterpret_cast<u32x4 *>(sm_q + i / PIECES * KSTRIDE + 16 * (i % PIECES)) = qpiece[j];
+  }
+  if (PENDING && wave == kWaves - 2 && lane < 32) sm_ml[lane] = ml_word;
+  if (row_wave && lane < 2 * PIECES) *reinterpret_cast<u32x4 *>(sm_new + 16 * lane) = new_piece;
+  __syncthreads();
   // query fragments: lane (g, kg) holds q[g][32*ks + 8*kg .. +7]
   bf16x8 qf[KS], qpf[KS];
-  const size_t qoff = ((size_t)b * p.Hq + (size_t)h * G + g) * D + 8 * kg;
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
-    qf[ks] = bf16x8{};
-    qpf[ks] = bf16x8{};
-    if (g < G) {
-      if (ATTEND) qf[ks] = load_bf16x8(p.q + qoff + 32 * ks);
-      if (PENDING) qpf[ks] = load_bf16x8(p.qprev + qoff + 32 * ks);
-    }
+    const unsigned char *src = sm_q + g * KSTRIDE + 64 * ks + 16 * kg;
+    if (ATTEND) qf[ks] = *reinterpret_cast<const bf16x8 *>(src);
+    if (PENDING) qpf[ks] = *reinterpret_cast<const bf16x8 *>(src + 16 * KSTRIDE);
   }
   // statistics of the deferred update for heads 4*kg .. 4*kg+3 (the rows this lane gets from
   // the swapped-operand MFMA)
   float mprev[4], inv_lprev[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    mprev[i] = 0.f;
-    inv_lprev[i] = 0.f;
-    const int gg = 4 * kg + i;
-    if (PENDING && gg < G) {
-      const float *ml = p.mlprev + ((size_t)b * p.Hq + (size_t)h * G + gg) * 2;
-      mprev[i] = ml[0];
-      inv_lprev[i] = ml[1];
-    }
+    mprev[i] = PENDING ? sm_ml[8 * kg + 2 * i] : 0.f;  // (0 past the group's heads)
+    inv_lprev[i] = PENDING ? sm_ml[8 * kg + 2 * i + 1] : 0.f;
   }
-
-  // the wave that takes the appended token asks for its row (and what goes with it) right away
-  const bool new_wave = APPEND && split == 0 && wave == 0;
-  bf16x8 kn[KS];
-  uint2 vn[CB];
-  int pos_new = 0;
-  float s_init = 0.f;
-  if (new_wave) {
-    const uint16_t *knew = p.k_new + unit * D;
-    const uint16_t *vnew = p.v_new + unit * D;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) kn[ks] = load_bf16x8(knew + 32 * ks + 8 * kg);  // every operand row is k_new
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb) vn[cb] = *reinterpret_cast<const uint2 *>(vnew + 16 * cb + 4 * kg);
-    if (p.s_new) s_init = p.s_new[unit];
-  }
-
-  // hand the three per-sequence words from wave 0 to the whole workgroup.  Everything above was only
-  // ISSUED (the tile loads are still in flight across this barrier); wave 0 waits for its three words,
-  // which it would have had to do next anyway.
-  if (tid < 5) sm_hdr[tid] = hdr_word;
-  __syncthreads();
   const int len_raw = sm_hdr[0];
   const int prev_raw = PENDING ? sm_hdr[1] : 0;
   const int pos_new_all = APPEND ? sm_hdr[2] : 0;
   const int M = sm_hdr[3];
   const int act_raw = sm_hdr[4];
-  pos_new = pos_new_all;
 
   // ---- what this launch does for sequence b (identical in every workgroup of b) ---------
   // n_rows cache slots are attended from the cache; when a token is appended in the same
@@ -424,11 +413,11 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   uint32_t seq_ticket = 0xffffffffu;
   auto seq_checkin = [&]() {
     if (ATTEND) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-    if (ATTEND && tid == 0) seq_ticket = draw_ticket(&p.seq_cnt[b]);
+    if (ATTEND && tid == 0) seq_ticket = draw_ticket(p.seq_cnt + (size_t)b * p.cnt_stride);
   };
   auto seq_settle = [&]() {
     if (ATTEND && tid == 0 && seq_ticket == (uint32_t)p.nsplit * p.Hkv - 1) {
-      __hip_atomic_store(&p.seq_cnt[b], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(p.seq_cnt + (size_t)b * p.cnt_stride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (p.track) p.nprev[b] = n_now;
       if (APPEND && appending) {
         p.seq_len[b] = n_now;
@@ -456,9 +445,12 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
 
   // keep this call's query for the next deferred score update (its own buffer: the old one is
   // still being read by the other workgroups of this launch)
-  if (ATTEND && p.track && split == 0 && wave == 0 && g < G && n_now > 0) {
+  if (ATTEND && p.track && split == 0 && n_now > 0) {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) store_bf16x8(p.qnext + qoff + 32 * ks, qf[ks]);
+    for (int j = 0; j < NQ; ++j) {
+      const int i = tid + j * kThreads;
+      if (i < 16 * PIECES && i / PIECES < G) store_u32x4(p.qnext + qrow0 + 8 * (size_t)i, qpiece[j]);
+    }
   }
 
   float m_run = -INFINITY, l_run = 0.f;
@@ -466,24 +458,29 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb) oacc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // ---- fused append: the new token is this wave's starting softmax state -----------------
+  // ---- fused append ------------------------------------------------------------------------
   // One wave of the unit takes the appended token: its logit is q.k_new for every head, its
   // weight relative to itself is 1, so the running state starts as (max = logit, sum = 1,
-  // output = v_new).  The same wave writes the row into the cache.  All of it overlaps the
+  // output = v_new).  Another wave writes the row into the cache.  All of it overlaps the
   // wait for the first tile.
   if (new_wave && appending) {
     f32x4 a0 = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) a0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kn[ks], qf[ks], a0, 0, 0, 0);
+    for (int ks = 0; ks < KS; ++ks) {  // every operand row is k_new
+      const bf16x8 kn = *reinterpret_cast<const bf16x8 *>(sm_new + 64 * ks + 16 * kg);
+      a0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kn, qf[ks], a0, 0, 0, 0);
+    }
     m_run = a0[0] * p.scale_log2;
     l_run = kg == 0 ? 1.f : 0.f;  // per-lane partial sums are added over kg at the end
     if (SPILL && kg == 0 && g < G) p.spill[(unit * G + g) * (size_t)p.cap_pad + n_old] = m_run;
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
       typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-      const bf16x4 v4 = __builtin_bit_cast(bf16x4, vn[cb]);
+      const bf16x4 v4 = *reinterpret_cast<const bf16x4 *>(sm_new + 2 * D + 32 * cb + 8 * kg);
       oacc[cb] = f32x4{(float)v4[0], (float)v4[1], (float)v4[2], (float)v4[3]};
     }
+  }
+  if (row_wave && appending) {
     size_t new_row = (size_t)n_old * D;  // element offset of the new row from Kb / Vb
     bool have_row = true;
     if (PAGED) {
@@ -509,15 +506,10 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
       have_row = pg >= 0 && pg < p.n_pages;
       new_row = ((size_t)(have_row ? pg : 0) * kPageSlots + n_old % kPageSlots) * D;
     }
-    if (r16 == 0 && have_row) {
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb) *reinterpret_cast<uint2 *>(Vb + new_row + 16 * cb + 4 * kg) = vn[cb];
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) store_bf16x8(Kb + new_row + 32 * ks + 8 * kg, kn[ks]);
-    }
+    if (lane < 2 * PIECES && have_row) store_u32x4((lane < PIECES ? Kb : Vb) + new_row + 8 * (lane % PIECES), new_piece);
     if (lane == 0) {
-      Sb[n_old] = s_init;
-      p.pos[unit * (size_t)p.cap + n_old] = pos_new;
+      Sb[n_old] = p.s_new ? p.s_new[unit] : 0.f;
+      p.pos[unit * (size_t)p.cap + n_old] = pos_new_all;
     }
   }
 
@@ -587,6 +579,17 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
     const int att_hi = hi < n_rows ? hi : n_rows;
     const int pend_hi = hi < n_prev ? hi : n_prev;
 
+    // the tile's K rows into operand order through the wave's LDS tile: lane (r, kg) gets row r, columns 32*ks + 8*kg .. +7.
+    // (A wave's LDS accesses are carried out in order, so K and V of one tile after another share the room.)
+#pragma unroll
+    for (int it = 0; it < VIT; ++it)
+      *reinterpret_cast<u32x4 *>(vst + (VROWS * it + vrow_l) * KSTRIDE + 16 * vpiece) = kr[it];
+    wave_lds_fence();
+    bf16x8 kf[2][KS];
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kf[s][ks] = *reinterpret_cast<const bf16x8 *>(vst + (16 * s + r16) * KSTRIDE + 64 * ks + 16 * kg);
     // logits for the current query (A = K rows, B = q) and for the previous one (swapped:
     // accp[s][i] = logit(slot t + 16 s + r16, head 4 kg + i))
     f32x4 acc[2], accp[2];
@@ -614,10 +617,10 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
     }
     if (STREAM && past) {
       DYNTS_OWN_BRANCH;
-      load_k_tile<D, true>(kf, Kb + nb, nt, r16, kg, nk_end);
+      load_tile<D, true>(kr, Kb + nb, nt, lane, nk_end);
       DYNTS_OWN_BRANCH;
     } else {
-      load_k_tile<D>(kf, Kb + nb, nt, r16, kg, nk_end);
+      load_tile<D>(kr, Kb + nb, nt, lane, nk_end);
     }
     if (PENDING) {
       const int tok = tn + (lane & (kTile - 1));
@@ -718,10 +721,10 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
       wave_lds_fence();
       if (STREAM && past) {
         DYNTS_OWN_BRANCH;
-        load_v_tile<D, true>(vf, Vb + nb, nt, lane, nv_end);
+        load_tile<D, true>(vf, Vb + nb, nt, lane, nv_end);
         DYNTS_OWN_BRANCH;
       } else {
-        load_v_tile<D>(vf, Vb + nb, nt, lane, nv_end);
+        load_tile<D>(vf, Vb + nb, nt, lane, nv_end);
       }
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) {
@@ -757,7 +760,7 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   // with several chunks per unit: draw this workgroup's ticket now, so that the round trip of the atomic
   // overlaps the combine below.  (The holder of the last ticket merges, whenever it gets there.)
   uint32_t unit_ticket = 0;
-  if (chunks_vis > 1 && tid == 0) unit_ticket = draw_ticket(&p.unit_cnt[unit]);
+  if (chunks_vis > 1 && tid == 0) unit_ticket = draw_ticket(p.unit_cnt + unit * p.cnt_stride);
   const bool has_partial = split < chunks_now;  // workgroup-uniform; false: the chunk only carried a deferred update
   if (chunks_vis == 1 && !has_partial) return;
 
@@ -850,7 +853,7 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   __syncthreads();
   const bool merger = sm_flag == (uint32_t)chunks_vis - 1;
   if (!merger) return;
-  if (tid == 0) __hip_atomic_store(&p.unit_cnt[unit], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (tid == 0) __hip_atomic_store(p.unit_cnt + unit * p.cnt_stride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (chunks_now == 0) return;
 
   // Merging: thread tid owns output elements tid + k * kThreads, k < E, in its own partial and in the merge; chunks are

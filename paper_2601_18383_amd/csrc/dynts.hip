@@ -26,6 +26,9 @@ namespace {
 constexpr size_t kAlign = 256;
 constexpr int kSelectLdsMax = 16384;  // candidates whose keys are cached in LDS (64 KiB)
 
+// Ticket counters lie 256 bytes apart: a line of 32 of them was handed from XCD to XCD for every ticket.
+constexpr int kCounterStride = 64;
+
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Plan {
@@ -74,8 +77,8 @@ Plan make_plan(const dynts_config &c, int target_wgs, int waves) {
   size_t off = 0;
   p.off_part_o = off;  off = align_up(off + rows * c.head_dim * sizeof(uint64_t));  // value + tag per word
   p.off_part_ml = off; off = align_up(off + rows * 2 * sizeof(uint64_t));
-  p.off_unit_cnt = off; off = align_up(off + (size_t)units * sizeof(uint32_t));
-  p.off_seq_cnt = off; off = align_up(off + (size_t)c.batch * sizeof(uint32_t));
+  p.off_unit_cnt = off; off = align_up(off + (size_t)units * kCounterStride * sizeof(uint32_t));
+  p.off_seq_cnt = off; off = align_up(off + (size_t)c.batch * kCounterStride * sizeof(uint32_t));
   const size_t LB = (size_t)c.n_layers * c.batch;
   p.off_qprev = off;   off = align_up(off + 2 * LB * c.n_q_heads * c.head_dim * sizeof(uint16_t));  // two copies, used in turn
   p.off_mlprev = off;  off = align_up(off + LB * c.n_q_heads * 2 * sizeof(float));
@@ -244,6 +247,7 @@ __global__ void clear_words_kernel(uint32_t *words, size_t n) {
 struct Transient {
   uint64_t *part_o, *part_ml;
   uint32_t *unit_cnt, *seq_cnt;
+  int cnt_stride;
 };
 
 // attend (optionally with fused append) and/or the deferred score update of one layer
@@ -263,6 +267,7 @@ int run_attend(dynts_ctx *ctx, int layer, const uint16_t *q, const uint16_t *k_n
     tr.part_ml = reinterpret_cast<uint64_t *>(ctx->ws + pl.off_part_ml);
     tr.unit_cnt = reinterpret_cast<uint32_t *>(ctx->ws + pl.off_unit_cnt);
     tr.seq_cnt = reinterpret_cast<uint32_t *>(ctx->ws + pl.off_seq_cnt);
+    tr.cnt_stride = kCounterStride;
   }
   const LayerView lv = layer_view(ctx, layer);
   const bool track = c.score_mode == DYNTS_SCORE_ACCUMULATE;
@@ -299,6 +304,7 @@ int run_attend(dynts_ctx *ctx, int layer, const uint16_t *q, const uint16_t *k_n
   p.cap_pad = pl.cap_pad;
   p.unit_cnt = tr.unit_cnt;
   p.seq_cnt = tr.seq_cnt;
+  p.cnt_stride = tr.cnt_stride;
   p.status = ctx->status;
   p.Nb = c.batch; p.Hq = c.n_q_heads; p.Hkv = c.n_kv_heads; p.G = pl.G; p.cap = c.capacity;
   p.nsplit = pl.nsplit; p.track = track ? 1 : 0; p.scale_log2 = ctx->scale_log2;
@@ -796,6 +802,8 @@ int dynts_decode_step_static(dynts_ctx *ctx, int32_t layer, const uint16_t *q, c
   Transient tr;
   tr.unit_cnt = reinterpret_cast<uint32_t *>(base);
   tr.seq_cnt = reinterpret_cast<uint32_t *>(base + kStaticCounters / 2);
+  tr.cnt_stride = kCounterStride;  // (as far apart as they all fit)
+  while (units * tr.cnt_stride * sizeof(uint32_t) > kStaticCounters / 2) tr.cnt_stride /= 2;
   tr.part_o = reinterpret_cast<uint64_t *>(base + kStaticCounters);
   tr.part_ml = reinterpret_cast<uint64_t *>(base + kStaticCounters + part_o_bytes);
   return fused_step(ctx, layer, q, k_new, v_new, ext ? s_new : nullptr, active, out, lse, true, st, &tr);
