@@ -118,27 +118,23 @@ __device__ __forceinline__ void store_bf16x8(uint16_t *p, bf16x8 v) {
 // (two branches that differ only in how they load would be merged into one)
 #define DYNTS_OWN_BRANCH asm volatile("; past the caches")
 
-// 16 bytes of a cache row; NT: past the caches (see AttendParams::fit_slots)
-template <bool NT>
-__device__ __forceinline__ u32x4 load_row_piece(const char *p) {
-  if (NT) return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-  return *reinterpret_cast<const u32x4 *>(p);
+// The first `rows` rows of a unit's cache (or of a page) as a buffer: a load past them reads zeros and fetches nothing, so that
+// the prefetch behind a wave's last tile needs no branch (behind one every wait would be a wait for all loads), no clamp, and
+// no memory.
+using RowBuffer = __amdgpu_buffer_rsrc_t;
+template <int D>
+__device__ __forceinline__ RowBuffer row_buffer(const uint16_t *base, int rows) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(base), 0, (rows > 0 ? rows : 0) * (2 * D), 0x00027000);
 }
 
-// The 32 rows of the tile at t, whole rows across 16-byte pieces: a load instruction reads contiguous memory.  (Read in the order in
-// which the MFMA operands want them, 16 rows x 64 bytes, a compute unit takes in 38 B/ns instead of 140.)  Rows past `end`
-// repeat row end-1.  Addresses are a uniform base plus a 32-bit byte offset (a unit's cache is far below 4 GiB).
+// The 32 rows of the tile at t: contiguous memory, 1 KB a load instruction.  (Read in the order in which the MFMA operands want
+// them, 16 rows x 64 bytes, a compute unit takes in 38 B/ns instead of 140.)  NT: past the caches (see AttendParams::fit_slots).
 template <int D, bool NT = false>
-__device__ __forceinline__ void load_tile(u32x4 (&f)[kTile / (64 / (D / 8))], const uint16_t *base_, int t, int lane, int end) {
-  constexpr int PIECES = D / 8, VROWS = 64 / PIECES;
-  const char *base = reinterpret_cast<const char *>(base_);
-  const uint32_t lane_off = 16u * (uint32_t)(lane % PIECES);
+__device__ __forceinline__ void load_tile(u32x4 (&f)[kTile * D / 512], RowBuffer rows, int t, int lane) {
+  const uint32_t off = (uint32_t)t * (uint32_t)(2 * D) + 16u * (uint32_t)lane;
 #pragma unroll
-  for (int it = 0; it < kTile / VROWS; ++it) {
-    int row = t + VROWS * it + lane / PIECES;
-    row = row < end ? row : end - 1;
-    f[it] = load_row_piece<NT>(base + ((uint32_t)row * (uint32_t)(2 * D) + lane_off));
-  }
+  for (int it = 0; it < kTile * D / 512; ++it)
+    f[it] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, off + 1024u * it, 0, NT ? 2 : 0));
 }
 // Cross-workgroup traffic inside one launch (split partials, arrival counters) consists of relaxed
 // agent-scope atomics only, which compile to sc1 accesses that are written through to, and read
@@ -203,7 +199,7 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   __shared__ __align__(16) unsigned char smem[kWaves * kTile * VSTRIDE];
   __shared__ float sm_m[kWaves][16];
   __shared__ float sm_l[kWaves][16];
-  __shared__ float sm_fin[2][16];
+  __shared__ float sm_max[16];
   __shared__ uint32_t sm_flag;
   __shared__ int32_t sm_hdr[5];
   __shared__ __align__(16) unsigned char sm_q[2 * 16 * KSTRIDE];  // this step's query rows, the previous step's
@@ -214,7 +210,7 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   __shared__ __align__(16) float sm_score[PENDING && BURST ? kWaves : 1][PENDING && BURST ? kScoreTiles * kTile : 4];
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kg = lane >> 4;
   const int g = r16;  // query head (within the group) of this lane's logits
   // Workgroup -> (unit, chunk).  Consecutive workgroup ids go to the 8 XCDs in turn; the chunks of one
@@ -303,36 +299,26 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   u32x4 kr[VIT], vf[VIT];
   float s_old = 0.f;
   const bool first_past = STREAM && p.rounds == 0;
+  // (paged: the first tile's page is looked up right away and its 32 rows fetched whole: a tile lies inside one page, and a page id
+  // is clamped into the pool, so the addresses are valid whatever the length turns out to be)
+  const size_t b0 = PAGED ? page_base(page_of(t)) : 0;
+  const int t0 = PAGED ? t & (kPageSlots - 1) : t;
+  const RowBuffer k_first = row_buffer<D>(Kb + b0, PAGED ? kPageSlots : p.cap);
   if (first_past) {
     DYNTS_OWN_BRANCH;
-    load_tile<D, true>(kr, Kb, t, lane, p.cap);
+    load_tile<D, true>(kr, k_first, t0, lane);
     DYNTS_OWN_BRANCH;
-  } else if (!PAGED) {
-    load_tile<D>(kr, Kb, t, lane, p.cap);
+  } else {
+    load_tile<D>(kr, k_first, t0, lane);
   }
   if (PENDING) {
     const int tok = t + (lane & (kTile - 1));
     s_old = Sb[tok < p.cap ? tok : p.cap - 1];
   }
-  if (ATTEND && first_past) {
-    DYNTS_OWN_BRANCH;
-    load_tile<D, true>(vf, Vb, t, lane, p.cap);
-    DYNTS_OWN_BRANCH;
-  } else if (ATTEND && !PAGED) {
-    load_tile<D>(vf, Vb, t, lane, p.cap);
-  }
-  if (PAGED) {
-    // The first tile's page is looked up right away and its 32 rows fetched whole (a tile lies inside one
-    // page, and a page id is clamped into the pool, so the addresses are valid whatever the length turns
-    // out to be; rows past the sequence hold finite stale data and meet masked logits and zero weights).
-    const size_t b0 = page_base(page_of(t));
-    const int tr = t & (kPageSlots - 1);
-    load_tile<D>(kr, Kb + b0, tr, lane, tr + kTile);
-    if (ATTEND) load_tile<D>(vf, Vb + b0, tr, lane, tr + kTile);
-  }
   __builtin_amdgcn_sched_barrier(0);
 
-  // Hand them round.  The tile loads are still in flight across this barrier.
+  // Hand them round.  The K tile's loads are still in flight across this barrier.  (V's leave behind it, when the length is
+  // known: a wave has to issue what it asks for in front of the barrier, and the rows past the sequence come as zeros.)
   if (tid < 5) sm_hdr[tid] = hdr_word;
 #pragma unroll
   for (int j = 0; j < NQ; ++j) {
@@ -388,6 +374,16 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   int n_prev = prev_raw;
   n_prev = n_prev < 0 ? 0 : (n_prev > p.cap ? p.cap : n_prev);
   const int n_vis = n_rows > n_prev ? n_rows : n_prev;
+  if (ATTEND) {
+    const RowBuffer v_first = row_buffer<D>(Vb + b0, PAGED ? (n_rows - (t - t0) < kPageSlots ? n_rows - (t - t0) : kPageSlots) : n_rows);
+    if (first_past) {
+      DYNTS_OWN_BRANCH;
+      load_tile<D, true>(vf, v_first, t0, lane);
+      DYNTS_OWN_BRANCH;
+    } else {
+      load_tile<D>(vf, v_first, t0, lane);
+    }
+  }
   // workgroups of this unit that produce an attention partial (chunk 0 always does when the
   // sequence is attended: it owns the appended token), and that have any work at all
   // (a workgroup has work iff its first wave's first tile starts inside the sequence)
@@ -404,15 +400,10 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   // back: thread 0 checks in, and its own wave made those reads and has already consumed their values
   // (they went through LDS above), so the atomic is issued after they completed.  The last workgroup
   // to check in advances the three words -- by then no workgroup of the sequence has a read of them
-  // outstanding.  The check-in is issued early and its answer looked at later, so it costs no round
-  // trip at the end of the workgroup.
-  // All of the prologue's loads are waited for right before it: answers come back in order, so a wait for one of
-  // those loads that the compiler puts behind the atomic is a wait for the atomic's round trip as well, which it did in
-  // some forms and not in others (15 x 8 units of 74 - 270 slots, head_dim 128: 10.3 us a step with such a wait, 9.6 so;
-  // one short sequence, head_dim 64: 6.95 and 6.74).
+  // outstanding.  It is issued behind the first tile (answers come back in order: a wait for one of the first loads would be
+  // a wait for the atomic as well) and its answer is looked at when the waves have been combined.
   uint32_t seq_ticket = 0xffffffffu;
   auto seq_checkin = [&]() {
-    if (ATTEND) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     if (ATTEND && tid == 0) seq_ticket = draw_ticket(p.seq_cnt + (size_t)b * p.cnt_stride);
   };
   auto seq_settle = [&]() {
@@ -513,30 +504,19 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
     }
   }
 
-  seq_checkin();
-
-  // the first tile was fetched before the length was known: keep rows past the sequence out of P.V
-  if (ATTEND && !PAGED && t + kTile > n_rows) {
-#pragma unroll
-    for (int it = 0; it < VIT; ++it) vf[it] = (t + VROWS * it + vrow_l < n_rows) ? vf[it] : u32x4{0u, 0u, 0u, 0u};
-  }
-  // Row clamps of the prefetches: a prefetch must not pull another wave's rows, so rows are
-  // clamped to the end of this wave's own range (or, with no range, of its first tile); the
-  // clamp row is always a valid row of the allocation.
+  // A prefetch must not pull another wave's rows: the buffers end where this wave's own range does (or, with no range, its last
+  // tile at a fixed place), V's at the end of the sequence.
   int t_fix = t;  // this wave's last tile at a fixed place
   if (STREAM) {
     for (int f = 1; f < rounds; ++f) t_fix = t_fix + kTile * NW < n_vis ? t_fix + kTile * NW : t_fix;
   }
   const int own_end = ra < rb ? rb : (t_fix + kTile < n_vis ? t_fix + kTile : n_vis);
-  const int k_last = own_end > 0 ? own_end : 1;
   const int v_end = own_end < n_rows ? own_end : n_rows;
-  // (paged: V rows are clamped like K rows, so that one page serves both; slots below n_vis are allocated,
-  // and whatever lies past n_rows meets a zero weight)
-  const int v_last = PAGED ? k_last : (v_end > 0 ? v_end : 1);
+  const RowBuffer k_rows = row_buffer<D>(Kb, own_end), v_rows = row_buffer<D>(Vb, v_end);
   const bool past_caches = STREAM && n_vis > p.fit_slots;
   // paged: the page of the next tile to fetch is looked up one tile ahead of its use
   int pg_nxt = 0;
-  if (PAGED) pg_nxt = page_of(clamp_tile(ra, k_last));
+  if (PAGED) pg_nxt = page_of(clamp_tile(ra, own_end));
 
   // ---- updated scores leave in bursts (kBurst) ----------------------------------------------------
   // A tile updates 32 scores (128 bytes).  Written tile by tile these are small writes scattered through
@@ -604,23 +584,23 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
       }
     }
     const float s_cur = s_old;
-    // where the next tile is fetched from: (base, first row, row clamp), page-relative in the paged layout
-    size_t nb = 0;
-    int nt = tn, nk_end = k_last, nv_end = v_last;
+    // where the next tile is fetched from; in the paged layout relative to its page
+    int nt = tn;
+    RowBuffer k_next = k_rows, v_next = v_rows;
     if (PAGED) {
-      const int tnp = clamp_tile(tn, k_last), page_start = tnp & ~(kPageSlots - 1);
-      nb = page_base(pg_nxt);
-      nt = tnp - page_start;
-      nk_end = k_last - page_start;
-      nv_end = v_last - page_start;
-      pg_nxt = page_of(clamp_tile(tn + kTile, k_last));
+      const int page_start = tn & ~(kPageSlots - 1), left_k = own_end - page_start, left_v = v_end - page_start;
+      const size_t nb = page_base(pg_nxt);
+      nt = tn - page_start;
+      k_next = row_buffer<D>(Kb + nb, left_k < kPageSlots ? left_k : kPageSlots);
+      v_next = row_buffer<D>(Vb + nb, left_v < kPageSlots ? left_v : kPageSlots);
+      pg_nxt = page_of(clamp_tile(tn + kTile, own_end));
     }
     if (STREAM && past) {
       DYNTS_OWN_BRANCH;
-      load_tile<D, true>(kr, Kb + nb, nt, lane, nk_end);
+      load_tile<D, true>(kr, k_next, nt, lane);
       DYNTS_OWN_BRANCH;
     } else {
-      load_tile<D>(kr, Kb + nb, nt, lane, nk_end);
+      load_tile<D>(kr, k_next, nt, lane);
     }
     if (PENDING) {
       const int tok = tn + (lane & (kTile - 1));
@@ -721,10 +701,10 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
       wave_lds_fence();
       if (STREAM && past) {
         DYNTS_OWN_BRANCH;
-        load_tile<D, true>(vf, Vb + nb, nt, lane, nv_end);
+        load_tile<D, true>(vf, v_next, nt, lane);
         DYNTS_OWN_BRANCH;
       } else {
-        load_tile<D>(vf, Vb + nb, nt, lane, nv_end);
+        load_tile<D>(vf, v_next, nt, lane);
       }
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) {
@@ -746,7 +726,7 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   };
 
   if (t < n_vis) tile(t, t + kTile < n_vis ? t + kTile : n_vis, t < t_fix ? t + kTile * NW : ra, t == t_fix && past_caches);
-  seq_settle();
+  seq_checkin();
   if (STREAM) {
     while (t < t_fix) {
       t += kTile * NW;
@@ -762,26 +742,27 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   uint32_t unit_ticket = 0;
   if (chunks_vis > 1 && tid == 0) unit_ticket = draw_ticket(p.unit_cnt + unit * p.cnt_stride);
   const bool has_partial = split < chunks_now;  // workgroup-uniform; false: the chunk only carried a deferred update
-  if (chunks_vis == 1 && !has_partial) return;
+  if (chunks_vis == 1 && !has_partial) {
+    seq_settle();
+    return;
+  }
 
   constexpr int NE = (16 * D + kThreads - 1) / kThreads;  // output elements per thread at the largest group size
   const int ne = (G * D + kThreads - 1) / kThreads;
   const size_t ubase = unit * p.nsplit * (size_t)G;
 
-  // ---- combine the four waves ------------------------------------------------------------
+  // ---- combine the waves -----------------------------------------------------------------
+  // (sm_l holds a wave's sum relative to the workgroup's maximum, sm_m[0] that maximum after the second barrier)
   float *ored = reinterpret_cast<float *>(smem);
   if (has_partial) {
   l_run += __shfl_xor(l_run, 16);
   l_run += __shfl_xor(l_run, 32);
-  if (kg == 0) {
-    sm_m[wave][g] = m_run;
-    sm_l[wave][g] = l_run;
-  }
+  if (kg == 0) sm_m[wave][g] = m_run;
   __syncthreads();
   float mstar = sm_m[0][g];
 #pragma unroll
   for (int w = 1; w < kWaves; ++w) mstar = fmaxf(mstar, sm_m[w][g]);
-  const float f = (m_run == -INFINITY) ? 0.f : exp2f(m_run - mstar);
+  const float f = (m_run == -INFINITY) ? 0.f : fast_exp2(m_run - mstar);
   if (g < G) {
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
@@ -789,21 +770,20 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
       *reinterpret_cast<f32x4 *>(ored + (wave * 16 + g) * OSTRIDE + 16 * cb + 4 * kg) = v;
     }
   }
-  if (tid < G) {
-    float ms = sm_m[0][tid];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) ms = fmaxf(ms, sm_m[w][tid]);
-    float ls = 0.f;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      const float mw = sm_m[w][tid];
-      ls += (mw == -INFINITY) ? 0.f : sm_l[w][tid] * exp2f(mw - ms);
-    }
-    sm_fin[0][tid] = ms;
-    sm_fin[1][tid] = ls;
+  if (kg == 0) {
+    sm_l[wave][g] = l_run * f;
+    if (wave == 0) sm_max[g] = mstar;
   }
   __syncthreads();
   }
+  auto sum_of = [&](int gg) {  // softmax sum of this workgroup's slots
+    float ls = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) ls += sm_l[w][gg];
+    return ls;
+  };
+
+  seq_settle();
 
   const size_t orow0 = (size_t)b * p.Hq + (size_t)h * G;  // first query head of this group
   if (chunks_vis == 1) {
@@ -813,13 +793,14 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
       float sum = 0.f;
 #pragma unroll
       for (int w = 0; w < kWaves; ++w) sum += ored[(w * 16 + gg) * OSTRIDE + c];
-      p.out[(orow0 + gg) * D + c] = sum / sm_fin[1][gg];
+      p.out[(orow0 + gg) * D + c] = sum / sum_of(gg);
     }
     if (tid < G) {
-      if (p.lse) p.lse[orow0 + tid] = (sm_fin[0][tid] + log2f(sm_fin[1][tid])) * 0.6931471805599453f;
+      const float ls = sum_of(tid);
+      if (p.lse) p.lse[orow0 + tid] = (sm_max[tid] + log2f(ls)) * 0.6931471805599453f;
       if (p.track) {
-        p.mlprev[(orow0 + tid) * 2] = sm_fin[0][tid];
-        p.mlprev[(orow0 + tid) * 2 + 1] = sm_fin[1][tid];
+        p.mlprev[(orow0 + tid) * 2] = sm_max[tid];
+        p.mlprev[(orow0 + tid) * 2 + 1] = ls;
       }
     }
     return;
@@ -844,8 +825,8 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
       }
     }
     if (tid < G) {
-      tagged_store(&p.part_ml[(pbase + tid) * 2 + 0], sm_fin[0][tid], p.tag);
-      tagged_store(&p.part_ml[(pbase + tid) * 2 + 1], sm_fin[1][tid], p.tag);
+      tagged_store(&p.part_ml[(pbase + tid) * 2 + 0], sm_max[tid], p.tag);
+      tagged_store(&p.part_ml[(pbase + tid) * 2 + 1], sum_of(tid), p.tag);
     }
   }
   // the ticket was drawn when this workgroup's first wave left its tile loop; its answer is looked at now
@@ -857,12 +838,14 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   if (chunks_now == 0) return;
 
   // Merging: thread tid owns output elements tid + k * kThreads, k < E, in its own partial and in the merge; chunks are
-  // merged N at a time, in chunk order.  Asking for a group means: every thread requests its elements of the group's
-  // partials, and threads 0 .. 16 * N - 1 the (max, sum) of one (chunk, head) each; this workgroup's own partial never
+  // merged N at a time.  Asking for a group means: threads 0 .. 16 * N - 1 request the (max, sum) of one (head, chunk) each, every
+  // thread its elements of the group's partials; this workgroup's own partial never
   // comes from memory.  A round of asking takes a trip to the level all XCDs share, so with few elements per thread and many
-  // chunks as many are asked for at once as the same registers hold.
-  constexpr int kMostChunks = WIDE ? kThreads / 16 : 4;  // whose statistics are asked for at once, one thread per (chunk, head)
-  __shared__ float sm_pm[kMostChunks][16], sm_pl[kMostChunks][16];
+  // chunks as many are asked for at once as the same registers hold.  The chunks' weights are formed once per head, across the
+  // lanes that hold its statistics.
+  constexpr int kMostChunks = WIDE ? kThreads / 16 : 4;  // whose statistics are asked for at once, one thread per (head, chunk)
+  __shared__ __align__(16) float sm_w[16][kMostChunks];
+  __shared__ float sm_old[16], sm_sum[16];  // weight of the groups before, sum so far
   auto merge = [&](auto E_, auto N_) {
     constexpr int E = decltype(E_)::value, N = decltype(N_)::value;
     static_assert(N <= kMostChunks && 16 * N <= kThreads, "one thread per (chunk, head)");
@@ -870,52 +853,60 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
     // (uniform.  At head_dim 64 it spares groups of up to eight heads the second element, 0.5 - 2 % of a launch of 10 to 33
     // chunks; at head_dim 128 it costs the eight-chunk merges 1 %)
     auto has = [&](int k) { return D == 128 || WIDE || k < ne; };
+    const int my_g = tid / N, my_j = tid % N;  // whose statistics this thread asks for
+    const bool asks = tid < 16 * N && my_g < G;
     auto ask_group = [&](int s0) {
+      ask_m = ask_l = (uint64_t)p.tag << 32;  // nothing to wait for
+      if (asks && s0 + my_j < chunks_now && !(has_partial && s0 + my_j == split)) {
+        const uint64_t *src = &p.part_ml[(ubase + (size_t)(s0 + my_j) * G + my_g) * 2];
+        ask_m = tagged_load(src);
+        ask_l = tagged_load(src + 1);
+      }
 #pragma unroll
       for (int k = 0; k < E; ++k) {
         const int idx = tid + k * kThreads;
 #pragma unroll
         for (int j = 0; j < N; ++j) {
           const int sj = s0 + j;
-          ask_o[k][j] = (uint64_t)p.tag << 32;  // nothing to wait for
+          ask_o[k][j] = (uint64_t)p.tag << 32;
           if (has(k) && idx < G * D && sj < chunks_now && !(has_partial && sj == split))
             ask_o[k][j] = tagged_load(&p.part_o[(ubase + (size_t)sj * G + idx / D) * D + idx % D]);
         }
       }
-      ask_m = ask_l = (uint64_t)p.tag << 32;
-      if (tid < 16 * N) {
-        const int sj = s0 + (tid >> 4), gg = tid & 15;
-        if (sj < chunks_now && gg < G && !(has_partial && sj == split)) {
-          const uint64_t *src = &p.part_ml[(ubase + (size_t)sj * G + gg) * 2];
-          ask_m = tagged_load(src);
-          ask_l = tagged_load(src + 1);
-        }
-      }
     };
     auto group_fresh = [&]() {
-      bool ok = tag_is(ask_m, p.tag) && tag_is(ask_l, p.tag);
+      uint32_t differs = ((uint32_t)(ask_m >> 32) ^ p.tag) | ((uint32_t)(ask_l >> 32) ^ p.tag);
 #pragma unroll
       for (int k = 0; k < E; ++k)
 #pragma unroll
-        for (int j = 0; j < N; ++j) ok = ok && tag_is(ask_o[k][j], p.tag);
-      return ok;
+        for (int j = 0; j < N; ++j) differs |= (uint32_t)(ask_o[k][j] >> 32) ^ p.tag;
+      return differs == 0;
     };
-    float m_e[E], L_e[E], o_e[E];
+    float m_all = -INFINITY, l_all = 0.f, o_e[E];
 #pragma unroll
-    for (int k = 0; k < E; ++k) {
-      m_e[k] = -INFINITY;
-      L_e[k] = 0.f;
-      o_e[k] = 0.f;
-    }
+    for (int k = 0; k < E; ++k) o_e[k] = 0.f;
     for (int s0 = 0; s0 < chunks_now; s0 += N) {
       ask_group(s0);
       while (!group_fresh()) ask_group(s0);  // a word that is not this launch's yet is on its way: ask again
-      if (tid < 16 * N) {
-        const int j = tid >> 4, gg = tid & 15, sj = s0 + j;
-        if (sj < chunks_now && gg < G) {
-          const bool mine = has_partial && sj == split;
-          sm_pm[j][gg] = mine ? sm_fin[0][gg] : tagged_value(ask_m);
-          sm_pl[j][gg] = mine ? sm_fin[1][gg] : tagged_value(ask_l);
+      if (asks) {
+        const int sj = s0 + my_j;
+        const bool mine = has_partial && sj == split, any = sj < chunks_now;
+        const float mj = !any ? -INFINITY : mine ? sm_max[my_g] : tagged_value(ask_m);
+        const float lj = !any ? 0.f : mine ? sum_of(my_g) : tagged_value(ask_l);
+        float mn = mj;
+#pragma unroll
+        for (int x = 1; x < N; x *= 2) mn = fmaxf(mn, __shfl_xor(mn, x));
+        mn = fmaxf(mn, m_all);  // finite: a chunk that has a partial has attended a slot
+        const float old = fast_exp2(m_all - mn), wj = fast_exp2(mj - mn);
+        float l = wj * lj;
+#pragma unroll
+        for (int x = 1; x < N; x *= 2) l += __shfl_xor(l, x);
+        l_all = fmaf(l_all, old, l);
+        m_all = mn;
+        sm_w[my_g][my_j] = wj;
+        if (my_j == 0) {
+          sm_old[my_g] = old;
+          sm_sum[my_g] = l_all;
         }
       }
       __syncthreads();
@@ -924,36 +915,30 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
         const int idx = tid + k * kThreads;
         if (has(k) && idx < G * D) {
           const int gg = idx / D;
+          float o = o_e[k] * sm_old[gg];
 #pragma unroll
-          for (int j = 0; j < N; ++j) {
-            if (s0 + j < chunks_now) {
-              const float ms = sm_pm[j][gg], ls = sm_pl[j][gg];
-              const float ov = (has_partial && s0 + j == split) ? own_o[k] : tagged_value(ask_o[k][j]);
-              const float mn = fmaxf(m_e[k], ms);  // finite: a chunk that has a partial has attended a slot
-              const float fa = fast_exp2(m_e[k] - mn), fb = fast_exp2(ms - mn);
-              L_e[k] = L_e[k] * fa + ls * fb;
-              o_e[k] = o_e[k] * fa + ov * fb;
-              m_e[k] = mn;
-            }
+          for (int j = 0; j < N; j += 4) {
+            const f32x4 w = *reinterpret_cast<const f32x4 *>(&sm_w[gg][j]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              o = fmaf((has_partial && s0 + j + i == split) ? own_o[k] : tagged_value(ask_o[k][j + i]), w[i], o);
           }
+          o_e[k] = o;
         }
       }
-      if (s0 + N < chunks_now) __syncthreads();  // the statistics' LDS is written again
+      if (s0 + N < chunks_now) __syncthreads();  // the weights' LDS is written again
+    }
+    if (asks && my_j == 0) {
+      if (p.lse) p.lse[orow0 + my_g] = (m_all + log2f(l_all)) * 0.6931471805599453f;
+      if (p.track) {
+        p.mlprev[(orow0 + my_g) * 2] = m_all;
+        p.mlprev[(orow0 + my_g) * 2 + 1] = l_all;
+      }
     }
 #pragma unroll
     for (int k = 0; k < E; ++k) {
       const int idx = tid + k * kThreads;
-      if (idx < G * D) {
-        const int gg = idx / D, c = idx % D;
-        p.out[(orow0 + gg) * D + c] = o_e[k] / L_e[k];
-        if (c == 0) {
-          if (p.lse) p.lse[orow0 + gg] = (m_e[k] + log2f(L_e[k])) * 0.6931471805599453f;
-          if (p.track) {
-            p.mlprev[(orow0 + gg) * 2] = m_e[k];
-            p.mlprev[(orow0 + gg) * 2 + 1] = L_e[k];
-          }
-        }
-      }
+      if (idx < G * D) p.out[orow0 * D + idx] = o_e[k] / sm_sum[idx / D];
     }
   };
   // (where the host chooses the wide merges: wide_merge in dynts.hip)
