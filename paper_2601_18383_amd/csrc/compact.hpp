@@ -33,6 +33,11 @@ struct CompactParams {
   int Hkv, cap, keep_stride;
 };
 
+// Waits for the load of v: behind the next barrier another wave may store to where it came from.  (The barrier by itself waits
+// for no load.)
+template <typename T>
+__device__ __forceinline__ void arrived(T &v) { asm volatile("" : "+v"(v)); }
+
 __device__ __forceinline__ int clamp_slot(int v, int cap) { return v < 0 ? 0 : (v >= cap ? cap - 1 : v); }
 
 // First destination whose source differs.  keep_idx[i] == i holds on a prefix only, so the boundary is found by
@@ -102,6 +107,8 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactP
     for (int i0 = first; i0 < m; i0 += TILE) {
       DYNTS_COMPACT_ROWS(nxt)
       DYNTS_COMPACT_IDX(i0 + 2 * TILE)
+#pragma unroll
+      for (int u = 0; u < kCompactUnroll; ++u) arrived(cur[u]);
       __syncthreads();
 #pragma unroll
       for (int u = 0; u < kCompactUnroll; ++u) {
@@ -130,8 +137,10 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactP
 #pragma unroll
       for (int u = 0; u < kScalarUnroll; ++u) {
         const int i = i0 + u * kCompactThreads + tid;
-        if (i < m) val[u] = eu[src[u]];
+        val[u] = i < m ? eu[src[u]] : 0u;
       }
+#pragma unroll
+      for (int u = 0; u < kScalarUnroll; ++u) arrived(val[u]);
       __syncthreads();
 #pragma unroll
       for (int u = 0; u < kScalarUnroll; ++u) {

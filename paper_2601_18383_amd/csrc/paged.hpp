@@ -168,6 +168,8 @@ __global__ __launch_bounds__(kCompactThreads) void paged_compact_kernel(const Co
       }
 #pragma unroll
       for (int u = 0; u < kCompactUnroll; ++u) buf[u] = *reinterpret_cast<const u32x4_t *>(pool + src[u] + 8 * piece);
+#pragma unroll
+      for (int u = 0; u < kCompactUnroll; ++u) arrived(buf[u]);
       __syncthreads();
 #pragma unroll
       for (int u = 0; u < kCompactUnroll; ++u) {
@@ -183,6 +185,7 @@ __global__ __launch_bounds__(kCompactThreads) void paged_compact_kernel(const Co
       const int i = i0 + tid;
       uint32_t val = 0;
       if (i < m) val = eu[clamp_slot(ku[i], p.cap)];
+      arrived(val);
       __syncthreads();
       if (i < m) eu[i] = val;
     }
