@@ -71,8 +71,8 @@ struct AttendParams {
   int score_tiles;          // updated scores are written out every so many tiles of a wave (1 .. 16)
   // When this step's own score update is expected to be asked for by itself (a trigger is known to follow, or it is the
   // unfused attention of a caller who asks for its update next), the step's scaled logits (log2 units) are kept,
-  // [Nb][Hkv][G][cap_pad] fp32, so that its score update can be applied from them (apply_spill_kernel) instead of by a
-  // second pass over K.  Null: not kept.
+  // [Nb][Hkv][G][cap_pad] fp32, so that its score update can be applied from them (apply_spill_kernel, select_kernel) instead of
+  // by a second pass over K.  Null: not kept.
   float *spill;
   int cap_pad;              // cap rounded up to a whole tile: row pitch of the kept logits (a tile's store stays inside its row)
   uint32_t *unit_cnt;       // [Nb][Hkv][cnt_stride] ticket counters, zero between launches
@@ -100,6 +100,11 @@ struct AttendParams {
 // Chunks of a unit are merged four at a time; in the WIDE kernels with one output element per thread more than kWideFrom1
 // of them 32 at a time, with two (head_dim 128 only) more than kWideFrom2 of them eight at a time.
 constexpr int kWideFrom1 = 16, kWideFrom2 = 4;
+
+// Where the kept logit of head g of a unit's slot j lies.
+__device__ __forceinline__ size_t spill_at(size_t unit, int cap_pad, int G, int g, int j) {
+  return (unit * (size_t)G + (size_t)g) * (size_t)cap_pad + (size_t)j;
+}
 
 constexpr int kStream = 1, kBurst = 2;  // forms of the kernel for large caches
 
@@ -463,7 +468,7 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
     }
     m_run = a0[0] * p.scale_log2;
     l_run = kg == 0 ? 1.f : 0.f;  // per-lane partial sums are added over kg at the end
-    if (SPILL && kg == 0 && g < G) p.spill[(unit * G + g) * (size_t)p.cap_pad + n_old] = m_run;
+    if (SPILL && kg == 0 && g < G) p.spill[spill_at(unit, p.cap_pad, G, g, n_old)] = m_run;
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
       typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -661,7 +666,7 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
       }
       if (SPILL && g < G) {  // this lane's 8 logits of head g: slots t + 16 s + 4 kg .. +3
         // (only slots this tile attends: the slot behind them may be the appended token's, kept by its own wave)
-        float *sp = p.spill + (unit * G + g) * (size_t)p.cap_pad + t + 4 * kg;
+        float *sp = p.spill + spill_at(unit, p.cap_pad, G, g, t) + 4 * kg;
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2) {
           const int s_lo = t + 16 * s2 + 4 * kg;
@@ -969,9 +974,9 @@ __global__ __launch_bounds__(256) void apply_spill_kernel(float *S, const float 
   for (int g = 0; g < G; ++g) {
     const float *ml = mlprev + ((size_t)b * Hq + (size_t)h * G + g) * 2;
     const float m = ml[0], inv_l = 1.0f / ml[1];
-    const f32x4 x = *reinterpret_cast<const f32x4 *>(spill + ((size_t)unit * G + g) * cap_pad + j0);
+    const f32x4 x = *reinterpret_cast<const f32x4 *>(spill + spill_at((size_t)unit, cap_pad, G, g, j0));
 #pragma unroll
-    for (int i = 0; i < kApplyPerThread; ++i) add[i] += fast_exp2(x[i] - m) * inv_l;
+    for (int i = 0; i < kApplyPerThread; ++i) add[i] = fmaf(fast_exp2(x[i] - m), inv_l, add[i]);
   }
   float *Su = S + (size_t)unit * cap;
 #pragma unroll

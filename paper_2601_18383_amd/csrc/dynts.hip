@@ -361,6 +361,16 @@ int apply_spill(dynts_ctx *ctx, int layer, hipStream_t st) {
   return rc;
 }
 
+// Whether a trigger's selection makes the update it owes from kept logits itself: one workgroup per unit then reads all of the
+// unit's, the first 4096 slots' of up to eight heads in one go, the rest in dependent rounds.  us for both, two launches / one:
+//   4 heads a group: 4 units of 240 slots 16.5 / 12.1; 8 of 4544 16.7 / 15.0, of 6100 17.4 / 18.0, of 16000 28.2 / 42.2; 256 of
+//     6100 24.0 / 21.6
+//   7 heads: 128 units of 2496 16.2 / 13.4, of 5300 20.3 / 21.2; 512 of 1200 19.2 / 18.8; 32 of 6100 19.3 / 22.3, of 9000 22.7 / 32.2
+//   16 heads: one unit of 4500 17.9 / 18.3, 32 units 20.2 / 22.0
+bool select_applies(const dynts_ctx *ctx) {
+  return ctx->cfg.capacity <= (dynts::kSelEarly + 1) * dynts::kSelThreads && ctx->plan.G <= dynts::kSelHeads;
+}
+
 // The buffer of kept logits is wanted for something else, or no longer: an update that rests on them alone is applied,
 // one that the next pass over K can make as well is left to that.
 int release_spill(dynts_ctx *ctx, hipStream_t st) {
@@ -824,18 +834,25 @@ int dynts_select_evict(dynts_ctx *ctx, int32_t layer, const uint8_t *trigger, in
   if (keep_stride <= 0) return DYNTS_ECAPACITY;
   const dynts_config &c = ctx->cfg;
   if (k_keep < 0) k_keep = c.budget;
-  rc = dynts_update_scores(ctx, layer, stream);
+  const bool apply = ctx->pending[layer] == 2 && select_applies(ctx);
+  if (!apply) rc = dynts_update_scores(ctx, layer, stream);
   if (rc != DYNTS_OK) return rc;
   const LayerView lv = layer_view(ctx, layer);
   dynts::SelectParams p{lv.S, lv.seq_len, ctx->n_prompt, trigger, keep_idx, new_len, ctx->status,
-                        c.n_kv_heads, c.capacity, c.window, k_keep, keep_stride};
-  const dim3 grid(c.n_kv_heads, c.batch);
+                        c.n_kv_heads, c.capacity, c.window, k_keep, keep_stride,
+                        reinterpret_cast<const float *>(ctx->ws + ctx->plan.off_spill), lv.mlprev, lv.nprev, ctx->plan.G, ctx->plan.cap_pad};
+  const dim3 grid(c.n_kv_heads, c.batch), block(dynts::kSelThreads);
+  const size_t lds = (size_t)c.capacity * 4;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (c.capacity <= kSelectLdsMax)
-    hipLaunchKernelGGL((dynts::select_kernel<true>), grid, dim3(dynts::kSelThreads), (size_t)c.capacity * 4, st, p);
-  else
-    hipLaunchKernelGGL((dynts::select_kernel<false>), grid, dim3(dynts::kSelThreads), 0, st, p);
-  return launch_status();
+  if (apply) hipLaunchKernelGGL((dynts::select_kernel<true, true>), grid, block, lds, st, p);
+  else if (c.capacity <= kSelectLdsMax) hipLaunchKernelGGL((dynts::select_kernel<true, false>), grid, block, lds, st, p);
+  else hipLaunchKernelGGL((dynts::select_kernel<false, false>), grid, block, 0, st, p);
+  rc = launch_status();
+  if (rc == DYNTS_OK && apply) {
+    ctx->pending[layer] = 0;
+    ctx->spill_layer = -1;
+  }
+  return rc;
 }
 
 int dynts_compact(dynts_ctx *ctx, int32_t layer, const uint8_t *trigger, const int32_t *keep_idx,

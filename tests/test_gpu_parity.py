@@ -178,6 +178,53 @@ def test_select_bit_exact_on_given_scores(B, nc, k_keep, window, M):
     assert int(cache.status.item()) == 0
 
 
+@pytest.mark.parametrize("nc,k_keep,window,M", [(1024, 512, 1, 0), (1025, 1024, 7, 3), (4097, 4096, 0, 0), (16300, 9000, 60, 16),
+                                                  (16385, 16384, 5, 2), (33000, 17000, 10, 40)])
+def test_select_at_the_edges_of_its_rounds(B, nc, k_keep, window, M):
+    """1024 candidates a round, 16 rounds counted together, 16384 slots whose keys are held in LDS."""
+    test_select_bit_exact_on_given_scores(B, nc, k_keep, window, M)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,cap,k_keep", [(2, 2, 64, 90, 30), (28, 4, 128, 1100, 600), (8, 1, 64, 1030, 1), (7, 1, 128, 4120, 3000),
+                                                 (16, 2, 64, 5120, 3000), (16, 2, 64, 5121, 3000), (9, 1, 128, 700, 300),
+                                                 (8, 2, 64, 9000, 8000)])
+def test_select_makes_the_update_from_kept_logits(B, Hq, Hkv, d, cap, k_keep):
+    """A trigger behind an announced step leaves the scores, bit for bit, that the update by a call of its own leaves, of triggered,
+    untriggered and idle sequences, and selects from them."""
+    rng = np.random.default_rng(cap + Hq)
+    Nb, M, window = 4, 11, 17
+    lens = np.array([cap - 1, cap // 2, cap - 3, M + 3], np.int32)
+    trig = torch.tensor([1, 1, 0, 1], dtype=torch.uint8, device="cuda")
+    active = torch.tensor([1, 0, 1, 1], dtype=torch.uint8, device="cuda")
+    K, V = _bf16(rng, Nb, Hkv, cap, d).cuda(), _bf16(rng, Nb, Hkv, cap, d).cuda()
+    S = torch.from_numpy(rng.random((Nb, Hkv, cap)).astype(np.float32)).cuda()
+    q, k, v = _bf16(rng, Nb, Hq, d).cuda(), _bf16(rng, Nb, Hkv, d).cuda(), _bf16(rng, Nb, Hkv, d).cuda()
+    out = torch.zeros(Nb, Hq, d, device="cuda")
+    got = []
+    for by_itself in (True, False):
+        c = B.Cache(1, Nb, Hq, Hkv, d, cap, 1, window, 1)
+        c.K[0].copy_(K); c.V[0].copy_(V); c.S[0].copy_(S)
+        c.seq_len[0].copy_(torch.from_numpy(lens)); c.next_pos[0].copy_(torch.from_numpy(lens)); c.n_prompt.fill_(M)
+        B.dynts_hint_trigger(c.ctx, 0)
+        B.dynts_decode_step(c.ctx, 0, q, k, v, out, active=active)
+        if by_itself:
+            B.dynts_update_scores(c.ctx, 0)
+        c.keep_idx.fill_(-1)
+        B.dynts_select_evict(c.ctx, 0, c.keep_idx, c.new_len, k_keep, trig)
+        scores = c.S.clone()
+        B.dynts_compact(c.ctx, 0, c.keep_idx, c.new_len, trig)  # (no update is owed any more)
+        got.append((scores, c.keep_idx.clone(), c.new_len.clone()))
+        assert int(c.status.item()) == 0
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
+    scores, keep, new_len = got[0]
+    n = (lens + np.array([1, 0, 1, 1])).astype(np.int32)
+    assert not torch.equal(scores[0, 0, :, M:int(n[0])], S[0, :, M:int(n[0])])
+    keep_ref, len_ref = orc.select(f64(scores[0]), np.broadcast_to(np.arange(cap, dtype=np.int32), (Nb, Hkv, cap)).copy(), n,
+                                   np.full(Nb, M, np.int32), window, k_keep, i32(trig).astype(np.uint8))
+    assert np.array_equal(i32(new_len), len_ref) and np.array_equal(i32(keep), keep_ref)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_compact_bit_exact(B, d):
     rng = np.random.default_rng(5 + d)
