@@ -136,7 +136,7 @@ __global__ void paged_append_kernel(const AppendParams p, PagedView pv) {
 // Eviction in paged storage: the same stable in-place gather as compact_kernel (a slot's storage is unique,
 // so "sources lie at or beyond destinations" protects rows exactly as in the dense layout), every row found
 // through the block table.  seq_len is left to paged_trim_kernel, which still needs the old length.
-// grid (2 * kSlices + 2, Hkv, Nb), 256 threads.
+// grid (2 * kSlices + 2, Hkv, Nb).
 template <int D>
 __global__ __launch_bounds__(kCompactThreads) void paged_compact_kernel(const CompactParams p, PagedView pv) {
   constexpr int kSlices = D * 2 / kCompactSliceBytes;
@@ -145,14 +145,12 @@ __global__ __launch_bounds__(kCompactThreads) void paged_compact_kernel(const Co
   constexpr int TILE = ROWS * kCompactUnroll;
   const int tid = threadIdx.x;
   const int what = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+  __shared__ int32_t sm_keep[kCompactKeep], sm_first[kCompactThreads / 64];
   if (p.trigger && !p.trigger[b]) return;
-  int m = p.new_len[b];
-  m = m < 0 ? 0 : (m > p.cap ? p.cap : m);
-  if (m > p.keep_stride) m = p.keep_stride;
   const size_t unit = (size_t)b * p.Hkv + h;
-  const int32_t *ku = p.keep_idx + unit * (size_t)p.keep_stride;
   const int32_t *tb = pv.block_table + unit * pv.max_pages;
-  const int first = first_moved(ku, m);
+  const KeepList keep = take_keep_list(p, (int)unit, b, sm_keep, sm_first);
+  const int m = keep.m, first = keep.first;
 
   if (what < 2 * kSlices) {
     uint16_t *pool = (what < kSlices ? pv.K : pv.V) + (kCompactSliceBytes / 2) * (what % kSlices);
@@ -164,7 +162,7 @@ __global__ __launch_bounds__(kCompactThreads) void paged_compact_kernel(const Co
 #pragma unroll
       for (int u = 0; u < kCompactUnroll; ++u) {
         const int i = i0 + u * ROWS + r;
-        src[u] = paged_row<D>(tb, i < m ? clamp_slot(ku[i], p.cap) : 0, pv.max_pages, pv.n_pages);
+        src[u] = paged_row<D>(tb, i < m ? keep.source(i) : 0, pv.max_pages, pv.n_pages);
       }
 #pragma unroll
       for (int u = 0; u < kCompactUnroll; ++u) buf[u] = *reinterpret_cast<const u32x4_t *>(pool + src[u] + 8 * piece);
@@ -184,7 +182,7 @@ __global__ __launch_bounds__(kCompactThreads) void paged_compact_kernel(const Co
     for (int i0 = first; i0 < m; i0 += kCompactThreads) {
       const int i = i0 + tid;
       uint32_t val = 0;
-      if (i < m) val = eu[clamp_slot(ku[i], p.cap)];
+      if (i < m) val = eu[keep.source(i)];
       arrived(val);
       __syncthreads();
       if (i < m) eu[i] = val;

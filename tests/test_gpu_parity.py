@@ -225,6 +225,30 @@ def test_select_makes_the_update_from_kept_logits(B, Hq, Hkv, d, cap, k_keep):
     assert np.array_equal(i32(new_len), len_ref) and np.array_equal(i32(keep), keep_ref)
 
 
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("d,cap", [(64, 4600), (128, 4096), (64, 100)])
+def test_compact_of_lists_beyond_what_is_held(B, d, cap, shift):
+    """4096 entries of the keep list are held on chip: one slot evicted in front of, at and behind them, and none."""
+    rng = np.random.default_rng(cap + d)
+    gone = [0, min(cap, 4096) - 1, cap - 1, cap]
+    c = B.Cache(1, len(gone), 1, 1, d, cap, 1, 1, 1)
+    K, V = _bf16(rng, len(gone), 1, cap, d).cuda(), _bf16(rng, len(gone), 1, cap, d).cuda()
+    c.K[0].copy_(K); c.V[0].copy_(V)
+    c.S[0].copy_(torch.arange(cap, device="cuda").float()); c.pos[0].copy_(torch.arange(cap, device="cuda"))
+    c.seq_len.fill_(cap)
+    for b, slot in enumerate(gone):
+        idx = torch.tensor([j for j in range(cap) if j != slot], dtype=torch.int32, device="cuda")[shift:]
+        c.keep_idx[b, 0, :len(idx)] = idx
+        c.new_len[b] = len(idx)
+    idx, m = c.keep_idx.clone(), c.new_len.tolist()
+    B.dynts_compact(c.ctx, 0, c.keep_idx, c.new_len)
+    assert c.seq_len[0].tolist() == m
+    for b in range(len(gone)):
+        src = idx[b, 0, :m[b]].long()
+        assert torch.equal(c.K[0, b, 0, :m[b]], K[b, 0, src]) and torch.equal(c.V[0, b, 0, :m[b]], V[b, 0, src])
+        assert torch.equal(c.pos[0, b, 0, :m[b]].long(), src) and torch.equal(c.S[0, b, 0, :m[b]], src.float())
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_compact_bit_exact(B, d):
     rng = np.random.default_rng(5 + d)
