@@ -71,10 +71,10 @@ struct AttendParams {
   int score_tiles;          // updated scores are written out every so many tiles of a wave (1 .. 16)
   // When this step's own score update is expected to be asked for by itself (a trigger is known to follow, or it is the
   // unfused attention of a caller who asks for its update next), the step's scaled logits (log2 units) are kept,
-  // [Nb][Hkv][G][cap_pad] fp32, so that its score update can be applied from them (apply_spill_kernel, select_kernel) instead of
-  // by a second pass over K.  Null: not kept.
+  // [Nb][Hkv][cap_pad / 32][G][32] fp32 (see spill_at), so that its score update can be applied from them (apply_spill_kernel,
+  // select_kernel) instead of by a second pass over K.  Null: not kept.
   float *spill;
-  int cap_pad;              // cap rounded up to a whole tile: row pitch of the kept logits (a tile's store stays inside its row)
+  int cap_pad;              // cap rounded up to a whole tile
   uint32_t *unit_cnt;       // [Nb][Hkv][cnt_stride] ticket counters, zero between launches
   uint32_t *seq_cnt;        // [Nb][cnt_stride]      arrival counters, zero between launches
   int cnt_stride;           // words from one counter to the next
@@ -101,9 +101,9 @@ struct AttendParams {
 // of them 32 at a time, with two (head_dim 128 only) more than kWideFrom2 of them eight at a time.
 constexpr int kWideFrom1 = 16, kWideFrom2 = 4;
 
-// Where the kept logit of head g of a unit's slot j lies.
+// Where the kept logit of head g of a unit's slot j lies: tile by tile, so that those of consecutive tiles are one run of memory.
 __device__ __forceinline__ size_t spill_at(size_t unit, int cap_pad, int G, int g, int j) {
-  return (unit * (size_t)G + (size_t)g) * (size_t)cap_pad + (size_t)j;
+  return (unit * (size_t)cap_pad + (size_t)(j & ~(kTile - 1))) * (size_t)G + (size_t)(kTile * g + (j & (kTile - 1)));
 }
 
 constexpr int kStream = 1, kBurst = 2;  // forms of the kernel for large caches
@@ -213,6 +213,10 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   // updated scores of up to kScoreTiles consecutive tiles per wave, written out together (see flush_scores)
   constexpr int kScoreTiles = 16;
   __shared__ __align__(16) float sm_score[PENDING && BURST ? kWaves : 1][PENDING && BURST ? kScoreTiles * kTile : 4];
+
+  // logits of consecutive tiles per wave, written out together (see flush_logits)
+  constexpr int kLogitRows = 32;  // heads times tiles
+  __shared__ __align__(16) float sm_logit[SPILL ? kWaves : 1][SPILL ? kLogitRows * kTile : 4];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -555,6 +559,32 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
     sc_n = 0;
   };
 
+  // ---- kept logits leave in bursts, too -----------------------------------------------------------
+  // Parked in LDS in the order in which they lie in memory; a run of consecutive tiles (32 / G of them at most) is written with
+  // 1 KB a store instruction.  lg_base: first slot of the run, lg_n: tiles in it, lg_hi: end of the slots it may write (the slot
+  // behind may be the appended token's, kept by its own wave).
+  float *lbuf = sm_logit[SPILL ? wave : 0];
+  int lg_base = 0, lg_n = 0, lg_hi = 0;
+  auto flush_logits = [&]() {
+    if (!SPILL || lg_n == 0) return;
+    wave_lds_fence();
+    float *dst = p.spill + spill_at(unit, p.cap_pad, G, 0, lg_base);
+    const bool whole = lg_base + kTile * lg_n <= lg_hi;
+    for (int off = 4 * lane; off < lg_n * G * kTile; off += 256) {
+      const f32x4 v = *reinterpret_cast<const f32x4 *>(lbuf + off);
+      const int s0 = lg_base + off / (G * kTile) * kTile + off % kTile;
+      if (whole || s0 + 4 <= lg_hi) {
+        *reinterpret_cast<f32x4 *>(dst + off) = v;
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (s0 + i < lg_hi) dst[off + i] = v[i];
+      }
+    }
+    wave_lds_fence();  // the buffer is written again
+    lg_n = 0;
+  };
+
   // ---- one 32-slot tile of this wave -------------------------------------------------------
   // Branch-free apart from two wave-uniform guards; the next tile's loads are issued
   // unconditionally (clamped), so the loop never drains its outstanding loads.
@@ -664,20 +694,16 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
           mx = fmaxf(mx, x[e]);
         }
       }
-      if (SPILL && g < G) {  // this lane's 8 logits of head g: slots t + 16 s + 4 kg .. +3
-        // (only slots this tile attends: the slot behind them may be the appended token's, kept by its own wave)
-        float *sp = p.spill + spill_at(unit, p.cap_pad, G, g, t) + 4 * kg;
+      if (SPILL) {
+        if (lg_n > 0 && (t != lg_base + kTile * lg_n || (lg_n + 1) * G > kLogitRows)) flush_logits();
+        if (lg_n == 0) lg_base = t;
+        if (g < G) {  // this lane's 8 logits of head g: slots t + 16 s + 4 kg .. +3
 #pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-          const int s_lo = t + 16 * s2 + 4 * kg;
-          if (s_lo + 4 <= att_hi) {
-            *reinterpret_cast<f32x4 *>(sp + 16 * s2) = f32x4{x[4 * s2], x[4 * s2 + 1], x[4 * s2 + 2], x[4 * s2 + 3]};
-          } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (s_lo + i < att_hi) sp[16 * s2 + i] = x[4 * s2 + i];
-          }
+          for (int s2 = 0; s2 < 2; ++s2)
+            *reinterpret_cast<f32x4 *>(lbuf + (lg_n * G + g) * kTile + 16 * s2 + 4 * kg) = f32x4{x[4 * s2], x[4 * s2 + 1], x[4 * s2 + 2], x[4 * s2 + 3]};
         }
+        ++lg_n;
+        lg_hi = att_hi;
       }
       mx = fmaxf(mx, __shfl_xor(mx, 16));
       mx = fmaxf(mx, __shfl_xor(mx, 32));
@@ -740,6 +766,7 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   }
   for (t = ra; t < rb; t += kTile) tile(t, rb, t + kTile, past_caches);
   flush_scores();
+  flush_logits();
 
   if (!ATTEND) return;
   // with several chunks per unit: draw this workgroup's ticket now, so that the round trip of the atomic
