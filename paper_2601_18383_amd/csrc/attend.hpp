@@ -196,7 +196,7 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   constexpr int VROWS = 64 / PIECES;      // rows covered by one wave-wide 16-byte load
   constexpr int VIT = kTile / VROWS;
   constexpr int VSTRIDE = 2 * D + 32;     // bytes per staged V row (+32: transposing reads hit distinct banks)
-  constexpr int KSTRIDE = 2 * D + 16;     // bytes per staged K or query row (+16: 16 rows' pieces lie in distinct banks)
+  constexpr int KSTRIDE = 2 * D + 32;     // bytes per staged K or query row (+32: the 16 lanes that a 16-byte read serves at a time hit distinct banks)
   constexpr int OSTRIDE = D + 4;          // floats per row of the cross-wave output reduction
   constexpr bool STREAM = LARGE == kStream, BURST = LARGE == kBurst;
   static_assert(!(STREAM && PAGED), "pages are loaded through the caches");
