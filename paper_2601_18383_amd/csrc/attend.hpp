@@ -26,7 +26,7 @@
 //     goes to the workspace and the LAST workgroup of the (sequence, KV head) to arrive
 //     (device-scope counter) merges the partials, writes `out`, and saves the query and the
 //     statistics that the next step's score update needs.  Every workgroup checks in on a
-//     per-sequence counter as it starts; the last one to do so advances seq_len / next_pos.
+//     per-sequence counter behind its first tile; the last one to do so advances seq_len / next_pos.
 //     No second kernel, no host round trip.
 //   * with APPEND the new token's K/V row is written to its slot by one workgroup and enters the
 //     softmax as the initial state of the first wave (max = q.k_new, sum = 1, output = v_new), so
