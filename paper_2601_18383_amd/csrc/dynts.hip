@@ -496,6 +496,48 @@ MlpPlan mlp_plan(const dynts_predictor *w, int batch) {
   return pl;
 }
 
+// Whether the two-launch form's 32-bit offsets reach everything: the hidden states, a workgroup's weights, the second layer's
+// operands, a grid's threads.
+bool mlp_fits_32_bits(const dynts_predictor *w, int batch) {
+  const long long limit = dynts::kMlpNowhere;
+  return 2LL * batch * w->d < limit && 32LL * w->d < limit && 64LL * 8 * w->m1 < limit && 8LL * w->m2 < limit;
+}
+
+struct MlpSplitPlan {
+  int bt;                // batch tiles of 16
+  int nsplit1, nsplit2;  // slices of K in either layer
+  size_t off_p1, off_yhi, off_ylo, off_p2, off_part, off_cnt, total;  // scratch
+};
+
+MlpSplitPlan mlp_split_plan(const dynts_predictor *w, int batch) {
+  MlpSplitPlan pl;
+  pl.bt = batch <= 16 ? 1 : batch <= 32 ? 2 : batch <= 64 ? 4 : 8;
+  auto slices = [&](int K, int parts) {
+    const int steps = dynts::mlp_slice_steps(pl.bt, parts);
+    return (K / 32 + steps - 1) / steps;
+  };
+  pl.nsplit1 = slices(w->d, 1);
+  pl.nsplit2 = slices(w->m1, 2);
+  size_t off = 0;
+  pl.off_p1 = off;
+  off += align_up((size_t)pl.nsplit1 * batch * w->m1 * sizeof(float));
+  pl.off_yhi = off;
+  off += align_up((size_t)batch * w->m1 * sizeof(uint16_t));
+  pl.off_ylo = off;
+  off += align_up((size_t)batch * w->m1 * sizeof(uint16_t));
+  pl.off_p2 = off;
+  off += align_up((size_t)pl.nsplit2 * batch * w->m2 * sizeof(float));
+  pl.off_part = off;
+  off += align_up((size_t)batch * ((w->m2 + 255) / 256) * sizeof(uint64_t));  // tagged words
+  pl.off_cnt = off;
+  off += align_up((size_t)batch * sizeof(uint32_t));
+  pl.total = off;
+  return pl;
+}
+
+// whether a call takes the form that cuts K of both layers (mlp_split_gemm_kernel)
+bool mlp_split(const dynts_predictor *w, int batch) { return !mlp_fits_32_bits(w, batch); }
+
 int check_predictor(const dynts_predictor *w, int batch) {
   if (!w) return DYNTS_ENULL;
   if (batch <= 0 || batch > 128) return DYNTS_EINVAL;
@@ -529,6 +571,35 @@ void launch_mlp(const dynts::MlpParams &p, int packed, int ft, int bt, int wgs, 
     if (ft == 1) launch_mlp_ft<1, SECOND, false>(p, bt, grid, st, e0, e1);
     else launch_mlp_ft<2, SECOND, false>(p, bt, grid, st, e0, e1);
   }
+}
+
+template <int PARTS, bool PACKED>
+void launch_mlp_split_gemm(const dynts::MlpSplitParams &p, int bt, int nsplit, hipStream_t st, hipEvent_t e0) {
+  const dim3 grid((p.m + dynts::kMlpSplitFeatures - 1) / dynts::kMlpSplitFeatures, nsplit);
+  const dim3 block(dynts::kMlpThreads);
+  switch (bt) {
+    case 1: hipExtLaunchKernelGGL((dynts::mlp_split_gemm_kernel<1, PARTS, PACKED>), grid, block, 0, st, e0, nullptr, 0, p); break;
+    case 2: hipExtLaunchKernelGGL((dynts::mlp_split_gemm_kernel<2, PARTS, PACKED>), grid, block, 0, st, e0, nullptr, 0, p); break;
+    case 4: hipExtLaunchKernelGGL((dynts::mlp_split_gemm_kernel<4, PARTS, PACKED>), grid, block, 0, st, e0, nullptr, 0, p); break;
+    default: hipExtLaunchKernelGGL((dynts::mlp_split_gemm_kernel<8, PARTS, PACKED>), grid, block, 0, st, e0, nullptr, 0, p); break;
+  }
+}
+
+void run_mlp_split(const dynts_predictor *w, const MlpSplitPlan &pl, const uint16_t *h, int batch, float *s_out, int n_rep,
+                   unsigned char *base, hipStream_t st, hipEvent_t start, hipEvent_t stop) {
+  float *P1 = reinterpret_cast<float *>(base + pl.off_p1), *P2 = reinterpret_cast<float *>(base + pl.off_p2);
+  uint16_t *yhi = reinterpret_cast<uint16_t *>(base + pl.off_yhi), *ylo = reinterpret_cast<uint16_t *>(base + pl.off_ylo);
+  const dynts::MlpSplitParams g1{w->W1, h, nullptr, P1, batch, w->m1, w->d}, g2{w->W2, yhi, ylo, P2, batch, w->m2, w->m1};
+  if (w->packed) launch_mlp_split_gemm<1, true>(g1, pl.bt, pl.nsplit1, st, start);
+  else launch_mlp_split_gemm<1, false>(g1, pl.bt, pl.nsplit1, st, start);
+  const size_t n1 = (size_t)batch * w->m1 / 4;
+  hipLaunchKernelGGL(dynts::mlp_split_act_kernel, dim3((unsigned)((n1 + 255) / 256)), dim3(256), 0, st, P1, w->b1, pl.nsplit1, batch,
+                     w->m1, w->activation, yhi, ylo, reinterpret_cast<dynts::u32x4 *>(base + pl.off_part), (pl.total - pl.off_part) / 16);
+  if (w->packed) launch_mlp_split_gemm<2, true>(g2, pl.bt, pl.nsplit2, st, nullptr);
+  else launch_mlp_split_gemm<2, false>(g2, pl.bt, pl.nsplit2, st, nullptr);
+  hipExtLaunchKernelGGL(dynts::mlp_split_dot_kernel, dim3((w->m2 + 255) / 256, batch), dim3(256), 0, st, nullptr, stop, 0, P2, w->b2,
+                        pl.nsplit2, batch, w->m2, w->activation, w->w3, w->b3, reinterpret_cast<uint64_t *>(base + pl.off_part),
+                        reinterpret_cast<uint32_t *>(base + pl.off_cnt), s_out, n_rep);
 }
 
 // ---- scratch that nobody allocates (dynts_decode_step_static) ----------------------------------------
@@ -977,7 +1048,14 @@ int dynts_predictor_pack(const uint16_t *W, int32_t m, int32_t K, uint16_t *W_pa
 
 size_t dynts_predict_scratch_bytes(const dynts_predictor *w, int32_t batch) {
   if (check_predictor(w, batch) != DYNTS_OK) return 0;
-  return mlp_plan(w, batch).total;
+  // what serves a batch serves every smaller one
+  size_t bytes = 0;
+  for (int edge = 16; edge < 128 + 16; edge += 16) {
+    const int nb = edge < batch ? edge : batch;
+    const size_t need = mlp_split(w, nb) ? mlp_split_plan(w, nb).total : mlp_plan(w, nb).total;
+    bytes = need > bytes ? need : bytes;
+  }
+  return bytes;
 }
 
 int dynts_predict_scores(const dynts_predictor *w, const uint16_t *h, int32_t batch, float *s_out, int32_t n_rep,
@@ -990,11 +1068,16 @@ int dynts_predict_scores(const dynts_predictor *w, const uint16_t *h, int32_t ba
   if (reinterpret_cast<uintptr_t>(h) % 16 || reinterpret_cast<uintptr_t>(w->W1) % 16 ||
       reinterpret_cast<uintptr_t>(w->W2) % 16)
     return DYNTS_EINVAL;
-  if ((long long)batch * w->d * 2 >= dynts::kMlpNowhere || (long long)w->m1 * 64 * 8 >= dynts::kMlpNowhere) return DYNTS_ESHAPE;  // 32-bit offsets
-  const MlpPlan pl = mlp_plan(w, batch);
-  if (scratch_bytes < pl.total || reinterpret_cast<uintptr_t>(scratch) % kAlign) return DYNTS_EWORKSPACE;
   unsigned char *base = static_cast<unsigned char *>(scratch);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (mlp_split(w, batch)) {
+    const MlpSplitPlan pl = mlp_split_plan(w, batch);
+    if (scratch_bytes < pl.total || reinterpret_cast<uintptr_t>(scratch) % kAlign) return DYNTS_EWORKSPACE;
+    run_mlp_split(w, pl, h, batch, s_out, n_rep, base, st, static_cast<hipEvent_t>(start), static_cast<hipEvent_t>(stop));
+    return launch_status();
+  }
+  const MlpPlan pl = mlp_plan(w, batch);
+  if (scratch_bytes < pl.total || reinterpret_cast<uintptr_t>(scratch) % kAlign) return DYNTS_EWORKSPACE;
   dynts::MlpParams p{};
   p.W = w->W1; p.x = h; p.bias = w->b1;
   p.Nb = batch; p.m = w->m1; p.K = w->d; p.act = w->activation;

@@ -206,3 +206,13 @@ def test_bench_trigger_schedule_matches_the_oracle_layer():
             if trig[0]:
                 keep, new_len = lay.select(trig)
                 lay.compact(keep, new_len, trig)
+
+
+@pytest.mark.parametrize("d,m1,m2", [(64, 128, 32), (3584, 7168, 1792), (4288, 8576, 2144), (16384, 32, 16), (512, 16384, 256),
+                                     (32, 1 << 22, 16), (1 << 23, 32, 16), (1 << 27, 32, 16)])
+def test_predictor_scratch_for_a_batch_serves_every_smaller_one(B, d, m1, m2):
+    """Whichever form a batch takes, also for sizes past 32-bit offsets."""
+    for packed in (0, 1):
+        w = B.dynts_predictor(d, m1, m2, 1, packed, 0, 0, 0, 0, 0, 0)
+        sizes = [B.dynts_predict_scratch_bytes(w, nb) for nb in range(1, 129)]
+        assert sizes[0] > 0 and sizes == sorted(sizes)

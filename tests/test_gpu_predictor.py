@@ -170,3 +170,35 @@ def test_one_scratch_serves_calls_of_any_batch(B):
         s = torch.zeros(batch, device=dev)
         B.dynts_predict_scores(pred, h.to(dev), s)
         assert_close(f64(s), orc.predictor(f64(h), *[f64(w) for w in ws], orc.ACT_RELU), "batch %d" % batch, tight=1e-4)
+
+
+def _chunked_product(x, W, step=1 << 20):
+    """x [Nb][K] fp64, W [m][K] bf16 -> x W^T in fp64, some columns at a time."""
+    acc = torch.zeros(x.shape[0], W.shape[0], dtype=torch.float64, device=x.device)
+    for c in range(0, W.shape[1], step):
+        acc += x[:, c:c + step] @ W[:, c:c + step].double().t()
+    return acc
+
+
+@pytest.mark.parametrize("d,m1,m2,batch,pack", [
+    (1 << 23, 32, 16, 128, True),      # the hidden states take 2 GiB
+    (32, 1 << 22, 32, 17, False),      # so do the second layer's operands for eight batch tiles
+    ((1 << 27) - 64, 32, 16, 1, True),  # 16 features' weights take 4 GiB
+    ((1 << 26) + 32, 32, 16, 2, False)])
+def test_sizes_past_32_bit_offsets(B, d, m1, m2, batch, pack):
+    """fp32 sums of K products of two normal values with a variance of 1 / K: errors of some 2^-24 of a result of order 1, times the
+    root of the number of terms a sum passes through at most (here some 65536 partial sums), far below the bound of the other sizes."""
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev).manual_seed(d % 1000 + batch)
+    bf = lambda m, k: torch.empty(m, k, dtype=torch.bfloat16, device=dev).normal_(0.0, k ** -0.5, generator=g)
+    W1, W2, w3 = bf(m1, d), bf(m2, m1), bf(1, m2)[0].contiguous()
+    h = torch.empty(batch, d, dtype=torch.bfloat16, device=dev).normal_(generator=g)
+    y = torch.relu(_chunked_product(h.double(), W1))
+    y = torch.relu(_chunked_product(y, W2))
+    want = (y @ w3.double()).cpu().numpy()
+    pred = B.Predictor(W1, None, W2, None, w3, None, activation=B.DYNTS_ACT_RELU, max_batch=batch, pack=pack)
+    s = torch.full((batch, 2), 7.0, device=dev)
+    B.dynts_predict_scores(pred, h, s)
+    got = f64(s)
+    assert np.array_equal(got[:, 0], got[:, 1])
+    assert_close(got[:, 0], want, "predictor d=%d m1=%d batch=%d" % (d, m1, batch), tight=1e-4)
