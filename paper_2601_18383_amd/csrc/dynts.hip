@@ -471,15 +471,21 @@ struct MlpPlan {
 //     d = 3584 22.2 / 22.0, 49.9 / 39.0
 //   (ft2, ns) = (1, 2) / (1, 4) / (2, 4) / (2, 8): d = 2048 (64 tiles) batch 4 13.6 / 13.9 / 14.8 / 14.8, batch 128 30.1 / 25.9 / 27.4 / 29.3;
 //     d = 2560 (80) 18.0 / 19.2 / 17.3 / 21.6, 34.8 / 40.3 / 32.2 / 38.9; d = 3584 22.1 / 23.2 / 21.5 / 26.8, 43.4 / 50.3 / 39.0 / 50.9
+//   Between 513 and 768 tiles two a workgroup are a second round that is nearly empty, which up to 32 sequences costs more than one a
+//     workgroup does (ft1 = 1 / 2): d = 4288 (536) batch 1 29.4 / 32.1, batch 32 35.3 / 37.1; d = 6144 (768) 39.8 / 41.5, 46.9 / 48.4; d = 6656 (832)
+//     53.2 / 52.0, 69.6 / 65.5; with 64 sequences d = 4288 45.3 / 44.2
+//   A long K is shared by as many as leave each 64 k-steps, above 32 sequences 32 (ns = 2, 4, 8, 16): d = 512, m2 = 16, m1 = 16384 batch 1 21.6,
+//     17.9, 16.2, 16.8, batch 128 60.4, 42.0, 32.7, 28.6; m1 = 8192 batch 128 36.0, 26.3, 20.8, 20.7; m1 = 4096 batch 1 11.8 with any
 MlpPlan mlp_plan(const dynts_predictor *w, int batch) {
   MlpPlan pl;
   pl.bt = batch <= 64 ? (batch + 15) / 16 : batch <= 96 ? 6 : 8;
   const int t1 = w->m1 / 16, t2 = w->m2 / 16;
-  pl.ft1 = t1 > 256 ? 2 : 1;
+  pl.ft1 = t1 > 256 && !(t1 > 512 && t1 <= 768 && pl.bt <= 2) ? 2 : 1;
   pl.ft2 = t2 > 64 ? 2 : 1;
   pl.wgs1 = (t1 + pl.ft1 - 1) / pl.ft1;
   pl.groups = (t2 + pl.ft2 - 1) / pl.ft2;
-  const int want = pl.ft2 == 2 || pl.bt > 2 ? 4 : 2, room = 256 / pl.groups, most = w->m1 / 32 / (2 * dynts::kMlpWaves);
+  const int some = pl.ft2 == 2 || pl.bt > 2 ? 4 : 2, many = w->m1 / 32 / (pl.bt > 2 ? 32 : 64);
+  const int want = some > many ? some : many, room = 256 / pl.groups, most = w->m1 / 32 / (2 * dynts::kMlpWaves);
   pl.ns = want < room ? want : room;
   pl.ns = pl.ns < most ? pl.ns : most;
   pl.ns = pl.ns < 1 ? 1 : pl.ns;
@@ -535,9 +541,6 @@ MlpSplitPlan mlp_split_plan(const dynts_predictor *w, int batch) {
   return pl;
 }
 
-// whether a call takes the form that cuts K of both layers (mlp_split_gemm_kernel)
-bool mlp_split(const dynts_predictor *w, int batch) { return !mlp_fits_32_bits(w, batch); }
-
 int check_predictor(const dynts_predictor *w, int batch) {
   if (!w) return DYNTS_ENULL;
   if (batch <= 0 || batch > 128) return DYNTS_EINVAL;
@@ -546,6 +549,24 @@ int check_predictor(const dynts_predictor *w, int batch) {
   if (w->activation < DYNTS_ACT_NONE || w->activation > DYNTS_ACT_SILU) return DYNTS_EINVAL;
   if (w->packed != 0 && w->packed != 1) return DYNTS_EINVAL;
   return DYNTS_OK;
+}
+
+// Whether a call takes the form that cuts K of both layers (mlp_split_gemm_kernel): sizes past 32-bit offsets, and two kinds of
+// layer 1 of which the other form leaves the chip idle.  (Neither has the proportions of the paper's heads, d -> 2d -> d/2.)
+//   Few features and a long K, of which a workgroup takes all: one with more than 1.4 MB of operands is slower, in launches of up to
+//     128 workgroups.  us a call, two launches / this form, m2 = 256: d = 4096, m1 = 512 batch 128 (1.2 MB) 23.8 / 26.1; d = 8192, m1 = 1472
+//     batch 64 (1.3) 24.3 / 26.1, batch 128 (2.4) 40.1 / 33.9; d = 16384, m1 = 512 batch 1 (1.0) 19.5 / 22.2, batch 64 (2.6) 34.3 / 25.9; d = 65536,
+//     m1 = 32 batch 1 (4.2) 48.5 / 20.7, batch 128 200 / 31.  17 - 32 sequences from 1.1 MB on: d = 12288, m1 = 32 17.7 / 16.1.
+//   Many features and a short K: thousands of workgroups, each little but its prologue.  m2 = 16: d = 512, m1 = 16384 batch 32 18.8 / 19.1,
+//     m1 = 32768 28.2 / 22.2; d = 256, m1 = 24576 batch 16 20.3 / 21.4, m1 = 65536 30.6 / 24.9; but with more sequences the other form's lead
+//     in partial sums counts: d = 1024, m1 = 65536 batch 128 73.4 / 79.8; d = 512, m1 = 32768, m2 = 1024 batch 64 42.2 / 44.0.
+bool mlp_split(const dynts_predictor *w, int batch) {
+  if (!mlp_fits_32_bits(w, batch)) return true;
+  const MlpPlan pl = mlp_plan(w, batch);
+  const long long taken = 32LL * w->d * (pl.ft1 + pl.bt);
+  if (pl.wgs1 <= 128 && taken > 1400000) return true;
+  if (pl.bt == 2 && pl.wgs1 <= 96 && taken > 1100000) return true;
+  return w->m1 > (w->d > 256 ? 16384 : 24576) && w->m1 > 32LL * w->d && (long long)batch * w->d <= 65536 && (long long)batch * w->m2 <= 32768;
 }
 
 template <int FT, bool SECOND, bool PACKED>

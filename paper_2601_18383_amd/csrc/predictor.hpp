@@ -17,7 +17,8 @@
 //     75 where a lane's 16 bytes lie 64 apart (packed weights), 38 where they lie in 16 rows (operand order of a row-major
 //     matrix).  So layer 1 reads the hidden states 8 rows x 128 bytes at a time and turns them into operands through LDS of the
 //     wave's own, and writes its output in the order in which layer 2's lanes read it.
-//   * Offsets are 32 bits wide; sizes past them take the form that cuts K of both layers (mlp_split_gemm_kernel).
+//   * Offsets are 32 bits wide; sizes past them, and layers that leave the chip idle so (mlp_split in dynts.hip), take the form that
+//     cuts K of both layers (mlp_split_gemm_kernel).
 //   * k-steps are dealt out to the waves in turn: with contiguous shares, a power of two apart, all of them met on the same memory
 //     channels (d = 4096, batch 32: 31.3 -> 27.7 us).
 // us a call, d = 3584 (77 MB, 11.5 us at the rate of a plain read stream), with partial sums of both layers reduced by kernels of
@@ -408,7 +409,7 @@ __global__ __launch_bounds__(256) void mlp_pack_kernel(const uint16_t *W, int m,
       *reinterpret_cast<const u32x4 *>(W + (tile * 16 + r) * (size_t)K + step * 32 + c);
 }
 
-// ---- the same head for sizes past 32-bit offsets ---------------------------------------------------
+// ---- the same head for sizes past 32-bit offsets, and for few features on a long K or many on a short one -----------------
 // P[split][b][o] = sum_{k in split} W[o][k] * x[b][k] for either layer, then a kernel that adds the parts: four launches, every
 // address 64 bits wide.  K is cut into as many slices as it has, so that a narrow layer fills the chip, too.
 

@@ -160,6 +160,17 @@ def test_tile_edges(B, d, m1, m2, batch):
     _run(B, np.random.default_rng(d + batch), d, m1, m2, batch, orc.ACT_RELU, bias=batch % 2 == 1, n_rep=2, pack=batch % 3 != 0)
 
 
+@pytest.mark.parametrize("d,m1,m2,batch", [
+    (12288, 32, 16, 16), (12288, 32, 16, 17), (12288, 160, 48, 64),   # few features and a long K: either side of 1.1 and 1.4 MB a workgroup
+    (10912, 64, 16, 48), (10976, 64, 16, 48), (16384, 2048, 16, 33), (16384, 2080, 16, 33),  # ... and of 128 workgroups
+    (32, 24576, 16, 5), (32, 24608, 16, 5), (288, 16416, 32, 128),    # many features and a short K
+    (512, 16416, 256, 128), (512, 16416, 272, 128),                   # ... with few and with more features in layer 2
+    (32, 8192, 16, 32), (32, 8224, 16, 32), (32, 12288, 16, 17), (32, 12320, 16, 17), (32, 8224, 16, 33),  # tiles a workgroup in layer 1
+    (32, 8192, 16, 1), (32, 16384, 16, 1), (32, 16384, 16, 128), (64, 16384, 528, 65)])  # workgroups that share K in layer 2
+def test_either_side_of_the_plan_rules(B, d, m1, m2, batch):
+    _run(B, np.random.default_rng(d + m1 + batch), d, m1, m2, batch, orc.ACT_SILU, bias=batch % 2 == 1, n_rep=2, pack=batch % 3 != 0)
+
+
 def test_one_scratch_serves_calls_of_any_batch(B):
     """The scratch's layout follows the batch: what a call of one batch leaves is never taken for a word of another's."""
     rng, dev = np.random.default_rng(3), torch.device("cuda:0")
