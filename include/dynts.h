@@ -276,8 +276,8 @@ int dynts_score_block(dynts_ctx *ctx, int32_t layer, const uint16_t *q_blk, cons
  *   h bf16 [batch][d], batch <= 128;  d and m1 multiples of 32, m2 a multiple of 16.
  *   s_out fp32 [batch][n_rep]: the score of sequence b written n_rep times (n_rep = n_kv_heads gives the
  *     [Nb][Hkv] layout of s_new: one score per token for every head, as in the paper).
- *   scratch: >= dynts_predict_scratch_bytes bytes, 256-byte aligned, zero-filled once by the caller before its
- *     first use (it may be shared by calls that are stream-ordered with respect to each other).
+ *   scratch: >= dynts_predict_scratch_bytes bytes, 256-byte aligned, contents irrelevant before and after (it may be shared by calls
+ *     that are stream-ordered with respect to each other).  What serves a batch serves every smaller one.
  *   start/stop: optional hipEvent_t handles attached to the first and the last kernel of the call. */
 #define DYNTS_ACT_NONE 0
 #define DYNTS_ACT_RELU 1

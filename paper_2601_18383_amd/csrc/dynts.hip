@@ -1113,7 +1113,7 @@ int dynts_predict_scores(const dynts_predictor *w, const uint16_t *h, int32_t ba
   p.part_dot = reinterpret_cast<uint64_t *>(base + pl.off_dot);
   p.group_cnt = reinterpret_cast<uint32_t *>(base + pl.off_group);
   p.done_cnt = reinterpret_cast<uint32_t *>(base + pl.off_done);
-  p.s_out = s_out; p.n_rep = n_rep; p.clear_dot = capturing(st) ? 1 : 0;
+  p.s_out = s_out; p.n_rep = n_rep;
   launch_mlp<true>(p, w->packed, pl.ft2, pl.bt, pl.groups * pl.ns, st, nullptr, static_cast<hipEvent_t>(stop));
   return launch_status();
 }

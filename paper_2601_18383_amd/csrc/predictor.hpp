@@ -54,7 +54,6 @@ struct MlpParams {
   uint32_t *done_cnt;   // tickets of the groups
   float *s_out;         // [Nb][n_rep]
   int n_rep;
-  int clear_dot;        // recorded into a graph: leave part_dot zeroed
 };
 
 __device__ __forceinline__ float mlp_act(float x, int act) {
@@ -389,8 +388,6 @@ __global__ __launch_bounds__(kMlpThreads, 2) void mlp_kernel(const MlpParams p) 
       for (int i = 1; i < KT; ++i) s += sm_sum[i * 16 * BT + ob];
       p.s_out[o] = s + b3;
     }
-    if (p.clear_dot)
-      for (int i = tid; i < n_groups * p.Nb; i += kMlpThreads) tagged_store(&p.part_dot[i], 0.f, 0u);
   }
 }
 

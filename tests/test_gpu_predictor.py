@@ -51,30 +51,35 @@ def test_small_shapes(B, d, m1, m2, batch, act):
     _run(B, rng, d, m1, m2, batch, act, bias=(batch % 2 == 1), n_rep=1 + batch % 4, pack=(act != 1))
 
 
-def test_replayed_calls_leave_no_partial_of_theirs(B):
-    """The replays of a recorded call share one tag, so the parts of the final dot product must not be there for the next."""
+@pytest.mark.parametrize("d,m1,m2,batch", [(256, 512, 592, 24),    # layer 2's workgroups take all of K
+                                            (256, 2048, 1040, 24),  # four share it
+                                            (12288, 32, 272, 24)])  # the form that cuts K of both layers
+def test_replays_take_no_partial_of_another_call(B, d, m1, m2, batch):
+    """Every call's words carry the same tag: those that an earlier replay, or a call of another batch on the same scratch, left
+    must not be taken for this one's."""
     rng = np.random.default_rng(17)
     dev = torch.device("cuda:0")
-    d, m1, m2, batch = 256, 512, 592, 24
     pred = B.Predictor(*[w.to(dev) for w in _make(rng, d, m1, m2)], max_batch=32)
-    hs = [torch.from_numpy(rng.standard_normal((batch, d)).astype(np.float32)).to(torch.bfloat16).to(dev) for _ in range(4)]
+    bf = lambda nb: torch.from_numpy(rng.standard_normal((nb, d)).astype(np.float32)).to(torch.bfloat16).to(dev)
+    hs, other = [bf(batch) for _ in range(6)], [bf(nb) for nb in (32, 1, 17)]
     h, s, want = hs[0].clone(), torch.zeros(batch, 1, device=dev), torch.zeros(batch, 1, device=dev)
-    n_parts = (m2 + 255) // 256 * batch
-    # the last room of the scratch: the counters, 4 bytes per sequence, in front of them the parts
-    end = B.dynts_predict_scratch_bytes(pred.w, batch) - 256
-    parts = pred.scratch[end - (8 * n_parts + 255) // 256 * 256:][:8 * n_parts]
+    aside = torch.zeros(32, 1, device=dev)
     graph = torch.cuda.CUDAGraph()
     torch.cuda.synchronize()
     with torch.cuda.graph(graph):
         B.dynts_predict_scores(pred, h, s)
-    for x in hs:
+    for i, x in enumerate(hs):
         B.dynts_predict_scores(pred, x, want)
         torch.cuda.synchronize()
-        assert parts.view(torch.int64).ne(0).all()  # (that is where they lie)
         h.copy_(x)
+        if i % 2:
+            o = other[i // 2]
+            B.dynts_predict_scores(pred, o, aside[:o.shape[0]])
+        if i == 4:  # words with the tag, counters that have counted
+            pred.scratch.view(torch.int32).fill_(1)
         graph.replay()
         torch.cuda.synchronize()
-        assert torch.equal(s, want) and not parts.any()
+        assert torch.equal(s, want)
 
 
 @pytest.mark.parametrize("d,batch,hkv", [(3584, 32, 4), (4096, 64, 8), (4096, 128, 8)])
