@@ -368,7 +368,29 @@ int apply_spill(dynts_ctx *ctx, int layer, hipStream_t st) {
 //   7 heads: 128 units of 2496 16.2 / 13.4, of 5300 20.3 / 21.2; 512 of 1200 19.2 / 18.8; 32 of 6100 19.3 / 22.3, of 9000 22.7 / 32.2
 //   16 heads: one unit of 4500 17.9 / 18.3, 32 units 20.2 / 22.0
 bool select_applies(const dynts_ctx *ctx) {
-  return ctx->cfg.capacity <= (dynts::kSelEarly + 1) * dynts::kSelThreads && ctx->plan.G <= dynts::kSelHeads;
+  return ctx->cfg.capacity <= 5 * 1024 && ctx->plan.G <= dynts::kSelHeads;
+}
+
+// Threads of a selection's workgroup.  1024 where a compute unit has one unit of the cache to look after: two of them fill it, so that
+// launches of more than 512 take turns, and to start them costs more than small caches have to do.  us a selection with 256 / 512 / 1024 (with 256 in
+// an older kernel), and a whole trigger from its step to its compaction:
+//   256 units of 1000 slots 7.5 / 7.6 / 7.5 (8.0), of 4800 17.7 / 11.9 / 9.8 (22.8); 300 of 400 7.0 / 7.0 / 7.7 (6.9), trigger 48.0 / 48.2 / 51.0 (52.8)
+//   512 of 2400 12.0 / 9.7 / 10.9 (16.2), trigger 395.2 / 387.4 / 385.6; 300 of 3200 14.0 / 10.9 / 11.6, trigger 358.6 / 344.1 / 339.7
+//   672 of 330 7.0 / 7.3 / 10.8 (7.4); 800 of 1000 8.4 / 9.3 / 13.3 (10.2), of 1600 11.0 / 11.1 / 15.4, trigger 216.6 / 215.5 / 218.9
+//   1024 of 66 7.0 / 7.8 / 13.0 (7.3), of 2400 14.9 / 13.8 / 18.7 (22.5); 2048 of 692 10.8 / 15.2 / 24.8 (11.8)
+int select_threads(const dynts_config &c) {
+  const long long units = (long long)c.batch * c.n_kv_heads;
+  if (units <= 256 || (units <= 512 && c.capacity > 2500)) return 1024;
+  return units <= 768 || c.capacity > 1200 ? 512 : 256;
+}
+
+template <int T>
+void launch_select(const dynts::SelectParams &p, const dynts_config &c, bool apply, hipStream_t st) {
+  const dim3 grid(c.n_kv_heads, c.batch);
+  const size_t lds = (size_t)c.capacity * 4;
+  if (apply) hipLaunchKernelGGL((dynts::select_kernel<T, true, true>), grid, dim3(T), lds, st, p);
+  else if (c.capacity <= kSelectLdsMax) hipLaunchKernelGGL((dynts::select_kernel<T, true, false>), grid, dim3(T), lds, st, p);
+  else hipLaunchKernelGGL((dynts::select_kernel<T, false, false>), grid, dim3(T), 0, st, p);
 }
 
 // The buffer of kept logits is wanted for something else, or no longer: an update that rests on them alone is applied,
@@ -933,12 +955,12 @@ int dynts_select_evict(dynts_ctx *ctx, int32_t layer, const uint8_t *trigger, in
   dynts::SelectParams p{lv.S, lv.seq_len, ctx->n_prompt, trigger, keep_idx, new_len, ctx->status,
                         c.n_kv_heads, c.capacity, c.window, k_keep, keep_stride,
                         reinterpret_cast<const float *>(ctx->ws + ctx->plan.off_spill), lv.mlprev, lv.nprev, ctx->plan.G, ctx->plan.cap_pad};
-  const dim3 grid(c.n_kv_heads, c.batch), block(dynts::kSelThreads);
-  const size_t lds = (size_t)c.capacity * 4;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (apply) hipLaunchKernelGGL((dynts::select_kernel<true, true>), grid, block, lds, st, p);
-  else if (c.capacity <= kSelectLdsMax) hipLaunchKernelGGL((dynts::select_kernel<true, false>), grid, block, lds, st, p);
-  else hipLaunchKernelGGL((dynts::select_kernel<false, false>), grid, block, 0, st, p);
+  switch (select_threads(c)) {
+    case 256: launch_select<256>(p, c, apply, st); break;
+    case 512: launch_select<512>(p, c, apply, st); break;
+    default: launch_select<1024>(p, c, apply, st); break;
+  }
   rc = launch_status();
   if (rc == DYNTS_OK && apply) {
     ctx->pending[layer] = 0;

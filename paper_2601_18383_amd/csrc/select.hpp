@@ -8,7 +8,8 @@
 // from the update to the selection in the same launch.
 //
 // What bounds it: a chain of dependent steps on few workgroups.  So everything that can be asked for before the sequence's
-// length is known leaves at once (the first 4096 scores and logits of the unit); 16 waves share the passes; a pass
+// length is known leaves at once (with 1024 threads the first 4096 scores and logits of the unit); up to 16 waves share the passes
+// (fewer where units outnumber the compute units: select_threads in dynts.hip); a pass
 // counts into eight copies of its histogram (scores of one trigger share their leading bits: in one copy all 64 lanes of a wave wait for the
 // same word), adds the copies up, and every wave finds the cut's bin for itself; and it ends as soon as the whole bin is kept.
 // 128 units of 2496 slots, 7 heads a group: 9.6 us with the update, where 256 threads took 13.2 us behind 5.7 us of update.
@@ -20,12 +21,10 @@
 
 namespace dynts {
 
-constexpr int kSelThreads = 1024;
-constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kSelCopies = 8, kSelPitch = 256 + 1;  // copies of the histogram, words from one to the next (+1: other banks)
 constexpr int kSelHeads = 8;    // heads of a group whose kept logits a workgroup takes (APPLY)
 constexpr int kSelEarly = 4;    // rounds of kSelThreads slots that are asked for before the length is known
-constexpr int kSelRounds = 16;  // rounds of candidates whose flags are counted together
+constexpr int kSelCounts = 256;  // counts of flags, one per wave and round of candidates, that are added up together
 
 struct SelectParams {
   float *S;                 // [Nb][Hkv][cap]
@@ -60,13 +59,15 @@ __device__ __forceinline__ int wave_inclusive_scan(int x) {
   return x;
 }
 
-template <bool USE_LDS, bool APPLY>
+template <int kSelThreads, bool USE_LDS, bool APPLY>
 __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelectParams p) {
   static_assert(USE_LDS || !APPLY, "the updated scores are handed on through LDS");
+  constexpr int kSelWaves = kSelThreads / 64, kSelRounds = kSelCounts / kSelWaves;
+  static_assert(kSelThreads >= 256 && kSelWaves % 4 == 0 && kSelCounts % kSelWaves == 0, "a thread per bin; four waves' counts a lane");
   extern __shared__ uint32_t keys[];  // candidate keys when USE_LDS
   __shared__ uint32_t hist[kSelCopies * kSelPitch];
   __shared__ __align__(16) uint32_t total[256];
-  __shared__ __align__(16) int cnt_gt[kSelRounds * kSelWaves], cnt_eq[kSelRounds * kSelWaves];  // per round and wave
+  __shared__ __align__(16) int cnt_gt[kSelCounts], cnt_eq[kSelCounts];  // per round and wave
   __shared__ float sm_m[kSelHeads], sm_inv[kSelHeads];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -99,7 +100,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelectParams 
     }
   }
   for (int i = tid; i < kSelCopies * kSelPitch; i += kSelThreads) hist[i] = 0;
-  if (tid < kSelRounds * kSelWaves) cnt_gt[tid] = cnt_eq[tid] = 0;
+  if (tid < kSelCounts) cnt_gt[tid] = cnt_eq[tid] = 0;
 
   int n = p.seq_len[b];
   n = n < 0 ? 0 : (n > p.cap ? p.cap : n);
@@ -173,16 +174,17 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelectParams 
       if ((u & himask) == prefix) atomicAdd(&own_hist[(u >> shift) & 255u], 1u);
     }
     __syncthreads();
-    if (tid < 512) {  // two threads a bin, four copies each, which are zeroed for the next pass
+    constexpr int PER = kSelThreads >= 512 ? 2 : 1;  // threads a bin, which share its copies
+    if (tid < 256 * PER) {                 // (zeroed for the next pass)
       uint32_t c = 0;
-      uint32_t *src = hist + (tid & 1) * (kSelCopies / 2) * kSelPitch + (tid >> 1);
+      uint32_t *src = hist + (tid % PER) * (kSelCopies / PER) * kSelPitch + tid / PER;
 #pragma unroll
-      for (int k = 0; k < kSelCopies / 2; ++k) {
+      for (int k = 0; k < kSelCopies / PER; ++k) {
         c += src[k * kSelPitch];
         src[k * kSelPitch] = 0;
       }
-      c += __shfl_xor(c, 1);
-      if ((tid & 1) == 0) total[tid >> 1] = c;
+      if (PER == 2) c += __shfl_xor(c, 1);
+      if (tid % PER == 0) total[tid / PER] = c;
     }
     __syncthreads();
     // lane L holds bins 255-4L .. 252-4L, walked from the top
@@ -213,7 +215,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelectParams 
     const int left = nc - j_first, rounds = (left + kSelThreads - 1) / kSelThreads < kSelRounds ? (left + kSelThreads - 1) / kSelThreads : kSelRounds;
     if (j_first > 0) {  // (the counts of the rounds before have been read)
       __syncthreads();
-      if (tid < kSelRounds * kSelWaves) cnt_gt[tid] = cnt_eq[tid] = 0;
+      if (tid < kSelCounts) cnt_gt[tid] = cnt_eq[tid] = 0;
       __syncthreads();
     }
     for (int c = 0; c < rounds; ++c) {
@@ -226,7 +228,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelectParams 
       }
     }
     __syncthreads();
-    // lane L: the four counts of round L / 4, waves 4 (L % 4) .. +3
+    // lane L: counts 4 L .. 4 L + 3, of four waves of one round
     typedef int i32x4 __attribute__((ext_vector_type(4)));
     const i32x4 g4 = *reinterpret_cast<const i32x4 *>(&cnt_gt[4 * lane]), e4 = *reinterpret_cast<const i32x4 *>(&cnt_eq[4 * lane]);
     const int g_in = wave_inclusive_scan(g4[0] + g4[1] + g4[2] + g4[3]), e_in = wave_inclusive_scan(e4[0] + e4[1] + e4[2] + e4[3]);
@@ -237,7 +239,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelectParams 
       const int j = j_first + c * kSelThreads + tid;
       const uint32_t u = j < nc ? key(j) : 0u;
       const bool is_gt = j < nc && u > T, is_eq = j < nc && u == T;
-      const int at = 4 * c + (wave >> 2);
+      const int at = (c * kSelWaves + wave) >> 2;
       const int gt_before = base_gt + __builtin_amdgcn_readlane(g_at, at) + __popcll(__ballot(is_gt) & below);
       const int eq_before = base_eq + __builtin_amdgcn_readlane(e_at, at) + __popcll(__ballot(is_eq) & below);
       const int off = gt_before + (eq_before < take_eq ? eq_before : take_eq);

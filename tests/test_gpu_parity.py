@@ -225,6 +225,64 @@ def test_select_makes_the_update_from_kept_logits(B, Hq, Hkv, d, cap, k_keep):
     assert np.array_equal(i32(new_len), len_ref) and np.array_equal(i32(keep), keep_ref)
 
 
+@pytest.mark.parametrize("Nb,nc,k_keep", [(129, 512, 300), (129, 2300, 2200), (257, 2600, 100),             # 512 threads a workgroup
+                                          (257, 16500, 9000),                                                # ... keys not held in LDS
+                                          (385, 255, 100), (385, 256, 255), (385, 1025, 1024), (400, 1150, 7)])  # 256 threads
+def test_select_of_many_units(B, Nb, nc, k_keep):
+    """Smaller workgroups: other numbers of rounds, of counts a round, and of threads a bin."""
+    rng = np.random.default_rng(nc + Nb)
+    Hkv, window, M = 2, 5, 11
+    n, cap = M + nc + window, M + nc + window + 3
+    cases = _score_cases(rng, nc + window)
+    cache = B.Cache(1, Nb, Hkv, Hkv, 64, cap, 1, window, 1, external_scores=True)
+    S = np.zeros((Nb, Hkv, cap), np.float32)
+    for b in range(Nb):
+        for h in range(Hkv):
+            S[b, h, M:n] = np.roll(cases[(b + h) % len(cases)], 37 * b)
+    S[:, :, :M] = np.inf
+    seq_len = np.where(np.arange(Nb) % 5 == 3, n - nc // 2, n).astype(np.int32)
+    cache.S[0].copy_(torch.from_numpy(S)); cache.seq_len[0].copy_(torch.from_numpy(seq_len)); cache.n_prompt.fill_(M)
+    trig = (np.arange(Nb) % 7 != 1).astype(np.uint8)
+    cache.keep_idx.fill_(-1)
+    B.dynts_select_evict(cache.ctx, 0, cache.keep_idx, cache.new_len, k_keep, torch.from_numpy(trig).cuda())
+    pos = np.broadcast_to(np.arange(cap, dtype=np.int32), (Nb, Hkv, cap)).copy()
+    keep_ref, len_ref = orc.select(S.astype(np.float64), pos, seq_len, np.full(Nb, M, np.int32), window, k_keep, trig)
+    assert np.array_equal(i32(cache.new_len), len_ref)
+    assert np.array_equal(i32(cache.keep_idx), keep_ref)
+    assert int(cache.status.item()) == 0
+
+
+@pytest.mark.parametrize("Nb,Hkv,G,cap", [(129, 2, 4, 700), (260, 2, 1, 2560), (260, 2, 2, 5120), (400, 2, 8, 100), (400, 2, 3, 1100)])
+def test_update_from_kept_logits_in_selections_of_many_units(B, Nb, Hkv, G, cap):
+    """The scores and lists that the update by a call of its own leads to, bit for bit, with the smaller workgroups."""
+    g = torch.Generator(device="cuda").manual_seed(cap)
+    bf = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    M, window, d = 7, 9, 64
+    K, V, q, k, v = bf(Nb, Hkv, cap, d), bf(Nb, Hkv, cap, d), bf(Nb, Hkv * G, d), bf(Nb, Hkv, d), bf(Nb, Hkv, d)
+    S = torch.rand(Nb, Hkv, cap, generator=g, device="cuda")
+    lens = torch.tensor([cap - 1 - (b * 13) % (cap // 2) for b in range(Nb)], dtype=torch.int32, device="cuda")
+    trig = torch.tensor([b % 4 != 2 for b in range(Nb)], dtype=torch.uint8, device="cuda")
+    active = torch.tensor([b % 5 != 1 for b in range(Nb)], dtype=torch.uint8, device="cuda")
+    out = torch.zeros(Nb, Hkv * G, d, device="cuda")
+    got = []
+    for by_itself in (True, False):
+        c = B.Cache(1, Nb, Hkv * G, Hkv, d, cap, 1, window, 1)
+        c.K[0].copy_(K); c.V[0].copy_(V); c.S[0].copy_(S)
+        c.seq_len[0].copy_(lens); c.next_pos[0].copy_(lens); c.n_prompt.fill_(M)
+        B.dynts_hint_trigger(c.ctx, 0)
+        B.dynts_decode_step(c.ctx, 0, q, k, v, out, active=active)
+        if by_itself:
+            B.dynts_update_scores(c.ctx, 0)
+        c.keep_idx.fill_(-1)
+        B.dynts_select_evict(c.ctx, 0, c.keep_idx, c.new_len, cap // 3, trig)
+        got.append((c.S.clone(), c.keep_idx.clone(), c.new_len.clone()))
+        assert int(c.status.item()) == 0
+        c.close()
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
+    assert not torch.equal(got[0][0][0], S)
+
+
 @pytest.mark.parametrize("shift", [0, 1])
 @pytest.mark.parametrize("d,cap", [(64, 4600), (128, 4096), (64, 100)])
 def test_compact_of_lists_beyond_what_is_held(B, d, cap, shift):
