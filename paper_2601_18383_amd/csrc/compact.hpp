@@ -13,9 +13,8 @@
 
 namespace dynts {
 
-constexpr int kCompactThreads = 512;
 constexpr int kCompactUnroll = 4;
-constexpr int kCompactKeepRounds = 8, kCompactKeep = kCompactKeepRounds * kCompactThreads;  // entries of the keep list held in LDS
+constexpr int compact_keep(int threads) { return threads >= 512 ? 4096 : 1024; }  // entries of the keep list held in LDS
 // A workgroup moves one column slice of this many bytes of every row: whole 128-byte lines, so that no line is
 // fetched by two workgroups (64-byte slices read 2.8 bytes per byte written on the 32-layer workload).
 constexpr int kCompactSliceBytes = 128;
@@ -39,7 +38,8 @@ __device__ __forceinline__ void arrived(T &v) { asm volatile("" : "+v"(v)); }
 __device__ __forceinline__ int clamp_slot(int v, int cap) { return v < 0 ? 0 : (v >= cap ? cap - 1 : v); }
 
 // First destination from lo on whose source differs.  keep_idx[i] == i holds on a prefix only, so the boundary is found by
-// cutting the range 512 ways at a time, every thread probing one position.  Called by all threads of the workgroup.
+// cutting the range kCompactThreads ways at a time, every thread probing one position.  Called by all threads of the workgroup.
+template <int kCompactThreads>
 __device__ __forceinline__ int first_moved(const int32_t *ku, int lo, int m) {
   const int tid = threadIdx.x;
   int hi = m;  // the boundary lies in [lo, hi]
@@ -59,10 +59,11 @@ __device__ __forceinline__ int first_moved(const int32_t *ku, int lo, int m) {
 }
 
 // A unit's keep list in a workgroup's hands: the new length, the first destination whose source differs, and the sources.
-// The first kCompactKeep entries are asked for at once, beside the new length, and kept in LDS, so that a trigger of that size
+// The first compact_keep entries are asked for at once, beside the new length, and kept in LDS, so that a trigger of that size
 // waits for one trip to memory before its first row, where a search and then a look-up made three or four.  With that and 512
-// threads instead of 256 (twice the rows in flight; with 1024 short moves take 3 us longer) 128 units that move 1150 of 2432 rows
+// threads instead of 256 (twice the rows in flight; with 1024 short moves take 3 us longer; compact_threads in dynts.hip says where 256 stay) 128 units that move 1150 of 2432 rows
 // on average take 28.7 us instead of 36.6: 151 MB read and written at 5.3 TB/s.
+template <int kCompactKeep>
 struct KeepList {
   const int32_t *ku;
   const int32_t *held;  // LDS
@@ -71,10 +72,12 @@ struct KeepList {
   __device__ __forceinline__ int source(int i) const { return clamp_slot(i < kCompactKeep ? held[i] : ku[i], cap); }
 };
 
-// Called by all threads; `held` has kCompactKeep words of LDS, `firsts` one per wave.
-__device__ __forceinline__ KeepList take_keep_list(const CompactParams &p, int unit, int b, int32_t *held, int32_t *firsts) {
+// Called by all threads; `held` has compact_keep words of LDS, `firsts` one per wave.
+template <int kCompactThreads, int kCompactKeep = compact_keep(kCompactThreads)>
+__device__ __forceinline__ KeepList<kCompactKeep> take_keep_list(const CompactParams &p, int unit, int b, int32_t *held, int32_t *firsts) {
+  constexpr int kCompactKeepRounds = kCompactKeep / kCompactThreads;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  KeepList k;
+  KeepList<kCompactKeep> k;
   k.ku = p.keep_idx + (size_t)unit * (size_t)p.keep_stride;
   k.held = held;
   k.cap = p.cap;
@@ -101,7 +104,7 @@ __device__ __forceinline__ KeepList take_keep_list(const CompactParams &p, int u
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < kCompactThreads / 64; ++w) first = firsts[w] < first ? firsts[w] : first;
-  if (first == k.m && k.m > kCompactKeep) first = first_moved(k.ku, kCompactKeep, k.m);
+  if (first == k.m && k.m > kCompactKeep) first = first_moved<kCompactThreads>(k.ku, kCompactKeep, k.m);
   k.first = first;
   return k;
 }
@@ -111,7 +114,7 @@ __device__ __forceinline__ KeepList take_keep_list(const CompactParams &p, int u
 // copies, so the in-place argument above holds for each of them; splitting a row over several
 // workgroups shortens the chain of dependent round trips (index, row, barrier, store) that bounds
 // this kernel: a trigger usually moves a few hundred rows per unit.
-template <int D>
+template <int D, int kCompactThreads>
 __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactParams p) {
   constexpr int kSlices = D * 2 / kCompactSliceBytes;   // column slices per row
   constexpr int LPS = kCompactSliceBytes / 16;          // lanes per row slice (16 bytes each)
@@ -119,10 +122,10 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactP
   constexpr int TILE = ROWS * kCompactUnroll;       // destinations per barrier
   const int tid = threadIdx.x;
   const int what = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  __shared__ int32_t sm_keep[kCompactKeep], sm_first[kCompactThreads / 64];
+  __shared__ int32_t sm_keep[compact_keep(kCompactThreads)], sm_first[kCompactThreads / 64];
   if (p.trigger && !p.trigger[b]) return;
   const size_t unit = (size_t)b * p.Hkv + h;
-  const KeepList keep = take_keep_list(p, (int)unit, b, sm_keep, sm_first);
+  const auto keep = take_keep_list<kCompactThreads>(p, (int)unit, b, sm_keep, sm_first);
   const int m = keep.m, first = keep.first;
 
   if (what < 2 * kSlices) {
@@ -164,7 +167,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactP
 #undef DYNTS_COMPACT_ROWS
   } else {
     // S (x == 2 * kSlices) or pos (the last x): 4-byte elements, kScalarUnroll per thread and pass
-    constexpr int kScalarUnroll = 4;
+    constexpr int kScalarUnroll = 2048 / kCompactThreads;
     constexpr int STILE = kCompactThreads * kScalarUnroll;
     uint32_t *eu = (what == 2 * kSlices ? reinterpret_cast<uint32_t *>(p.S) : reinterpret_cast<uint32_t *>(p.pos)) +
                    unit * (size_t)p.cap;

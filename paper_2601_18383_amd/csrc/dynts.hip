@@ -393,6 +393,34 @@ void launch_select(const dynts::SelectParams &p, const dynts_config &c, bool app
   else hipLaunchKernelGGL((dynts::select_kernel<T, false, false>), grid, dim3(T), 0, st, p);
 }
 
+// Threads of a compaction's workgroup.  512 (twice the rows in flight, 4096 entries of the keep list on chip) unless there are more than
+// the chip holds, four a compute unit: what is left over of a second round is then not worth its start, and with more rounds that start is
+// more than small caches have to do.  us with 256 (1024 entries) / 512, a tenth to a third of the rows moved (in brackets with 256
+// and nothing on chip), head_dim 128, 6 workgroups a unit:
+//   16 units of 700 slots 13.5 / 12.0 (14.1), of 333 11.2 / 11.1, paged 15.6 / 13.2 (15.8); 512 of 66 12.8 / 16.4 (13.2); 1024 of 66 16.7 / 23.2
+//     (17.4), of 333 54.7 / 54.5
+//   172 units of 1200 41.5 / 38.5 (39.9); 256 of 1200 53.1 / 54.5 (54.4), of 5000 278.1 / 295.7 (279.8); 512 of 1200 112.8 / 108.2 (115.3), of 5000
+//     572.9 / 553.9 (575.8)
+int compact_threads(const dynts_ctx *ctx) {
+  const dynts_config &c = ctx->cfg;
+  const long long wgs = (long long)c.batch * c.n_kv_heads * (2 * (c.head_dim * 2 / dynts::kCompactSliceBytes) + 2);
+  return wgs > 1280 && (wgs < 2048 || c.capacity <= 300) ? 256 : 512;
+}
+
+template <int T>
+void launch_compact(const dynts::CompactParams &p, const dynts_ctx *ctx, const dynts::PagedView &pv, hipStream_t st) {
+  const dynts_config &c = ctx->cfg;
+  const dim3 grid(2 * (c.head_dim * 2 / dynts::kCompactSliceBytes) + 2, c.n_kv_heads, c.batch), block(T);
+  if (ctx->paged) {
+    if (c.head_dim == 128) hipLaunchKernelGGL((dynts::paged_compact_kernel<128, T>), grid, block, 0, st, p, pv);
+    else hipLaunchKernelGGL((dynts::paged_compact_kernel<64, T>), grid, block, 0, st, p, pv);
+  } else if (c.head_dim == 128) {
+    hipLaunchKernelGGL((dynts::compact_kernel<128, T>), grid, block, 0, st, p);
+  } else {
+    hipLaunchKernelGGL((dynts::compact_kernel<64, T>), grid, block, 0, st, p);
+  }
+}
+
 // The buffer of kept logits is wanted for something else, or no longer: an update that rests on them alone is applied,
 // one that the next pass over K can make as well is left to that.
 int release_spill(dynts_ctx *ctx, hipStream_t st) {
@@ -980,19 +1008,13 @@ int dynts_compact(dynts_ctx *ctx, int32_t layer, const uint8_t *trigger, const i
   const LayerView lv = layer_view(ctx, layer);
   dynts::CompactParams p{lv.K, lv.V, lv.S, lv.pos, lv.seq_len, trigger, keep_idx, new_len,
                          c.n_kv_heads, c.capacity, keep_stride};
-  const dim3 grid(2 * (c.head_dim * 2 / dynts::kCompactSliceBytes) + 2, c.n_kv_heads, c.batch);
+  const dynts::PagedView pv{lv.K, lv.V, lv.block_table, ctx->free_stack, ctx->free_top, ctx->max_pages, ctx->n_pages};
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (ctx->paged) {
-    const dynts::PagedView pv{lv.K, lv.V, lv.block_table, ctx->free_stack, ctx->free_top, ctx->max_pages, ctx->n_pages};
-    if (c.head_dim == 128) hipLaunchKernelGGL((dynts::paged_compact_kernel<128>), grid, dim3(dynts::kCompactThreads), 0, st, p, pv);
-    else hipLaunchKernelGGL((dynts::paged_compact_kernel<64>), grid, dim3(dynts::kCompactThreads), 0, st, p, pv);
+  if (compact_threads(ctx) == 256) launch_compact<256>(p, ctx, pv, st);
+  else launch_compact<512>(p, ctx, pv, st);
+  if (ctx->paged)
     hipLaunchKernelGGL(dynts::paged_trim_kernel, dim3((c.batch + 63) / 64), dim3(64), 0, st, pv, trigger, new_len,
                        lv.seq_len, c.batch, c.n_kv_heads, c.capacity, keep_stride);
-  } else if (c.head_dim == 128) {
-    hipLaunchKernelGGL((dynts::compact_kernel<128>), grid, dim3(dynts::kCompactThreads), 0, st, p);
-  } else {
-    hipLaunchKernelGGL((dynts::compact_kernel<64>), grid, dim3(dynts::kCompactThreads), 0, st, p);
-  }
   return launch_status();
 }
 

@@ -137,7 +137,7 @@ __global__ void paged_append_kernel(const AppendParams p, PagedView pv) {
 // so "sources lie at or beyond destinations" protects rows exactly as in the dense layout), every row found
 // through the block table.  seq_len is left to paged_trim_kernel, which still needs the old length.
 // grid (2 * kSlices + 2, Hkv, Nb).
-template <int D>
+template <int D, int kCompactThreads>
 __global__ __launch_bounds__(kCompactThreads) void paged_compact_kernel(const CompactParams p, PagedView pv) {
   constexpr int kSlices = D * 2 / kCompactSliceBytes;
   constexpr int LPS = kCompactSliceBytes / 16;
@@ -145,11 +145,11 @@ __global__ __launch_bounds__(kCompactThreads) void paged_compact_kernel(const Co
   constexpr int TILE = ROWS * kCompactUnroll;
   const int tid = threadIdx.x;
   const int what = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  __shared__ int32_t sm_keep[kCompactKeep], sm_first[kCompactThreads / 64];
+  __shared__ int32_t sm_keep[compact_keep(kCompactThreads)], sm_first[kCompactThreads / 64];
   if (p.trigger && !p.trigger[b]) return;
   const size_t unit = (size_t)b * p.Hkv + h;
   const int32_t *tb = pv.block_table + unit * pv.max_pages;
-  const KeepList keep = take_keep_list(p, (int)unit, b, sm_keep, sm_first);
+  const auto keep = take_keep_list<kCompactThreads>(p, (int)unit, b, sm_keep, sm_first);
   const int m = keep.m, first = keep.first;
 
   if (what < 2 * kSlices) {

@@ -307,6 +307,36 @@ def test_compact_of_lists_beyond_what_is_held(B, d, cap, shift):
         assert torch.equal(c.pos[0, b, 0, :m[b]].long(), src) and torch.equal(c.S[0, b, 0, :m[b]], src.float())
 
 
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("d,Nb,Hkv,cap", [(64, 3, 2, 400), (64, 170, 2, 1100), (128, 107, 2, 1100), (64, 256, 2, 300), (64, 256, 2, 301),
+                                          (64, 161, 2, 1400)])
+def test_compact_with_either_workgroup(B, d, Nb, Hkv, cap, paged):
+    """256 threads where there are 1281 to 2047 workgroups, or more and the cache is small, 512 elsewhere; lists up to, at and beyond the 1024 entries
+    that the smaller ones hold on chip."""
+    g = torch.Generator(device="cuda").manual_seed(cap + d)
+    c = (B.PagedCache if paged else B.Cache)(1, Nb, Hkv, Hkv, d, cap, 1, 1, 1)
+    bf = lambda: torch.empty(Nb, Hkv, cap, d, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    K, V = bf(), bf()
+    B.dynts_prefill(c.ctx, 0, K, V, torch.full((Nb,), cap, dtype=torch.int32, device="cuda"))
+    c.S[0].copy_(torch.arange(cap, device="cuda").float()); c.pos[0].copy_(torch.arange(cap, device="cuda"))
+    some = [cap // 3, cap - 1, min(cap, 1024), min(cap, 1025), cap]  # entries of the list
+    idx = torch.zeros(Nb, Hkv, cap, dtype=torch.int64, device="cuda")
+    m = [some[b % len(some)] for b in range(Nb)]
+    for b in range(Nb):
+        pick = torch.rand(Hkv, cap, generator=g, device="cuda").argsort(dim=1)[:, :m[b]]
+        idx[b, :, :m[b]] = pick.sort(dim=1).values
+    c.keep_idx.copy_(idx)
+    c.new_len.copy_(torch.tensor(m, dtype=torch.int32))
+    B.dynts_compact(c.ctx, 0, c.keep_idx, c.new_len)
+    assert c.seq_len[0].tolist() == m
+    Kc, Vc = c.K[0], c.V[0]
+    for b in range(Nb):
+        src = idx[b, :, :m[b]]
+        rows = src.unsqueeze(-1).expand(Hkv, m[b], d)
+        assert torch.equal(Kc[b, :, :m[b]], torch.gather(K[b], 1, rows)) and torch.equal(Vc[b, :, :m[b]], torch.gather(V[b], 1, rows))
+        assert torch.equal(c.pos[0, b, :, :m[b]].long(), src) and torch.equal(c.S[0, b, :, :m[b]], src.float())
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_compact_bit_exact(B, d):
     rng = np.random.default_rng(5 + d)
