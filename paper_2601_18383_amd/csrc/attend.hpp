@@ -200,14 +200,20 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   constexpr int OSTRIDE = D + 4;          // floats per row of the cross-wave output reduction
   constexpr bool STREAM = LARGE == kStream, BURST = LARGE == kBurst;
   static_assert(!(STREAM && PAGED), "pages are loaded through the caches");
-  static_assert(kWaves * kTile * VSTRIDE >= kWaves * 16 * OSTRIDE * 4, "LDS tile is reused for the reduction");
-  __shared__ __align__(16) unsigned char smem[kWaves * kTile * VSTRIDE];
+  static_assert(kTile * VSTRIDE >= 16 * OSTRIDE * 4, "LDS tile is reused for the reduction");
+  // A pass over K alone turns it 16 rows at a time: with room for whole tiles (83 KB at head_dim 128) no second workgroup fits on a compute
+  // unit beside one, which short caches of many units need.  us, 32 / 16 rows at a time (in brackets with K in operand order from memory): 1024 units of
+  // 66 slots 12.7 / 10.2 (11.5), of 300 17.9 / 15.1 (17.0), of 900 40.6 / 38.0 (42.0); 512 of 300 11.0 / 9.4 (10.9); 2048 of 300 42.1 / 29.1
+  // (31.3); 512 of 2640 56.5 / 57.4 (65.7); 128 of 2464 15.8 / 15.5 (16.0)
+  constexpr int KROWS = ATTEND ? kTile : 16, QPREV = ATTEND ? 16 : 0;  // (and holds the previous step's query rows only)
+  constexpr int kStage = ATTEND ? kTile * VSTRIDE : KROWS * KSTRIDE;   // bytes of LDS a wave turns its tiles in
+  __shared__ __align__(16) unsigned char smem[kWaves * kStage];
   __shared__ float sm_m[kWaves][16];
   __shared__ float sm_l[kWaves][16];
   __shared__ float sm_max[16];
   __shared__ uint32_t sm_flag;
   __shared__ int32_t sm_hdr[5];
-  __shared__ __align__(16) unsigned char sm_q[2 * 16 * KSTRIDE];  // this step's query rows, the previous step's
+  __shared__ __align__(16) unsigned char sm_q[(QPREV + 16) * KSTRIDE];  // this step's query rows, the previous step's
   __shared__ __align__(16) float sm_ml[32];                       // statistics of the previous step
   __shared__ __align__(16) unsigned char sm_new[APPEND ? 4 * D : 16];  // the appended token's K and V row
   // updated scores of up to kScoreTiles consecutive tiles per wave, written out together (see flush_scores)
@@ -253,7 +259,7 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   };
   auto page_base = [&](int pg) -> size_t { return (size_t)pg * kPageSlots * D; };  // element offset of a page
   float *Sb = p.S + unit * (size_t)p.cap;
-  unsigned char *vst = smem + wave * (kTile * VSTRIDE);
+  unsigned char *vst = smem + wave * kStage;
   const int vrow_l = lane / PIECES, vpiece = lane % PIECES;
   // Work split of one (sequence, KV head) over its nsplit * W waves: wave wi first takes tile wi
   // (a position known before the sequence length is, so its loads can leave at once); the slots
@@ -332,7 +338,8 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
 #pragma unroll
   for (int j = 0; j < NQ; ++j) {
     const int i = tid + j * kThreads;
-    if (i < (PENDING ? 2 : 1) * 16 * PIECES) *reinterpret_cast<u32x4 *>(sm_q + i / PIECES * KSTRIDE + 16 * (i % PIECES)) = qpiece[j];
+    if (i < (PENDING ? 2 : 1) * 16 * PIECES && (ATTEND || i >= 16 * PIECES))
+      *reinterpret_cast<u32x4 *>(sm_q + (i / PIECES - 16 + QPREV) * KSTRIDE + 16 * (i % PIECES)) = qpiece[j];
   }
   if (PENDING && wave == kWaves - 2 && lane < 32) sm_ml[lane] = ml_word;
   if (row_wave && lane < 2 * PIECES) *reinterpret_cast<u32x4 *>(sm_new + 16 * lane) = new_piece;
@@ -343,7 +350,7 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
   for (int ks = 0; ks < KS; ++ks) {
     const unsigned char *src = sm_q + g * KSTRIDE + 64 * ks + 16 * kg;
     if (ATTEND) qf[ks] = *reinterpret_cast<const bf16x8 *>(src);
-    if (PENDING) qpf[ks] = *reinterpret_cast<const bf16x8 *>(src + 16 * KSTRIDE);
+    if (PENDING) qpf[ks] = *reinterpret_cast<const bf16x8 *>(src + QPREV * KSTRIDE);
   }
   // statistics of the deferred update for heads 4*kg .. 4*kg+3 (the rows this lane gets from
   // the swapped-operand MFMA)
@@ -596,15 +603,20 @@ __global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p)
 
     // the tile's K rows into operand order through the wave's LDS tile: lane (r, kg) gets row r, columns 32*ks + 8*kg .. +7.
     // (A wave's LDS accesses are carried out in order, so K and V of one tile after another share the room.)
-#pragma unroll
-    for (int it = 0; it < VIT; ++it)
-      *reinterpret_cast<u32x4 *>(vst + (VROWS * it + vrow_l) * KSTRIDE + 16 * vpiece) = kr[it];
-    wave_lds_fence();
     bf16x8 kf[2][KS];
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
+    for (int row0 = 0; row0 < kTile; row0 += KROWS) {
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) kf[s][ks] = *reinterpret_cast<const bf16x8 *>(vst + (16 * s + r16) * KSTRIDE + 64 * ks + 16 * kg);
+      for (int it = 0; it < KROWS / VROWS; ++it)
+        *reinterpret_cast<u32x4 *>(vst + (VROWS * it + vrow_l) * KSTRIDE + 16 * vpiece) = kr[row0 / VROWS + it];
+      wave_lds_fence();
+#pragma unroll
+      for (int s = 0; s < KROWS / 16; ++s)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+          kf[row0 / 16 + s][ks] = *reinterpret_cast<const bf16x8 *>(vst + (16 * s + r16) * KSTRIDE + 64 * ks + 16 * kg);
+      if (KROWS < kTile) wave_lds_fence();
+    }
     // logits for the current query (A = K rows, B = q) and for the previous one (swapped:
     // accp[s][i] = logit(slot t + 16 s + r16, head 4 kg + i))
     f32x4 acc[2], accp[2];

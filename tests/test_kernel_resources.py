@@ -50,3 +50,11 @@ def test_eight_wave_attention_kernels_do_not_spill(kernels):
     assert len(eight) > 40
     for name, k in eight.items():
         assert k["vgpr_spill_count"] == 0, name
+
+
+def test_passes_over_k_alone_keep_two_workgroups_per_compute_unit(kernels):
+    """The score update by itself, eight waves: short caches of many units hang on the second workgroup."""
+    alone = {n: k for n, k in kernels.items() if re.search(r"attend_kernelILi(64|128)ELi8ELb0E", n)}
+    assert len(alone) >= 8
+    for name, k in alone.items():
+        assert k["vgpr_count"] <= 128 and 2 * k["group_segment_fixed_size"] <= 160 * 1024, name
