@@ -186,9 +186,17 @@ __device__ __forceinline__ void wave_lds_fence() {
 // paged launches 5 % slower, and with them bursts gained nothing in the dense layout.)
 // SPILL: the step keeps its logits (AttendParams::spill).
 // WIDE: with the merges of 32 and of 8 chunks at a time (see merge below), whose registers every wave of the kernel pays for.
+// Registers: two waves a SIMD.  Steps on large paged caches of head_dim 64 need four (128 registers, where the compiler would take 131), two workgroups a
+// compute unit, as the other eight-wave forms of head_dim 64 have by themselves.  us a step, 131 / 128 registers (in brackets with K in operand order from memory,
+// 144): 260 units of 8000 slots 166.7 / 128.4 (145.6), 384 of 5000 114.8 / 103.4 (107.2), 800 of 4000 191.4 / 170.4 (178.7), 520 of 4000
+// 141.7 / 134.8 (127.9: eight workgroups wait for a place), 256 of 8000 103.2 / 103.4 (102.3).
+constexpr int min_waves(int D, int W, bool append, bool paged, int large, bool spill) {
+  return append && paged && D == 64 && W == 8 && large == kBurst && !spill ? 4 : 2;
+}
+
 template <int D, int W, bool ATTEND, bool PENDING, bool APPEND, bool PAGED = false, int LARGE = 0, bool SPILL = false,
           bool WIDE = false>
-__global__ __launch_bounds__(W * 64, 2) void attend_kernel(const AttendParams p) {
+__global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL)) void attend_kernel(const AttendParams p) {
   constexpr int kWaves = W, kThreads = W * 64;
   constexpr int KS = D / 32;              // MFMA k-steps per K row
   constexpr int CB = D / 16;              // 16-column blocks of the output

@@ -58,3 +58,10 @@ def test_passes_over_k_alone_keep_two_workgroups_per_compute_unit(kernels):
     assert len(alone) >= 8
     for name, k in alone.items():
         assert k["vgpr_count"] <= 128 and 2 * k["group_segment_fixed_size"] <= 160 * 1024, name
+
+
+def test_steps_on_large_paged_caches_of_head_dim_64_keep_two_workgroups_per_compute_unit(kernels):
+    burst = {n: k for n, k in kernels.items() if re.search(r"attend_kernelILi64ELi8ELb1ELb1ELb1ELb1ELi2ELb0ELb0EE", n)}
+    assert len(burst) == 1
+    for name, k in burst.items():
+        assert k["vgpr_count"] <= 128 and 2 * k["group_segment_fixed_size"] <= 160 * 1024, name
