@@ -396,18 +396,22 @@ void launch_select(const dynts::SelectParams &p, const dynts_config &c, bool app
   else hipLaunchKernelGGL((dynts::select_kernel<T, false, false>), grid, dim3(T), 0, st, p);
 }
 
-// Threads of a compaction's workgroup.  512 (twice the rows in flight, 4096 entries of the keep list on chip) unless there are more than
-// the chip holds, four a compute unit: what is left over of a second round is then not worth its start, and with more rounds that start is
-// more than small caches have to do.  us with 256 (1024 entries) / 512, a tenth to a third of the rows moved (in brackets with 256
-// and nothing on chip), head_dim 128, 6 workgroups a unit:
+// Threads of a compaction's workgroup.  512 (twice the rows in flight, 4096 entries of the keep list on chip) unless there are more workgroups
+// than the chip holds, four a compute unit: what is left over of a second round is then not worth its start, and with more rounds that
+// start is more than the smallest caches have to do.  Long lists want their entries on chip, the more so on pages.  us with 256 (1024 entries) /
+// 512 (in brackets with 256 and nothing on chip), a tenth to a third of the rows moved, head_dim 128, 6 workgroups a unit:
 //   16 units of 700 slots 13.5 / 12.0 (14.1), of 333 11.2 / 11.1, paged 15.6 / 13.2 (15.8); 512 of 66 12.8 / 16.4 (13.2); 1024 of 66 16.7 / 23.2
-//     (17.4), of 333 54.7 / 54.5
-//   172 units of 1200 41.5 / 38.5 (39.9); 256 of 1200 53.1 / 54.5 (54.4), of 5000 278.1 / 295.7 (279.8); 512 of 1200 112.8 / 108.2 (115.3), of 5000
-//     572.9 / 553.9 (575.8)
+//     (17.4), of 333 54.7 / 54.5; 512 of 1200 112.8 / 108.2 (115.3)
+//   172 units of 1200 41.5 / 38.5 (39.9); 236 of 300 14.9 / 16.0, paged 19.2 / 19.3, of 700 27.2 / 27.4, paged 31.5 / 29.9, of 2400 92.6 / 84.3, paged
+//     84.8 / 75.4; 288 of 700 30.1 / 31.1, of 1200 47.0 / 47.2
+//   256 units of 5000 278 / 296 (280), of 7400 322 / 342, paged 370 / 320; 336 of 4500 249 / 243; head_dim 64: 320 of 4500 156 / 142
 int compact_threads(const dynts_ctx *ctx) {
   const dynts_config &c = ctx->cfg;
   const long long wgs = (long long)c.batch * c.n_kv_heads * (2 * (c.head_dim * 2 / dynts::kCompactSliceBytes) + 2);
-  return wgs > 1280 && (wgs < 2048 || c.capacity <= 300) ? 256 : 512;
+  if (wgs <= 1280) return 512;
+  if (c.capacity <= 300) return 256;
+  if (ctx->paged || wgs >= 2048) return 512;
+  return c.capacity <= 1000 || (c.capacity > 4000 && c.head_dim == 128 && wgs > 1400 && wgs < 1700) ? 256 : 512;
 }
 
 template <int T>

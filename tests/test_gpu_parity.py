@@ -308,10 +308,10 @@ def test_compact_of_lists_beyond_what_is_held(B, d, cap, shift):
 
 
 @pytest.mark.parametrize("paged", [False, True])
-@pytest.mark.parametrize("d,Nb,Hkv,cap", [(64, 3, 2, 400), (64, 170, 2, 1100), (128, 107, 2, 1100), (64, 256, 2, 300), (64, 256, 2, 301),
-                                          (64, 161, 2, 1400)])
+@pytest.mark.parametrize("d,Nb,Hkv,cap", [(64, 3, 2, 400), (64, 161, 2, 1000), (128, 107, 2, 1100), (64, 256, 2, 300), (64, 256, 2, 301),
+                                          (128, 118, 2, 4200)])
 def test_compact_with_either_workgroup(B, d, Nb, Hkv, cap, paged):
-    """256 threads where there are 1281 to 2047 workgroups, or more and the cache is small, 512 elsewhere; lists up to, at and beyond the 1024 entries
+    """256 threads where there are more than 1280 workgroups and the cache is small (or beyond 4000 slots), 512 elsewhere; lists up to, at and beyond the 1024 entries
     that the smaller ones hold on chip."""
     g = torch.Generator(device="cuda").manual_seed(cap + d)
     c = (B.PagedCache if paged else B.Cache)(1, Nb, Hkv, Hkv, d, cap, 1, 1, 1)
