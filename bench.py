@@ -584,7 +584,7 @@ def run_predictor(args, wl):
     ev.close()
     alg = 2 * (m1 * d + m2 * m1 + m2) + 4 * (m1 + m2 + 1) + nb * d * 2 + nb * wl.n_kv_heads * 4
     achieved = alg / (call_ms * 1e-3) / 1e9
-    roofline = {"bound": "hbm", "kernel": "mlp_gemm x2 + reductions (one dynts_predict_scores call)",
+    roofline = {"bound": "hbm", "kernel": "mlp_kernel x2 (one dynts_predict_scores call)",
                 "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None, "call_avg_us": round(call_ms * 1e3, 2),
                 "algorithmic_bytes_per_call": alg, "flops_per_call": 2.0 * nb * (m1 * d + m2 * m1 + m2)}

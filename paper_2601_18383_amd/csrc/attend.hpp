@@ -113,12 +113,6 @@ constexpr int kPageSlots = 64;  // slots per page: two tiles, so a tile never st
 
 __device__ __forceinline__ u32x4 load_u32x4(const uint16_t *p) { return *reinterpret_cast<const u32x4 *>(p); }
 __device__ __forceinline__ void store_u32x4(uint16_t *p, u32x4 v) { *reinterpret_cast<u32x4 *>(p) = v; }
-__device__ __forceinline__ bf16x8 load_bf16x8(const uint16_t *p) {
-  return __builtin_bit_cast(bf16x8, load_u32x4(p));
-}
-__device__ __forceinline__ void store_bf16x8(uint16_t *p, bf16x8 v) {
-  store_u32x4(p, __builtin_bit_cast(u32x4, v));
-}
 
 // (two branches that differ only in how they load would be merged into one)
 #define DYNTS_OWN_BRANCH asm volatile("; past the caches")
@@ -804,7 +798,7 @@ __global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL
   const size_t ubase = unit * p.nsplit * (size_t)G;
 
   // ---- combine the waves -----------------------------------------------------------------
-  // (sm_l holds a wave's sum relative to the workgroup's maximum, sm_m[0] that maximum after the second barrier)
+  // (sm_l holds a wave's sum relative to the workgroup's maximum, sm_max that maximum, behind the second barrier)
   float *ored = reinterpret_cast<float *>(smem);
   if (has_partial) {
   l_run += __shfl_xor(l_run, 16);

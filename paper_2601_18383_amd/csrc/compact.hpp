@@ -2,7 +2,7 @@
 // bookkeeping kernels (prompt fill, append) that write cache rows.
 //
 // In-place safety: keep_idx is strictly ascending, so source >= destination for every row.
-// A workgroup walks its unit in ascending tiles of kCompactRows destinations; it loads the
+// A workgroup walks its unit in ascending tiles of destinations (TILE below); it loads the
 // whole tile's source rows into registers, meets at a barrier, then stores.  The sources of
 // any later tile lie at or beyond the end of this tile's destinations, so no row is
 // overwritten before it has been read.  Rows before the first evicted slot do not move and

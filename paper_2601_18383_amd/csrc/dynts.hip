@@ -183,15 +183,14 @@ LayerView layer_view(const dynts_ctx *ctx, int layer) {
   return v;
 }
 
-// Whether a launch takes the kernel with the wide merges.  Their registers (226 against 121 - 198) are every wave's, so a
+// Whether a launch takes the kernel with the wide merges.  Their registers (228 - 233 against 108 - 209) are every wave's, so a
 // head_dim 64 launch has them only where it has no second workgroup on a compute unit to lose (32 of an XCD's units'
 // chunks).  us a step, groups of four / wide:
-//   head_dim 128, 4 heads a group, 8 units: 10 chunks 14.2 / 14.5, 17 chunks 19.8 / 18.6, 18 chunks 17.4 / 16.1;
-//     12 units: 17 chunks 28.7 / 26.8; 16 units: 9 chunks 17.3 / 18.1, 11 chunks 21.5 / 22.0; 32 units: 6 chunks 20.1 / 22.1
-//   head_dim 128, 7 or 8 heads: 8 units, 10 chunks 15.5 / 14.6; 48 units, 5 chunks 25.4 / 24.3; every size between likewise
-//   head_dim 64, 4 heads: 8 units, 18 chunks 14.2 / 13.3, 17 chunks 15.0 / 14.4, 10 chunks 11.3 / 12.2; 12 units, 18 chunks
-//     16.4 / 17.6; 4 units (four XCDs), 33 chunks 19.0 / 21.2
-//   head_dim 64, 16 heads: 8 units, 18 chunks 16.3 / 16.8; 20 units, 9 chunks 14.8 / 15.4
+//   head_dim 128, 4 heads a group, 8 units: 10 chunks 11.5 / 12.2, 17 chunks 16.4 / 14.9, 18 chunks 13.9 / 12.4;
+//     12 units: 17 chunks 22.7 / 21.4; 16 units: 9 chunks 14.1 / 14.8, 11 chunks 18.7 / 19.4; 32 units: 6 chunks 18.3 / 20.2
+//   head_dim 128, 7 or 8 heads: 8 units, 10 chunks 12.2 / 12.0; 48 units, 5 chunks 16.9 / 16.3; every size between likewise
+//   head_dim 64, 4 heads: 8 units, 18 chunks 12.6 / 12.0, 17 chunks 13.5 / 13.0, 10 chunks 9.7 / 11.2; 12 units, 18 chunks
+//     13.7 / 15.2; 4 units (four XCDs), 33 chunks 17.1 / 18.6
 bool wide_merge(int D, int waves, int G, int nsplit, long long grid) {
   const int ne = (G * D + 64 * waves - 1) / (64 * waves);  // output elements per thread
   if (waves != 8) return false;
@@ -219,7 +218,7 @@ void launch_partial(const dynts::AttendParams &p, dim3 grid, hipStream_t st, hip
     else { DYNTS_LAUNCH2(true, 0, false); }
   } else if (p.fit_slots < p.cap) {
     DYNTS_LAUNCH2(false, dynts::kStream, false);
-  } else if (ATTEND && wide_merge(D, W, p.G, p.nsplit, grid.x)) {  // (before bursts: 16 units of 30000 slots 46.3 us with those, 45.4 so)
+  } else if (ATTEND && wide_merge(D, W, p.G, p.nsplit, grid.x)) {  // (before bursts: 16 units of 30000 slots 46.3 us with those, 45.4 so, when K did not go through LDS)
     DYNTS_LAUNCH2(false, 0, (ATTEND && W == 8));
   } else if (PENDING && p.score_tiles > 1) {
     DYNTS_LAUNCH2(false, kIfPending, false);
@@ -284,14 +283,14 @@ int run_attend(dynts_ctx *ctx, int layer, const uint16_t *q, const uint16_t *k_n
   p.part_o = tr.part_o;
   p.part_ml = tr.part_ml;
   p.tag = next_launch_tag();
-  // K and V past the memory-side cache: only when all layers together are more than what still gains from it (but for 2 % at
-  // 303 MB), and for launches of 128 or more units and 100 MB or more.  us a step, through it / past it:
-  //   one layer, 128 units: 303 MB 53.4 / 52.5, 314 MB 57.0 / 55.2, 323 MB 59.3 / 55.0, 382 MB 76.4 / 65.8
-  //   2 layers of 512 units of 2640 slots 129.2 / 114.4, 8 of them 133.5 / 129.7; 384 units of 2464 99.8 / 88.9; 4 layers of
-  //     128 units of 2464 37.3 / 33.4, 28 of them 37.6 / 34.5; 8 layers of 100 MB 26.0 / 24.1
-  //   short launches lose: 16 layers of 128 units of 700 17.4 / 18.1.  (The line is a cautious one: 96 units of 8000 would take
-  //     90.2 instead of 99.5, 8 layers of 64 units of 4000 28.8 instead of 30.9.)
-  // 272 MB of fixed places: with 320 MB 384 units of 2464 take 92.2 instead of 88.9, with 410 MB 103.9.
+  // K and V past the memory-side cache: only when all layers together are more than what still gains from it, and for launches of
+  // 128 or more units and 100 MB or more.  us a step, through it / past it:
+  //   one layer, 128 units: 303 MB 50.5 / 50.2, 314 MB 55.3 / 53.7, 323 MB 57.2 / 54.1, 382 MB 76.0 / 64.5
+  //   2 layers of 512 units of 2640 slots 130.7 / 114.5, 8 of them 132.3 / 122.5; 384 units of 2464 98.9 / 82.6; 4 layers of
+  //     128 units of 2464 36.2 / 32.3, 28 of them 35.5 / 33.0; 8 layers of 100 MB 24.8 / 23.4
+  //   short launches lose: 16 layers of 128 units of 700 15.5 / 15.8.  (The line is a cautious one: 96 units of 8000 would take
+  //     83.6 instead of 93.3, 8 layers of 64 units of 4000 28.0 instead of 30.9, 3 of 32 units of 16000 49.3 instead of 57.7.)
+  // 272 MB of fixed places: with 320 MB 384 units of 2464 take 85.5 instead of 83.1, with 410 MB 99.3.
   const double kv_bytes = 4.0 * c.batch * c.n_kv_heads * (double)c.capacity * c.head_dim;
   const double slot_bytes = 4.0 * c.n_layers * c.batch * c.n_kv_heads * c.head_dim;
   const bool stream_bound = (long long)c.batch * c.n_kv_heads >= 128 && kv_bytes >= 100e6;
@@ -300,8 +299,8 @@ int run_attend(dynts_ctx *ctx, int layer, const uint16_t *q, const uint16_t *k_n
   p.rounds = (int)(rounds < 1e6 ? rounds : 1e6);
   // Scores in bursts: where a layer's K and V do not fit the memory-side cache with room to spare, dense caches (those not loaded
   // past it) only when all layers together do not fit.  us a step, tile by tile / in bursts: 64 units of 12000 slots
-  // 77.9 / 76.1, of 9800 60.6 / 57.8; 120 units of 6000 75.0 / 71.7; two layers of 112 units of 4000 49.1 / 48.0; head_dim 64, 64
-  // units of 24000 81.4 / 78.7; but one layer of 250 MB 42.3 / 42.7, of 295 MB 49.9 / 50.4.
+  // 78.9 / 77.5, of 9800 58.8 / 56.7; 120 units of 6000 74.9 / 73.2; two layers of 112 units of 4000 51.4 / 51.1; head_dim 64, 64
+  // units of 24000 80.4 / 78.2; four layers of 40 units of 9800 46.3 / 47.0; one layer of 250 MB 42.3 / 42.7, of 295 MB 49.6 / 49.5.
   p.score_tiles = kv_bytes > 192e6 && (ctx->paged || kv_bytes * c.n_layers > 310e6) ? 16 : 1;
   p.spill = keep_logits ? reinterpret_cast<float *>(ctx->ws + pl.off_spill) : nullptr;
   p.cap_pad = pl.cap_pad;
@@ -455,12 +454,13 @@ void unfused_ends(dynts_ctx *ctx, bool paired) {
 
 // Kept logits are written and read once, 8 bytes per slot and head of the group; without them the update reads the slot's
 // K row again, 2 bytes per element.  us for both calls, second pass over K / kept:
-//   up to a quarter of the K row: 128 units of 5000 slots 82.2 / 62.3 (head_dim 128, 4 heads), 44.6 / 34.7 (64, 4); 8 units of
-//     5000 21.9 / 20.9 (128, 4), 24.0 / 24.4 (128, 8), 17.1 / 17.2 (64, 4)
-//   up to half of it: 128 units of 5000 44.2 / 37.7 (64, 8), 84.7 / 80.8 (128, 16); of 1200 16.9 / 18.1 (64, 8); 512 units of 1200
-//     40.0 / 35.3 (64, 8), 78.9 / 78.1 (128, 16); 8 units of 5000 17.7 / 19.5 (64, 8), 28.9 / 31.4 (128, 16); paged, 128 units of
-//     5000 85.6 / 94.9 (128, 16)
-//   all of it: 128 units of 1200 17.3 / 21.4 (64, 16), of 5000 44.5 / 43.8
+//   up to a quarter of the K row: 128 units of 5000 slots 80.8 / 62.9 (head_dim 128, 4 heads), 42.4 / 35.1 (64, 4), of 1200 24.6 / 23.1 (128, 4);
+//     but where K is less than some 30 MB the pass over it has become the faster one: 128 units of 1200 14.8 / 16.4 (64, 4), 8 units of
+//     5000 16.8 / 17.3 (128, 4), 18.1 / 20.2 (128, 8)
+//   up to half of it: 128 units of 5000 42.1 / 38.5 (64, 8), 81.7 / 80.2 (128, 16); of 1200 15.1 / 18.6 (64, 8); 512 units of 1200
+//     40.1 / 37.0 (64, 8), 76.8 / 75.8 (128, 16); 8 units of 5000 15.8 / 18.1 (64, 8), 21.6 / 27.0 (128, 16); paged, 128 units of
+//     5000 82.9 / 91.0 (128, 16)
+//   all of it: 128 units of 1200 15.7 / 22.5 (64, 16), of 5000 42.4 / 45.3
 bool kept_logits_pay(const dynts_ctx *ctx) {
   const dynts_config &c = ctx->cfg;
   const int G = ctx->plan.G;

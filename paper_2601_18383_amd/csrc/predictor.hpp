@@ -21,9 +21,11 @@
 //     cuts K of both layers (mlp_split_gemm_kernel).
 //   * k-steps are dealt out to the waves in turn: with contiguous shares, a power of two apart, all of them met on the same memory
 //     channels (d = 4096, batch 32: 31.3 -> 27.7 us).
-// us a call, d = 3584 (77 MB, 11.5 us at the rate of a plain read stream), with partial sums of both layers reduced by kernels of
+// us a call on the same weights again and again (77 MB, which the memory-side cache holds; 11.5 us at the rate of a plain read
+// stream), d = 3584, with partial sums of both layers reduced by kernels of
 // their own / so: batch 1 27.9 / 21.7, batch 32 30.0 / 24.5, batch 64 37.1 / 28.8, batch 128 65.3 / 39.0; d = 1024: 20.7 / 11.6,
-// 20.8 / 12.7, -, 27.1 / 17.8.  Of the 24.5: layer 1 11.3, gap 1.3, layer 2's loop 9, two hand-offs with what lies between 3.4.
+// 20.8 / 12.7, -, 27.1 / 17.8.  Weights that come from HBM, eight heads in turn: d = 3584, batch 32 28.4 instead of 24.3, 128 49.2 instead of 39.2.  Of the 24.5, by timestamps and so to within a
+// microsecond: layer 1 11.3, gap 1.3, layer 2's loop 9, two hand-offs with what lies between 3.4.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
