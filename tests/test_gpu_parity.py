@@ -283,6 +283,33 @@ def test_update_from_kept_logits_in_selections_of_many_units(B, Nb, Hkv, G, cap)
     assert not torch.equal(got[0][0][0], S)
 
 
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("d,Nb,Hkv,G,n,cap", [(128, 3, 2, 7, 2600, 2610), (128, 3, 2, 16, 2400, 2500), (128, 150, 4, 1, 47, 60),
+                                              (64, 150, 4, 4, 330, 340), (64, 2, 1, 16, 2700, 2705)])
+def test_update_by_itself_from_a_pass_over_k(B, d, Nb, Hkv, G, n, cap, paged):
+    """K turned half a tile at a time; caches on either side of 2500 slots, more and fewer units than compute units, ragged lengths."""
+    g = torch.Generator(device="cuda").manual_seed(cap + d)
+    bf = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    M, Hq = 5, Hkv * G
+    c = (B.PagedCache if paged else B.Cache)(1, Nb, Hq, Hkv, d, cap, 1, 1, 1)
+    K, q, out = bf(Nb, Hkv, n, d), bf(Nb, Hq, d), torch.zeros(Nb, Hq, d, device="cuda")
+    m = torch.tensor([n - (b % 3) * (n // 4) for b in range(Nb)], dtype=torch.int32, device="cuda")
+    B.dynts_prefill(c.ctx, 0, K, bf(Nb, Hkv, n, d), m)
+    c.n_prompt.fill_(M)
+    c.S.fill_(0.0)
+    B.dynts_decode_attend_update(c.ctx, 0, q, out)
+    B.dynts_update_scores(c.ctx, 0)
+    got = c.S[0].double()
+    for b in range(Nb):
+        nb = int(m[b])
+        x = torch.matmul(q[b].double().view(Hkv, G, d), K[b, :, :nb].double().transpose(1, 2)) / np.sqrt(d)
+        w = torch.softmax(x, dim=-1).sum(1)
+        w[:, :M] = 0.0
+        assert_close(got[b, :, :nb].cpu().numpy(), w.cpu().numpy(), "S of sequence %d" % b)
+        assert not got[b, :, nb:].any()
+    assert int(c.status.item()) == 0
+
+
 @pytest.mark.parametrize("shift", [0, 1])
 @pytest.mark.parametrize("d,cap", [(64, 4600), (128, 4096), (64, 100)])
 def test_compact_of_lists_beyond_what_is_held(B, d, cap, shift):
