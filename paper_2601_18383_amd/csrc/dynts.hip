@@ -18,6 +18,7 @@
 #include "paged.hpp"
 #include "predictor.hpp"
 #include "probe.hpp"
+#include "resident.hpp"
 #include "score_block.hpp"
 #include "select.hpp"
 
@@ -98,6 +99,7 @@ struct dynts_ctx {
   Plan plan;
   float scale_log2;
   bool bound = false;
+  bool shaped = false;                 // the launch shape is the caller's (dynts_set_launch_shape)
   uint16_t *K = nullptr, *V = nullptr;
   float *S = nullptr;
   int32_t *pos = nullptr, *seq_len = nullptr, *next_pos = nullptr, *n_prompt = nullptr, *status = nullptr;
@@ -491,6 +493,67 @@ int fused_step(dynts_ctx *ctx, int layer, const uint16_t *q, const uint16_t *k_n
   return rc;
 }
 
+// ---- consecutive steps in one launch ----------------------------------------------------------------
+// Whether a run of steps of a layer is one launch that keeps the cache on the chip (resident_kernel): dense caches of as many slots as its
+// waves hold, which gains everywhere (us a step, a launch each / so: 1 unit of 120 slots of 16 heads 6.1 / 2.9, 1024 units of 120 slots
+// 11.1 / 7.1, of 510 47.2 / 14.9; the least: 1 unit of 400 slots of 16 heads, in two chunks, 8.7 / 5.2).  More slots do not fit the
+// registers of eight waves at head_dim 128.  Not where every attend launch is to be timed or has a shape of the caller's, and not under
+// capture: replays take turns between the two places of the saved query step by step.
+bool keeps_resident(const dynts_ctx *ctx, hipStream_t st) {
+  return !ctx->paged && ctx->cfg.capacity <= dynts::kResTiles * dynts::kResSlots && !ctx->shaped && !ctx->ev_start &&
+         ctx->ev_list_next >= ctx->ev_list_start.size() && !capturing(st);
+}
+
+template <int D>
+void launch_resident(const dynts::ResidentParams &p, int chunks, dim3 grid, dim3 block, hipStream_t st) {
+  if (p.cap <= dynts::kResSlots) hipLaunchKernelGGL((dynts::resident_kernel<D, 1, false>), grid, block, 0, st, p);
+  else if (chunks == 1) hipLaunchKernelGGL((dynts::resident_kernel<D, 2, false>), grid, block, 0, st, p);
+  else hipLaunchKernelGGL((dynts::resident_kernel<D, 2, true>), grid, block, 0, st, p);
+}
+
+// Steps [0, steps) of one layer, inputs of step 0 given.  evict: a trigger follows the last, which keeps its logits.
+int resident_steps(dynts_ctx *ctx, int layer, int steps, bool evict, const uint16_t *q, const uint16_t *k_new, const uint16_t *v_new,
+                   const float *s_new, const uint8_t *active, float *out, size_t out_stride, hipStream_t st) {
+  if ((reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(k_new) | reinterpret_cast<uintptr_t>(v_new)) % 16) return DYNTS_EINVAL;
+  const dynts_config &c = ctx->cfg;
+  const bool track = c.score_mode == DYNTS_SCORE_ACCUMULATE;
+  const bool keep = track && evict;
+  ctx->hint[layer] = 0;
+  if (keep || ctx->unfused_layer == layer) unfused_ends(ctx, false);
+  int rc = DYNTS_OK;
+  if (ctx->pending[layer] == 2) rc = apply_spill(ctx, layer, st);
+  if (ctx->pending[layer] == 3 || keep) rc = rc == DYNTS_OK ? release_spill(ctx, st) : rc;
+  if (rc != DYNTS_OK) return rc;
+  const LayerView lv = layer_view(ctx, layer);
+  dynts::ResidentParams p;
+  p.K = lv.K; p.V = lv.V; p.S = lv.S; p.pos = lv.pos;
+  p.seq_len = lv.seq_len; p.n_prompt = ctx->n_prompt; p.next_pos = lv.next_pos;
+  p.q = q; p.k_new = k_new; p.v_new = v_new; p.s_new = s_new; p.active = active; p.out = out;
+  p.q_stride = (size_t)c.n_layers * c.batch * c.n_q_heads * c.head_dim;
+  p.kv_stride = (size_t)c.n_layers * c.batch * c.n_kv_heads * c.head_dim;
+  p.out_stride = out_stride;
+  p.steps = steps;
+  p.qprev = lv.qprev; p.qnext = lv.qnext; p.mlprev = lv.mlprev; p.nprev = lv.nprev;
+  p.seq_cnt = reinterpret_cast<uint32_t *>(ctx->ws + ctx->plan.off_seq_cnt);
+  p.cnt_stride = kCounterStride;
+  p.status = ctx->status;
+  p.Nb = c.batch; p.Hq = c.n_q_heads; p.Hkv = c.n_kv_heads; p.G = ctx->plan.G; p.cap = c.capacity;
+  p.track = track ? 1 : 0;
+  p.owed = ctx->pending[layer] == 1 ? 1 : 0;
+  p.spill = keep ? reinterpret_cast<float *>(ctx->ws + ctx->plan.off_spill) : nullptr;
+  p.cap_pad = ctx->plan.cap_pad;
+  p.scale_log2 = ctx->scale_log2;
+  const dim3 grid((unsigned)(c.batch * c.n_kv_heads)), block(dynts::kResThreads);
+  if (c.head_dim == 128) launch_resident<128>(p, ctx->plan.nsplit, grid, block, st);
+  else launch_resident<64>(p, ctx->plan.nsplit, grid, block, st);
+  rc = launch_status();
+  if (rc != DYNTS_OK) return rc;
+  if (track) ctx->qslot[layer] ^= 1;
+  ctx->pending[layer] = track ? (keep ? 2 : 1) : 0;
+  if (keep) ctx->spill_layer = layer;
+  return DYNTS_OK;
+}
+
 // ---- block scoring ----------------------------------------------------------------------------------
 // bytes of one key range's denominators
 size_t score_block_stats_bytes(const dynts_config &c, int n_queries) {
@@ -760,6 +823,7 @@ int dynts_set_launch_shape(dynts_ctx *ctx, int32_t target_workgroups, int32_t wa
   if (target_workgroups < 0 || (waves_per_workgroup != 0 && waves_per_workgroup != 4 && waves_per_workgroup != 8))
     return DYNTS_EINVAL;
   ctx->plan = make_plan(ctx->cfg, target_workgroups, waves_per_workgroup);
+  ctx->shaped = target_workgroups > 0 || waves_per_workgroup > 0;
   ctx->bound = false;  // the workspace layout changed
   return DYNTS_OK;
 }
@@ -1220,22 +1284,37 @@ int dynts_decode_loop(dynts_ctx *ctx, int32_t n_steps, const uint16_t *q, const 
   if (evict_steps && (!keep_idx || !new_len)) return DYNTS_ENULL;
   const size_t q_layer = (size_t)c.batch * c.n_q_heads * c.head_dim;
   const size_t kv_layer = (size_t)c.batch * c.n_kv_heads * c.head_dim;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  auto trigger_of = [&](int i, int l) {
+    const uint8_t *trig = trigger ? trigger + (size_t)i * c.batch : nullptr;
+    const int rc2 = dynts_select_evict(ctx, l, trig, c.budget, keep_idx, c.capacity, new_len, stream);
+    return rc2 == DYNTS_OK ? dynts_compact(ctx, l, trig, keep_idx, c.capacity, new_len, stream) : rc2;
+  };
   for (int i = 0; i < n_steps; ++i) {
     const uint8_t *act = active ? active + (size_t)i * c.batch : nullptr;
     const float *sn = ext ? s_new + (size_t)i * c.batch * c.n_kv_heads : nullptr;
+    int run = 1;  // steps up to the next trigger's, where they can be one launch
+    if (keeps_resident(ctx, st))
+      while (i + run < n_steps && run < dynts::kResSteps && !(evict_steps && evict_steps[i + run - 1])) ++run;
+    if (run > 1) {
+      const bool evict = evict_steps && evict_steps[i + run - 1];
+      for (int l = 0; l < c.n_layers; ++l) {
+        const size_t sl = (size_t)i * c.n_layers + l;
+        rc = resident_steps(ctx, l, run, evict, q + sl * q_layer, k_new + sl * kv_layer, v_new + sl * kv_layer, sn, act,
+                            out + (size_t)i * out_step_stride + (size_t)l * q_layer, out_step_stride, st);
+        if (rc == DYNTS_OK && evict) rc = trigger_of(i + run - 1, l);
+        if (rc != DYNTS_OK) return rc;
+      }
+      i += run - 1;
+      continue;
+    }
     for (int l = 0; l < c.n_layers; ++l) {
       const size_t sl = (size_t)i * c.n_layers + l;
       if (evict_steps && evict_steps[i]) ctx->hint[l] = 1;  // the trigger below follows this step
       rc = dynts_decode_step(ctx, l, q + sl * q_layer, k_new + sl * kv_layer, v_new + sl * kv_layer, sn, act,
                              out + (size_t)i * out_step_stride + (size_t)l * q_layer, nullptr, stream);
+      if (rc == DYNTS_OK && evict_steps && evict_steps[i]) rc = trigger_of(i, l);
       if (rc != DYNTS_OK) return rc;
-      if (evict_steps && evict_steps[i]) {
-        const uint8_t *trig = trigger ? trigger + (size_t)i * c.batch : nullptr;
-        rc = dynts_select_evict(ctx, l, trig, c.budget, keep_idx, c.capacity, new_len, stream);
-        if (rc != DYNTS_OK) return rc;
-        rc = dynts_compact(ctx, l, trig, keep_idx, c.capacity, new_len, stream);
-        if (rc != DYNTS_OK) return rc;
-      }
     }
   }
   return DYNTS_OK;

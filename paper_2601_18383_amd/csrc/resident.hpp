@@ -1,0 +1,496 @@
+// Consecutive decode steps of one layer on a small cache, in one launch (dynts_decode_loop between two triggers).
+//
+// A step on a cache of a few hundred slots takes 5 us a launch whatever it computes: the launch itself, the sequence's words,
+// K, V behind them, the combination of the waves, each a trip to memory that the next one waits for.  So here the cache stays on the chip: one
+// workgroup of eight waves per (sequence, KV head), and a wave keeps T tiles of 32 slots as MFMA operands in its registers through
+// all steps of the launch.  A step then reads its query and its new row, which are asked for two steps ahead, and writes its
+// output; a new row is put into the registers of the wave whose tile its slot lies in, and rows, scores and positions go to
+// memory once, at the end.
+//
+// The arithmetic is attend_kernel's to the last bit, so that it makes no difference which of the two made a step: which wave takes which
+// tile, the new token as the first wave's initial state, tiles of a wave one after the other, SPLIT: two chunks of 256 slots
+// combined by themselves and then merged.  So are the things it leaves: the last step's update is owed (query, statistics, slots), or its
+// logits are kept for the trigger that follows.
+//
+// What bounds it now: a chain of about 400 dependent instructions a wave and step -- logits, maximum, weights, products, two barriers
+// around the waves' combination, division, scores.  us a step, a launch each / so, runs of 32 steps: head_dim 64, 4 heads a group,
+// caches of 250 slots, 8 units 5.53 / 1.97, 256 5.91 / 2.10, 1024 15.84 / 7.90; of 510 slots 8 units 7.09 / 3.31 (two chunks), 256 9.05 / 2.84; head_dim 128, 7
+// heads, of 120 slots, 4 units 6.15 / 2.64, 1024 23.7 / 10.7; of 510, 4 units 8.75 / 4.73, 256 14.8 / 3.98, 1024 48.7 / 16.0.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "attend.hpp"
+
+namespace dynts {
+
+constexpr int kResWaves = 8, kResThreads = 64 * kResWaves;
+constexpr int kResSlots = kResWaves * kTile;  // slots that one tile a wave holds
+constexpr int kResTiles = 2;                  // tiles a wave keeps at most
+constexpr int kResSteps = 1024;               // steps of a launch at most
+
+struct ResidentParams {
+  uint16_t *K, *V;          // layer base, [Nb][Hkv][cap][D]
+  float *S;                 // [Nb][Hkv][cap]
+  int32_t *pos;             // [Nb][Hkv][cap]
+  int32_t *seq_len;         // [Nb]
+  const int32_t *n_prompt;  // [Nb]
+  int32_t *next_pos;        // [Nb]
+  // step i's: base + i * stride elements
+  const uint16_t *q;        // [Nb][Hq][D], q_stride
+  const uint16_t *k_new, *v_new;  // [Nb][Hkv][D], kv_stride
+  const float *s_new;       // [Nb][Hkv] or null, Nb * Hkv
+  const uint8_t *active;    // [Nb] or null, Nb
+  float *out;               // [Nb][Hq][D], out_stride
+  size_t q_stride, kv_stride, out_stride;
+  int steps;
+  // the deferred update (see AttendParams): the one owed from before (owed != 0), and where the last step's is kept
+  const uint16_t *qprev;
+  uint16_t *qnext;
+  float *mlprev;
+  int32_t *nprev;
+  uint32_t *seq_cnt;        // [Nb][cnt_stride] arrival counters, zero between launches
+  int cnt_stride;
+  int32_t *status;
+  int Nb, Hq, Hkv, G, cap;
+  int track;                // scores are accumulated from attention
+  int owed;                 // an update is owed from before this launch
+  float *spill;             // the last step's logits are kept (see AttendParams), or null
+  int cap_pad;
+  float scale_log2;
+};
+
+// A lane's x and that of the lane 16 (32) further on in the pair of rows (halves) of the wave: no trip through LDS.
+struct Pair {
+  float low, high;
+};
+__device__ __forceinline__ Pair over_16(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ __forceinline__ Pair over_32(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+// over a wave's four rows of 16 lanes, in every lane
+__device__ __forceinline__ float max_over_rows(float x) {
+  Pair p = over_16(x);
+  p = over_32(fmaxf(p.low, p.high));
+  return fmaxf(p.low, p.high);
+}
+__device__ __forceinline__ float sum_over_rows(float x) {
+  Pair p = over_16(x);
+  p = over_32(p.low + p.high);
+  return p.low + p.high;
+}
+
+template <int D, int T, bool SPLIT>
+__global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const ResidentParams p) {
+  static_assert(!SPLIT || T == 2, "a chunk is a tile a wave");
+  constexpr int C = SPLIT ? 2 : 1;  // chunks
+  constexpr int KS = D / 32, CB = D / 16, PIECES = D / 8;
+  constexpr int VROWS = 64 / PIECES, VIT = kTile / VROWS;  // rows of one wave-wide 16-byte load
+  constexpr int STRIDE = 2 * D + 32;                       // bytes per staged row (see attend_kernel)
+  constexpr int OSTRIDE = D + 4;
+  constexpr int NE = (16 * D + kResThreads - 1) / kResThreads;  // output elements per thread at the largest group
+  static_assert(kTile * STRIDE >= 16 * OSTRIDE * 4, "the tiles' LDS is reused for the outputs");
+  __shared__ __align__(16) unsigned char smem[kResWaves * kTile * STRIDE];
+  constexpr int IN = 18 * STRIDE;  // a step's query rows, its K and its V row
+  __shared__ __align__(16) unsigned char sm_in[2 * IN];  // of even and of odd steps
+  __shared__ __align__(16) float sm_m[16][kResWaves], sm_l[16][kResWaves];
+  struct Stats { float m[16], l[16], inv_l[16], w0[16], w1[16]; };  // of a step's softmax: maximum, sum, weights of the chunks
+  __shared__ __align__(16) Stats sm_stats[kResWaves];         // (each wave its own: no barrier)
+  __shared__ int32_t sm_hdr[5];
+  __shared__ int16_t sm_step[kResSlots * T];                  // the step that appended each new row
+  __shared__ uint8_t sm_active[kResSteps + 4];                // of each step
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, kg = lane >> 4, g = r16;
+  // (a division leaves uniform values in vector registers, and every address formed from them)
+  const int unit = blockIdx.x, b = __builtin_amdgcn_readfirstlane(unit / p.Hkv), h = unit - b * p.Hkv, G = p.G;
+  uint16_t *Kb = p.K + (size_t)unit * p.cap * D, *Vb = p.V + (size_t)unit * p.cap * D;
+  float *Sb = p.S + (size_t)unit * p.cap;
+  const size_t row0 = (size_t)b * p.Hq + (size_t)h * G;  // the group's first query head
+
+  // ---- a step's inputs, asked for two steps ahead: 16 bytes a thread of its query rows, its K and its V row --------
+  // (no branch and no wait but for what is used: threads without a piece repeat the first)
+  const int n_pieces = (G + 2) * PIECES, my_row = tid / PIECES;
+  const bool has_piece = tid < n_pieces;
+  const uint16_t *src = p.q + row0 * D + (my_row < G ? 8 * tid : 0);
+  if (has_piece && my_row >= G) src = (my_row == G ? p.k_new : p.v_new) + (size_t)unit * D + 8 * (tid % PIECES);
+  const size_t src_stride = has_piece && my_row >= G ? p.kv_stride : p.q_stride;
+  unsigned char *put = sm_in + (my_row < G ? my_row : 16 + my_row - G) * STRIDE + 16 * (tid % PIECES);
+  auto fetch = [&](int i, u32x4 &piece) {  // (called for one step after the other; behind the last, for the last again)
+    piece = load_u32x4(src);
+    if (i + 1 < p.steps) src += src_stride;
+  };
+  auto stage = [&](int i, const u32x4 &piece) {
+    if (has_piece) *reinterpret_cast<u32x4 *>(put + (i & 1) * IN) = piece;
+  };
+  for (int i = tid; i < p.steps; i += kResThreads) sm_active[i] = p.active ? p.active[(size_t)i * p.Nb + b] : 1;
+
+  // The words of the sequence are rewritten by the last of its workgroups to check in, which each does when its wave 0 has them.
+  if (tid < 5) {
+    const int32_t *w = tid == 0 ? p.seq_len : tid == 1 ? p.nprev : tid == 2 ? p.next_pos : p.n_prompt;
+    sm_hdr[tid] = tid < 4 ? w[b] : 0;
+  }
+  u32x4 piece_a, piece_b;
+  fetch(0, piece_a);
+  for (int i = tid; i < 2 * (16 - G) * PIECES; i += kResThreads)  // (rows past the group's heads)
+    *reinterpret_cast<u32x4 *>(sm_in + (i & 1) * IN + (G + (i >> 1) / PIECES) * STRIDE + 16 * ((i >> 1) % PIECES)) = u32x4{0u, 0u, 0u, 0u};
+  __syncthreads();
+  uint32_t seq_ticket = 0xffffffffu;
+  if (tid == 0) seq_ticket = draw_ticket(p.seq_cnt + (size_t)b * p.cnt_stride);
+  int n = __builtin_amdgcn_readfirstlane(sm_hdr[0]);
+  n = n < 0 ? 0 : (n > p.cap ? p.cap : n);
+  const int n_entry = n, M = __builtin_amdgcn_readfirstlane(sm_hdr[3]);
+
+  // Tile j of this wave starts at slot first(j).  (Without chunks a wave's second tile lies where attend_kernel has it, counted from the end.)
+  auto first = [&](int j) { return kTile * (j == 0 ? wave : SPLIT ? kResWaves + wave : 2 * kResWaves - 1 - wave); };
+
+  // ---- the cache, as operands (see attend_kernel); rows past the sequence are zeros ---------------------------------
+  bf16x8 kf[T][2][KS];
+  i16x8 vt[T][CB];
+  float s_reg[T];  // lane < 32: score of slot first(tile) + lane
+  unsigned char *vst = smem + wave * kTile * STRIDE;
+#pragma unroll
+  for (int j = 0; j < T; ++j) {
+    const int t = first(j);
+    u32x4 kr[VIT], vr[VIT];
+    load_tile<D>(kr, row_buffer<D>(Kb, n), t, lane);
+    load_tile<D>(vr, row_buffer<D>(Vb, n), t, lane);
+    const int tok = t + (lane & (kTile - 1));
+    s_reg[j] = tok < n ? Sb[tok] : 0.f;
+#pragma unroll
+    for (int it = 0; it < VIT; ++it)
+      *reinterpret_cast<u32x4 *>(vst + (VROWS * it + lane / PIECES) * STRIDE + 16 * (lane % PIECES)) = kr[it];
+    wave_lds_fence();
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        kf[j][s][ks] = *reinterpret_cast<const bf16x8 *>(vst + (16 * s + r16) * STRIDE + 64 * ks + 16 * kg);
+    wave_lds_fence();
+#pragma unroll
+    for (int it = 0; it < VIT; ++it)
+      *reinterpret_cast<u32x4 *>(vst + (VROWS * it + lane / PIECES) * STRIDE + 16 * (lane % PIECES)) = vr[it];
+    wave_lds_fence();
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {  // lane (c = 16 cb + r16, kg): V[t + 16 s + 4 kg + i][c] as element 4 s + i
+      const unsigned char *at = vst + (4 * kg + (r16 >> 2)) * STRIDE + 2 * (16 * cb + 4 * (r16 & 3));
+      const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(at));
+      const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(at + 16 * STRIDE));
+      vt[j][cb] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+    wave_lds_fence();
+  }
+
+  // S[slot] += sum over the group of 2^(logit - m) / l for the thinking slots below lim of tile j; m, inv_l: of heads 4 kg .. 4 kg + 3
+  auto score_tile = [&](int j, const bf16x8 (&qv)[KS], const f32x4 &m, const f32x4 &inv_l, int lim) {
+    if (first(j) >= lim) return;
+    float part[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      f32x4 e = f32x4{0.f, 0.f, 0.f, 0.f};  // logit of slot 16 s + r16, head 4 kg + i
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) e = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv[ks], kf[j][s][ks], e, 0, 0, 0);
+      float a = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a += fast_exp2(e[i] * p.scale_log2 - m[i]) * inv_l[i];
+      if (G > 8) {
+        a = sum_over_rows(a);
+      } else if (G > 4) {
+        const Pair r = over_16(a);
+        a = r.low + r.high;
+      }
+      part[s] = a;
+    }
+    if (G <= 4) part[1] = over_16(part[1]).low;  // (the first row's lanes hold the sums; the second takes sub-tile 1)
+    const int tok = first(j) + lane;
+    if (lane < kTile && tok < lim && tok >= M) s_reg[j] += kg == 0 ? part[0] : part[1];
+  };
+
+  // ---- the update owed from before ------------------------------------------------------------------------------
+  if (p.owed) {
+    int n_prev = __builtin_amdgcn_readfirstlane(sm_hdr[1]);
+    n_prev = n_prev < 0 ? 0 : (n_prev > n ? n : n_prev);
+    if (n_prev > 0) {
+      f32x4 m = {0.f, 0.f, 0.f, 0.f}, inv_l = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (4 * kg + i < G) {
+          m[i] = p.mlprev[(row0 + 4 * kg + i) * 2];
+          inv_l[i] = 1.0f / p.mlprev[(row0 + 4 * kg + i) * 2 + 1];
+        }
+      }
+      bf16x8 qp[KS];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        qp[ks] = __builtin_bit_cast(bf16x8, g < G ? load_u32x4(p.qprev + (row0 + g) * D + 32 * ks + 8 * kg) : u32x4{0u, 0u, 0u, 0u});
+#pragma unroll
+      for (int j = 0; j < T; ++j) score_tile(j, qp, m, inv_l, n_prev);
+    }
+  }
+  __syncthreads();  // the tiles' LDS becomes the outputs'; every wave has its operands
+  __builtin_amdgcn_s_waitcnt(0x0f70);  // (every load so far: one that the loop might still be owed would be waited for in each round)
+  stage(0, piece_a);
+  fetch(1, piece_b);
+  fetch(2, piece_a);
+  __syncthreads();
+
+  float *ored = reinterpret_cast<float *>(smem);
+  bool last_attended = false;
+  int n_dropped = 0;
+  int act_next = sm_active[0];
+  float *const out_rows = p.out + row0 * D;
+  Stats &stats = sm_stats[wave];
+
+  auto load_q = [&](bf16x8 (&qf)[KS], const unsigned char *in) {  // lane (g, kg): q[g][32 ks + 8 kg .. +7]
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(in + g * STRIDE + 64 * ks + 16 * kg);
+  };
+  // Step i; LAST: the launch's last, whose update is left owed (all the others, steps below `most`, make theirs).
+  const int most = p.steps - 1;
+  auto step = [&](auto LAST, int i, u32x4 &next) {
+    constexpr bool last = decltype(LAST)::value;
+    // ---- what this step does (the same in the whole workgroup) ---------------------------------------------
+    const unsigned char *in = sm_in + (i & 1) * IN;
+    const bool act = __builtin_amdgcn_readfirstlane(last ? (int)sm_active[most] : act_next) != 0 && (last || i < most);
+    act_next = sm_active[i + 1];
+    const int n_rows = __builtin_amdgcn_readfirstlane(n);
+    const bool attended = act && n_rows < p.cap;
+    n_dropped += act && !attended ? 1 : 0;
+    if (last) last_attended = attended;
+    n = attended ? n_rows + 1 : n_rows;
+    float mstar[C], lsum[C], o_part[C][NE];  // of the chunks
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      float m_run = -INFINITY, l_run = 0.f;
+      f32x4 oacc[CB];
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) oacc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (attended) {
+        bf16x8 qf[KS];
+        load_q(qf, in);
+        if (c == 0 && wave == 0) {  // the new token (see attend_kernel)
+          f32x4 a0 = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) {
+            const bf16x8 kn = *reinterpret_cast<const bf16x8 *>(in + 16 * STRIDE + 64 * ks + 16 * kg);
+            a0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kn, qf[ks], a0, 0, 0, 0);
+          }
+          m_run = a0[0] * p.scale_log2;
+          l_run = kg == 0 ? 1.f : 0.f;
+          if (last && p.spill && kg == 0 && g < G) p.spill[spill_at((size_t)unit, p.cap_pad, G, g, n_rows)] = m_run;
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb) {
+            typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+            const bf16x4 v4 = *reinterpret_cast<const bf16x4 *>(in + 17 * STRIDE + 32 * cb + 8 * kg);
+            oacc[cb] = f32x4{(float)v4[0], (float)v4[1], (float)v4[2], (float)v4[3]};
+          }
+        }
+        // ---- this wave's slots -------------------------------------------------------------------------------
+#pragma unroll
+        for (int j = 0; j < T; ++j) {
+          const int t = first(j);
+          if ((SPLIT && j != c) || t >= n_rows) continue;
+          f32x4 acc[2];
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) acc[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[j][s][ks], qf[ks], acc[s], 0, 0, 0);
+          }
+          float x[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) x[k] = acc[k >> 2][k & 3] * p.scale_log2;
+          if (t + kTile > n_rows) {
+            DYNTS_OWN_BRANCH;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) x[k] = t + 16 * (k >> 2) + 4 * kg + (k & 3) < n_rows ? x[k] : -INFINITY;
+          }
+          float mx = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
+          if (last && p.spill && g < G) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+              const int tok = t + 16 * (k >> 2) + 4 * kg + (k & 3);
+              if (tok < n_rows) p.spill[spill_at((size_t)unit, p.cap_pad, G, g, tok)] = x[k];
+            }
+          }
+          mx = max_over_rows(mx);
+          const float m_new = fmaxf(m_run, mx);
+          const float corr = fast_exp2(m_run - m_new);
+          if (SPLIT ? c == 0 && wave == 0 : j > 0 || wave == 0) {  // (else there is nothing to correct)
+            DYNTS_OWN_BRANCH;
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) oacc[cb] *= corr;
+          }
+          m_run = m_new;
+          bf16x8 ph, pl;
+          float psum = 0.f;
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            const float pe = fast_exp2(x[k] - m_new);
+            psum += pe;
+            const __bf16 hi = (__bf16)pe;
+            ph[k] = hi;
+            pl[k] = (__bf16)(pe - (float)hi);
+          }
+          l_run = l_run * corr + psum;
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb) {
+            const bf16x8 v = __builtin_bit_cast(bf16x8, vt[j][cb]);
+            oacc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, ph, oacc[cb], 0, 0, 0);
+            oacc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, pl, oacc[cb], 0, 0, 0);
+          }
+        }
+        l_run = sum_over_rows(l_run);
+        if (kg == 0) sm_m[g][wave] = m_run;
+        // ---- the new row, into the operands of the wave that has its slot ----------------------------------
+        if (c == C - 1 && tid == 0) sm_step[n_rows - n_entry] = i;
+#pragma unroll
+        for (int j = 0; c == C - 1 && j < T; ++j) {
+          if ((n_rows & ~(kTile - 1)) != first(j)) continue;
+          const int r = n_rows & (kTile - 1), dw_at = 2 * (r >> 4) + ((r & 3) >> 1);
+          const bool k_lane = r16 == (r & 15);
+          const uint32_t keep = kg != ((r & 15) >> 2) ? 0xffffffffu : (r & 1) ? 0x0000ffffu : 0xffff0000u;
+          // (one of two, one of four: branches, not selections between all)
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            if (s == r >> 4) {
+              DYNTS_OWN_BRANCH;
+#pragma unroll
+              for (int ks = 0; ks < KS; ++ks) {
+                const bf16x8 k_row = *reinterpret_cast<const bf16x8 *>(in + 16 * STRIDE + 64 * ks + 16 * kg);
+                kf[j][s][ks] = k_lane ? k_row : kf[j][s][ks];
+              }
+            }
+          }
+#pragma unroll
+          for (int dw = 0; dw < 4; ++dw) {
+            if (dw == dw_at) {
+              DYNTS_OWN_BRANCH;
+#pragma unroll
+              for (int cb = 0; cb < CB; ++cb) {
+                const uint32_t x = *reinterpret_cast<const uint16_t *>(in + 17 * STRIDE + 2 * (16 * cb + r16));
+                u32x4 v = __builtin_bit_cast(u32x4, vt[j][cb]);
+                v[dw] = (v[dw] & keep) | ((x | (x << 16)) & ~keep);
+                vt[j][cb] = __builtin_bit_cast(i16x8, v);
+              }
+            }
+          }
+          if (lane == r) s_reg[j] = 0.f;
+        }
+      }
+      __syncthreads();  // maxima; this step's inputs have been read
+      if (c == C - 1 && !last) {
+        stage(i + 1, next);
+        fetch(i + 3, next);
+      }
+      const f32x4 ma = *reinterpret_cast<const f32x4 *>(&sm_m[g][0]), mb = *reinterpret_cast<const f32x4 *>(&sm_m[g][4]);
+      mstar[c] = fmaxf(fmaxf(fmaxf(ma[0], ma[1]), fmaxf(ma[2], ma[3])), fmaxf(fmaxf(mb[0], mb[1]), fmaxf(mb[2], mb[3])));
+      if (attended) {
+        const float f = m_run == -INFINITY ? 0.f : fast_exp2(m_run - mstar[c]);
+        if (g < G) {
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb) *reinterpret_cast<f32x4 *>(ored + (wave * 16 + g) * OSTRIDE + 16 * cb + 4 * kg) = oacc[cb] * f;
+        }
+        if (kg == 0) sm_l[g][wave] = l_run * f;
+      }
+      __syncthreads();
+      const f32x4 la = *reinterpret_cast<const f32x4 *>(&sm_l[g][0]), lb = *reinterpret_cast<const f32x4 *>(&sm_l[g][4]);
+      lsum[c] = ((((((la[0] + la[1]) + la[2]) + la[3]) + lb[0]) + lb[1]) + lb[2]) + lb[3];
+#pragma unroll
+      for (int k = 0; k < NE; ++k) {
+        const int idx = tid + k * kResThreads, gg = idx / D;
+        o_part[c][k] = 0.f;
+        if (k == 0 || k * kResThreads < G * D) {
+#pragma unroll
+          for (int w = 0; w < kResWaves; ++w) o_part[c][k] += ored[(w * 16 + gg) * OSTRIDE + idx % D];
+        }
+      }
+    }
+    // the chunks together
+    float m_all = mstar[0], l_all = lsum[0], w0 = 1.f, w1 = 0.f;
+    if constexpr (SPLIT) {
+#pragma clang fp contract(off)
+      m_all = fmaxf(mstar[0], mstar[1]);
+      w0 = fast_exp2(mstar[0] - m_all);
+      w1 = fast_exp2(mstar[1] - m_all);
+      const float l1 = w1 * lsum[1];
+      l_all = fmaf(w0, lsum[0], l1);
+    }
+    if (attended && kg == 0) {
+      stats.m[g] = m_all;
+      stats.l[g] = l_all;
+      stats.inv_l[g] = g < G ? 1.0f / l_all : 0.f;
+      if (SPLIT) {
+        stats.w0[g] = w0;
+        stats.w1[g] = w1;
+      }
+    }
+    wave_lds_fence();
+    // (a buffer that ends behind the group's heads, or is empty: no branch, so that a wait for a step's inputs is no wait for stores)
+    const RowBuffer out = __builtin_amdgcn_make_buffer_rsrc(out_rows + (size_t)i * p.out_stride, 0, __builtin_amdgcn_readfirstlane(attended ? G * D * 4 : 0), 0x00027000);
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+      const int idx = tid + k * kResThreads, gg = idx / D;
+      float o = 0.f;
+      if (k == 0 || k * kResThreads < G * D)
+        o = (SPLIT ? fmaf(o_part[C - 1][k], stats.w1[gg], o_part[0][k] * stats.w0[gg]) : o_part[0][k]) / stats.l[gg];
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o), out, 4u * (uint32_t)idx, 0, 0);
+    }
+    if (attended && p.track && !last) {
+      const f32x4 m = *reinterpret_cast<const f32x4 *>(&stats.m[4 * kg]), inv_l = *reinterpret_cast<const f32x4 *>(&stats.inv_l[4 * kg]);
+      bf16x8 qf[KS];
+      load_q(qf, in);
+#pragma unroll
+      for (int j = 0; j < T; ++j) score_tile(j, qf, m, inv_l, n);
+    }
+    wave_lds_fence();  // the statistics are written again
+  };
+  for (int i = 0; i < most; i += 2) {     // (behind an odd number of steps one in which nothing happens: a branch around it
+    step(std::false_type{}, i, piece_b);  // would have its inputs copied, and waited for, in every round)
+    step(std::false_type{}, i + 1, piece_a);
+  }
+  step(std::true_type{}, most, piece_a);
+
+  // ---- to memory: scores, new rows, positions, what the next deferred update needs, the sequence's words -----------
+#pragma unroll
+  for (int j = 0; j < T; ++j) {
+    const int tok = first(j) + lane;
+    if (lane < kTile && tok < n && p.track && (tok >= n_entry || tok >= M)) Sb[tok] = s_reg[j];
+  }
+  const int n_new = n - n_entry;
+  const int pos0 = sm_hdr[2];
+  for (int i = tid; i < 2 * n_new * PIECES; i += kResThreads) {
+    const bool v = i >= n_new * PIECES;
+    const int at = v ? i - n_new * PIECES : i, r = at / PIECES, piece = 8 * (at % PIECES);
+    const size_t from = (size_t)sm_step[r] * p.kv_stride + (size_t)unit * D + piece;
+    store_u32x4((v ? Vb : Kb) + (size_t)(n_entry + r) * D + piece, load_u32x4((v ? p.v_new : p.k_new) + from));
+  }
+  for (int r = tid; r < n_new; r += kResThreads) {
+    p.pos[(size_t)unit * p.cap + n_entry + r] = pos0 + r;
+    if (!p.track) Sb[n_entry + r] = p.s_new ? p.s_new[(size_t)sm_step[r] * p.Nb * p.Hkv + unit] : 0.f;
+  }
+  const bool owes = p.track && last_attended;
+  if (owes) {
+    for (int i = tid; i < G * PIECES; i += kResThreads)
+      store_u32x4(p.qnext + row0 * D + 8 * (size_t)i, *reinterpret_cast<const u32x4 *>(sm_in + ((p.steps - 1) & 1) * IN + (i / PIECES) * STRIDE + 16 * (i % PIECES)));
+    if (tid < G) {
+      p.mlprev[(row0 + tid) * 2] = stats.m[tid];
+      p.mlprev[(row0 + tid) * 2 + 1] = stats.l[tid];
+    }
+  }
+  if (n_dropped > 0 && h == 0 && tid == 0) atomicOr(p.status, 1);
+  if (tid == 0 && seq_ticket == (uint32_t)p.Hkv - 1) {
+    __hip_atomic_store(p.seq_cnt + (size_t)b * p.cnt_stride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (p.track) p.nprev[b] = owes ? n : 0;
+    if (n_new > 0) {
+      p.seq_len[b] = n;
+      p.next_pos[b] = pos0 + n_new;
+    }
+  }
+}
+
+}  // namespace dynts

@@ -570,6 +570,67 @@ def test_native_loop_equals_single_calls(B, external):
     assert int(a.status.item()) == 0 and int(b_.status.item()) == 0
 
 
+@pytest.mark.parametrize("L,Nb,Hq,Hkv,d,M,budget,window,E,T,external,masked", [
+    (1, 1, 8, 2, 64, 64, 128, 32, 16, 200, False, False),      # one tile a wave
+    (2, 3, 28, 4, 128, 37, 150, 19, 13, 230, False, True),
+    (1, 2, 16, 1, 128, 17, 100, 9, 7, 150, True, True),
+    (1, 1, 12, 1, 64, 255, 1, 0, 1, 9, False, False),          # runs of one step and of none
+    (1, 3, 16, 1, 64, 1, 255, 0, 1, 260, False, True),         # every slot of the first tiles, one more
+    (1, 2, 28, 4, 128, 100, 300, 40, 30, 420, False, True),    # two chunks, the second empty at first
+    (2, 2, 8, 2, 64, 50, 350, 61, 51, 600, False, True),
+    (1, 2, 16, 2, 128, 250, 250, 8, 4, 280, False, False),     # all 512 slots
+    (1, 45, 32, 8, 128, 60, 330, 50, 40, 460, False, False),   # two tiles a wave, one chunk
+    (1, 90, 4, 2, 64, 60, 330, 50, 40, 460, True, True),
+    (1, 3, 8, 2, 64, 20, 30, 10, 200, 250, False, True)])      # two triggers' worth of steps and no more room than that
+def test_loop_on_small_caches_equals_single_calls(B, L, Nb, Hq, Hkv, d, M, budget, window, E, T, external, masked):
+    """Runs of steps that the loop makes in one launch, in two calls of it (an update is owed in between): outputs, cache,
+    scores before and after the owed update, lengths and status word of the same calls issued one by one, bit for bit."""
+    rng = np.random.default_rng(T + d)
+    dev = torch.device("cuda:0")
+    cap = M + budget + window + E
+    q = _bf16(rng, T, L, Nb, Hq, d, scale=1.5).to(dev)
+    k, v = _bf16(rng, T, L, Nb, Hkv, d).to(dev), _bf16(rng, T, L, Nb, Hkv, d).to(dev)
+    s = torch.from_numpy(rng.integers(0, 6, (T, Nb, Hkv)).astype(np.float32)).to(dev) if external else None
+    act = torch.from_numpy((rng.random((T, Nb)) < 0.9).astype(np.uint8)).to(dev) if masked else None
+    flags = torch.zeros(T, dtype=torch.uint8)
+    flags[budget + window + E - 1::E] = 1
+    K0, V0 = _bf16(rng, Nb, Hkv, M, d).to(dev), _bf16(rng, Nb, Hkv, M, d).to(dev)
+    m = torch.from_numpy(rng.integers(0 if masked else M, M + 1, Nb).astype(np.int32)).to(dev)
+    a, b = (B.Cache(L, Nb, Hq, Hkv, d, cap, budget, window, E, external_scores=external) for _ in range(2))
+    for c in (a, b):
+        for l in range(L):
+            B.dynts_prefill(c.ctx, l, K0, V0, m)
+    outs_a = torch.zeros((T, L, Nb, Hq, d), dtype=torch.float32, device=dev)
+    outs_b = torch.zeros_like(outs_a)
+    cut = T // 3 | 1
+    for lo, hi in ((0, cut), (cut, T)):
+        B.dynts_decode_loop(a.ctx, hi - lo, q[lo:hi], k[lo:hi], v[lo:hi], outs_a[lo:hi], a.keep_idx, a.new_len, s_new=s[lo:hi] if external else None,
+                            active=act[lo:hi] if masked else None, evict_steps=flags[lo:hi].clone(), out_step_stride=outs_a[0].numel())
+    for t in range(T):
+        for l in range(L):
+            if flags[t]:
+                B.dynts_hint_trigger(b.ctx, l)
+            B.dynts_decode_step(b.ctx, l, q[t, l], k[t, l], v[t, l], outs_b[t, l], s_new=s[t] if external else None, active=act[t] if masked else None)
+            if flags[t]:
+                B.dynts_select_evict(b.ctx, l, b.keep_idx, b.new_len, budget)
+                B.dynts_compact(b.ctx, l, b.keep_idx, b.new_len)
+
+    def same():
+        assert torch.equal(outs_a, outs_b)
+        assert torch.equal(a.seq_len, b.seq_len) and torch.equal(a.next_pos, b.next_pos) and torch.equal(a.status, b.status)
+        for l in range(L):
+            for bb in range(Nb):
+                n = int(a.seq_len[l, bb])
+                for x, y in ((a.K, b.K), (a.V, b.V), (a.S, b.S), (a.pos, b.pos)):
+                    assert torch.equal(x[l, bb, :, :n], y[l, bb, :, :n])
+
+    same()
+    for l in range(L):
+        B.dynts_update_scores(a.ctx, l)
+        B.dynts_update_scores(b.ctx, l)
+    same()
+
+
 @pytest.mark.parametrize("d,Hq,Hkv", [(64, 8, 2), (128, 14, 2), (128, 3, 3)])
 def test_attend_then_update_by_any_route(B, d, Hq, Hkv):
     """The unfused attend call keeps its logits for the update behind it.  Two layers share the room for them: whoever
