@@ -36,6 +36,9 @@ struct Plan {
   int G = 0, waves = 0, chunk = 0, nsplit = 0;
   size_t off_part_o = 0, off_part_ml = 0, off_unit_cnt = 0, off_seq_cnt = 0, off_qprev = 0, off_mlprev = 0, off_nprev = 0, off_spill = 0;
   int cap_pad = 0;
+  // runs of steps (resident_kernel): a cache of several chunks, each of one tile a wave; steps of a run whose partials there is room for, or 0
+  int run_steps = 0;
+  size_t off_run_o = 0, off_run_ml = 0, off_run_stats = 0, off_run_n = 0, off_run_rec = 0;
   size_t bytes = 0;
 };
 
@@ -88,6 +91,18 @@ Plan make_plan(const dynts_config &c, int target_wgs, int waves) {
   p.cap_pad = (c.capacity + dynts::kTile - 1) / dynts::kTile * dynts::kTile;
   p.off_spill = off;
   if (c.score_mode == DYNTS_SCORE_ACCUMULATE) off = align_up(off + (size_t)units * p.G * p.cap_pad * sizeof(float));
+  // Room for the partials of a run's steps: of as many as lie between two triggers, but 16 to 64, and 64 MB of them at most.
+  if (target_wgs == 0 && waves == 0 && p.nsplit > 1 && p.nsplit == quanta) {
+    const long long fit = (64ll << 20) / (long long)(rows * (c.head_dim + 2) * sizeof(float));
+    const int between = c.evict_every < 16 ? 16 : c.evict_every < dynts::kPartSteps ? c.evict_every : dynts::kPartSteps;
+    p.run_steps = (int)(fit < between ? fit : between);
+    const size_t R = (size_t)p.run_steps;
+    p.off_run_o = off;     off = align_up(off + R * rows * c.head_dim * sizeof(float));
+    p.off_run_ml = off;    off = align_up(off + R * rows * 2 * sizeof(float));
+    p.off_run_stats = off; off = align_up(off + R * (size_t)units * 32 * sizeof(float));
+    p.off_run_n = off;     off = align_up(off + R * c.batch * sizeof(int32_t));
+    p.off_run_rec = off;   off = align_up(off + (size_t)c.batch * 4 * sizeof(int32_t));
+  }
   p.bytes = off;
   return p;
 }
@@ -494,21 +509,38 @@ int fused_step(dynts_ctx *ctx, int layer, const uint16_t *q, const uint16_t *k_n
 }
 
 // ---- consecutive steps in one launch ----------------------------------------------------------------
-// Whether a run of steps of a layer is one launch that keeps the cache on the chip (resident_kernel): dense caches of as many slots as its
-// waves hold, which gains everywhere (us a step, a launch each / so: 1 unit of 120 slots of 16 heads 6.1 / 2.9, 1024 units of 120 slots
-// 11.1 / 7.1, of 510 47.2 / 14.9; the least: 1 unit of 400 slots of 16 heads, in two chunks, 8.7 / 5.2).  More slots do not fit the
-// registers of eight waves at head_dim 128.  Not where every attend launch is to be timed or has a shape of the caller's, and not under
-// capture: replays take turns between the two places of the saved query step by step.
-bool keeps_resident(const dynts_ctx *ctx, hipStream_t st) {
-  return !ctx->paged && ctx->cfg.capacity <= dynts::kResTiles * dynts::kResSlots && !ctx->shaped && !ctx->ev_start &&
-         ctx->ev_list_next >= ctx->ev_list_start.size() && !capturing(st);
+// How many consecutive steps of a layer are made by one launch that keeps the cache on the chip (resident_kernel), 0: a launch each.
+// Dense caches of as many slots as its waves hold, and those of several chunks that are one tile a wave each (about one workgroup a
+// compute unit then), which leave partials for two kernels that merge them and make the score updates.  Runs of three steps or more gain everywhere;
+// us a step, a launch each / so:
+//   one chunk, runs of 32: 1 unit of 120 slots of 16 heads 6.1 / 2.9, 1024 units of 120 slots 11.1 / 7.1, of 510 47.2 / 14.9
+//   several: 8 units of 700 slots 8.4 / 3.2, of 4544 11.7 / 3.3, of 8000 13.4 / 3.2; 64 of 1000 9.6 / 3.6; one of 8000 of 16 heads 22.9 / 4.0;
+//     head_dim 64, 2 units of 400 6.7 / 2.3, 128 of 510 7.7 / 2.9, 32 of 2000 8.4 / 2.6
+//   by the run's length, 2 / 3 / 4 / 8 / 16: 8 units of 1000 9.2 / 10.5, 8.9 / 7.7, 8.9 / 6.6, 8.7 / 4.7, 8.6 / 3.7; 512 units of 510, head_dim 64,
+//     15.3 / 15.5, 15.4 / 11.6, 15.0 / 10.3, 14.7 / 7.8, 14.6 / 6.5
+// Caches that the chip's registers do not hold are read again for every step, one launch each.
+// Not where every attend launch is to be timed or has a shape of the caller's, and not under capture: replays
+// take turns between the two places of the saved query step by step.
+constexpr int kLeastRun = 3;
+int resident_run(const dynts_ctx *ctx, hipStream_t st) {
+  const Plan &pl = ctx->plan;
+  const bool whole = pl.nsplit == 1 && ctx->cfg.capacity <= dynts::kResTiles * dynts::kResSlots;
+  if (ctx->paged || ctx->shaped || !(whole || pl.run_steps >= kLeastRun)) return 0;
+  if (ctx->ev_start || ctx->ev_list_next < ctx->ev_list_start.size() || capturing(st)) return 0;
+  return whole ? dynts::kResSteps : pl.run_steps;
 }
 
 template <int D>
-void launch_resident(const dynts::ResidentParams &p, int chunks, dim3 grid, dim3 block, hipStream_t st) {
-  if (p.cap <= dynts::kResSlots) hipLaunchKernelGGL((dynts::resident_kernel<D, 1, false>), grid, block, 0, st, p);
-  else if (chunks == 1) hipLaunchKernelGGL((dynts::resident_kernel<D, 2, false>), grid, block, 0, st, p);
-  else hipLaunchKernelGGL((dynts::resident_kernel<D, 2, true>), grid, block, 0, st, p);
+void launch_resident(const dynts::ResidentParams &p, hipStream_t st) {
+  const dim3 block(dynts::kResThreads);
+  if (p.chunks == 1) {
+    if (p.cap <= dynts::kResSlots) hipLaunchKernelGGL((dynts::resident_kernel<D, 1, false>), dim3(p.units), block, 0, st, p);
+    else hipLaunchKernelGGL((dynts::resident_kernel<D, 2, false>), dim3(p.units), block, 0, st, p);
+    return;
+  }
+  hipLaunchKernelGGL((dynts::resident_kernel<D, 1, true>), dim3(p.units * p.chunks), block, 0, st, p);
+  hipLaunchKernelGGL(dynts::merge_run_kernel<D>, dim3(p.units, p.steps), block, 0, st, p);
+  if (p.track) hipLaunchKernelGGL(dynts::run_scores_kernel<D>, dim3(p.units * p.chunks), block, 0, st, p);
 }
 
 // Steps [0, steps) of one layer, inputs of step 0 given.  evict: a trigger follows the last, which keeps its logits.
@@ -543,9 +575,17 @@ int resident_steps(dynts_ctx *ctx, int layer, int steps, bool evict, const uint1
   p.spill = keep ? reinterpret_cast<float *>(ctx->ws + ctx->plan.off_spill) : nullptr;
   p.cap_pad = ctx->plan.cap_pad;
   p.scale_log2 = ctx->scale_log2;
-  const dim3 grid((unsigned)(c.batch * c.n_kv_heads)), block(dynts::kResThreads);
-  if (c.head_dim == 128) launch_resident<128>(p, ctx->plan.nsplit, grid, block, st);
-  else launch_resident<64>(p, ctx->plan.nsplit, grid, block, st);
+  const Plan &pl = ctx->plan;
+  p.units = c.batch * c.n_kv_heads;
+  p.chunks = pl.nsplit;
+  p.part_o = reinterpret_cast<float *>(ctx->ws + pl.off_run_o);
+  p.part_ml = reinterpret_cast<float *>(ctx->ws + pl.off_run_ml);
+  p.stats = reinterpret_cast<float *>(ctx->ws + pl.off_run_stats);
+  p.n_of = reinterpret_cast<int32_t *>(ctx->ws + pl.off_run_n);
+  p.rec = reinterpret_cast<int32_t *>(ctx->ws + pl.off_run_rec);
+  p.wide = wide_merge(c.head_dim, 8, pl.G, pl.nsplit, (long long)(p.units + 7) / 8 * 8 * pl.nsplit) ? 1 : 0;
+  if (c.head_dim == 128) launch_resident<128>(p, st);
+  else launch_resident<64>(p, st);
   rc = launch_status();
   if (rc != DYNTS_OK) return rc;
   if (track) ctx->qslot[layer] ^= 1;
@@ -1294,9 +1334,9 @@ int dynts_decode_loop(dynts_ctx *ctx, int32_t n_steps, const uint16_t *q, const 
     const uint8_t *act = active ? active + (size_t)i * c.batch : nullptr;
     const float *sn = ext ? s_new + (size_t)i * c.batch * c.n_kv_heads : nullptr;
     int run = 1;  // steps up to the next trigger's, where they can be one launch
-    if (keeps_resident(ctx, st))
-      while (i + run < n_steps && run < dynts::kResSteps && !(evict_steps && evict_steps[i + run - 1])) ++run;
-    if (run > 1) {
+    const int most = resident_run(ctx, st);
+    while (i + run < n_steps && run < most && !(evict_steps && evict_steps[i + run - 1])) ++run;
+    if (run >= kLeastRun) {
       const bool evict = evict_steps && evict_steps[i + run - 1];
       for (int l = 0; l < c.n_layers; ++l) {
         const size_t sl = (size_t)i * c.n_layers + l;

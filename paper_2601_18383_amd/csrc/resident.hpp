@@ -1,21 +1,23 @@
-// Consecutive decode steps of one layer on a small cache, in one launch (dynts_decode_loop between two triggers).
+// Consecutive decode steps of one layer on a cache that the chip holds, in one launch (dynts_decode_loop between two triggers).
 //
-// A step on a cache of a few hundred slots takes 5 us a launch whatever it computes: the launch itself, the sequence's words,
-// K, V behind them, the combination of the waves, each a trip to memory that the next one waits for.  So here the cache stays on the chip: one
-// workgroup of eight waves per (sequence, KV head), and a wave keeps T tiles of 32 slots as MFMA operands in its registers through
-// all steps of the launch.  A step then reads its query and its new row, which are asked for two steps ahead, and writes its
-// output; a new row is put into the registers of the wave whose tile its slot lies in, and rows, scores and positions go to
-// memory once, at the end.
+// A step on a small cache takes 5 to 13 us a launch whatever it computes: the launch itself, the sequence's words, K, V behind them, the
+// combination of the waves, the hand-over between workgroups, each a trip to memory that the next one waits for.  So here the
+// cache stays on the chip: one workgroup of eight waves per (sequence, KV head), and a wave keeps T tiles of 32 slots as MFMA operands in its registers
+// through all steps of the launch.  A step then reads its query and its new row, which are asked for two steps ahead, and writes
+// its output; a new row is put into the registers of the wave whose tile its slot lies in, and rows, scores and positions go to memory
+// once, at the end.
+//
+// Caches of several chunks of 256 slots (PART) have a workgroup per chunk, which never waits for another one: it leaves its partials of every step,
+// merge_run_kernel merges those of all steps at once, and run_scores_kernel makes the updates, a wave a tile of K.
 //
 // The arithmetic is attend_kernel's to the last bit, so that it makes no difference which of the two made a step: which wave takes which
-// tile, the new token as the first wave's initial state, tiles of a wave one after the other, SPLIT: two chunks of 256 slots
-// combined by themselves and then merged.  So are the things it leaves: the last step's update is owed (query, statistics, slots), or its
-// logits are kept for the trigger that follows.
+// tile, the new token as the first wave's initial state, tiles of a wave one after the other, chunks merged in the same groups.  So are the
+// things it leaves: the last step's update is owed (query, statistics, slots), or its logits are kept for the trigger that follows.
 //
-// What bounds it now: a chain of about 400 dependent instructions a wave and step -- logits, maximum, weights, products, two barriers
-// around the waves' combination, division, scores.  us a step, a launch each / so, runs of 32 steps: head_dim 64, 4 heads a group,
-// caches of 250 slots, 8 units 5.53 / 1.97, 256 5.91 / 2.10, 1024 15.84 / 7.90; of 510 slots 8 units 7.09 / 3.31 (two chunks), 256 9.05 / 2.84; head_dim 128, 7
-// heads, of 120 slots, 4 units 6.15 / 2.64, 1024 23.7 / 10.7; of 510, 4 units 8.75 / 4.73, 256 14.8 / 3.98, 1024 48.7 / 16.0.
+// What bounds it now: a chain of some 400 dependent instructions a wave and step -- logits, maximum, weights, products, two barriers
+// around the waves' combination, division, scores.  us a step, a launch each / so, runs of 32 steps: head_dim 64, 4 heads a group, caches of
+// 250 slots, 8 units 5.53 / 1.97, 256 5.91 / 2.10, 1024 15.84 / 7.90; head_dim 128, 7 heads, of 120 slots, 4 units 6.15 / 2.64, 1024 23.7 / 10.7; of
+// 510, 4 units 8.75 / 3.2 (two chunks), 256 14.8 / 3.9, 1024 48.7 / 16.0; 4 heads, 8 units of 4544 (18 chunks) 11.7 / 3.3, of which 0.3 merge and 0.6 scores.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -27,7 +29,8 @@ namespace dynts {
 constexpr int kResWaves = 8, kResThreads = 64 * kResWaves;
 constexpr int kResSlots = kResWaves * kTile;  // slots that one tile a wave holds
 constexpr int kResTiles = 2;                  // tiles a wave keeps at most
-constexpr int kResSteps = 1024;               // steps of a launch at most
+constexpr int kResSteps = 1024;               // steps of a launch at most,
+constexpr int kPartSteps = 64;                // and of one that leaves partials
 
 struct ResidentParams {
   uint16_t *K, *V;          // layer base, [Nb][Hkv][cap][D]
@@ -58,6 +61,13 @@ struct ResidentParams {
   float *spill;             // the last step's logits are kept (see AttendParams), or null
   int cap_pad;
   float scale_log2;
+  // caches of several chunks: a launch of their steps leaves
+  int units, chunks;        // Nb * Hkv; of 256 slots
+  float *part_o, *part_ml;  // [steps][units][chunks][G][D], [..][G][2]: the chunks' partials (see attend_kernel)
+  float *stats;             // [steps][units][16][2]: (max, sum) of the steps' softmax (merge_run_kernel)
+  int32_t *n_of;            // [steps][Nb]: slots that the step attended in the cache, -1: the sequence was not attended
+  int32_t *rec;             // [Nb][4]: slots before and behind the run, next position, whether the last step attended
+  int wide;                 // merges of 32 and of 8 chunks at a time (wide_merge in dynts.hip)
 };
 
 // A lane's x and that of the lane 16 (32) further on in the pair of rows (halves) of the wave: no trip through LDS.
@@ -84,10 +94,9 @@ __device__ __forceinline__ float sum_over_rows(float x) {
   return p.low + p.high;
 }
 
-template <int D, int T, bool SPLIT>
+template <int D, int T, bool PART>
 __global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const ResidentParams p) {
-  static_assert(!SPLIT || T == 2, "a chunk is a tile a wave");
-  constexpr int C = SPLIT ? 2 : 1;  // chunks
+  static_assert(!PART || T == 1, "a chunk is a tile a wave");
   constexpr int KS = D / 32, CB = D / 16, PIECES = D / 8;
   constexpr int VROWS = 64 / PIECES, VIT = kTile / VROWS;  // rows of one wave-wide 16-byte load
   constexpr int STRIDE = 2 * D + 32;                       // bytes per staged row (see attend_kernel)
@@ -98,7 +107,7 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const Resident
   constexpr int IN = 18 * STRIDE;  // a step's query rows, its K and its V row
   __shared__ __align__(16) unsigned char sm_in[2 * IN];  // of even and of odd steps
   __shared__ __align__(16) float sm_m[16][kResWaves], sm_l[16][kResWaves];
-  struct Stats { float m[16], l[16], inv_l[16], w0[16], w1[16]; };  // of a step's softmax: maximum, sum, weights of the chunks
+  struct Stats { float m[16], l[16], inv_l[16]; };            // of a step's softmax: maximum, sum, its inverse
   __shared__ __align__(16) Stats sm_stats[kResWaves];         // (each wave its own: no barrier)
   __shared__ int32_t sm_hdr[5];
   __shared__ int16_t sm_step[kResSlots * T];                  // the step that appended each new row
@@ -107,7 +116,8 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const Resident
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kg = lane >> 4, g = r16;
   // (a division leaves uniform values in vector registers, and every address formed from them)
-  const int unit = blockIdx.x, b = __builtin_amdgcn_readfirstlane(unit / p.Hkv), h = unit - b * p.Hkv, G = p.G;
+  const int unit = PART ? __builtin_amdgcn_readfirstlane(blockIdx.x / p.chunks) : blockIdx.x, chunk = PART ? blockIdx.x - unit * p.chunks : 0;
+  const int b = __builtin_amdgcn_readfirstlane(unit / p.Hkv), h = unit - b * p.Hkv, G = p.G;
   uint16_t *Kb = p.K + (size_t)unit * p.cap * D, *Vb = p.V + (size_t)unit * p.cap * D;
   float *Sb = p.S + (size_t)unit * p.cap;
   const size_t row0 = (size_t)b * p.Hq + (size_t)h * G;  // the group's first query head
@@ -140,13 +150,14 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const Resident
     *reinterpret_cast<u32x4 *>(sm_in + (i & 1) * IN + (G + (i >> 1) / PIECES) * STRIDE + 16 * ((i >> 1) % PIECES)) = u32x4{0u, 0u, 0u, 0u};
   __syncthreads();
   uint32_t seq_ticket = 0xffffffffu;
-  if (tid == 0) seq_ticket = draw_ticket(p.seq_cnt + (size_t)b * p.cnt_stride);
+  if (!PART && tid == 0) seq_ticket = draw_ticket(p.seq_cnt + (size_t)b * p.cnt_stride);
   int n = __builtin_amdgcn_readfirstlane(sm_hdr[0]);
   n = n < 0 ? 0 : (n > p.cap ? p.cap : n);
   const int n_entry = n, M = __builtin_amdgcn_readfirstlane(sm_hdr[3]);
+  if (PART && chunk > 0 && kResSlots * chunk > n + p.steps) return;  // no step gets so far
 
-  // Tile j of this wave starts at slot first(j).  (Without chunks a wave's second tile lies where attend_kernel has it, counted from the end.)
-  auto first = [&](int j) { return kTile * (j == 0 ? wave : SPLIT ? kResWaves + wave : 2 * kResWaves - 1 - wave); };
+  // Tile j of this wave starts at slot first(j).  (A wave's second tile lies where attend_kernel has it, counted from the end.)
+  auto first = [&](int j) { return kResSlots * chunk + kTile * (j == 0 ? wave : 2 * kResWaves - 1 - wave); };
 
   // ---- the cache, as operands (see attend_kernel); rows past the sequence are zeros ---------------------------------
   bf16x8 kf[T][2][KS];
@@ -262,192 +273,181 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const Resident
     n_dropped += act && !attended ? 1 : 0;
     if (last) last_attended = attended;
     n = attended ? n_rows + 1 : n_rows;
-    float mstar[C], lsum[C], o_part[C][NE];  // of the chunks
+    const bool here = attended && (!PART || chunk == 0 || kResSlots * chunk < n_rows);  // (the new token is the first chunk's)
+    if (PART && h == 0 && chunk == 0 && tid == 0) p.n_of[(size_t)i * p.Nb + b] = attended ? n_rows : -1;
+    float m_run = -INFINITY, l_run = 0.f;
+    f32x4 oacc[CB];
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      float m_run = -INFINITY, l_run = 0.f;
-      f32x4 oacc[CB];
+    for (int cb = 0; cb < CB; ++cb) oacc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (here) {
+      bf16x8 qf[KS];
+      load_q(qf, in);
+      if (chunk == 0 && wave == 0) {  // the new token (see attend_kernel)
+        f32x4 a0 = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb) oacc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (attended) {
-        bf16x8 qf[KS];
-        load_q(qf, in);
-        if (c == 0 && wave == 0) {  // the new token (see attend_kernel)
-          f32x4 a0 = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int ks = 0; ks < KS; ++ks) {
-            const bf16x8 kn = *reinterpret_cast<const bf16x8 *>(in + 16 * STRIDE + 64 * ks + 16 * kg);
-            a0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kn, qf[ks], a0, 0, 0, 0);
-          }
-          m_run = a0[0] * p.scale_log2;
-          l_run = kg == 0 ? 1.f : 0.f;
-          if (last && p.spill && kg == 0 && g < G) p.spill[spill_at((size_t)unit, p.cap_pad, G, g, n_rows)] = m_run;
-#pragma unroll
-          for (int cb = 0; cb < CB; ++cb) {
-            typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-            const bf16x4 v4 = *reinterpret_cast<const bf16x4 *>(in + 17 * STRIDE + 32 * cb + 8 * kg);
-            oacc[cb] = f32x4{(float)v4[0], (float)v4[1], (float)v4[2], (float)v4[3]};
-          }
+        for (int ks = 0; ks < KS; ++ks) {
+          const bf16x8 kn = *reinterpret_cast<const bf16x8 *>(in + 16 * STRIDE + 64 * ks + 16 * kg);
+          a0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kn, qf[ks], a0, 0, 0, 0);
         }
-        // ---- this wave's slots -------------------------------------------------------------------------------
+        m_run = a0[0] * p.scale_log2;
+        l_run = kg == 0 ? 1.f : 0.f;
+        if (last && p.spill && kg == 0 && g < G) p.spill[spill_at((size_t)unit, p.cap_pad, G, g, n_rows)] = m_run;
 #pragma unroll
-        for (int j = 0; j < T; ++j) {
-          const int t = first(j);
-          if ((SPLIT && j != c) || t >= n_rows) continue;
-          f32x4 acc[2];
+        for (int cb = 0; cb < CB; ++cb) {
+          typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+          const bf16x4 v4 = *reinterpret_cast<const bf16x4 *>(in + 17 * STRIDE + 32 * cb + 8 * kg);
+          oacc[cb] = f32x4{(float)v4[0], (float)v4[1], (float)v4[2], (float)v4[3]};
+        }
+      }
+      // ---- this wave's slots -------------------------------------------------------------------------------
 #pragma unroll
-          for (int s = 0; s < 2; ++s) {
-            acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < T; ++j) {
+        const int t = first(j);
+        if (t >= n_rows) continue;
+        f32x4 acc[2];
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) acc[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[j][s][ks], qf[ks], acc[s], 0, 0, 0);
-          }
-          float x[8];
+        for (int s = 0; s < 2; ++s) {
+          acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int k = 0; k < 8; ++k) x[k] = acc[k >> 2][k & 3] * p.scale_log2;
-          if (t + kTile > n_rows) {
-            DYNTS_OWN_BRANCH;
+          for (int ks = 0; ks < KS; ++ks) acc[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[j][s][ks], qf[ks], acc[s], 0, 0, 0);
+        }
+        float x[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) x[k] = t + 16 * (k >> 2) + 4 * kg + (k & 3) < n_rows ? x[k] : -INFINITY;
-          }
-          float mx = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
-          if (last && p.spill && g < G) {
+        for (int k = 0; k < 8; ++k) x[k] = acc[k >> 2][k & 3] * p.scale_log2;
+        if (t + kTile > n_rows) {
+          DYNTS_OWN_BRANCH;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-              const int tok = t + 16 * (k >> 2) + 4 * kg + (k & 3);
-              if (tok < n_rows) p.spill[spill_at((size_t)unit, p.cap_pad, G, g, tok)] = x[k];
-            }
-          }
-          mx = max_over_rows(mx);
-          const float m_new = fmaxf(m_run, mx);
-          const float corr = fast_exp2(m_run - m_new);
-          if (SPLIT ? c == 0 && wave == 0 : j > 0 || wave == 0) {  // (else there is nothing to correct)
-            DYNTS_OWN_BRANCH;
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb) oacc[cb] *= corr;
-          }
-          m_run = m_new;
-          bf16x8 ph, pl;
-          float psum = 0.f;
+          for (int k = 0; k < 8; ++k) x[k] = t + 16 * (k >> 2) + 4 * kg + (k & 3) < n_rows ? x[k] : -INFINITY;
+        }
+        float mx = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
+        if (last && p.spill && g < G) {
 #pragma unroll
           for (int k = 0; k < 8; ++k) {
-            const float pe = fast_exp2(x[k] - m_new);
-            psum += pe;
-            const __bf16 hi = (__bf16)pe;
-            ph[k] = hi;
-            pl[k] = (__bf16)(pe - (float)hi);
-          }
-          l_run = l_run * corr + psum;
-#pragma unroll
-          for (int cb = 0; cb < CB; ++cb) {
-            const bf16x8 v = __builtin_bit_cast(bf16x8, vt[j][cb]);
-            oacc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, ph, oacc[cb], 0, 0, 0);
-            oacc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, pl, oacc[cb], 0, 0, 0);
+            const int tok = t + 16 * (k >> 2) + 4 * kg + (k & 3);
+            if (tok < n_rows) p.spill[spill_at((size_t)unit, p.cap_pad, G, g, tok)] = x[k];
           }
         }
-        l_run = sum_over_rows(l_run);
-        if (kg == 0) sm_m[g][wave] = m_run;
-        // ---- the new row, into the operands of the wave that has its slot ----------------------------------
-        if (c == C - 1 && tid == 0) sm_step[n_rows - n_entry] = i;
+        mx = max_over_rows(mx);
+        const float m_new = fmaxf(m_run, mx);
+        const float corr = fast_exp2(m_run - m_new);
+        if (j > 0 || (chunk == 0 && wave == 0)) {  // (else there is nothing to correct)
+          DYNTS_OWN_BRANCH;
 #pragma unroll
-        for (int j = 0; c == C - 1 && j < T; ++j) {
-          if ((n_rows & ~(kTile - 1)) != first(j)) continue;
-          const int r = n_rows & (kTile - 1), dw_at = 2 * (r >> 4) + ((r & 3) >> 1);
-          const bool k_lane = r16 == (r & 15);
-          const uint32_t keep = kg != ((r & 15) >> 2) ? 0xffffffffu : (r & 1) ? 0x0000ffffu : 0xffff0000u;
-          // (one of two, one of four: branches, not selections between all)
+          for (int cb = 0; cb < CB; ++cb) oacc[cb] *= corr;
+        }
+        m_run = m_new;
+        bf16x8 ph, pl;
+        float psum = 0.f;
 #pragma unroll
-          for (int s = 0; s < 2; ++s) {
-            if (s == r >> 4) {
-              DYNTS_OWN_BRANCH;
+        for (int k = 0; k < 8; ++k) {
+          const float pe = fast_exp2(x[k] - m_new);
+          psum += pe;
+          const __bf16 hi = (__bf16)pe;
+          ph[k] = hi;
+          pl[k] = (__bf16)(pe - (float)hi);
+        }
+        l_run = l_run * corr + psum;
 #pragma unroll
-              for (int ks = 0; ks < KS; ++ks) {
-                const bf16x8 k_row = *reinterpret_cast<const bf16x8 *>(in + 16 * STRIDE + 64 * ks + 16 * kg);
-                kf[j][s][ks] = k_lane ? k_row : kf[j][s][ks];
-              }
+        for (int cb = 0; cb < CB; ++cb) {
+          const bf16x8 v = __builtin_bit_cast(bf16x8, vt[j][cb]);
+          oacc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, ph, oacc[cb], 0, 0, 0);
+          oacc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, pl, oacc[cb], 0, 0, 0);
+        }
+      }
+      l_run = sum_over_rows(l_run);
+      if (kg == 0) sm_m[g][wave] = m_run;
+    }
+    if (attended) {
+      // ---- the new row, into the operands of the wave that has its slot ----------------------------------
+      if (tid == 0) sm_step[n_rows - n_entry] = i;
+#pragma unroll
+      for (int j = 0; j < T; ++j) {
+        if ((n_rows & ~(kTile - 1)) != first(j)) continue;
+        const int r = n_rows & (kTile - 1), dw_at = 2 * (r >> 4) + ((r & 3) >> 1);
+        const bool k_lane = r16 == (r & 15);
+        const uint32_t keep = kg != ((r & 15) >> 2) ? 0xffffffffu : (r & 1) ? 0x0000ffffu : 0xffff0000u;
+        // (one of two, one of four: branches, not selections between all)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          if (s == r >> 4) {
+            DYNTS_OWN_BRANCH;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+              const bf16x8 k_row = *reinterpret_cast<const bf16x8 *>(in + 16 * STRIDE + 64 * ks + 16 * kg);
+              kf[j][s][ks] = k_lane ? k_row : kf[j][s][ks];
             }
           }
+        }
 #pragma unroll
-          for (int dw = 0; dw < 4; ++dw) {
-            if (dw == dw_at) {
-              DYNTS_OWN_BRANCH;
+        for (int dw = 0; dw < 4; ++dw) {
+          if (dw == dw_at) {
+            DYNTS_OWN_BRANCH;
 #pragma unroll
-              for (int cb = 0; cb < CB; ++cb) {
-                const uint32_t x = *reinterpret_cast<const uint16_t *>(in + 17 * STRIDE + 2 * (16 * cb + r16));
-                u32x4 v = __builtin_bit_cast(u32x4, vt[j][cb]);
-                v[dw] = (v[dw] & keep) | ((x | (x << 16)) & ~keep);
-                vt[j][cb] = __builtin_bit_cast(i16x8, v);
-              }
+            for (int cb = 0; cb < CB; ++cb) {
+              const uint32_t x = *reinterpret_cast<const uint16_t *>(in + 17 * STRIDE + 2 * (16 * cb + r16));
+              u32x4 v = __builtin_bit_cast(u32x4, vt[j][cb]);
+              v[dw] = (v[dw] & keep) | ((x | (x << 16)) & ~keep);
+              vt[j][cb] = __builtin_bit_cast(i16x8, v);
             }
           }
-          if (lane == r) s_reg[j] = 0.f;
         }
-      }
-      __syncthreads();  // maxima; this step's inputs have been read
-      if (c == C - 1 && !last) {
-        stage(i + 1, next);
-        fetch(i + 3, next);
-      }
-      const f32x4 ma = *reinterpret_cast<const f32x4 *>(&sm_m[g][0]), mb = *reinterpret_cast<const f32x4 *>(&sm_m[g][4]);
-      mstar[c] = fmaxf(fmaxf(fmaxf(ma[0], ma[1]), fmaxf(ma[2], ma[3])), fmaxf(fmaxf(mb[0], mb[1]), fmaxf(mb[2], mb[3])));
-      if (attended) {
-        const float f = m_run == -INFINITY ? 0.f : fast_exp2(m_run - mstar[c]);
-        if (g < G) {
-#pragma unroll
-          for (int cb = 0; cb < CB; ++cb) *reinterpret_cast<f32x4 *>(ored + (wave * 16 + g) * OSTRIDE + 16 * cb + 4 * kg) = oacc[cb] * f;
-        }
-        if (kg == 0) sm_l[g][wave] = l_run * f;
-      }
-      __syncthreads();
-      const f32x4 la = *reinterpret_cast<const f32x4 *>(&sm_l[g][0]), lb = *reinterpret_cast<const f32x4 *>(&sm_l[g][4]);
-      lsum[c] = ((((((la[0] + la[1]) + la[2]) + la[3]) + lb[0]) + lb[1]) + lb[2]) + lb[3];
-#pragma unroll
-      for (int k = 0; k < NE; ++k) {
-        const int idx = tid + k * kResThreads, gg = idx / D;
-        o_part[c][k] = 0.f;
-        if (k == 0 || k * kResThreads < G * D) {
-#pragma unroll
-          for (int w = 0; w < kResWaves; ++w) o_part[c][k] += ored[(w * 16 + gg) * OSTRIDE + idx % D];
-        }
+        if (lane == r) s_reg[j] = 0.f;
       }
     }
-    // the chunks together
-    float m_all = mstar[0], l_all = lsum[0], w0 = 1.f, w1 = 0.f;
-    if constexpr (SPLIT) {
-#pragma clang fp contract(off)
-      m_all = fmaxf(mstar[0], mstar[1]);
-      w0 = fast_exp2(mstar[0] - m_all);
-      w1 = fast_exp2(mstar[1] - m_all);
-      const float l1 = w1 * lsum[1];
-      l_all = fmaf(w0, lsum[0], l1);
+    __syncthreads();  // maxima; this step's inputs have been read
+    if (!last) {
+      stage(i + 1, next);
+      fetch(i + 3, next);
     }
-    if (attended && kg == 0) {
-      stats.m[g] = m_all;
-      stats.l[g] = l_all;
-      stats.inv_l[g] = g < G ? 1.0f / l_all : 0.f;
-      if (SPLIT) {
-        stats.w0[g] = w0;
-        stats.w1[g] = w1;
+    const f32x4 ma = *reinterpret_cast<const f32x4 *>(&sm_m[g][0]), mb = *reinterpret_cast<const f32x4 *>(&sm_m[g][4]);
+    const float mstar = fmaxf(fmaxf(fmaxf(ma[0], ma[1]), fmaxf(ma[2], ma[3])), fmaxf(fmaxf(mb[0], mb[1]), fmaxf(mb[2], mb[3])));
+    if (here) {
+      const float f = m_run == -INFINITY ? 0.f : fast_exp2(m_run - mstar);
+      if (g < G) {
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) *reinterpret_cast<f32x4 *>(ored + (wave * 16 + g) * OSTRIDE + 16 * cb + 4 * kg) = oacc[cb] * f;
       }
+      if (kg == 0) sm_l[g][wave] = l_run * f;
     }
-    wave_lds_fence();
+    __syncthreads();
+    const f32x4 la = *reinterpret_cast<const f32x4 *>(&sm_l[g][0]), lb = *reinterpret_cast<const f32x4 *>(&sm_l[g][4]);
+    const float lsum = ((((((la[0] + la[1]) + la[2]) + la[3]) + lb[0]) + lb[1]) + lb[2]) + lb[3];
+    if (!PART) {
+      if (here && kg == 0) {
+        stats.m[g] = mstar;
+        stats.l[g] = lsum;
+        stats.inv_l[g] = g < G ? 1.0f / lsum : 0.f;
+      }
+      wave_lds_fence();
+    }
     // (a buffer that ends behind the group's heads, or is empty: no branch, so that a wait for a step's inputs is no wait for stores)
-    const RowBuffer out = __builtin_amdgcn_make_buffer_rsrc(out_rows + (size_t)i * p.out_stride, 0, __builtin_amdgcn_readfirstlane(attended ? G * D * 4 : 0), 0x00027000);
+    const size_t part_row = (((size_t)i * p.units + unit) * p.chunks + chunk) * G;
+    const RowBuffer out = __builtin_amdgcn_make_buffer_rsrc(PART ? p.part_o + part_row * D : out_rows + (size_t)i * p.out_stride, 0,
+                                                            __builtin_amdgcn_readfirstlane(here ? G * D * 4 : 0), 0x00027000);
 #pragma unroll
     for (int k = 0; k < NE; ++k) {
       const int idx = tid + k * kResThreads, gg = idx / D;
       float o = 0.f;
-      if (k == 0 || k * kResThreads < G * D)
-        o = (SPLIT ? fmaf(o_part[C - 1][k], stats.w1[gg], o_part[0][k] * stats.w0[gg]) : o_part[0][k]) / stats.l[gg];
+      if (k == 0 || k * kResThreads < G * D) {
+#pragma unroll
+        for (int w = 0; w < kResWaves; ++w) o += ored[(w * 16 + gg) * OSTRIDE + idx % D];
+        if (!PART) o /= stats.l[gg];
+      }
       __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o), out, 4u * (uint32_t)idx, 0, 0);
     }
-    if (attended && p.track && !last) {
+    if (PART) {
+      const RowBuffer ml = __builtin_amdgcn_make_buffer_rsrc(p.part_ml + part_row * 2, 0, __builtin_amdgcn_readfirstlane(here ? G * 8 : 0), 0x00027000);
+      const uint32_t off = wave == 0 && kg == 0 ? 8u * g : 1u << 30;  // (16 lanes; the others lie past the end)
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(mstar), ml, off, 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(lsum), ml, off + 4u, 0, 0);
+    } else if (here && p.track && !last) {
       const f32x4 m = *reinterpret_cast<const f32x4 *>(&stats.m[4 * kg]), inv_l = *reinterpret_cast<const f32x4 *>(&stats.inv_l[4 * kg]);
       bf16x8 qf[KS];
       load_q(qf, in);
 #pragma unroll
       for (int j = 0; j < T; ++j) score_tile(j, qf, m, inv_l, n);
     }
-    wave_lds_fence();  // the statistics are written again
+    if (!PART) wave_lds_fence();  // the statistics are written again
   };
   for (int i = 0; i < most; i += 2) {     // (behind an odd number of steps one in which nothing happens: a branch around it
     step(std::false_type{}, i, piece_b);  // would have its inputs copied, and waited for, in every round)
@@ -456,33 +456,38 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const Resident
   step(std::true_type{}, most, piece_a);
 
   // ---- to memory: scores, new rows, positions, what the next deferred update needs, the sequence's words -----------
+  // (PART: run_scores_kernel makes the run's updates and begins the new slots' scores)
 #pragma unroll
   for (int j = 0; j < T; ++j) {
     const int tok = first(j) + lane;
-    if (lane < kTile && tok < n && p.track && (tok >= n_entry || tok >= M)) Sb[tok] = s_reg[j];
+    if (lane < kTile && p.track && (PART ? p.owed && tok < n_entry && tok >= M : tok < n && (tok >= n_entry || tok >= M))) Sb[tok] = s_reg[j];
   }
-  const int n_new = n - n_entry;
-  const int pos0 = sm_hdr[2];
-  for (int i = tid; i < 2 * n_new * PIECES; i += kResThreads) {
-    const bool v = i >= n_new * PIECES;
-    const int at = v ? i - n_new * PIECES : i, r = at / PIECES, piece = 8 * (at % PIECES);
+  const int n_new = n - n_entry, pos0 = sm_hdr[2];
+  const int lo = PART ? kResSlots * chunk - n_entry : 0, r_lo = lo > 0 ? lo : 0, r_hi = PART && lo + kResSlots < n_new ? lo + kResSlots : n_new;
+  for (int i = tid; i < 2 * (r_hi - r_lo) * PIECES; i += kResThreads) {
+    const bool v = i >= (r_hi - r_lo) * PIECES;
+    const int at = v ? i - (r_hi - r_lo) * PIECES : i, r = r_lo + at / PIECES, piece = 8 * (at % PIECES);
     const size_t from = (size_t)sm_step[r] * p.kv_stride + (size_t)unit * D + piece;
     store_u32x4((v ? Vb : Kb) + (size_t)(n_entry + r) * D + piece, load_u32x4((v ? p.v_new : p.k_new) + from));
   }
-  for (int r = tid; r < n_new; r += kResThreads) {
+  for (int r = r_lo + tid; r < r_hi; r += kResThreads) {
     p.pos[(size_t)unit * p.cap + n_entry + r] = pos0 + r;
     if (!p.track) Sb[n_entry + r] = p.s_new ? p.s_new[(size_t)sm_step[r] * p.Nb * p.Hkv + unit] : 0.f;
   }
   const bool owes = p.track && last_attended;
-  if (owes) {
+  if (owes && chunk == 0) {
     for (int i = tid; i < G * PIECES; i += kResThreads)
       store_u32x4(p.qnext + row0 * D + 8 * (size_t)i, *reinterpret_cast<const u32x4 *>(sm_in + ((p.steps - 1) & 1) * IN + (i / PIECES) * STRIDE + 16 * (i % PIECES)));
-    if (tid < G) {
+    if (!PART && tid < G) {
       p.mlprev[(row0 + tid) * 2] = stats.m[tid];
       p.mlprev[(row0 + tid) * 2 + 1] = stats.l[tid];
     }
   }
-  if (n_dropped > 0 && h == 0 && tid == 0) atomicOr(p.status, 1);
+  if (n_dropped > 0 && h == 0 && chunk == 0 && tid == 0) atomicOr(p.status, 1);
+  if (PART) {
+    if (h == 0 && chunk == 0 && tid < 4) p.rec[4 * b + tid] = tid == 0 ? n_entry : tid == 1 ? n : tid == 2 ? pos0 + n_new : (int)last_attended;
+    return;
+  }
   if (tid == 0 && seq_ticket == (uint32_t)p.Hkv - 1) {
     __hip_atomic_store(p.seq_cnt + (size_t)b * p.cnt_stride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (p.track) p.nprev[b] = owes ? n : 0;
@@ -491,6 +496,189 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const Resident
       p.next_pos[b] = pos0 + n_new;
     }
   }
+}
+
+// ---- the partials of a run's steps, merged: outputs, statistics, the sequences' words ---------------------------
+// grid (units, steps), 512 threads; the groups of chunks and the order of every sum are attend_kernel's.
+template <int D>
+__global__ __launch_bounds__(kResThreads) void merge_run_kernel(const ResidentParams p) {
+  constexpr int NE = (16 * D + kResThreads - 1) / kResThreads, kMostChunks = kResThreads / 16;
+  __shared__ __align__(16) float sm_w[16][kMostChunks];
+  __shared__ float sm_old[16], sm_sum[16];
+  const int unit = blockIdx.x, i = blockIdx.y, tid = threadIdx.x, G = p.G;
+  const int b = __builtin_amdgcn_readfirstlane(unit / p.Hkv);
+  if (i == 0 && unit == b * p.Hkv && tid == 0) {
+    const int32_t *rec = p.rec + 4 * b;
+    if (p.track) p.nprev[b] = rec[3] ? rec[1] : 0;
+    if (rec[1] > rec[0]) {
+      p.seq_len[b] = rec[1];
+      p.next_pos[b] = rec[2];
+    }
+  }
+  const int n_rows = p.n_of[(size_t)i * p.Nb + b];
+  if (n_rows < 0) return;
+  int chunks = (n_rows + kResSlots - 1) / kResSlots;
+  chunks = chunks < 1 ? 1 : (chunks > p.chunks ? p.chunks : chunks);
+  const size_t row = ((size_t)i * p.units + unit) * p.chunks;
+  const float *po = p.part_o + row * G * D, *pml = p.part_ml + row * G * 2;
+  const size_t orow0 = (size_t)unit * G;  // (= b * Hq + h * G)
+  const bool last = i + 1 == p.steps;
+  auto merge = [&](auto N_) {
+    constexpr int N = decltype(N_)::value;
+    const int my_g = tid / N, my_j = tid % N;
+    const bool asks = tid < 16 * N && my_g < G;
+    float m_all = -INFINITY, l_all = 0.f, o_e[NE];
+#pragma unroll
+    for (int k = 0; k < NE; ++k) o_e[k] = 0.f;
+    for (int s0 = 0; s0 < chunks; s0 += N) {
+      float part[NE][N];
+#pragma unroll
+      for (int k = 0; k < NE; ++k) {
+        const int idx = tid + k * kResThreads;
+#pragma unroll
+        for (int j = 0; j < N; ++j) part[k][j] = idx < G * D && s0 + j < chunks ? po[(size_t)(s0 + j) * G * D + idx] : 0.f;
+      }
+      if (asks) {
+        const int sj = s0 + my_j;
+        const bool any = sj < chunks;
+        const float mj = any ? pml[((size_t)sj * G + my_g) * 2] : -INFINITY;
+        const float lj = any ? pml[((size_t)sj * G + my_g) * 2 + 1] : 0.f;
+        float mn = mj;
+#pragma unroll
+        for (int x = 1; x < N; x *= 2) mn = fmaxf(mn, __shfl_xor(mn, x));
+        mn = fmaxf(mn, m_all);
+        const float old = fast_exp2(m_all - mn), wj = fast_exp2(mj - mn);
+        float l = wj * lj;
+#pragma unroll
+        for (int x = 1; x < N; x *= 2) l += __shfl_xor(l, x);
+        l_all = fmaf(l_all, old, l);
+        m_all = mn;
+        sm_w[my_g][my_j] = wj;
+        if (my_j == 0) {
+          sm_old[my_g] = old;
+          sm_sum[my_g] = l_all;
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < NE; ++k) {
+        const int idx = tid + k * kResThreads;
+        if (idx < G * D) {
+          const int gg = idx / D;
+          float o = o_e[k] * sm_old[gg];
+#pragma unroll
+          for (int j = 0; j < N; ++j) o = fmaf(part[k][j], sm_w[gg][j], o);
+          o_e[k] = o;
+        }
+      }
+      __syncthreads();  // the weights' LDS is written again
+    }
+    if (asks && my_j == 0) {
+      float *st = p.stats + (((size_t)i * p.units + unit) * 16 + my_g) * 2;
+      st[0] = m_all;
+      st[1] = l_all;
+      if (last && p.track) {
+        p.mlprev[(orow0 + my_g) * 2] = m_all;
+        p.mlprev[(orow0 + my_g) * 2 + 1] = l_all;
+      }
+    }
+    float *out = p.out + (size_t)i * p.out_stride + orow0 * D;
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+      const int idx = tid + k * kResThreads;
+      if (idx < G * D) out[idx] = o_e[k] / sm_sum[idx / D];
+    }
+  };
+  const int ne = (G * D + kResThreads - 1) / kResThreads;
+  if (p.wide && ne == 1 && chunks > kWideFrom1) merge(std::integral_constant<int, 32>{});
+  else if (p.wide && D == 128 && ne == 2 && chunks > kWideFrom2) merge(std::integral_constant<int, 8>{});
+  else merge(std::integral_constant<int, 4>{});
+}
+
+// ---- the score updates of a run's steps but the last (whose is owed), from the cache as the run left it -----------------
+// grid units * chunks, 512 threads: a wave its tile of K, on its own.
+template <int D>
+__global__ __launch_bounds__(kResThreads) void run_scores_kernel(const ResidentParams p) {
+  constexpr int KS = D / 32, PIECES = D / 8, VROWS = 64 / PIECES, VIT = kTile / VROWS, STRIDE = 2 * D + 32;
+  __shared__ __align__(16) unsigned char smem[kResWaves * kTile * STRIDE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, kg = lane >> 4, g = r16, G = p.G;
+  const int unit = __builtin_amdgcn_readfirstlane(blockIdx.x / p.chunks), chunk = blockIdx.x - unit * p.chunks;
+  const int b = __builtin_amdgcn_readfirstlane(unit / p.Hkv);
+  const int n_entry = p.rec[4 * b], n = p.rec[4 * b + 1], M = p.n_prompt[b];
+  const int t = kResSlots * chunk + kTile * wave;
+  if (t >= n) return;
+  const int tok = t + lane;
+  float *Sb = p.S + (size_t)unit * p.cap;
+  float s = lane < kTile && tok < n_entry ? Sb[tok] : 0.f;
+  // (lane i: step i's)
+  const int n_lane = lane < p.steps - 1 ? p.n_of[(size_t)lane * p.Nb + b] : -1;
+  bf16x8 kf[2][KS];
+  {
+    u32x4 kr[VIT];
+    load_tile<D>(kr, row_buffer<D>(p.K + (size_t)unit * p.cap * D, n), t, lane);
+    unsigned char *vst = smem + wave * kTile * STRIDE;
+#pragma unroll
+    for (int it = 0; it < VIT; ++it)
+      *reinterpret_cast<u32x4 *>(vst + (VROWS * it + lane / PIECES) * STRIDE + 16 * (lane % PIECES)) = kr[it];
+    wave_lds_fence();
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kf[x][ks] = *reinterpret_cast<const bf16x8 *>(vst + (16 * x + r16) * STRIDE + 64 * ks + 16 * kg);
+  }
+  // A step's query, lane (g, kg): q[g][32 ks + 8 kg .. +7], and the statistics of heads 4 kg .. 4 kg + 3, asked for one step ahead
+  // (rows past the group's heads repeat its last: their weight is 0)
+  const uint16_t *src = p.q + ((size_t)unit * G + (g < G ? g : G - 1)) * D + 8 * kg;
+  const float *st = p.stats + (size_t)unit * 32 + 8 * kg;
+  bf16x8 q_next[KS];
+  f32x4 st_next[2];
+  auto fetch = [&](int i) {
+    const uint16_t *at = src + (size_t)i * p.q_stride;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) q_next[ks] = *reinterpret_cast<const bf16x8 *>(at + 32 * ks);
+    const f32x4 *sv = reinterpret_cast<const f32x4 *>(st + (size_t)i * p.units * 32);
+    st_next[0] = sv[0];
+    st_next[1] = sv[1];
+  };
+  fetch(0);
+  for (int i = 0; i + 1 < p.steps; ++i) {
+    bf16x8 qf[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qf[ks] = q_next[ks];
+    const f32x4 a = st_next[0], c = st_next[1];
+    fetch(i + 2 < p.steps ? i + 1 : i);
+    const int n_rows = __builtin_amdgcn_readlane(n_lane, i), lim = n_rows + 1;
+    if (n_rows < 0 || t >= lim) continue;
+    const f32x4 l = {a[1], a[3], c[1], c[3]};
+    f32x4 m = {a[0], a[2], c[0], c[2]};
+    float inv_l[4], part[2];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float r = 1.0f / l[k];
+      inv_l[k] = 4 * kg + k < G ? r : 0.f;
+      m[k] = 4 * kg + k < G ? m[k] : 1e30f;
+    }
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      f32x4 e = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) e = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[ks], kf[x][ks], e, 0, 0, 0);
+      float sum = 0.f;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) sum += fast_exp2(e[k] * p.scale_log2 - m[k]) * inv_l[k];
+      if (G > 8) {
+        sum = sum_over_rows(sum);
+      } else if (G > 4) {
+        const Pair r = over_16(sum);
+        sum = r.low + r.high;
+      }
+      part[x] = sum;
+    }
+    if (G <= 4) part[1] = over_16(part[1]).low;
+    if (tok < lim && tok >= M) s += kg == 0 ? part[0] : part[1];
+  }
+  if (lane < kTile && tok < n && (tok >= n_entry || tok >= M)) Sb[tok] = s;
 }
 
 }  // namespace dynts

@@ -576,13 +576,19 @@ def test_native_loop_equals_single_calls(B, external):
     (1, 2, 16, 1, 128, 17, 100, 9, 7, 150, True, True),
     (1, 1, 12, 1, 64, 255, 1, 0, 1, 9, False, False),          # runs of one step and of none
     (1, 3, 16, 1, 64, 1, 255, 0, 1, 260, False, True),         # every slot of the first tiles, one more
-    (1, 2, 28, 4, 128, 100, 300, 40, 30, 420, False, True),    # two chunks, the second empty at first
+    (1, 2, 28, 4, 128, 100, 300, 40, 30, 420, False, True),    # two chunks, the second empty at first: partials
     (2, 2, 8, 2, 64, 50, 350, 61, 51, 600, False, True),
     (1, 2, 16, 2, 128, 250, 250, 8, 4, 280, False, False),     # all 512 slots
+    (1, 1, 28, 4, 128, 200, 900, 50, 40, 1100, False, True),   # five chunks, a run longer than there is room for partials
+    (2, 2, 8, 2, 64, 100, 1400, 61, 51, 1700, False, True),
+    (1, 1, 32, 8, 128, 256, 4096, 128, 64, 4420, False, False),  # 18 chunks: merges of 32 at a time
+    (1, 1, 8, 1, 128, 30, 2500, 100, 70, 2800, False, False),  # eight at a time
+    (1, 1, 8, 1, 64, 30, 4500, 100, 70, 4800, False, True),
+    (1, 1, 16, 1, 128, 30, 1500, 100, 70, 1800, True, False),  # four elements a thread, scores from outside
     (1, 45, 32, 8, 128, 60, 330, 50, 40, 460, False, False),   # two tiles a wave, one chunk
     (1, 90, 4, 2, 64, 60, 330, 50, 40, 460, True, True),
     (1, 3, 8, 2, 64, 20, 30, 10, 200, 250, False, True)])      # two triggers' worth of steps and no more room than that
-def test_loop_on_small_caches_equals_single_calls(B, L, Nb, Hq, Hkv, d, M, budget, window, E, T, external, masked):
+def test_loop_on_caches_that_stay_on_the_chip_equals_single_calls(B, L, Nb, Hq, Hkv, d, M, budget, window, E, T, external, masked):
     """Runs of steps that the loop makes in one launch, in two calls of it (an update is owed in between): outputs, cache,
     scores before and after the owed update, lengths and status word of the same calls issued one by one, bit for bit."""
     rng = np.random.default_rng(T + d)
