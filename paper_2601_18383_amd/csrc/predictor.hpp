@@ -134,9 +134,6 @@ __global__ __launch_bounds__(kMlpThreads, 2) void mlp_kernel(const MlpParams p) 
 #pragma unroll
     for (int ft = 0; ft < FT; ++ft) wf[slot][ft] = __builtin_bit_cast(bf16x8, mlp_load(wbuf[ft], off));
   };
-#pragma unroll
-  for (int j = 0; j < DW; ++j) load_w(j, j);
-
   // What the end of the kernel needs is asked for here, too: a first read of it there would cost a trip to memory.
   // Element e of a thread's share of the sums: layer 1 takes f32x4 pieces, layer 2 single values.
   constexpr int NE = SECOND ? (NT * 256 + kMlpThreads - 1) / kMlpThreads : (NT * 64 + kMlpThreads - 1) / kMlpThreads;
@@ -181,10 +178,17 @@ __global__ __launch_bounds__(kMlpThreads, 2) void mlp_kernel(const MlpParams p) 
       for (int part = 0; part < PARTS; ++part)
         xf[slot][bt][part] = __builtin_bit_cast(bf16x8, mlp_load(xbuf, off + (bt * PARTS + part) * 1024));
     };
+    // (in the order of the loop's last steps: a wait counts loads in the order in which either path to it issued them, and in
+    // another order the one for a step's activations would be one for the weights just asked for)
 #pragma unroll
-    for (int j = 0; j < DX; ++j)
+    for (int j = 0; j < DW; ++j) {
+      if (j >= DW - DX) {
 #pragma unroll
-      for (int bt = 0; bt < BT; ++bt) load_x(j, bt, j);
+        for (int bt = 0; bt < BT; ++bt) load_x(j - (DW - DX), bt, j - (DW - DX));
+      }
+      load_w(j, j);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     for (int sb = 0; sb < n; sb += DW) {
 #pragma unroll
       for (int j = 0; j < DW; ++j) {
@@ -223,8 +227,13 @@ __global__ __launch_bounds__(kMlpThreads, 2) void mlp_kernel(const MlpParams p) 
 #pragma unroll
       for (int i = 0; i < 2 * BT; ++i) raw[slot][i] = mlp_load(xbuf, x_row[i] + col);
     };
+    // (in the order of the loop's last steps, see above)
 #pragma unroll
-    for (int j = 0; j < DX; ++j) load_x(j, j);
+    for (int j = 0; j < DW; ++j) {
+      if (j % 2 == 0 && j >= DW - 2 * DX) load_x((j - (DW - 2 * DX)) / 2, (j - (DW - 2 * DX)) / 2);
+      load_w(j, j);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     // the second layer's words, zeroed while the first loads are on their way
     for (uint32_t i = blockIdx.x * kMlpThreads + tid; i < p.n_clear; i += gridDim.x * kMlpThreads)
       reinterpret_cast<u32x4 *>(p.clear)[i] = u32x4{0u, 0u, 0u, 0u};
