@@ -28,6 +28,10 @@
 //     statistics that the next step's score update needs.  Every workgroup checks in on a
 //     per-sequence counter behind its first tile; the last one to do so advances seq_len / next_pos.
 //     No second kernel, no host round trip.
+//   * the loop waits for no more than it uses: loads are waited for by their number, so every way through a tile issues the same ones in the
+//     same order (no branch around V's part, one loop per way of loading, page numbers by the scalar cache).  Where the wait for the next
+//     tile's K rows had been one for its V rows, and on pages one for everything: 128 units of 2464 slots 30.2 -> 29.5 us a step, on pages
+//     31.2 -> 30.5, two layers of 512 units of 2640 111.7 -> 110.4, of 1190 50.1 -> 49.1.
 //   * with APPEND the new token's K/V row is written to its slot by one workgroup and enters the
 //     softmax as the initial state of the first wave (max = q.k_new, sum = 1, output = v_new), so
 //     no wave has to wait for the row to become visible.
@@ -85,7 +89,7 @@ struct AttendParams {
   // Dense layout, K and V of all layers together beyond the 256 MB memory-side cache (the STREAM kernels): a cache that is
   // read whole, step after step, through a cache it does not fit evicts every row before its next use.  So the slots
   // below 32 * waves * rounds of each unit go through it and stay, the ones behind are loaded past it (non-temporal
-  // loads), once a sequence has more than fit_slots.  rounds = 0: the first tiles do not fit either.
+  // loads), once a sequence has more than fit_slots.  (rounds = 0: the first tiles do not fit either; they are loaded through the caches all the same.)
   int fit_slots;            // slots per unit up to which everything fits
   int rounds;               // tiles of a wave at fixed places
   // paged layout only: K and V are page pools [n_pages][kPageSlots][D]; slot j of a unit lives in page
@@ -123,7 +127,8 @@ __device__ __forceinline__ void store_u32x4(uint16_t *p, u32x4 v) { *reinterpret
 using RowBuffer = __amdgpu_buffer_rsrc_t;
 template <int D>
 __device__ __forceinline__ RowBuffer row_buffer(const uint16_t *base, int rows) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(base), 0, (rows > 0 ? rows : 0) * (2 * D), 0x00027000);
+  // (uniform, and told so to the compiler: it would load each time in a loop over the values that lanes might have)
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(base), 0, __builtin_amdgcn_readfirstlane((rows > 0 ? rows : 0) * (2 * D)), 0x00027000);
 }
 
 // The 32 rows of the tile at t: contiguous memory, 1 KB a load instruction.  (Read in the order in which the MFMA operands want
@@ -236,9 +241,11 @@ __global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL
   // about 0.55 us inside an XCD, 0.7 - 0.9 us across).  Nothing depends on the placement but speed.
   // grid = round_up(units, 8) * nsplit; the padding workgroups leave at once.
   const int wg = blockIdx.x, per_grp = 8 * p.nsplit;
-  const int split = (wg % per_grp) >> 3, u_lin = (wg / per_grp) * 8 + (wg & 7);
+  const int grp = __builtin_amdgcn_readfirstlane(wg / per_grp);
+  const int split = (wg - grp * per_grp) >> 3, u_lin = grp * 8 + (wg & 7);
   if (u_lin >= p.Nb * p.Hkv) return;
-  const int b = u_lin / p.Hkv, h = u_lin - b * p.Hkv;
+  // (a division leaves uniform values in vector registers, and every address formed from them)
+  const int b = __builtin_amdgcn_readfirstlane(u_lin / p.Hkv), h = u_lin - b * p.Hkv;
   const int G = p.G;
 
   const size_t unit = (size_t)b * p.Hkv + h;
@@ -246,13 +253,16 @@ __global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL
   uint16_t *Kb = PAGED ? p.K : p.K + unit * (size_t)p.cap * D;
   uint16_t *Vb = PAGED ? p.V : p.V + unit * (size_t)p.cap * D;
   const int32_t *tb = PAGED ? p.block_table + unit * (size_t)p.max_pages : nullptr;
+  // Looked up through the scalar cache: as a vector load, whose answer comes behind those of all loads in flight, a lookup a tile had the
+  // wave wait for its next tile's rows.  (What a launch writes, the page that its appended row opens, it does not read.)
+  const auto *tb_scalar = (const __attribute__((address_space(4))) int32_t *)tb;
   // Paged addressing of one tile: the tile start is first pulled back into the tile that holds row end-1
   // (so every clamped row stays in ONE page); the tile is then loaded relative to that page: base = pool +
   // page * 64 rows, rows and the clamp counted from the page's first slot.
   auto page_of = [&](int tp) -> int {
     int pi = tp / kPageSlots;
     pi = pi < p.max_pages ? pi : p.max_pages - 1;
-    int pg = tb[pi];
+    int pg = tb_scalar[pi];
     return pg < 0 ? 0 : (pg >= p.n_pages ? p.n_pages - 1 : pg);  // never followed out of the pool
   };
   auto clamp_tile = [&](int tt, int end) -> int {
@@ -315,19 +325,12 @@ __global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL
   __builtin_amdgcn_sched_barrier(0);
   u32x4 kr[VIT], vf[VIT];
   float s_old = 0.f;
-  const bool first_past = STREAM && p.rounds == 0;
   // (paged: the first tile's page is looked up right away and its 32 rows fetched whole: a tile lies inside one page, and a page id
   // is clamped into the pool, so the addresses are valid whatever the length turns out to be)
   const size_t b0 = PAGED ? page_base(page_of(t)) : 0;
   const int t0 = PAGED ? t & (kPageSlots - 1) : t;
   const RowBuffer k_first = row_buffer<D>(Kb + b0, PAGED ? kPageSlots : p.cap);
-  if (first_past) {
-    DYNTS_OWN_BRANCH;
-    load_tile<D, true>(kr, k_first, t0, lane);
-    DYNTS_OWN_BRANCH;
-  } else {
-    load_tile<D>(kr, k_first, t0, lane);
-  }
+  load_tile<D>(kr, k_first, t0, lane);
   if (PENDING) {
     const int tok = t + (lane & (kTile - 1));
     s_old = Sb[tok < p.cap ? tok : p.cap - 1];
@@ -362,11 +365,12 @@ __global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL
     mprev[i] = PENDING ? sm_ml[8 * kg + 2 * i] : 0.f;  // (0 past the group's heads)
     inv_lprev[i] = PENDING ? sm_ml[8 * kg + 2 * i + 1] : 0.f;
   }
-  const int len_raw = sm_hdr[0];
-  const int prev_raw = PENDING ? sm_hdr[1] : 0;
-  const int pos_new_all = APPEND ? sm_hdr[2] : 0;
-  const int M = sm_hdr[3];
-  const int act_raw = sm_hdr[4];
+  // (the same in every lane, and told so to the compiler: ranges, branches and buffers formed from them are scalar then)
+  const int len_raw = __builtin_amdgcn_readfirstlane(sm_hdr[0]);
+  const int prev_raw = PENDING ? __builtin_amdgcn_readfirstlane(sm_hdr[1]) : 0;
+  const int pos_new_all = APPEND ? __builtin_amdgcn_readfirstlane(sm_hdr[2]) : 0;
+  const int M = __builtin_amdgcn_readfirstlane(sm_hdr[3]);
+  const int act_raw = __builtin_amdgcn_readfirstlane(sm_hdr[4]);
 
   // ---- what this launch does for sequence b (identical in every workgroup of b) ---------
   // n_rows cache slots are attended from the cache; when a token is appended in the same
@@ -374,33 +378,15 @@ __global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL
   const bool act = act_raw != 0;
   int n_old = len_raw;
   n_old = n_old < 0 ? 0 : (n_old > p.cap ? p.cap : n_old);
-  int n_now = 0, n_rows = 0;
-  bool appending = false;
-  if (ATTEND && act) {
-    if (APPEND) {
-      if (n_old < p.cap) {
-        n_now = n_old + 1;
-        n_rows = n_old;
-        appending = true;
-      } else if (tid == 0 && split == 0 && h == 0) {
-        atomicOr(p.status, 1);
-      }
-    } else {
-      n_now = n_rows = n_old;
-    }
-  }
+  const bool appending = ATTEND && APPEND && act && n_old < p.cap;
+  const int n_rows = ATTEND && act && (!APPEND || appending) ? n_old : 0, n_now = appending ? n_old + 1 : n_rows;
+  if (ATTEND && APPEND && act && !appending && tid == 0 && split == 0 && h == 0) atomicOr(p.status, 1);
   int n_prev = prev_raw;
   n_prev = n_prev < 0 ? 0 : (n_prev > p.cap ? p.cap : n_prev);
   const int n_vis = n_rows > n_prev ? n_rows : n_prev;
   if (ATTEND) {
     const RowBuffer v_first = row_buffer<D>(Vb + b0, PAGED ? (n_rows - (t - t0) < kPageSlots ? n_rows - (t - t0) : kPageSlots) : n_rows);
-    if (first_past) {
-      DYNTS_OWN_BRANCH;
-      load_tile<D, true>(vf, v_first, t0, lane);
-      DYNTS_OWN_BRANCH;
-    } else {
-      load_tile<D>(vf, v_first, t0, lane);
-    }
+    load_tile<D>(vf, v_first, t0, lane);
   }
   // workgroups of this unit that produce an attention partial (chunk 0 always does when the
   // sequence is attended: it owns the appended token), and that have any work at all
@@ -599,7 +585,8 @@ __global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL
   // unconditionally (clamped), so the loop never drains its outstanding loads.
   // t: first slot of the tile; hi: end of the slots of this tile that belong to this wave;
   // tn: first slot of the wave's next tile (any value when there is none: the loads are clamped)
-  auto tile = [&](int t, int hi, int tn, bool past) {
+  auto tile = [&](auto PAST, int t, int hi, int tn) {
+    constexpr bool past = decltype(PAST)::value;
     const int att_hi = hi < n_rows ? hi : n_rows;
     const int pend_hi = hi < n_prev ? hi : n_prev;
 
@@ -644,13 +631,7 @@ __global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL
       v_next = row_buffer<D>(Vb + nb, left_v < kPageSlots ? left_v : kPageSlots);
       pg_nxt = page_of(clamp_tile(tn + kTile, own_end));
     }
-    if (STREAM && past) {
-      DYNTS_OWN_BRANCH;
-      load_tile<D, true>(kr, k_next, nt, lane);
-      DYNTS_OWN_BRANCH;
-    } else {
-      load_tile<D>(kr, k_next, nt, lane);
-    }
+    load_tile<D, past>(kr, k_next, nt, lane);
     if (PENDING) {
       const int tok = tn + (lane & (kTile - 1));
       s_old = Sb[tok < p.cap ? tok : p.cap - 1];
@@ -690,7 +671,9 @@ __global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL
     }
 
     // ---- attention for the current query --------------------------------------------------
-    if (ATTEND && t < att_hi) {
+    // (also of a tile behind the slots it attends, which the owed update alone may have: its weights are 0.  Around a branch the wait
+    // for the next tile's K rows would be one for its V rows, too: loads are waited for by their number, and the way with fewer counts.)
+    if (ATTEND) {
       // acc[s][i] = logit(slot t + 16 s + 4 kg + i, head g)
       float x[8];
       float mx = -INFINITY;
@@ -708,7 +691,7 @@ __global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL
           mx = fmaxf(mx, x[e]);
         }
       }
-      if (SPILL) {
+      if (SPILL && t < att_hi) {
         if (lg_n > 0 && (t != lg_base + kTile * lg_n || (lg_n + 1) * G > kLogitRows)) flush_logits();
         if (lg_n == 0) lg_base = t;
         if (g < G) {  // this lane's 8 logits of head g: slots t + 16 s + 4 kg .. +3
@@ -721,9 +704,10 @@ __global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL
       }
       mx = fmaxf(mx, __shfl_xor(mx, 16));
       mx = fmaxf(mx, __shfl_xor(mx, 32));
-      const float m_new = fmaxf(m_run, mx);     // finite: the tile holds at least one valid slot
+      const float m_run_next = fmaxf(m_run, mx);
+      const float m_new = m_run_next == -INFINITY ? 0.f : m_run_next;  // (-inf: no slot so far)
       const float corr = fast_exp2(m_run - m_new);  // m_run = -inf on the first tile -> 0
-      m_run = m_new;
+      m_run = m_run_next;
       bf16x8 ph, pl;
       float psum = 0.f;
 #pragma unroll
@@ -744,13 +728,7 @@ __global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL
       for (int it = 0; it < VIT; ++it)
         *reinterpret_cast<u32x4 *>(vst + (VROWS * it + vrow_l) * VSTRIDE + 16 * vpiece) = vf[it];
       wave_lds_fence();
-      if (STREAM && past) {
-        DYNTS_OWN_BRANCH;
-        load_tile<D, true>(vf, v_next, nt, lane);
-        DYNTS_OWN_BRANCH;
-      } else {
-        load_tile<D>(vf, v_next, nt, lane);
-      }
+      load_tile<D, past>(vf, v_next, nt, lane);
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) {
         // V^T operand: lane (c = 16 cb + r16, kg) gets V[t + 16 s + 4 kg + i][c] as element 4 s + i.
@@ -770,15 +748,25 @@ __global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL
     }
   };
 
-  if (t < n_vis) tile(t, t + kTile < n_vis ? t + kTile : n_vis, t < t_fix ? t + kTile * NW : ra, t == t_fix && past_caches);
-  seq_checkin();
-  if (STREAM) {
-    while (t < t_fix) {
-      t += kTile * NW;
-      tile(t, t + kTile < n_vis ? t + kTile : n_vis, t < t_fix ? t + kTile * NW : ra, t == t_fix && past_caches);
+  constexpr std::false_type kThrough{};
+  constexpr std::true_type kPast{};
+  if constexpr (!STREAM) {
+    if (t < n_vis) tile(kThrough, t, t + kTile < n_vis ? t + kTile : n_vis, ra);
+    seq_checkin();
+    for (t = ra; t < rb; t += kTile) tile(kThrough, t, rb, t + kTile);
+  } else {
+    // The tiles at fixed places, then the wave's range: one loop over those whose next tile is loaded through the caches, one over the others.
+    // (Both ways of loading in one loop leave their rows in different registers, and to bring those together is to wait for the loads.)
+    auto behind = [&](int at) { return at < t_fix ? at + kTile * NW : at == t_fix ? ra : at + kTile; };
+    auto end_of = [&](int at) { return at > t_fix ? rb : at + kTile < n_vis ? at + kTile : n_vis; };
+    seq_checkin();
+    if (t < n_vis) {
+      const int through_end = past_caches ? t_fix : t_fix < rb ? rb : t_fix + 1;
+      for (; t < through_end; t = behind(t)) tile(kThrough, t, end_of(t), behind(t));
+      if (past_caches)
+        for (; t <= t_fix || t < rb; t = behind(t)) tile(kPast, t, end_of(t), behind(t));
     }
   }
-  for (t = ra; t < rb; t += kTile) tile(t, rb, t + kTile, past_caches);
   flush_scores();
   flush_logits();
 
