@@ -64,7 +64,7 @@ struct ResidentParams {
   // caches of several chunks: a launch of their steps leaves
   int units, chunks;        // Nb * Hkv; of 256 slots
   float *part_o, *part_ml;  // [steps][units][chunks][G][D], [..][G][2]: the chunks' partials (see attend_kernel)
-  float *stats;             // [steps][units][16][2]: (max, sum) of the steps' softmax (merge_run_kernel)
+  float *stats;             // [steps][units][16][2]: (max, 1 / sum) of the steps' softmax (merge_run_kernel)
   int32_t *n_of;            // [steps][Nb]: slots that the step attended in the cache, -1: the sequence was not attended
   int32_t *rec;             // [Nb][4]: slots before and behind the run, next position, whether the last step attended
   int wide;                 // merges of 32 and of 8 chunks at a time (wide_merge in dynts.hip)
@@ -573,11 +573,11 @@ __global__ __launch_bounds__(kResThreads) void merge_run_kernel(const ResidentPa
       }
       __syncthreads();  // the weights' LDS is written again
     }
-    if (asks && my_j == 0) {
+    if (tid < 16 * N && my_j == 0) {  // (of rows past the group's heads: no weight)
       float *st = p.stats + (((size_t)i * p.units + unit) * 16 + my_g) * 2;
-      st[0] = m_all;
-      st[1] = l_all;
-      if (last && p.track) {
+      st[0] = asks ? m_all : 1e30f;
+      st[1] = asks ? 1.0f / l_all : 0.f;
+      if (asks && last && p.track) {
         p.mlprev[(orow0 + my_g) * 2] = m_all;
         p.mlprev[(orow0 + my_g) * 2 + 1] = l_all;
       }
@@ -596,23 +596,27 @@ __global__ __launch_bounds__(kResThreads) void merge_run_kernel(const ResidentPa
 }
 
 // ---- the score updates of a run's steps but the last (whose is owed), from the cache as the run left it -----------------
-// grid units * chunks, 512 threads: a wave its tile of K, on its own.
+// grid units * chunks, 512 threads: a wave its tile of K.  Queries and statistics reach the waves through LDS, eight steps at a time: fetched by
+// every wave for itself, in operand order, they alone took 0.6 us a step.
 template <int D>
 __global__ __launch_bounds__(kResThreads) void run_scores_kernel(const ResidentParams p) {
   constexpr int KS = D / 32, PIECES = D / 8, VROWS = 64 / PIECES, VIT = kTile / VROWS, STRIDE = 2 * D + 32;
+  constexpr int kSteps = 8, kBuf = kSteps * 16 * STRIDE;  // steps at a time
+  constexpr int NP = (16 * PIECES * kSteps + kResThreads - 1) / kResThreads;
+  static_assert(kResWaves * kTile * STRIDE == 2 * kBuf && kPartSteps <= 64, "the tiles' LDS is reused for the queries; a lane per step");
   __shared__ __align__(16) unsigned char smem[kResWaves * kTile * STRIDE];
+  __shared__ __align__(16) float sm_stats[2][kSteps * 32];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kg = lane >> 4, g = r16, G = p.G;
   const int unit = __builtin_amdgcn_readfirstlane(blockIdx.x / p.chunks), chunk = blockIdx.x - unit * p.chunks;
   const int b = __builtin_amdgcn_readfirstlane(unit / p.Hkv);
   const int n_entry = p.rec[4 * b], n = p.rec[4 * b + 1], M = p.n_prompt[b];
-  const int t = kResSlots * chunk + kTile * wave;
-  if (t >= n) return;
-  const int tok = t + lane;
+  if (kResSlots * chunk >= n) return;
+  const int t = kResSlots * chunk + kTile * wave, tok = t + lane;
   float *Sb = p.S + (size_t)unit * p.cap;
   float s = lane < kTile && tok < n_entry ? Sb[tok] : 0.f;
-  // (lane i: step i's)
-  const int n_lane = lane < p.steps - 1 ? p.n_of[(size_t)lane * p.Nb + b] : -1;
+  // (lane i: slots of step i; -1: nothing to add)
+  const int n_lane = lane + 1 < p.steps ? p.n_of[(size_t)lane * p.Nb + b] : -1;
   bf16x8 kf[2][KS];
   {
     u32x4 kr[VIT];
@@ -627,56 +631,84 @@ __global__ __launch_bounds__(kResThreads) void run_scores_kernel(const ResidentP
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) kf[x][ks] = *reinterpret_cast<const bf16x8 *>(vst + (16 * x + r16) * STRIDE + 64 * ks + 16 * kg);
   }
-  // A step's query, lane (g, kg): q[g][32 ks + 8 kg .. +7], and the statistics of heads 4 kg .. 4 kg + 3, asked for one step ahead
-  // (rows past the group's heads repeat its last: their weight is 0)
-  const uint16_t *src = p.q + ((size_t)unit * G + (g < G ? g : G - 1)) * D + 8 * kg;
-  const float *st = p.stats + (size_t)unit * 32 + 8 * kg;
-  bf16x8 q_next[KS];
-  f32x4 st_next[2];
-  auto fetch = [&](int i) {
-    const uint16_t *at = src + (size_t)i * p.q_stride;
+  __syncthreads();
+  for (int i = tid; i < 2 * kSteps * (16 - G) * PIECES; i += kResThreads) {  // (rows past the group's heads)
+    const int row = i / PIECES, in_step = row % (16 - G);
+    *reinterpret_cast<u32x4 *>(smem + (row / (16 - G) * 16 + G + in_step) * STRIDE + 16 * (i % PIECES)) = u32x4{0u, 0u, 0u, 0u};
+  }
+  // eight steps' queries and statistics, a piece of 16 bytes a thread
+  u32x4 piece[NP];
+  float stat = 0.f;
+  const uint16_t *qb = p.q + (size_t)unit * G * D;
+  auto fetch = [&](int i0) {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) q_next[ks] = *reinterpret_cast<const bf16x8 *>(at + 32 * ks);
-    const f32x4 *sv = reinterpret_cast<const f32x4 *>(st + (size_t)i * p.units * 32);
-    st_next[0] = sv[0];
-    st_next[1] = sv[1];
+    for (int k = 0; k < NP; ++k) {
+      const int at = tid + k * kResThreads, st = at / (G * PIECES), i = i0 + st;
+      if (st < kSteps && i < p.steps) piece[k] = load_u32x4(qb + (size_t)i * p.q_stride + 8 * (at - st * (G * PIECES)));
+    }
+    if (tid < kSteps * 32 && i0 + tid / 32 < p.steps) stat = p.stats[((size_t)(i0 + tid / 32) * p.units + unit) * 32 + tid % 32];
   };
   fetch(0);
-  for (int i = 0; i + 1 < p.steps; ++i) {
-    bf16x8 qf[KS];
+  for (int i0 = 0; i0 < p.steps - 1; i0 += kSteps) {
+    const int buf = (i0 / kSteps) & 1;
+    unsigned char *qs = smem + buf * kBuf;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[ks] = q_next[ks];
-    const f32x4 a = st_next[0], c = st_next[1];
-    fetch(i + 2 < p.steps ? i + 1 : i);
-    const int n_rows = __builtin_amdgcn_readlane(n_lane, i), lim = n_rows + 1;
-    if (n_rows < 0 || t >= lim) continue;
-    const f32x4 l = {a[1], a[3], c[1], c[3]};
-    f32x4 m = {a[0], a[2], c[0], c[2]};
-    float inv_l[4], part[2];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float r = 1.0f / l[k];
-      inv_l[k] = 4 * kg + k < G ? r : 0.f;
-      m[k] = 4 * kg + k < G ? m[k] : 1e30f;
+    for (int k = 0; k < NP; ++k) {
+      const int at = tid + k * kResThreads, st = at / (G * PIECES), in_step = at - st * (G * PIECES);
+      if (st < kSteps) *reinterpret_cast<u32x4 *>(qs + (16 * st + in_step / PIECES) * STRIDE + 16 * (in_step % PIECES)) = piece[k];
     }
+    if (tid < kSteps * 32) sm_stats[buf][tid] = stat;
+    __syncthreads();
+    fetch(i0 + kSteps);
+    if (t >= n) continue;
+    // Two steps side by side, whose chains of products, exponentials and sums then hide one another's latencies; added one after the other.
+#pragma unroll 2
+    for (int at = 0; at < kSteps; at += 2) {
+      f32x4 e[2][2];
+      float part[2][2];
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
-      f32x4 e = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < 2; ++j) {
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) e = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[ks], kf[x][ks], e, 0, 0, 0);
-      float sum = 0.f;
+        for (int x = 0; x < 2; ++x) e[j][x] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int k = 0; k < 4; ++k) sum += fast_exp2(e[k] * p.scale_log2 - m[k]) * inv_l[k];
-      if (G > 8) {
-        sum = sum_over_rows(sum);
-      } else if (G > 4) {
-        const Pair r = over_16(sum);
-        sum = r.low + r.high;
+        for (int ks = 0; ks < KS; ++ks) {
+          const bf16x8 qf = *reinterpret_cast<const bf16x8 *>(qs + (16 * (at + j) + g) * STRIDE + 64 * ks + 16 * kg);
+#pragma unroll
+          for (int x = 0; x < 2; ++x) e[j][x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf, kf[x][ks], e[j][x], 0, 0, 0);
+        }
       }
-      part[x] = sum;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const f32x4 *st = reinterpret_cast<const f32x4 *>(&sm_stats[buf][32 * (at + j) + 8 * kg]);  // of heads 4 kg .. 4 kg + 3
+        const f32x4 a = st[0], c = st[1], m = {a[0], a[2], c[0], c[2]}, inv_l = {a[1], a[3], c[1], c[3]};
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          float sum = 0.f;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) sum += fast_exp2(e[j][x][k] * p.scale_log2 - m[k]) * inv_l[k];
+          part[j][x] = sum;
+        }
+      }
+      if (G > 8) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) part[j >> 1][j & 1] = sum_over_rows(part[j >> 1][j & 1]);
+      } else if (G > 4) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const Pair r = over_16(part[j >> 1][j & 1]);
+          part[j >> 1][j & 1] = r.low + r.high;
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) part[j][1] = over_16(part[j][1]).low;
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int i = i0 + at + j, n_rows = __builtin_amdgcn_readlane(n_lane, i < 64 ? i : 63);
+        const float add = kg == 0 ? part[j][0] : part[j][1];
+        if (tok <= n_rows && tok >= M) s += add;  // (the new slot too)
+      }
     }
-    if (G <= 4) part[1] = over_16(part[1]).low;
-    if (tok < lim && tok >= M) s += kg == 0 ? part[0] : part[1];
   }
   if (lane < kTile && tok < n && (tok >= n_entry || tok >= M)) Sb[tok] = s;
 }
