@@ -14,10 +14,13 @@
 // tile, the new token as the first wave's initial state, tiles of a wave one after the other, chunks merged in the same groups.  So are the
 // things it leaves: the last step's update is owed (query, statistics, slots), or its logits are kept for the trigger that follows.
 //
-// What bounds it now: a chain of some 400 dependent instructions a wave and step -- logits, maximum, weights, products, two barriers
-// around the waves' combination, division, scores.  us a step, a launch each / so, runs of 32 steps: head_dim 64, 4 heads a group, caches of
-// 250 slots, 8 units 5.53 / 1.97, 256 5.91 / 2.10, 1024 15.84 / 7.90; head_dim 128, 7 heads, of 120 slots, 4 units 6.15 / 2.64, 1024 23.7 / 10.7; of
-// 510, 4 units 8.75 / 3.2 (two chunks), 256 14.8 / 3.9, 1024 48.7 / 16.0; 4 heads, 8 units of 4544 (18 chunks) 11.7 / 3.3, of which 0.3 merge and 0.6 scores.
+// What bounds it now: a chain of some 400 dependent instructions a wave and step, two waves a SIMD -- logits, maximum, weights, products, two
+// barriers around the waves' combination, division, scores.  What that chain waits for is kept short: reads of LDS are asked for in groups
+// before the first is used, the new row is put in between the barriers, with masks (its wave is waited for), and a score tile's two halves go side by
+// side.  Each read and half waited for by itself, a launch of 64 steps on 18 chunks took 147 us and takes 129; 16 steps of head_dim 64 33.0 and 31.4.
+// One barrier instead of two, each wave weighing all eight waves' outputs, took 0.2 to 0.4 us a step more.
+// us a step, a launch each / so, runs of 32 steps: head_dim 64, 4 heads a group, 2 units of 250 slots 5.46 / 1.86, 128 of 510 (two chunks) 7.6 / 2.9;
+// head_dim 128, 4 heads, 8 units of 250 6.6 / 2.5, of 1000 8.5 / 3.2, of 4544 (18 chunks) 11.7 / 3.3; 7 heads, 512 units of 510 26.3 / 7.5.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -199,24 +202,30 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const Resident
   // S[slot] += sum over the group of 2^(logit - m) / l for the thinking slots below lim of tile j; m, inv_l: of heads 4 kg .. 4 kg + 3
   auto score_tile = [&](int j, const bf16x8 (&qv)[KS], const f32x4 &m, const f32x4 &inv_l, int lim) {
     if (first(j) >= lim) return;
+    f32x4 e[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};  // [s]: logit of slot 16 s + r16, head 4 kg + i
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) e[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv[ks], kf[j][s][ks], e[s], 0, 0, 0);
     float part[2];
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      f32x4 e = f32x4{0.f, 0.f, 0.f, 0.f};  // logit of slot 16 s + r16, head 4 kg + i
+    for (int s = 0; s < 2; ++s) {  // (both sub-tiles, and then the group's size once)
+      part[s] = 0.f;
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) e = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qv[ks], kf[j][s][ks], e, 0, 0, 0);
-      float a = 0.f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a += fast_exp2(e[i] * p.scale_log2 - m[i]) * inv_l[i];
-      if (G > 8) {
-        a = sum_over_rows(a);
-      } else if (G > 4) {
-        const Pair r = over_16(a);
-        a = r.low + r.high;
-      }
-      part[s] = a;
+      for (int i = 0; i < 4; ++i) part[s] += fast_exp2(e[s][i] * p.scale_log2 - m[i]) * inv_l[i];
     }
-    if (G <= 4) part[1] = over_16(part[1]).low;  // (the first row's lanes hold the sums; the second takes sub-tile 1)
+    if (G > 8) {
+      part[0] = sum_over_rows(part[0]);
+      part[1] = sum_over_rows(part[1]);
+    } else if (G > 4) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const Pair r = over_16(part[s]);
+        part[s] = r.low + r.high;
+      }
+    } else {
+      part[1] = over_16(part[1]).low;  // (the first row's lanes hold the sums; the second takes sub-tile 1)
+    }
     const int tok = first(j) + lane;
     if (lane < kTile && tok < lim && tok >= M) s_reg[j] += kg == 0 ? part[0] : part[1];
   };
@@ -316,8 +325,9 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const Resident
         for (int k = 0; k < 8; ++k) x[k] = acc[k >> 2][k & 3] * p.scale_log2;
         if (t + kTile > n_rows) {
           DYNTS_OWN_BRANCH;
+          const int rows = n_rows - t - 4 * kg;  // (against constants: eight slot numbers a tile are not kept over the loop)
 #pragma unroll
-          for (int k = 0; k < 8; ++k) x[k] = t + 16 * (k >> 2) + 4 * kg + (k & 3) < n_rows ? x[k] : -INFINITY;
+          for (int k = 0; k < 8; ++k) x[k] = 16 * (k >> 2) + (k & 3) < rows ? x[k] : -INFINITY;
         }
         float mx = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
         if (last && p.spill && g < G) {
@@ -357,43 +367,6 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const Resident
       l_run = sum_over_rows(l_run);
       if (kg == 0) sm_m[g][wave] = m_run;
     }
-    if (attended) {
-      // ---- the new row, into the operands of the wave that has its slot ----------------------------------
-      if (tid == 0) sm_step[n_rows - n_entry] = i;
-#pragma unroll
-      for (int j = 0; j < T; ++j) {
-        if ((n_rows & ~(kTile - 1)) != first(j)) continue;
-        const int r = n_rows & (kTile - 1), dw_at = 2 * (r >> 4) + ((r & 3) >> 1);
-        const bool k_lane = r16 == (r & 15);
-        const uint32_t keep = kg != ((r & 15) >> 2) ? 0xffffffffu : (r & 1) ? 0x0000ffffu : 0xffff0000u;
-        // (one of two, one of four: branches, not selections between all)
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-          if (s == r >> 4) {
-            DYNTS_OWN_BRANCH;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-              const bf16x8 k_row = *reinterpret_cast<const bf16x8 *>(in + 16 * STRIDE + 64 * ks + 16 * kg);
-              kf[j][s][ks] = k_lane ? k_row : kf[j][s][ks];
-            }
-          }
-        }
-#pragma unroll
-        for (int dw = 0; dw < 4; ++dw) {
-          if (dw == dw_at) {
-            DYNTS_OWN_BRANCH;
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb) {
-              const uint32_t x = *reinterpret_cast<const uint16_t *>(in + 17 * STRIDE + 2 * (16 * cb + r16));
-              u32x4 v = __builtin_bit_cast(u32x4, vt[j][cb]);
-              v[dw] = (v[dw] & keep) | ((x | (x << 16)) & ~keep);
-              vt[j][cb] = __builtin_bit_cast(i16x8, v);
-            }
-          }
-        }
-        if (lane == r) s_reg[j] = 0.f;
-      }
-    }
     __syncthreads();  // maxima; this step's inputs have been read
     if (!last) {
       stage(i + 1, next);
@@ -409,9 +382,61 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const Resident
       }
       if (kg == 0) sm_l[g][wave] = l_run * f;
     }
+    if (attended) {
+      // ---- the new row, into the operands of the wave that has its slot ----------------------------------
+      // (the others wait for this one: all its reads before the first is used, masks and no branches)
+      if (tid == 0) sm_step[n_rows - n_entry] = i;
+#pragma unroll
+      for (int j = 0; j < T; ++j) {
+        if ((n_rows & ~(kTile - 1)) != first(j)) continue;
+        DYNTS_OWN_BRANCH;
+        const int r = n_rows & (kTile - 1), dw_at = 2 * (r >> 4) + ((r & 3) >> 1);
+        u32x4 k_row[KS];
+        uint32_t v_row[CB];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) k_row[ks] = *reinterpret_cast<const u32x4 *>(in + 16 * STRIDE + 64 * ks + 16 * kg);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) v_row[cb] = *reinterpret_cast<const uint16_t *>(in + 17 * STRIDE + 2 * (16 * cb + r16));
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const bool mine = r16 == (r & 15) && s == r >> 4;
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) kf[j][s][ks] = mine ? __builtin_bit_cast(bf16x8, k_row[ks]) : kf[j][s][ks];
+        }
+        const uint32_t half = kg != ((r & 15) >> 2) ? 0u : (r & 1) ? 0xffff0000u : 0x0000ffffu;
+        uint32_t put_at[4];
+#pragma unroll
+        for (int dw = 0; dw < 4; ++dw) put_at[dw] = dw == dw_at ? half : 0u;
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+          const uint32_t x = v_row[cb] | (v_row[cb] << 16);
+          u32x4 v = __builtin_bit_cast(u32x4, vt[j][cb]);
+#pragma unroll
+          for (int dw = 0; dw < 4; ++dw) v[dw] = (v[dw] & ~put_at[dw]) | (x & put_at[dw]);
+          vt[j][cb] = __builtin_bit_cast(i16x8, v);
+        }
+        if (lane == r) s_reg[j] = 0.f;
+      }
+    }
     __syncthreads();
+    // (every read before the first sum, those of the outputs before the wait for the statistics)
     const f32x4 la = *reinterpret_cast<const f32x4 *>(&sm_l[g][0]), lb = *reinterpret_cast<const f32x4 *>(&sm_l[g][4]);
     const float lsum = ((((((la[0] + la[1]) + la[2]) + la[3]) + lb[0]) + lb[1]) + lb[2]) + lb[3];
+    float o[NE];
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+      const int idx = tid + k * kResThreads, gg = idx / D;
+      o[k] = 0.f;
+      if (k == 0 || k * kResThreads < G * D) {
+        float part[kResWaves];
+#pragma unroll
+        for (int w = 0; w < kResWaves; ++w) part[w] = ored[(w * 16 + gg) * OSTRIDE + idx % D];
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int w = 0; w < kResWaves; ++w) o[k] += part[w];
+      }
+    }
     if (!PART) {
       if (here && kg == 0) {
         stats.m[g] = mstar;
@@ -426,14 +451,9 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const Resident
                                                             __builtin_amdgcn_readfirstlane(here ? G * D * 4 : 0), 0x00027000);
 #pragma unroll
     for (int k = 0; k < NE; ++k) {
-      const int idx = tid + k * kResThreads, gg = idx / D;
-      float o = 0.f;
-      if (k == 0 || k * kResThreads < G * D) {
-#pragma unroll
-        for (int w = 0; w < kResWaves; ++w) o += ored[(w * 16 + gg) * OSTRIDE + idx % D];
-        if (!PART) o /= stats.l[gg];
-      }
-      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o), out, 4u * (uint32_t)idx, 0, 0);
+      const int idx = tid + k * kResThreads;
+      if (!PART && (k == 0 || k * kResThreads < G * D)) o[k] /= stats.l[idx / D];
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o[k]), out, 4u * (uint32_t)idx, 0, 0);
     }
     if (PART) {
       const RowBuffer ml = __builtin_amdgcn_make_buffer_rsrc(p.part_ml + part_row * 2, 0, __builtin_amdgcn_readfirstlane(here ? G * 8 : 0), 0x00027000);
