@@ -1330,11 +1330,14 @@ int dynts_decode_loop(dynts_ctx *ctx, int32_t n_steps, const uint16_t *q, const 
     const int rc2 = dynts_select_evict(ctx, l, trig, c.budget, keep_idx, c.capacity, new_len, stream);
     return rc2 == DYNTS_OK ? dynts_compact(ctx, l, trig, keep_idx, c.capacity, new_len, stream) : rc2;
   };
+  // Outputs of steps that overlap in part are left to launches in order (size_t: a stride may lead backwards).
+  const size_t slab = c.n_layers * q_layer;
+  const bool apart = out_step_stride == 0 || (out_step_stride >= slab && (size_t)0 - out_step_stride >= slab);
   for (int i = 0; i < n_steps; ++i) {
     const uint8_t *act = active ? active + (size_t)i * c.batch : nullptr;
     const float *sn = ext ? s_new + (size_t)i * c.batch * c.n_kv_heads : nullptr;
     int run = 1;  // steps up to the next trigger's, where they can be one launch
-    const int most = resident_run(ctx, st);
+    const int most = apart ? resident_run(ctx, st) : 0;
     while (i + run < n_steps && run < most && !(evict_steps && evict_steps[i + run - 1])) ++run;
     if (run >= kLeastRun) {
       const bool evict = evict_steps && evict_steps[i + run - 1];

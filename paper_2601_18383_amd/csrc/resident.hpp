@@ -47,7 +47,7 @@ struct ResidentParams {
   const uint16_t *k_new, *v_new;  // [Nb][Hkv][D], kv_stride
   const float *s_new;       // [Nb][Hkv] or null, Nb * Hkv
   const uint8_t *active;    // [Nb] or null, Nb
-  float *out;               // [Nb][Hq][D], out_stride
+  float *out;               // [Nb][Hq][D], out_stride (0, or so large that no two steps' overlap)
   size_t q_stride, kv_stride, out_stride;
   int steps;
   // the deferred update (see AttendParams): the one owed from before (owed != 0), and where the last step's is kept
@@ -543,6 +543,10 @@ __global__ __launch_bounds__(kResThreads) void merge_run_kernel(const ResidentPa
   const float *po = p.part_o + row * G * D, *pml = p.part_ml + row * G * 2;
   const size_t orow0 = (size_t)unit * G;  // (= b * Hq + h * G)
   const bool last = i + 1 == p.steps;
+  // Where every step's outputs go to one place, those of the last step that attended the sequence stay: the steps' workgroups have no order.
+  bool stays = true;
+  if (p.out_stride == 0)
+    for (int s = i + 1; s < p.steps; ++s) stays = stays && p.n_of[(size_t)s * p.Nb + b] < 0;
   auto merge = [&](auto N_) {
     constexpr int N = decltype(N_)::value;
     const int my_g = tid / N, my_j = tid % N;
@@ -606,7 +610,7 @@ __global__ __launch_bounds__(kResThreads) void merge_run_kernel(const ResidentPa
 #pragma unroll
     for (int k = 0; k < NE; ++k) {
       const int idx = tid + k * kResThreads;
-      if (idx < G * D) out[idx] = o_e[k] / sm_sum[idx / D];
+      if (stays && idx < G * D) out[idx] = o_e[k] / sm_sum[idx / D];
     }
   };
   const int ne = (G * D + kResThreads - 1) / kResThreads;

@@ -637,6 +637,37 @@ def test_loop_on_caches_that_stay_on_the_chip_equals_single_calls(B, L, Nb, Hq, 
     same()
 
 
+@pytest.mark.parametrize("L,Nb,Hq,Hkv,d,cap", [(1, 3, 8, 2, 64, 200), (2, 2, 28, 4, 128, 700), (1, 2, 16, 1, 64, 2000), (2, 1, 32, 8, 128, 4544)])
+@pytest.mark.parametrize("stride", ["none", "part"])
+def test_loop_whose_steps_share_their_outputs(B, L, Nb, Hq, Hkv, d, cap, stride):
+    """Without a stride between the steps the outputs that stay are those of the last step that attended the sequence; with less than
+    a step's outputs between them later steps overwrite parts of earlier ones: as single calls in order leave them, bit for bit."""
+    rng = np.random.default_rng(cap + d)
+    dev = torch.device("cuda:0")
+    T, M = 40, 30
+    q = _bf16(rng, T, L, Nb, Hq, d, scale=1.5).to(dev)
+    k, v = _bf16(rng, T, L, Nb, Hkv, d).to(dev), _bf16(rng, T, L, Nb, Hkv, d).to(dev)
+    act = torch.from_numpy((rng.random((T, Nb)) < 0.7).astype(np.uint8)).to(dev)
+    act[T - 5:, 0] = 0
+    n0 = cap - T
+    K0, V0 = _bf16(rng, Nb, Hkv, n0, d).to(dev), _bf16(rng, Nb, Hkv, n0, d).to(dev)
+    lens = torch.full((Nb,), n0, dtype=torch.int32, device=dev)
+    slab = L * Nb * Hq * d
+    step = 0 if stride == "none" else Hq * d // 2
+    flat = [torch.zeros(slab + T * step, dtype=torch.float32, device=dev) for _ in range(2)]
+    a, b = (B.Cache(L, Nb, Hq, Hkv, d, cap, cap - M - 64, 32, 32) for _ in range(2))
+    for c in (a, b):
+        for l in range(L):
+            B.dynts_prefill(c.ctx, l, K0, V0, lens)
+    B.dynts_decode_loop(a.ctx, T, q, k, v, flat[0], a.keep_idx, a.new_len, active=act, out_step_stride=step)
+    for t in range(T):
+        for l in range(L):
+            out = flat[1][t * step + l * Nb * Hq * d:][:Nb * Hq * d].view(Nb, Hq, d)
+            B.dynts_decode_step(b.ctx, l, q[t, l], k[t, l], v[t, l], out, active=act[t])
+    assert torch.equal(flat[0], flat[1]) and bool((flat[0] != 0).any())
+    assert torch.equal(a.seq_len, b.seq_len) and torch.equal(a.status, b.status)
+
+
 @pytest.mark.parametrize("d,Hq,Hkv", [(64, 8, 2), (128, 14, 2), (128, 3, 3)])
 def test_attend_then_update_by_any_route(B, d, Hq, Hkv):
     """The unfused attend call keeps its logits for the update behind it.  Two layers share the room for them: whoever
