@@ -338,14 +338,15 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const Resident
           }
         }
         mx = max_over_rows(mx);
-        const float m_new = fmaxf(m_run, mx);
+        const float m_next = fmaxf(m_run, mx);
+        const float m_new = m_next == -INFINITY ? 0.f : m_next;  // (-inf: no logit above it so far)
         const float corr = fast_exp2(m_run - m_new);
         if (j > 0 || (chunk == 0 && wave == 0)) {  // (else there is nothing to correct)
           DYNTS_OWN_BRANCH;
 #pragma unroll
           for (int cb = 0; cb < CB; ++cb) oacc[cb] *= corr;
         }
-        m_run = m_new;
+        m_run = m_next;
         bf16x8 ph, pl;
         float psum = 0.f;
 #pragma unroll

@@ -637,6 +637,36 @@ def test_loop_on_caches_that_stay_on_the_chip_equals_single_calls(B, L, Nb, Hq, 
     same()
 
 
+@pytest.mark.parametrize("d,Hq,Hkv,cap", [(64, 8, 2, 200), (128, 28, 4, 500), (128, 8, 2, 900)])
+def test_loop_with_whole_tiles_at_minus_infinity(B, d, Hq, Hkv, cap):
+    """Logits that overflow to -inf, over whole tiles of 32 slots (a wave's first among them), weigh nothing, in a run of steps as in
+    single calls: every other slot has a logit of zero, so the outputs are the mean of their V rows (sums of fp32: 1e-5)."""
+    rng = np.random.default_rng(cap + d)
+    dev = torch.device("cuda:0")
+    T, n0 = 5, cap - 40
+    big = torch.tensor(3e38).bfloat16()
+    K0 = torch.zeros((1, Hkv, n0, d), dtype=torch.bfloat16)
+    K0[:, :, 32:64] = -big
+    K0[:, :, 96:160] = -big
+    V0 = _bf16(rng, 1, Hkv, n0, d)
+    q = big.expand(T, 1, 1, Hq, d).contiguous().to(dev)
+    k = torch.zeros((T, 1, 1, Hkv, d), dtype=torch.bfloat16, device=dev)
+    v = _bf16(rng, T, 1, 1, Hkv, d).to(dev)
+    a, b = (B.Cache(1, 1, Hq, Hkv, d, cap, cap - 80, 32, 16) for _ in range(2))
+    for c in (a, b):
+        B.dynts_prefill(c.ctx, 0, K0.to(dev), V0.to(dev), torch.tensor([n0], dtype=torch.int32, device=dev))
+    outs_a, outs_b = torch.zeros((T, 1, 1, Hq, d), dtype=torch.float32, device=dev), torch.zeros((T, 1, 1, Hq, d), dtype=torch.float32, device=dev)
+    B.dynts_decode_loop(a.ctx, T, q, k, v, outs_a, a.keep_idx, a.new_len, out_step_stride=outs_a[0].numel())
+    for t in range(T):
+        B.dynts_decode_step(b.ctx, 0, q[t, 0], k[t, 0], v[t, 0], outs_b[t, 0])
+    assert torch.equal(outs_a, outs_b)
+    alive = torch.cat([V0[0, :, :32], V0[0, :, 64:96], V0[0, :, 160:]], 1).double()
+    rows = torch.cat([alive, v[:, 0, 0].cpu().double().transpose(0, 1)], 1)
+    for t in range(T):
+        want = rows[:, :alive.shape[1] + t + 1].mean(1).repeat_interleave(Hq // Hkv, 0)
+        assert float((outs_a[t, 0, 0].cpu().double() - want).abs().max()) <= 1e-5
+
+
 @pytest.mark.parametrize("L,Nb,Hq,Hkv,d,cap", [(1, 3, 8, 2, 64, 200), (2, 2, 28, 4, 128, 700), (1, 2, 16, 1, 64, 2000), (2, 1, 32, 8, 128, 4544)])
 @pytest.mark.parametrize("stride", ["none", "part"])
 def test_loop_whose_steps_share_their_outputs(B, L, Nb, Hq, Hkv, d, cap, stride):
