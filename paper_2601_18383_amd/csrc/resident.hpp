@@ -544,10 +544,6 @@ __global__ __launch_bounds__(kResThreads) void merge_run_kernel(const ResidentPa
   const float *po = p.part_o + row * G * D, *pml = p.part_ml + row * G * 2;
   const size_t orow0 = (size_t)unit * G;  // (= b * Hq + h * G)
   const bool last = i + 1 == p.steps;
-  // Where every step's outputs go to one place, those of the last step that attended the sequence stay: the steps' workgroups have no order.
-  bool stays = true;
-  if (p.out_stride == 0)
-    for (int s = i + 1; s < p.steps; ++s) stays = stays && p.n_of[(size_t)s * p.Nb + b] < 0;
   auto merge = [&](auto N_) {
     constexpr int N = decltype(N_)::value;
     const int my_g = tid / N, my_j = tid % N;
@@ -607,11 +603,16 @@ __global__ __launch_bounds__(kResThreads) void merge_run_kernel(const ResidentPa
         p.mlprev[(orow0 + my_g) * 2 + 1] = l_all;
       }
     }
+    // Where every step's outputs go to one place, those of the last step that attended the sequence stay: the steps' workgroups have no
+    // order.  (Looked up here: in front of the merge its loads wait behind it, 11.6 instead of 7.4 us for 64 steps of 18 chunks.)
+    if (p.out_stride == 0)
+      for (int s = i + 1; s < p.steps; ++s)
+        if (p.n_of[(size_t)s * p.Nb + b] >= 0) return;
     float *out = p.out + (size_t)i * p.out_stride + orow0 * D;
 #pragma unroll
     for (int k = 0; k < NE; ++k) {
       const int idx = tid + k * kResThreads;
-      if (stays && idx < G * D) out[idx] = o_e[k] / sm_sum[idx / D];
+      if (idx < G * D) out[idx] = o_e[k] / sm_sum[idx / D];
     }
   };
   const int ne = (G * D + kResThreads - 1) / kResThreads;
