@@ -134,6 +134,8 @@ __global__ __launch_bounds__(kMlpThreads, 2) void mlp_kernel(const MlpParams p) 
 #pragma unroll
     for (int ft = 0; ft < FT; ++ft) wf[slot][ft] = __builtin_bit_cast(bf16x8, mlp_load(wbuf[ft], off));
   };
+#pragma unroll
+  for (int j = 0; j < DW; ++j) load_w(j, j);
   // What the end of the kernel needs is asked for here, too: a first read of it there would cost a trip to memory.
   // Element e of a thread's share of the sums: layer 1 takes f32x4 pieces, layer 2 single values.
   constexpr int NE = SECOND ? (NT * 256 + kMlpThreads - 1) / kMlpThreads : (NT * 64 + kMlpThreads - 1) / kMlpThreads;
@@ -178,18 +180,11 @@ __global__ __launch_bounds__(kMlpThreads, 2) void mlp_kernel(const MlpParams p) 
       for (int part = 0; part < PARTS; ++part)
         xf[slot][bt][part] = __builtin_bit_cast(bf16x8, mlp_load(xbuf, off + (bt * PARTS + part) * 1024));
     };
-    // (in the order of the loop's last steps: a wait counts loads in the order in which either path to it issued them, and in
-    // another order the one for a step's activations would be one for the weights just asked for)
 #pragma unroll
-    for (int j = 0; j < DW; ++j) {
-      if (j >= DW - DX) {
+    for (int j = 0; j < DX; ++j)
 #pragma unroll
-        for (int bt = 0; bt < BT; ++bt) load_x(j - (DW - DX), bt, j - (DW - DX));
-      }
-      load_w(j, j);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    for (int sb = 0; sb < n; sb += DW) {
+      for (int bt = 0; bt < BT; ++bt) load_x(j, bt, j);
+    auto round = [&](int sb) {
 #pragma unroll
       for (int j = 0; j < DW; ++j) {
         // (a tile's next activations are asked for as soon as its products have been issued; past the last step both
@@ -207,7 +202,14 @@ __global__ __launch_bounds__(kMlpThreads, 2) void mlp_kernel(const MlpParams p) 
         load_w(j, sb + j + DW);
         __builtin_amdgcn_sched_barrier(0);
       }
-    }
+    };
+    // (The first round by itself: a wait counts loads in the order in which either path to it issued them, and the ones above come in
+    // another order than a round's own; a loop entered with them would wait for weights it has just asked for.  us a call, so before / now, other
+    // weights each call: from the memory-side cache d = 2048, 16 sequences 13.9 / 13.5, 128 24.7 / 23.9; from HBM d = 3584, 32 27.9 / 27.5, 128 48.9 / 47.8,
+    // d = 4096, 32 31.4 / 31.2.  Asked for in a round's order instead, weights behind the biases, the cached ones take 12.9 and 24.6, but those from HBM
+    // 28.8, 48.6 and 32.6: there every moment counts by which the first weights leave earlier.)
+    round(0);
+    for (int sb = DW; sb < n; sb += DW) round(sb);
   } else {
     // A load covers 8 sequences x 128 bytes, which a wave turns into operands through LDS of its own
     unsigned char *xs = smem + wave * XBYTES;
@@ -227,17 +229,12 @@ __global__ __launch_bounds__(kMlpThreads, 2) void mlp_kernel(const MlpParams p) 
 #pragma unroll
       for (int i = 0; i < 2 * BT; ++i) raw[slot][i] = mlp_load(xbuf, x_row[i] + col);
     };
-    // (in the order of the loop's last steps, see above)
 #pragma unroll
-    for (int j = 0; j < DW; ++j) {
-      if (j % 2 == 0 && j >= DW - 2 * DX) load_x((j - (DW - 2 * DX)) / 2, (j - (DW - 2 * DX)) / 2);
-      load_w(j, j);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    for (int j = 0; j < DX; ++j) load_x(j, j);
     // the second layer's words, zeroed while the first loads are on their way
     for (uint32_t i = blockIdx.x * kMlpThreads + tid; i < p.n_clear; i += gridDim.x * kMlpThreads)
       reinterpret_cast<u32x4 *>(p.clear)[i] = u32x4{0u, 0u, 0u, 0u};
-    for (int sb = 0; sb < n; sb += DW) {
+    auto round = [&](int sb) {
 #pragma unroll
       for (int j = 0; j < DW; ++j) {
         if (j % 2 == 0) {
@@ -258,7 +255,9 @@ __global__ __launch_bounds__(kMlpThreads, 2) void mlp_kernel(const MlpParams p) 
         load_w(j, sb + j + DW);
         __builtin_amdgcn_sched_barrier(0);
       }
-    }
+    };
+    round(0);  // (by itself, see above)
+    for (int sb = DW; sb < n; sb += DW) round(sb);
     __syncthreads();  // the waves' buffers are used again below
   }
 
