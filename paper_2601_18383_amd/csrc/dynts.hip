@@ -519,8 +519,8 @@ int fused_step(dynts_ctx *ctx, int layer, const uint16_t *q, const uint16_t *k_n
 //   by the run's length, 2 / 3 / 4 / 8 / 16: 8 units of 1000 9.2 / 10.5, 8.9 / 7.7, 8.9 / 6.6, 8.7 / 4.7, 8.6 / 3.7; 512 units of 510, head_dim 64,
 //     15.3 / 15.5, 15.4 / 11.6, 15.0 / 10.3, 14.7 / 7.8, 14.6 / 6.5
 // Caches that the chip's registers do not hold are read again for every step, one launch each.
-// Not where every attend launch is to be timed or has a shape of the caller's, and not under capture: replays
-// take turns between the two places of the saved query step by step.
+// Not where every attend launch is to be timed or has a shape of the caller's, and not under capture: a replayed step finds and leaves
+// the saved query by itself.
 constexpr int kLeastRun = 3;
 int resident_run(const dynts_ctx *ctx, hipStream_t st) {
   const Plan &pl = ctx->plan;
@@ -565,7 +565,9 @@ int resident_steps(dynts_ctx *ctx, int layer, int steps, bool evict, const uint1
   p.kv_stride = (size_t)c.n_layers * c.batch * c.n_kv_heads * c.head_dim;
   p.out_stride = out_stride;
   p.steps = steps;
-  p.qprev = lv.qprev; p.qnext = lv.qnext; p.mlprev = lv.mlprev; p.nprev = lv.nprev;
+  // The two places of the saved query take turns step by step: the run leaves its last one where as many single steps would, so that
+  // recorded steps replayed behind it find it where they look for it.
+  p.qprev = lv.qprev; p.qnext = steps % 2 ? lv.qnext : lv.qprev; p.mlprev = lv.mlprev; p.nprev = lv.nprev;
   p.seq_cnt = reinterpret_cast<uint32_t *>(ctx->ws + ctx->plan.off_seq_cnt);
   p.cnt_stride = kCounterStride;
   p.status = ctx->status;
@@ -588,7 +590,7 @@ int resident_steps(dynts_ctx *ctx, int layer, int steps, bool evict, const uint1
   else launch_resident<64>(p, st);
   rc = launch_status();
   if (rc != DYNTS_OK) return rc;
-  if (track) ctx->qslot[layer] ^= 1;
+  if (track) ctx->qslot[layer] ^= steps % 2;
   ctx->pending[layer] = track ? (keep ? 2 : 1) : 0;
   if (keep) ctx->spill_layer = layer;
   return DYNTS_OK;

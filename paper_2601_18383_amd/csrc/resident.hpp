@@ -52,7 +52,7 @@ struct ResidentParams {
   int steps;
   // the deferred update (see AttendParams): the one owed from before (owed != 0), and where the last step's is kept
   const uint16_t *qprev;
-  uint16_t *qnext;
+  uint16_t *qnext;          // (behind an even number of steps the same place: written when every chunk's workgroup has read it)
   float *mlprev;
   int32_t *nprev;
   uint32_t *seq_cnt;        // [Nb][cnt_stride] arrival counters, zero between launches
@@ -496,10 +496,10 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const Resident
     if (!p.track) Sb[n_entry + r] = p.s_new ? p.s_new[(size_t)sm_step[r] * p.Nb * p.Hkv + unit] : 0.f;
   }
   const bool owes = p.track && last_attended;
-  if (owes && chunk == 0) {
+  if (!PART && owes) {  // (PART: merge_run_kernel)
     for (int i = tid; i < G * PIECES; i += kResThreads)
       store_u32x4(p.qnext + row0 * D + 8 * (size_t)i, *reinterpret_cast<const u32x4 *>(sm_in + ((p.steps - 1) & 1) * IN + (i / PIECES) * STRIDE + 16 * (i % PIECES)));
-    if (!PART && tid < G) {
+    if (tid < G) {
       p.mlprev[(row0 + tid) * 2] = stats.m[tid];
       p.mlprev[(row0 + tid) * 2 + 1] = stats.l[tid];
     }
@@ -519,7 +519,7 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const Resident
   }
 }
 
-// ---- the partials of a run's steps, merged: outputs, statistics, the sequences' words ---------------------------
+// ---- the partials of a run's steps, merged: outputs, statistics, what the next deferred update needs, the sequences' words ---------------------------
 // grid (units, steps), 512 threads; the groups of chunks and the order of every sum are attend_kernel's.
 template <int D>
 __global__ __launch_bounds__(kResThreads) void merge_run_kernel(const ResidentParams p) {
@@ -544,6 +544,10 @@ __global__ __launch_bounds__(kResThreads) void merge_run_kernel(const ResidentPa
   const float *po = p.part_o + row * G * D, *pml = p.part_ml + row * G * 2;
   const size_t orow0 = (size_t)unit * G;  // (= b * Hq + h * G)
   const bool last = i + 1 == p.steps;
+  // the last step's query, a piece of 16 bytes a thread: kept with its statistics
+  const bool keeps_q = last && p.track && tid < G * (D / 8);
+  u32x4 q_piece = u32x4{0u, 0u, 0u, 0u};
+  if (keeps_q) q_piece = load_u32x4(p.q + (size_t)i * p.q_stride + orow0 * D + 8 * (size_t)tid);
   auto merge = [&](auto N_) {
     constexpr int N = decltype(N_)::value;
     const int my_g = tid / N, my_j = tid % N;
@@ -603,6 +607,7 @@ __global__ __launch_bounds__(kResThreads) void merge_run_kernel(const ResidentPa
         p.mlprev[(orow0 + my_g) * 2 + 1] = l_all;
       }
     }
+    if (keeps_q) store_u32x4(p.qnext + orow0 * D + 8 * (size_t)tid, q_piece);
     // Where every step's outputs go to one place, those of the last step that attended the sequence stay: the steps' workgroups have no
     // order.  (Looked up here: in front of the merge its loads wait behind it, 11.6 instead of 7.4 us for 64 steps of 18 chunks.)
     if (p.out_stride == 0)
