@@ -50,6 +50,7 @@ typedef short i16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kTile = 32;           // cache slots one wave handles per iteration
+constexpr float kLowest = -3.4028234663852886e38f;  // the lowest finite value
 // A workgroup has W waves (4 or 8).
 
 struct AttendParams {
@@ -916,7 +917,8 @@ __global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL
         for (int j = 0; j < N; ++j) differs |= (uint32_t)(ask_o[k][j] >> 32) ^ p.tag;
       return differs == 0;
     };
-    float m_all = -INFINITY, l_all = 0.f, o_e[E];
+    // (finite: chunks without a finite logit weigh exp2(-inf - m_all) = 0 then, also where no other one has come before them)
+    float m_all = kLowest, l_all = 0.f, o_e[E];
 #pragma unroll
     for (int k = 0; k < E; ++k) o_e[k] = 0.f;
     for (int s0 = 0; s0 < chunks_now; s0 += N) {
@@ -930,7 +932,7 @@ __global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL
         float mn = mj;
 #pragma unroll
         for (int x = 1; x < N; x *= 2) mn = fmaxf(mn, __shfl_xor(mn, x));
-        mn = fmaxf(mn, m_all);  // finite: a chunk that has a partial has attended a slot
+        mn = fmaxf(mn, m_all);
         const float old = fast_exp2(m_all - mn), wj = fast_exp2(mj - mn);
         float l = wj * lj;
 #pragma unroll

@@ -552,7 +552,7 @@ __global__ __launch_bounds__(kResThreads) void merge_run_kernel(const ResidentPa
     constexpr int N = decltype(N_)::value;
     const int my_g = tid / N, my_j = tid % N;
     const bool asks = tid < 16 * N && my_g < G;
-    float m_all = -INFINITY, l_all = 0.f, o_e[NE];
+    float m_all = kLowest, l_all = 0.f, o_e[NE];  // (see attend_kernel)
 #pragma unroll
     for (int k = 0; k < NE; ++k) o_e[k] = 0.f;
     for (int s0 = 0; s0 < chunks; s0 += N) {

@@ -96,3 +96,40 @@ def test_replays_around_runs(B, Nb, Hq, Hkv, d, cap):
     for c in (a, b):
         B.dynts_update_scores(c.ctx, 0)
     _same(a, b, 1, Nb)
+
+
+# merges of four, of eight and of 32 chunks of 256 slots at a time: the slots of the first group, and more, have no finite logit
+@pytest.mark.parametrize("Hq,Hkv,d,cap,dead", [(8, 2, 128, 1600, 1024), (8, 2, 64, 1600, 1300), (8, 1, 128, 2700, 2048), (8, 2, 128, 8900, 8192)])
+@pytest.mark.parametrize("paged", [False, True])
+def test_chunks_whose_logits_are_all_minus_infinity(B, Hq, Hkv, d, cap, dead, paged):
+    """They weigh nothing, the new tokens' among them: every other slot has a logit of zero, so the outputs are the mean of their V rows
+    (sums of fp32: 1e-5), and each gains 1 / their number from each of the group's heads (an exponential and a reciprocal: 1e-6 of it)."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(cap)
+    T, n0 = 5, cap - 40
+    big = torch.tensor(3e38).bfloat16()
+    K0 = torch.zeros((1, Hkv, n0, d), dtype=torch.bfloat16, device=DEV)
+    K0[:, :, :dead] = -big
+    V0 = _normal(g, 1, Hkv, n0, d)
+    q, k = big.expand(T, 1, 1, Hq, d).contiguous().to(DEV), (-big).expand(T, 1, 1, Hkv, d).contiguous().to(DEV)
+    v = _normal(g, T, 1, 1, Hkv, d)
+    a, b = ((B.PagedCache if paged else B.Cache)(1, 1, Hq, Hkv, d, cap, cap - 80, 32, 16) for _ in range(2))
+    for c in (a, b):
+        B.dynts_prefill(c.ctx, 0, K0, V0, torch.tensor([n0], dtype=torch.int32, device=DEV))
+        c.n_prompt.fill_(0)
+        c.S.zero_()
+    want = V0[0, :, dead:].double().mean(1).repeat_interleave(Hq // Hkv, 0)
+    got, single = (torch.zeros(T, 1, 1, Hq, d, device=DEV) for _ in range(2))
+    B.dynts_decode_loop(a.ctx, T, q, k, v, got, a.keep_idx, a.new_len, out_step_stride=got[0].numel())
+    _single_steps(B, b, (q, k, v), single)
+    alone, lse = torch.zeros(1, Hq, d, device=DEV), torch.zeros(1, Hq, device=DEV)
+    for c in (a, b):
+        B.dynts_update_scores(c.ctx, 0)
+    gain = torch.zeros(Hkv, n0 + T, dtype=torch.float64, device=DEV)
+    gain[:, dead:n0] = T * (Hq // Hkv) / (n0 - dead)
+    for c in (a, b):
+        assert float((c.S[0, 0, :, :n0 + T].double() - gain).abs().max()) <= 1e-6 * float(gain.max())
+    B.dynts_decode_attend(b.ctx, 0, q[0, 0], alone, lse=lse)
+    for x in (got, single, alone):
+        assert float((x.double().view(-1, Hq, d) - want).abs().max()) <= 1e-5
+    assert float((lse.double() - np.log(n0 - dead)).abs().max()) <= 1e-5
