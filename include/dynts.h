@@ -81,8 +81,8 @@ const char *dynts_strerror(int code);
 int dynts_create(const dynts_config *cfg, dynts_ctx **out);
 int dynts_destroy(dynts_ctx *ctx);
 
-/* Bytes of device scratch the kernels need for `cfg` (split partials, the saved query and
- * softmax statistics of the deferred score update).  0 if cfg is invalid. */
+/* Bytes of device scratch the kernels need for `cfg` (split partials, the saved query and softmax statistics of the
+ * deferred score update, the kept logits of one layer).  0 if cfg is invalid. */
 size_t dynts_workspace_bytes(const dynts_config *cfg);
 
 /* Launch shape of the attention kernel, for tuning and for tests that must reach a particular shape at a
@@ -92,7 +92,10 @@ size_t dynts_workspace_bytes(const dynts_config *cfg);
  * workspace layout: call it before dynts_bind (it unbinds), and size the workspace with
  * dynts_ctx_workspace_bytes. */
 int dynts_set_launch_shape(dynts_ctx *ctx, int32_t target_workgroups, int32_t waves_per_workgroup);
-/* Bytes of workspace this context needs (= dynts_workspace_bytes(cfg) unless the launch shape was changed). */
+/* Bytes of workspace with which this context has all its forms: what it needs (dynts_workspace_bytes(cfg), another size if the launch
+ * shape was changed) and behind it, on caches whose steps dynts_decode_loop can make in runs and that are split over several workgroups,
+ * room for the partials of 16 to 64 steps, 4 * (head_dim + 2) bytes a step, workgroup and query head of its group, 64 MB at most.  A workspace
+ * without that room is accepted: the loop then makes every step a launch of its own.  Paged contexts never use it. */
 size_t dynts_ctx_workspace_bytes(const dynts_ctx *ctx);
 
 /* Attach the caller's device buffers (layout above).  `workspace` must be 256-byte aligned

@@ -351,7 +351,9 @@ class PagedCache:
         self.next_pos = torch.zeros((L, Nb), dtype=torch.int32, device=dev)
         self.n_prompt = torch.zeros((Nb,), dtype=torch.int32, device=dev)
         self.status = torch.zeros((1,), dtype=torch.int32, device=dev)
-        self.workspace = torch.zeros((dynts_ctx_workspace_bytes(self.ctx),), dtype=torch.uint8, device=dev)
+        # (without the room for runs of steps, which paged contexts never make)
+        need = dynts_workspace_bytes(self.cfg) if launch_shape is None else dynts_ctx_workspace_bytes(self.ctx)
+        self.workspace = torch.zeros((need,), dtype=torch.uint8, device=dev)
         self.keep_idx = torch.zeros((Nb, Hkv, cap), dtype=torch.int32, device=dev)
         self.new_len = torch.zeros((Nb,), dtype=torch.int32, device=dev)
         dynts_bind_paged(self.ctx, self.K_pool, self.V_pool, self.block_table, self.free_stack, self.free_top, self.S,

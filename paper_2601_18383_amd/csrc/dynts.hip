@@ -36,10 +36,12 @@ struct Plan {
   int G = 0, waves = 0, chunk = 0, nsplit = 0;
   size_t off_part_o = 0, off_part_ml = 0, off_unit_cnt = 0, off_seq_cnt = 0, off_qprev = 0, off_mlprev = 0, off_nprev = 0, off_spill = 0;
   int cap_pad = 0;
-  // runs of steps (resident_kernel): a cache of several chunks, each of one tile a wave; steps of a run whose partials there is room for, or 0
+  size_t bytes = 0;  // that every call needs
+  // runs of steps (resident_kernel): a cache of several chunks, each of one tile a wave; steps of a run whose partials the room behind has place
+  // for, or 0; the bytes of both
   int run_steps = 0;
   size_t off_run_o = 0, off_run_ml = 0, off_run_stats = 0, off_run_n = 0, off_run_rec = 0;
-  size_t bytes = 0;
+  size_t run_bytes = 0;
 };
 
 int check_config(const dynts_config *c) {
@@ -91,7 +93,9 @@ Plan make_plan(const dynts_config &c, int target_wgs, int waves) {
   p.cap_pad = (c.capacity + dynts::kTile - 1) / dynts::kTile * dynts::kTile;
   p.off_spill = off;
   if (c.score_mode == DYNTS_SCORE_ACCUMULATE) off = align_up(off + (size_t)units * p.G * p.cap_pad * sizeof(float));
-  // Room for the partials of a run's steps: of as many as lie between two triggers, but 16 to 64, and 64 MB of them at most.
+  p.bytes = off;
+  // Room for the partials of a run's steps: of as many as lie between two triggers, but 16 to 64, and 64 MB of them at most (23 steps or more:
+  // chunks of one tile a wave are at most 341 for all units).
   if (target_wgs == 0 && waves == 0 && p.nsplit > 1 && p.nsplit == quanta) {
     const long long fit = (64ll << 20) / (long long)(rows * (c.head_dim + 2) * sizeof(float));
     const int between = c.evict_every < 16 ? 16 : c.evict_every < dynts::kPartSteps ? c.evict_every : dynts::kPartSteps;
@@ -103,7 +107,7 @@ Plan make_plan(const dynts_config &c, int target_wgs, int waves) {
     p.off_run_n = off;     off = align_up(off + R * c.batch * sizeof(int32_t));
     p.off_run_rec = off;   off = align_up(off + (size_t)c.batch * 4 * sizeof(int32_t));
   }
-  p.bytes = off;
+  p.run_bytes = off;
   return p;
 }
 
@@ -119,6 +123,7 @@ struct dynts_ctx {
   float *S = nullptr;
   int32_t *pos = nullptr, *seq_len = nullptr, *next_pos = nullptr, *n_prompt = nullptr, *status = nullptr;
   unsigned char *ws = nullptr;
+  int run_steps = 0;                   // the plan's, where the workspace has the room for them
   // per layer: a score update is owed (1: by a pass over K, 2: from kept logits; 3: either, the next fused step's pass
   // over K or the kept logits, whichever is asked for first)
   std::vector<unsigned char> pending;
@@ -525,9 +530,9 @@ constexpr int kLeastRun = 3;
 int resident_run(const dynts_ctx *ctx, hipStream_t st) {
   const Plan &pl = ctx->plan;
   const bool whole = pl.nsplit == 1 && ctx->cfg.capacity <= dynts::kResTiles * dynts::kResSlots;
-  if (ctx->paged || ctx->shaped || !(whole || pl.run_steps >= kLeastRun)) return 0;
+  if (ctx->paged || ctx->shaped || !(whole || ctx->run_steps > 0)) return 0;
   if (ctx->ev_start || ctx->ev_list_next < ctx->ev_list_start.size() || capturing(st)) return 0;
-  return whole ? dynts::kResSteps : pl.run_steps;
+  return whole ? dynts::kResSteps : ctx->run_steps;
 }
 
 template <int D>
@@ -870,7 +875,7 @@ int dynts_set_launch_shape(dynts_ctx *ctx, int32_t target_workgroups, int32_t wa
   return DYNTS_OK;
 }
 
-size_t dynts_ctx_workspace_bytes(const dynts_ctx *ctx) { return ctx ? ctx->plan.bytes : 0; }
+size_t dynts_ctx_workspace_bytes(const dynts_ctx *ctx) { return ctx ? ctx->plan.run_bytes : 0; }
 
 size_t dynts_workspace_bytes(const dynts_config *cfg) {
   if (check_config(cfg) != DYNTS_OK) return 0;
@@ -884,6 +889,7 @@ int dynts_bind(dynts_ctx *ctx, uint16_t *K, uint16_t *V, float *S, int32_t *pos,
   if ((reinterpret_cast<uintptr_t>(K) | reinterpret_cast<uintptr_t>(V)) % 16) return DYNTS_EINVAL;
   ctx->K = K; ctx->V = V; ctx->S = S; ctx->pos = pos; ctx->seq_len = seq_len; ctx->next_pos = next_pos;
   ctx->n_prompt = n_prompt; ctx->ws = static_cast<unsigned char *>(workspace); ctx->status = status;
+  ctx->run_steps = workspace_bytes >= ctx->plan.run_bytes ? ctx->plan.run_steps : 0;
   ctx->paged = false; ctx->block_table = nullptr; ctx->free_stack = nullptr; ctx->free_top = nullptr;
   ctx->max_pages = ctx->n_pages = 0;
   ctx->pending.assign(ctx->pending.size(), 0);

@@ -216,3 +216,25 @@ def test_predictor_scratch_for_a_batch_serves_every_smaller_one(B, d, m1, m2):
         w = B.dynts_predictor(d, m1, m2, 1, packed, 0, 0, 0, 0, 0, 0)
         sizes = [B.dynts_predict_scratch_bytes(w, nb) for nb in range(1, 129)]
         assert sizes[0] > 0 and sizes == sorted(sizes)
+
+
+@pytest.mark.parametrize("kw,runs", [
+    (dict(capacity=400), True), (dict(batch=1, n_kv_heads=8, capacity=4544), True), (dict(batch=32, n_q_heads=28, n_kv_heads=4, capacity=512), True),
+    (dict(capacity=256, budget=100), False),           # one chunk: runs need no room
+    (dict(batch=32, capacity=2496, n_q_heads=28, n_kv_heads=4), False)])  # chunks of several tiles a wave: no runs
+def test_workspace_without_the_room_for_runs(B, kw, runs):
+    """What every call needs is the size of a context whose launch shape is the caller's (the same shape, and no runs); the room for runs
+    comes on top, 64 MB and the runs' statistics at most, and is not asked for by a bind."""
+    cfg = _cfg(B, **kw)
+    one = C.c_void_p(16)
+    ctx = B.dynts_create(cfg)
+    need, full = B.dynts_workspace_bytes(cfg), B.dynts_ctx_workspace_bytes(ctx)
+    assert (full > need) == runs and full - need < 80 << 20
+    for size, code in ((full, 0), (need, 0), (need - 1, B.DYNTS_EWORKSPACE)):
+        assert B.lib.dynts_bind(ctx, *([one] * 7), C.c_void_p(256), size, one) == code
+    page = [one, one, 4096, one, (cfg.capacity + 63) // 64, one, one, one, one, one, one, one, C.c_void_p(256)]
+    assert B.lib.dynts_bind_paged(ctx, *page, need, one) == 0
+    assert B.lib.dynts_bind_paged(ctx, *page, need - 1, one) == B.DYNTS_EWORKSPACE
+    B.dynts_set_launch_shape(ctx, 256, 8)
+    assert B.dynts_ctx_workspace_bytes(ctx) == need
+    B.dynts_destroy(ctx)

@@ -133,3 +133,25 @@ def test_chunks_whose_logits_are_all_minus_infinity(B, Hq, Hkv, d, cap, dead, pa
     for x in (got, single, alone):
         assert float((x.double().view(-1, Hq, d) - want).abs().max()) <= 1e-5
     assert float((lse.double() - np.log(n0 - dead)).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("Nb,Hq,Hkv,d,cap", FORMS[2:])
+@pytest.mark.parametrize("room", ["none", "part", "all"])
+def test_loops_with_and_without_room_for_runs(B, Nb, Hq, Hkv, d, cap, room):
+    """A workspace that ends before, inside and behind the room for the partials of runs: the same bits, and nothing written behind it."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(cap + 3)
+    T = 20
+    a, b = _caches(B, g, 1, Nb, Hq, Hkv, d, cap, torch.tensor(cap - 50))
+    need, full = B.dynts_workspace_bytes(a.cfg), B.dynts_ctx_workspace_bytes(a.ctx)
+    size = {"none": need, "part": (need + full) // 2, "all": full}[room]
+    space = torch.zeros(full + 4096, dtype=torch.uint8, device=DEV)
+    space[size:] = 0xA5
+    B.dynts_bind(a.ctx, a.K, a.V, a.S, a.pos, a.seq_len, a.next_pos, a.n_prompt, space[:size], a.status)
+    x = _tokens(g, T, 1, Nb, Hq, Hkv, d)
+    got, want = (torch.zeros(T, 1, Nb, Hq, d, device=DEV) for _ in range(2))
+    B.dynts_decode_loop(a.ctx, T, *x, got, a.keep_idx, a.new_len, out_step_stride=got[0].numel())
+    _single_steps(B, b, x, want)
+    assert torch.equal(got, want) and bool((space[size:] == 0xA5).all())
+    assert bool(space[need:size].any()) == (room == "all")  # (that is where a run leaves its partials)
+    _same(a, b, 1, Nb)
