@@ -14,8 +14,9 @@ def B():
 
 
 DEV = "cuda:0"
-# one tile a wave, two, and several chunks with merges of four, of eight and of 32 at a time: Nb, Hq, Hkv, d, cap
-FORMS = [(3, 8, 2, 64, 200), (45, 32, 8, 128, 490), (2, 28, 4, 128, 700), (2, 8, 1, 128, 1500), (1, 32, 8, 128, 4544)]
+# one tile a wave, two, and several chunks with merges of four, of eight and of 32 at a time, to the most chunks there are: Nb, Hq, Hkv, d, cap
+FORMS = [(3, 8, 2, 64, 200), (45, 32, 8, 128, 490), (2, 28, 4, 128, 700), (2, 8, 1, 128, 1500), (1, 32, 8, 128, 4544), (1, 16, 1, 64, 20000),
+         (1, 4, 1, 128, 65536)]
 
 
 def _normal(g, *shape, scale=1.0):
@@ -96,6 +97,74 @@ def test_replays_around_runs(B, Nb, Hq, Hkv, d, cap):
     for c in (a, b):
         B.dynts_update_scores(c.ctx, 0)
     _same(a, b, 1, Nb)
+
+
+@pytest.mark.parametrize("Nb,Hq,Hkv,d,cap", FORMS)
+@pytest.mark.parametrize("stride", ["none", "slab"])
+def test_runs_past_full_caches(B, Nb, Hq, Hkv, d, cap, stride):
+    """Sequences that fill up at different steps of a run, one before it: their later steps are dropped, outputs left alone, the status
+    bit set, no update owed by them."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(cap + 1)
+    L, T = 2, 30
+    lens = torch.tensor([cap - (0, 7, T - 1, 40, 19)[(i + 1) % 5] for i in range(Nb)], dtype=torch.int32)
+    a, b = _caches(B, g, L, Nb, Hq, Hkv, d, cap, lens)
+    active = (torch.rand((T, Nb), generator=g, device=DEV) < 0.9).to(torch.uint8)
+    step = L * Nb * Hq * d if stride == "slab" else 0
+    got, want = (torch.full(((T if step else 1) * L * Nb * Hq * d,), 7.0, device=DEV) for _ in range(2))
+    for part in range(2):  # an update of the first is owed to the second
+        x = _tokens(g, T, L, Nb, Hq, Hkv, d)
+        B.dynts_decode_loop(a.ctx, T, *x, got, a.keep_idx, a.new_len, active=active, out_step_stride=step)
+        _single_steps(B, b, x, want.view(-1, L, Nb, Hq, d).expand(T, L, Nb, Hq, d), active)
+        assert torch.equal(got, want) and bool((got != 7.0).any())
+        _same(a, b, L, Nb)
+    assert int(a.status.item()) == 1
+    for l in range(L):
+        B.dynts_update_scores(a.ctx, l)
+        B.dynts_update_scores(b.ctx, l)
+    _same(a, b, L, Nb)
+
+
+@pytest.mark.parametrize("Nb,Hq,Hkv,d,cap", FORMS)
+@pytest.mark.parametrize("before", ["attend 0", "attend 0, attend 1", "hinted 0", "hinted 0, hinted 1", "hinted 1, attend 0"])
+@pytest.mark.parametrize("trigger", [False, True])
+def test_runs_behind_updates_owed_in_every_form(B, Nb, Hq, Hkv, d, cap, before, trigger):
+    """A run begins behind an unfused attention (whose update may be made from its kept logits or by a pass over K) or behind an announced
+    step (from its kept logits alone), on the same layer or the other one, which shares the room for them."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(cap + 2)
+    L, T = 2, 12
+    a, b = _caches(B, g, L, Nb, Hq, Hkv, d, cap, torch.tensor(cap - 40))
+    one = _tokens(g, 1, L, Nb, Hq, Hkv, d)
+    out = torch.zeros(L, Nb, Hq, d, device=DEV)
+    for c in (a, b):
+        for what in before.split(", "):
+            kind, l = what.split()
+            l = int(l)
+            if kind == "attend":
+                B.dynts_decode_attend(c.ctx, l, one[0][0, l], out[l])
+            else:
+                B.dynts_hint_trigger(c.ctx, l)
+                B.dynts_decode_step(c.ctx, l, one[0][0, l], one[1][0, l], one[2][0, l], out[l])
+    x = _tokens(g, T, L, Nb, Hq, Hkv, d)
+    got, want = (torch.zeros(T, L, Nb, Hq, d, device=DEV) for _ in range(2))
+    flags = torch.tensor([0] * (T - 1) + [int(trigger)], dtype=torch.uint8)
+    B.dynts_decode_loop(a.ctx, T, *x, got, a.keep_idx, a.new_len, evict_steps=flags, out_step_stride=got[0].numel())
+    _single_steps(B, b, [y[:T - 1] for y in x], want)
+    for l in range(L):
+        if trigger:
+            B.dynts_hint_trigger(b.ctx, l)
+        B.dynts_decode_step(b.ctx, l, x[0][-1, l], x[1][-1, l], x[2][-1, l], want[-1, l])
+        if trigger:
+            B.dynts_select_evict(b.ctx, l, b.keep_idx, b.new_len, b.cfg.budget)
+            B.dynts_compact(b.ctx, l, b.keep_idx, b.new_len)
+    assert torch.equal(got, want)
+    _same(a, b, L, Nb)
+    for l in range(L):
+        B.dynts_update_scores(a.ctx, l)
+        B.dynts_update_scores(b.ctx, l)
+    _same(a, b, L, Nb)
+    assert int(a.status.item()) == 0
 
 
 # merges of four, of eight and of 32 chunks of 256 slots at a time: the slots of the first group, and more, have no finite logit
