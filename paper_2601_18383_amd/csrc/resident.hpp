@@ -100,6 +100,8 @@ __device__ __forceinline__ float sum_over_rows(float x) {
 template <int D, int T, bool PART>
 __global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const ResidentParams p) {
   static_assert(!PART || T == 1, "a chunk is a tile a wave");
+  constexpr bool FULL = D == 128 && T == 2;  // no register of the 256 is left in the loop (32 steps and their trigger on 512 units of 510 slots, 7
+                                             // heads: 264 us with two values more, in scratch memory, 262 so; the other forms have room)
   constexpr int KS = D / 32, CB = D / 16, PIECES = D / 8;
   constexpr int VROWS = 64 / PIECES, VIT = kTile / VROWS;  // rows of one wave-wide 16-byte load
   constexpr int STRIDE = 2 * D + 32;                       // bytes per staged row (see attend_kernel)
@@ -253,6 +255,7 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const Resident
   }
   __syncthreads();  // the tiles' LDS becomes the outputs'; every wave has its operands
   __builtin_amdgcn_s_waitcnt(0x0f70);  // (every load so far: one that the loop might still be owed would be waited for in each round)
+  if (FULL && tid == 0) sm_hdr[4] = (int32_t)seq_ticket;
   stage(0, piece_a);
   fetch(1, piece_b);
   fetch(2, piece_a);
@@ -478,6 +481,8 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const Resident
 
   // ---- to memory: scores, new rows, positions, what the next deferred update needs, the sequence's words -----------
   // (PART: run_scores_kernel makes the run's updates and begins the new slots' scores)
+  int at_end = FULL ? 64 * wave + lane : tid;  // (formed anew, so that nothing derived from it is kept over the loop)
+  if (FULL) asm volatile("" : "+v"(at_end));
 #pragma unroll
   for (int j = 0; j < T; ++j) {
     const int tok = first(j) + lane;
@@ -485,31 +490,31 @@ __global__ __launch_bounds__(kResThreads, 2) void resident_kernel(const Resident
   }
   const int n_new = n - n_entry, pos0 = sm_hdr[2];
   const int lo = PART ? kResSlots * chunk - n_entry : 0, r_lo = lo > 0 ? lo : 0, r_hi = PART && lo + kResSlots < n_new ? lo + kResSlots : n_new;
-  for (int i = tid; i < 2 * (r_hi - r_lo) * PIECES; i += kResThreads) {
+  for (int i = at_end; i < 2 * (r_hi - r_lo) * PIECES; i += kResThreads) {
     const bool v = i >= (r_hi - r_lo) * PIECES;
     const int at = v ? i - (r_hi - r_lo) * PIECES : i, r = r_lo + at / PIECES, piece = 8 * (at % PIECES);
     const size_t from = (size_t)sm_step[r] * p.kv_stride + (size_t)unit * D + piece;
     store_u32x4((v ? Vb : Kb) + (size_t)(n_entry + r) * D + piece, load_u32x4((v ? p.v_new : p.k_new) + from));
   }
-  for (int r = r_lo + tid; r < r_hi; r += kResThreads) {
+  for (int r = r_lo + at_end; r < r_hi; r += kResThreads) {
     p.pos[(size_t)unit * p.cap + n_entry + r] = pos0 + r;
     if (!p.track) Sb[n_entry + r] = p.s_new ? p.s_new[(size_t)sm_step[r] * p.Nb * p.Hkv + unit] : 0.f;
   }
   const bool owes = p.track && last_attended;
   if (!PART && owes) {  // (PART: merge_run_kernel)
-    for (int i = tid; i < G * PIECES; i += kResThreads)
+    for (int i = at_end; i < G * PIECES; i += kResThreads)
       store_u32x4(p.qnext + row0 * D + 8 * (size_t)i, *reinterpret_cast<const u32x4 *>(sm_in + ((p.steps - 1) & 1) * IN + (i / PIECES) * STRIDE + 16 * (i % PIECES)));
-    if (tid < G) {
-      p.mlprev[(row0 + tid) * 2] = stats.m[tid];
-      p.mlprev[(row0 + tid) * 2 + 1] = stats.l[tid];
+    if (at_end < G) {
+      p.mlprev[(row0 + at_end) * 2] = stats.m[at_end];
+      p.mlprev[(row0 + at_end) * 2 + 1] = stats.l[at_end];
     }
   }
-  if (n_dropped > 0 && h == 0 && chunk == 0 && tid == 0) atomicOr(p.status, 1);
+  if (n_dropped > 0 && h == 0 && chunk == 0 && at_end == 0) atomicOr(p.status, 1);
   if (PART) {
-    if (h == 0 && chunk == 0 && tid < 4) p.rec[4 * b + tid] = tid == 0 ? n_entry : tid == 1 ? n : tid == 2 ? pos0 + n_new : (int)last_attended;
+    if (h == 0 && chunk == 0 && at_end < 4) p.rec[4 * b + at_end] = at_end == 0 ? n_entry : at_end == 1 ? n : at_end == 2 ? pos0 + n_new : (int)last_attended;
     return;
   }
-  if (tid == 0 && seq_ticket == (uint32_t)p.Hkv - 1) {
+  if (at_end == 0 && (FULL ? (uint32_t)sm_hdr[4] : seq_ticket) == (uint32_t)p.Hkv - 1) {
     __hip_atomic_store(p.seq_cnt + (size_t)b * p.cnt_stride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (p.track) p.nprev[b] = owes ? n : 0;
     if (n_new > 0) {

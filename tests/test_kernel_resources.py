@@ -65,3 +65,11 @@ def test_steps_on_large_paged_caches_of_head_dim_64_keep_two_workgroups_per_comp
     assert len(burst) == 1
     for name, k in burst.items():
         assert k["vgpr_count"] <= 128 and 2 * k["group_segment_fixed_size"] <= 160 * 1024, name
+
+
+def test_kernels_for_runs_of_steps_do_not_spill(kernels):
+    """The cache stays in registers from the first step to the last: none of it, and nothing else, in scratch memory.  Two waves a SIMD."""
+    run = {n: k for n, k in kernels.items() if re.search(r"(resident|merge_run|run_scores)_kernelILi(64|128)E", n)}
+    assert len(run) == 10  # one and two tiles a wave, chunks; the two kernels behind them
+    for name, k in run.items():
+        assert k["vgpr_spill_count"] == 0 and k["vgpr_count"] <= 256 and k["group_segment_fixed_size"] <= 160 * 1024, name
