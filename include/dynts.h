@@ -231,8 +231,11 @@ int dynts_compact(dynts_ctx *ctx, int32_t layer, const uint8_t *trigger, const i
  *   out    fp32 [L][Nb][Hq][d], overwritten every step (out_step_stride = 0) or one slab
  *          per step (out_step_stride = L*Nb*Hq*d elements)
  *   keep_idx int32 [Nb][Hkv][cap], new_len int32 [Nb]: scratch for the triggers.
- * On dense caches that the chip's registers hold, runs of steps between two triggers are made a layer at a time, by one to three launches,
- * with the results of a launch per step; launches whose kernel events are asked for (below), and recorded ones, stay one per step. */
+ * On dense caches that the chip's registers hold, runs of three or more steps between two triggers are made a layer at a time, by one to three
+ * launches, with the results of a launch per step, and the cache is read once a run.  That serves callers who have the inputs of several steps in
+ * hand: replay of a known text, teacher forcing, scoring.  A model that forms step t + 1's query from step t's output calls with n_steps = 1, and
+ * pays a launch a step.  Launches whose kernel events are asked for (below), recorded ones, and those on a workspace without the
+ * room that dynts_ctx_workspace_bytes counts, stay one per step. */
 int dynts_decode_loop(dynts_ctx *ctx, int32_t n_steps, const uint16_t *q, const uint16_t *k_new,
                       const uint16_t *v_new, const float *s_new, const uint8_t *active,
                       const uint8_t *evict_steps, const uint8_t *trigger, float *out,

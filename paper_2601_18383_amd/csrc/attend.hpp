@@ -26,12 +26,12 @@
 //     goes to the workspace and the LAST workgroup of the (sequence, KV head) to arrive
 //     (device-scope counter) merges the partials, writes `out`, and saves the query and the
 //     statistics that the next step's score update needs.  Every workgroup checks in on a
-//     per-sequence counter behind its first tile; the last one to do so advances seq_len / next_pos.
+//     per-sequence counter behind its first tile (kStream: in front of it); the last one to do so advances seq_len / next_pos.
 //     No second kernel, no host round trip.
 //   * the loop waits for no more than it uses: loads are waited for by their number, so every way through a tile issues the same ones in the
 //     same order (no branch around V's part, one loop per way of loading, page numbers by the scalar cache).  Where the wait for the next
-//     tile's K rows had been one for its V rows, and on pages one for everything: 128 units of 2464 slots 30.2 -> 29.5 us a step, on pages
-//     31.2 -> 30.5, two layers of 512 units of 2640 111.7 -> 110.4, of 1190 50.1 -> 49.1.
+//     tile's K rows had been one for its V rows, and on pages one for everything: 64 steps and a trigger on 128 units of 2464 slots 1970 -> 1922 us, on
+//     pages 2009 -> 1975; 8 steps of four layers of 512 units of 1184 1850 -> 1772; 16 of two layers of 512 of 2624 3580 -> 3535.
 //   * with APPEND the new token's K/V row is written to its slot by one workgroup and enters the
 //     softmax as the initial state of the first wave (max = q.k_new, sum = 1, output = v_new), so
 //     no wave has to wait for the row to become visible.
@@ -255,7 +255,9 @@ __global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL
   uint16_t *Vb = PAGED ? p.V : p.V + unit * (size_t)p.cap * D;
   const int32_t *tb = PAGED ? p.block_table + unit * (size_t)p.max_pages : nullptr;
   // Looked up through the scalar cache: as a vector load, whose answer comes behind those of all loads in flight, a lookup a tile had the
-  // wave wait for its next tile's rows.  (What a launch writes, the page that its appended row opens, it does not read.)
+  // wave wait for its next tile's rows.  (One entry may be written meanwhile, that of the page which the appended row opens.  A wave whose first tile
+  // lies there may find the old or the new value, once or each time: every use clamps it into the pool, and the tile's rows lie past the
+  // sequence, so they are masked.)
   const auto *tb_scalar = (const __attribute__((address_space(4))) int32_t *)tb;
   // Paged addressing of one tile: the tile start is first pulled back into the tile that holds row end-1
   // (so every clamped row stays in ONE page); the tile is then loaded relative to that page: base = pool +
@@ -406,7 +408,9 @@ __global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL
   // (they went through LDS above), so the atomic is issued after they completed.  The last workgroup
   // to check in advances the three words -- by then no workgroup of the sequence has a read of them
   // outstanding.  It is issued behind the first tile (answers come back in order: a wait for one of the first loads would be
-  // a wait for the atomic as well) and its answer is looked at when the waves have been combined.
+  // a wait for the atomic as well) and its answer is looked at when the waves have been combined.  In the kStream form, whose two loops both may
+  // begin with the first tile, it is issued in front of that tile: 8 steps of four layers of 512 units of 1184 slots 1772 us so, 1779 with it
+  // behind all tiles, 1830 with the first tile of either loop by itself and the check-in behind it (two layers of 512 units of 2624: the same three times).
   uint32_t seq_ticket = 0xffffffffu;
   auto seq_checkin = [&]() {
     if (ATTEND && tid == 0) seq_ticket = draw_ticket(p.seq_cnt + (size_t)b * p.cnt_stride);

@@ -523,7 +523,8 @@ int fused_step(dynts_ctx *ctx, int layer, const uint16_t *q, const uint16_t *k_n
 //     head_dim 64, 2 units of 400 6.7 / 2.3, 128 of 510 7.7 / 2.9, 32 of 2000 8.4 / 2.6
 //   by the run's length, 2 / 3 / 4 / 8 / 16: 8 units of 1000 9.2 / 10.5, 8.9 / 7.7, 8.9 / 6.6, 8.7 / 4.7, 8.6 / 3.7; 512 units of 510, head_dim 64,
 //     15.3 / 15.5, 15.4 / 11.6, 15.0 / 10.3, 14.7 / 7.8, 14.6 / 6.5
-// Caches that the chip's registers do not hold are read again for every step, one launch each.
+// Caches that the chip's registers do not hold are read again for every step, one launch each.  (Only callers who hand over the inputs of three or
+// more steps at once have runs: a decoder that forms each query from the step before pays a launch a step.)
 // Not where every attend launch is to be timed or has a shape of the caller's, and not under capture: a replayed step finds and leaves
 // the saved query by itself.
 constexpr int kLeastRun = 3;
