@@ -257,7 +257,7 @@ __global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL
   // Looked up through the scalar cache: as a vector load, whose answer comes behind those of all loads in flight, a lookup a tile had the
   // wave wait for its next tile's rows.  (One entry may be written meanwhile, that of the page which the appended row opens.  A wave whose first tile
   // lies there may find the old or the new value, once or each time: every use clamps it into the pool, and the tile's rows lie past the
-  // sequence, so they are masked.)
+  // sequence, so they are masked.  The compiler takes the table as constant and may look an entry up again for each use of it.)
   const auto *tb_scalar = (const __attribute__((address_space(4))) int32_t *)tb;
   // Paged addressing of one tile: the tile start is first pulled back into the tile that holds row end-1
   // (so every clamped row stays in ONE page); the tile is then loaded relative to that page: base = pool +
@@ -265,8 +265,9 @@ __global__ __launch_bounds__(W * 64, min_waves(D, W, APPEND, PAGED, LARGE, SPILL
   auto page_of = [&](int tp) -> int {
     int pi = tp / kPageSlots;
     pi = pi < p.max_pages ? pi : p.max_pages - 1;
-    int pg = tb_scalar[pi];
-    return pg < 0 ? 0 : (pg >= p.n_pages ? p.n_pages - 1 : pg);  // never followed out of the pool
+    // never followed out of the pool (least, then greatest, so that the value looked up has one use: see above)
+    const int pg = __builtin_elementwise_min(tb_scalar[pi], p.n_pages - 1);
+    return __builtin_elementwise_max(pg, 0);
   };
   auto clamp_tile = [&](int tt, int end) -> int {
     const int last_tile = (end - 1) & ~(kTile - 1);
