@@ -27,7 +27,8 @@
 // per chunk counts.  32x32 tiles take half the MFMA issue slots and LDS reads per product of 16x16 ones, and one row
 // per staging thread leaves one address to advance.  A block of 512 queries over 2464 slots
 // (128 units, 28 query heads on 4): 664 -> 597 us a call against 16x16 tiles with a running maximum, 67 % of that mix's
-// rate; 64 queries: 126 -> 98 us.  Tried and slower: products of one tile interleaved by hand with the exponentials of
+// rate; 64 queries: 126 -> 98 us.  What lies between: with operands that do not toggle, zeros or one constant, the same instructions take 462 us (87 %);
+// the 29 % on top are the clock that random products leave (64 queries: 77 and 90 us).  Tried and slower: products of one tile interleaved by hand with the exponentials of
 // another in one wave (600 -> 640 us and more: registers).
 #pragma once
 #include <hip/hip_runtime.h>
